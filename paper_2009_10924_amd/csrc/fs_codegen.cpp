@@ -140,9 +140,21 @@ std::string kChunkOrderPin(const char* a, const char* b) {
   return b ? fmt("  asm volatile(\"\" : \"+v\"(%s), \"+v\"(%s));\n", a, b) : fmt("  asm volatile(\"\" : \"+v\"(%s));\n", a);
 }
 
+// Rows that end inside a step may store their last step whole (GenRow, AGAIN) where every element has been read before
+// any is stored: behind a row reduction, unless a later pass reads the row again.
+bool stores_again(const RowProgP& p) {
+  if (p.cols % (uint32_t)p.vec == 0 || (p.col_chunks > 1 && p.col_kept < p.col_chunks)) return false;
+  for (int i = 0; i < p.n_instr; ++i) {
+    if (p.instr[i].op == PO_STORE) return false;
+    if (p.instr[i].op == PO_RSUM || p.instr[i].op == PO_RMAX || p.instr[i].op == PO_RSUMSQ) return true;
+  }
+  return false;
+}
+
 std::string instruction_text(const RowProgP& p, const ProgInstr& in, bool block, int n_waves, int* reduction_no, ChunkPass* cp = nullptr) {
   std::string t;
   const bool scalar = (in.flags & PF_SCALAR) != 0, keep = (in.flags & PF_KEEP) != 0;
+  const char* again = stores_again(p) ? ", true" : "";
   if (cp) {
     if ((in.op == PO_STORE && !cp->last_pass) || (in.op == PO_STORE_SCAL && !(cp->last_pass && cp->last_chunk))) return t;
     if (in.op == PO_RSUM || in.op == PO_RMAX || in.op == PO_RSUMSQ) {
@@ -174,9 +186,9 @@ std::string instruction_text(const RowProgP& p, const ProgInstr& in, bool block,
   switch (in.op) {
     case PO_STORE:
       if ((p.out_perm >> in.dst) & 1u)   // stored through a folded transpose: the row lands at its permuted place
-        t += fmt("  row.store_at<%s>(a.out[%d], %s, acc);\n", storage_type(in.aux), in.dst, stretched_row(p.oms[in.dst]).c_str());
+        t += fmt("  row.store_at<%s%s>(a.out[%d], %s, acc);\n", storage_type(in.aux), again, in.dst, stretched_row(p.oms[in.dst]).c_str());
       else
-        t += fmt("  row.store<%s>(a.out[%d], acc);\n", storage_type(in.aux), in.dst);
+        t += fmt("  row.store<%s%s>(a.out[%d], acc);\n", storage_type(in.aux), again, in.dst);
       return t;
     case PO_STORE_SCAL:
       t += fmt("  row.store_scalar<%s>(a.rout[%d], sacc);\n", storage_type(in.aux), in.dst);
@@ -483,8 +495,9 @@ std::string body_with_entry(const RowProgP& p, const char* entry, bool member) {
     if (R > 2u) s += fmt("#pragma unroll 1\n  for (uint32_t it = 1u; it < %uu; ++it) round(it, Yes{});\n", R - 1u);
     s += fmt("  round(%uu, No{});\n", R - 1u);
     for (int i = 0; i < p.n_colsum; ++i)
-      s += fmt("  Row::colsum_flush(cs%d, %s, static_cast<float*>(a.ws) + (size_t)row_wg * %uu + %uu + tile * %uu);\n", i,
-               block ? "nullptr" : fmt("colred[%d]", i).c_str(), (uint32_t)p.n_colsum * p.cols, (uint32_t)i * p.cols, p.cols / CT);
+      s += fmt("  nrow.colsum_flush(cs%d, %s, static_cast<float*>(a.ws) + (size_t)row_wg * %uu + %uu + tile * %uu);\n", i,
+               block ? "nullptr" : fmt("colred[%d]", i).c_str(), (uint32_t)p.n_colsum * colsum_pitch(p.cols), (uint32_t)i * colsum_pitch(p.cols),
+               p.cols / CT);
   }
   s += "}\n";
   return s;

@@ -39,23 +39,25 @@ CostResult evaluate(const KernelCost& k, int32_t vgprs_compiled) {
   const double cycles = wave_instr * (k.valu_per_elem * d.cycles_valu + k.trans_per_elem * d.cycles_trans) +
                         k.xlane_steps * d.cycles_xlane;
   const double simd_share = std::max(1.0, resident / (d.n_cu * d.simd_per_cu));
-  // two or three waves on a SIMD do not cover each other's instruction latencies (dependent transcendental chains show:
-  // measured 4 % on rows kept in registers at two waves against four)
-  const double issue_stall = r.waves_per_simd < 4 ? 1.0 + 0.025 * (4 - r.waves_per_simd) : 1.0;
+  // two or three waves on a SIMD do not cover each other's instruction latencies
+  const double issue_stall = r.waves_per_simd < 4 ? 1.0 + 0.6 * (4 - r.waves_per_simd) : 1.0;
   const double t_issue = cycles * simd_share * issue_stall / d.clock_hz;
   const double t_trip = k.dep_phases * d.mem_latency_s + k.barriers * d.barrier_s + t_issue;
   const double t_latency = rounds * k.rows_per_wave_loop * t_trip;
 
   // Streaming floor.  Achievable bandwidth = the measured copy rate, derated for
   //   * bytes in flight (Little's law),
-  //   * short contiguous runs per access (a row group of L lanes touches L*16 bytes),
+  //   * short contiguous runs per access (a row group of L lanes touches L*16 bytes): below a 128-byte line each
+  //     access wastes part of one, and where rows are no multiple of a line apart every run ends inside lines that
+  //     the next access touches again,
   //   * lanes that hold padding (their clamped loads still occupy the memory pipeline),
   //   * a last, partly filled round of wavefronts.
   const double in_flight = resident * 64.0 * k.bytes_in_flight_per_lane * util;
-  double bw = std::min(d.hbm_peak_Bps * d.stream_fraction, in_flight / d.mem_latency_s);
-  if (k.access_run_bytes > 0 && k.access_run_bytes < 128) bw /= 1.0 + 0.2 * (128.0 / k.access_run_bytes - 1.0);
+  double bw = std::min(d.hbm_peak_Bps * d.stream_fraction, in_flight / d.queue_latency_s);
+  if (k.access_run_bytes > 0 && k.access_run_bytes < 128) bw /= 1.0 + (128.0 / k.access_run_bytes - 1.0);
+  if (k.access_run_bytes > 0 && k.row_bytes > 0 && std::fmod(k.row_bytes, 128.0) != 0.0) bw /= 1.0 + 1.65 * std::min(4.0, 128.0 / k.access_run_bytes);
   if (k.store_run_bytes > 0 && k.store_run_bytes < 512) bw *= 0.97;
-  bw /= 1.0 + 0.3 * (1.0 / util - 1.0);
+  bw /= 1.0 + 0.12 * (1.0 / util - 1.0);
   bw /= 1.0 + 0.25 * (rounds / rounds_exact - 1.0);
   if (occ < 4) bw /= 1.0 + 0.04 * (4.0 - occ);   // few waves per SIMD: a wave's own stalls are not covered
   const double t_hbm = k.hbm_bytes / bw;
@@ -74,7 +76,7 @@ CostResult evaluate(const KernelCost& k, int32_t vgprs_compiled) {
   // of their own time shows, measured on the patterns with per-column operands)
   const double t_stream = std::max(t_hbm + 0.25 * t_cache + t_lds, t_alu);
   const double t_body = std::max(t_latency, t_stream) + 0.10 * std::min(t_latency, t_stream);
-  r.seconds = d.launch_s + t_body + t_ramp + k.serial_tail_s;
+  r.seconds = d.kernel_fixed_s + t_body + t_ramp + k.serial_tail_s;
   return r;
 }
 

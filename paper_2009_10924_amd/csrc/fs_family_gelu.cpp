@@ -3,7 +3,7 @@
 
 namespace fs {
 
-void make_fold_launch(Launch* f, uint32_t n_rows, uint32_t width, uint32_t split, uint32_t stride, int32_t out_dt) {
+void make_fold_launch(Launch* f, uint32_t n_rows, uint32_t width, uint32_t split, uint32_t out_cols, uint32_t stride, int32_t out_dt) {
   f->kernel = K_COLFOLD;
   GeluP fp{};
   fp.dt = out_dt;
@@ -11,6 +11,7 @@ void make_fold_launch(Launch* f, uint32_t n_rows, uint32_t width, uint32_t split
   fp.cols = stride ? stride : width;   // distance between partial rows (a fold may take a slice of wider rows)
   fp.fold_cols = width;
   fp.fold_split = split;
+  fp.fold_out_cols = out_cols;
   fp.fold_quads = n_rows > 128 ? 4 : 16;
   f->args.u.gelu = fp;
   f->shape.block[0] = 256;
@@ -128,7 +129,7 @@ bool build_gelu(const fs_graph& g, std::vector<Candidate>* out, PackForm* pack) 
           // the global hand-off: a second launch folds the row blocks' partial sums
           c.launches.emplace_back();
           Launch& f = c.launches.back();
-          make_fold_launch(&f, n_rb, p.cols, p.cols);
+          make_fold_launch(&f, n_rb, p.cols, p.cols, p.cols);
           f.ptr[0] = ws_ref(0);
           f.ptr[1] = out_ref(d.output_slot);
           c.info.n_kernels = 2;
@@ -151,6 +152,8 @@ bool build_gelu(const fs_graph& g, std::vector<Candidate>* out, PackForm* pack) 
         kc.barriers = 1;
         kc.lds_bytes_per_block = c.info.lds_bytes;
         kc.rows_per_wave_loop = std::max(1.0, (double)p.rows / ((double)n_rb * tile_rows));
+        kc.access_run_bytes = 1024.0;   // 64 lanes of one row
+        kc.row_bytes = (double)p.cols * esz;
         kc.dep_phases = 0;   // software pipelined: only the first tile's load latency is exposed (added below)
         // the fold: a second launch spread over the chip
         kc.serial_tail_s = device().mem_latency_s + 0.5 * device().launch_s + device().mem_latency_s * std::ceil(n_rb / 16.0 / 8.0) * 0.5;

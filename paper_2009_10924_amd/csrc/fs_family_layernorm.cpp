@@ -156,7 +156,8 @@ bool build_layernorm(const fs_graph& g, std::vector<Candidate>* out, PackForm* p
     kc.xlane_steps = 2 * steps;
     kc.cache_bytes = n / p.cols * (double)n_vec_inputs * p.cols * in_b;   // bias/gamma/beta re-read per row from L1/L2
     kc.lane_utilisation = (double)nvec / ((double)L * K);
-    kc.access_run_bytes = std::min<double>(L, nvec) * 16.0;
+    kc.access_run_bytes = L * 16.0;
+    kc.row_bytes = (double)p.cols * in_b;
     char var[40];
     snprintf(var, sizeof var, "<%s,%s,K%d,L%u>", dtype_name(p.in_dt), dtype_name(p.out_dt), K, L);
     finish_candidate(&c, var, kc);
@@ -207,6 +208,8 @@ bool build_layernorm(const fs_graph& g, std::vector<Candidate>* out, PackForm* p
     kc.lds_bytes_per_block = 64;
     kc.cache_bytes = n / p.cols * (double)n_vec_inputs * p.cols * in_b;
     kc.lane_utilisation = (double)nvec / ((double)T * K);
+    kc.access_run_bytes = 1024.0;
+    kc.row_bytes = (double)p.cols * in_b;
     char var[40];
     snprintf(var, sizeof var, "<%s,%s,K%d,T%u>", dtype_name(p.in_dt), dtype_name(p.out_dt), K, T);
     finish_candidate(&c, var, kc);
@@ -298,7 +301,7 @@ bool build_layernorm_backward(const fs_graph& g, std::vector<Candidate>* out, Pa
         }
         c.launches.emplace_back();
         Launch& f = c.launches.back();
-        make_fold_launch(&f, n_rb, 2 * p.cols, p.cols);
+        make_fold_launch(&f, n_rb, 2 * p.cols, p.cols, p.cols);
         f.ptr[0] = ws_ref(0);
         f.ptr[1] = out_ref(g.tensors[t_dg].output_slot);
         f.ptr[2] = out_ref(g.tensors[t_db].output_slot);
@@ -325,7 +328,8 @@ bool build_layernorm_backward(const fs_graph& g, std::vector<Candidate>* out, Pa
         kc.rows_per_wave_loop = std::max(1.0, (double)n_tiles / n_rb);
         kc.dep_phases = 1;
         kc.lane_utilisation = (double)nvec / ((double)L * K);
-        kc.access_run_bytes = std::min<double>(L, nvec) * 16.0;
+        kc.access_run_bytes = L * 16.0;
+        kc.row_bytes = (double)p.cols * esz;
         kc.serial_tail_s = device().mem_latency_s + 0.5 * device().launch_s + device().mem_latency_s * std::ceil(n_rb / 16.0 / 8.0) * 0.5;
         char var[56];
         snprintf(var, sizeof var, "<%s,K%d,L%u,W%d,R%d,RB%u>", dtype_name(p.dt), K, L, sh.waves, sh.r, n_rb);

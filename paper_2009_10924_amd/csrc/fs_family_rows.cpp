@@ -88,7 +88,8 @@ void emit_row_candidates(const fs_graph& g, const RowMatch& m, std::vector<Candi
     for (uint32_t s = 1; s < L; s <<= 1) ++steps;
     kc.xlane_steps = steps;
     kc.lane_utilisation = (double)nvec / ((double)L * K);
-    kc.access_run_bytes = std::min<double>(L, nvec) * 16.0;
+    kc.access_run_bytes = L * 16.0;
+    kc.row_bytes = (double)p.cols * esz;
     char var[48];
     snprintf(var, sizeof var, "<%s,%s,K%d,L%u>", m.name, dtype_name(p.dt), K, L);
     finish_candidate(&c, var, kc);
@@ -131,6 +132,8 @@ void emit_row_candidates(const fs_graph& g, const RowMatch& m, std::vector<Candi
     kc.barriers = 1;
     kc.lds_bytes_per_block = 64;
     kc.lane_utilisation = (double)nvec / ((double)T * K);
+    kc.access_run_bytes = 1024.0;
+    kc.row_bytes = (double)p.cols * esz;
     char var[48];
     snprintf(var, sizeof var, "<%s,%s,K%d,T%u>", m.name, dtype_name(p.dt), K, T);
     finish_candidate(&c, var, kc);

@@ -133,7 +133,8 @@ bool build_softmax(const fs_graph& g, std::vector<Candidate>* out, PackForm* pac
       for (uint32_t s = 1; s < L; s <<= 1) ++steps;
       kc.xlane_steps = 2 * steps;
       kc.lane_utilisation = (double)nvec / ((double)L * K);
-      kc.access_run_bytes = std::min<double>(L, nvec) * 16.0;
+      kc.access_run_bytes = L * 16.0;
+      kc.row_bytes = (double)p.cols * esz;
       char var[32];
       snprintf(var, sizeof var, "<%s,K%d,L%u>", dtype_name(p.in_dt), K, L);
       finish_candidate(&c, var, kc);
@@ -171,6 +172,8 @@ bool build_softmax(const fs_graph& g, std::vector<Candidate>* out, PackForm* pac
       kc.barriers = 2;
       kc.lds_bytes_per_block = 32;
       kc.lane_utilisation = (double)nvec / ((double)T * K);
+      kc.access_run_bytes = 1024.0;
+      kc.row_bytes = (double)p.cols * esz;
       char var[32];
       snprintf(var, sizeof var, "<%s,K%d,T%u>", dtype_name(p.in_dt), K, T);
       finish_candidate(&c, var, kc);

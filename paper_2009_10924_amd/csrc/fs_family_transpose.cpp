@@ -84,7 +84,8 @@ bool build_tchain(const fs_graph& g, std::vector<Candidate>* out, PackForm* pack
         kc.lds_traffic_bytes = lds ? 2 * n * 4 : 0;
         kc.store_run_bytes = lds ? (double)s_tile * p.D * esz : (double)p.D * esz;
         kc.lane_utilisation = (double)nvec / ((double)L * K) * (double)tile_rows / (passes * groups);
-        kc.access_run_bytes = std::min<double>(L, nvec) * 16.0;
+        kc.access_run_bytes = L * 16.0;
+        kc.row_bytes = (double)p.D * esz;
         char var[48];
         snprintf(var, sizeof var, "<%s,K%d,L%u,S%u,P%u>", dtype_name(p.dt), K, L, s_tile, passes);
         finish_candidate(&c, var, kc);

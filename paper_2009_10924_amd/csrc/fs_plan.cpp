@@ -187,6 +187,7 @@ fs_status fs::run_launches(const fs_plan* p, const void* const* inputs, void* co
         t.width[k] = fp.fold_cols;
         t.stride[k] = fp.cols;
         t.split[k] = fp.fold_split;
+        t.out_cols[k] = fp.fold_out_cols;
         t.quads[k] = fp.fold_quads;
         t.out_dt[k] = fp.dt;
         blocks += f.shape.grid[0];

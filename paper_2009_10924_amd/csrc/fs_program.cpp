@@ -166,6 +166,7 @@ static fs_status run_program(const fs_program* p, int32_t first_stage, int32_t l
       t.width[k] = f.fold_cols;
       t.stride[k] = f.cols;
       t.split[k] = f.fold_split;
+      t.out_cols[k] = f.fold_out_cols;
       t.quads[k] = f.fold_quads;
       t.out_dt[k] = f.dt;
       blocks += l.shape.grid[0];

@@ -457,11 +457,11 @@ struct Compiler {
       }
       if (T.output_slot >= 0 && view_src[t] < 0) return false;   // an input handed straight to an output is no computation
     }
-    // lane geometry by elements: the narrowest vector input still moves in 128-bit accesses where the row length
-    // allows it; otherwise 4 elements per step (16-bit inputs then move in 64-bit accesses) or, for rows that are
-    // no multiple of 4 elements, single elements (the last two forms exist as generated kernels only)
-    p.vec = (narrow && cols % 8 == 0) ? 8 : (cols % 4 == 0 ? 4 : 1);
-    interpretable = p.vec == 8 || (p.vec == 4 && !narrow);
+    // lane geometry by elements: the narrowest vector input moves in 128-bit accesses.  Where the row length is no
+    // multiple of a step, steps start at any element and the row's last one slides back to end with the row (generated
+    // kernels only); rows shorter than 8 elements take steps of 4, those shorter than 4 single elements.
+    p.vec = (narrow && cols >= 8) ? 8 : (cols >= 4 ? 4 : 1);
+    interpretable = cols % p.vec == 0 && (p.vec == 8 || (p.vec == 4 && !narrow));
     p.rows = rows;
     p.cols = cols;
     return true;
@@ -515,7 +515,7 @@ struct Compiler {
             val[op.out].kind = V_FULL;
             break;
           }
-          if (op.opcode == FS_REDUCE_SUM && op.axis == 0 && src.rank == rank && ka == V_FULL && !stretched_rows(src) && cols % 4 == 0 &&
+          if (op.opcode == FS_REDUCE_SUM && op.axis == 0 && src.rank == rank && ka == V_FULL && !stretched_rows(src) &&
               sum_chain[i] == 0) {
             const int end = column_sum_chain_end(i);
             const Tensor* last = end >= 0 ? &g.tensors[g.ops[end].out] : nullptr;
@@ -720,13 +720,14 @@ struct Shape {
 // Step widths to offer.  A pattern whose 16-bit vector inputs ask for 8 elements per step may also move float32
 // rows (an input, or an output stored as float32): those take two 128-bit accesses per step, 32 bytes apart per
 // lane, which the memory system likes less than one; 4 elements per step turns that around (float32 in one
-// access, the 16-bit operands in 64-bit ones).  Both are offered then, the narrower one as generated kernels.
+// access, the 16-bit operands in 64-bit ones).  Both are offered then, the narrower one as generated kernels; also for
+// row lengths that are no multiple of 8, where steps of 4 may be the aligned ones.
 std::vector<int> step_widths(const RowProgP& base) {
   bool moves_f32_rows = false;
   for (int i = 0; i < base.n_full; ++i) moves_f32_rows = moves_f32_rows || base.full_dt[i] == DT_F32;
   for (int i = 0; i < base.n_instr; ++i) moves_f32_rows = moves_f32_rows || (base.instr[i].op == PO_STORE && base.instr[i].aux == DT_F32);
   std::vector<int> widths(1, base.vec);
-  if (base.vec == 8 && moves_f32_rows && codegen_enabled()) widths.push_back(4);
+  if (base.vec == 8 && (moves_f32_rows || base.cols % 8 != 0) && codegen_enabled()) widths.push_back(4);
   return widths;
 }
 
@@ -759,7 +760,7 @@ std::vector<Shape> with_rows_per_group(const std::vector<Shape>& shapes, uint32_
 }
 
 std::vector<Shape> enumerate_shapes(const Compiler& c, int vec, bool interpretable) {
-  const uint32_t nvec = c.p.cols / vec;
+  const uint32_t nvec = (c.p.cols + vec - 1) / vec;
   std::vector<Shape> shapes;
   if (interpretable) {
     for (int K : {1, 2, 4}) {
@@ -773,8 +774,8 @@ std::vector<Shape> enumerate_shapes(const Compiler& c, int vec, bool interpretab
   }
   if (!codegen_enabled()) return shapes;
   // generated kernels (listed after the interpreted ones, whose indices stay): any number of steps per lane up to
-  // 8 (32 single-element steps), so a row can fill its lanes exactly (768 floats: 32 lanes x 6 vectors)
-  const uint32_t max_k = vec == 1 ? 32 : 8;
+  // 8, so a row can fill its lanes exactly (768 floats: 32 lanes x 6 vectors)
+  const uint32_t max_k = 8;
   for (uint32_t L = 1; L <= 64; L <<= 1) {
     const uint32_t K = (nvec + L - 1) / L;
     if (K >= 1 && K <= max_k && (L == 1 || (uint64_t)(L / 2) * K < nvec)) shapes.push_back({L, (int)K, false, true});
@@ -814,7 +815,7 @@ std::vector<Shape> enumerate_shapes(const Compiler& c, int vec, bool interpretab
   if (c.n_reductions == 0 && c.n_rout == 0)
     for (int K : {1, 2}) {
       const uint32_t tile_vecs = 64u * K;
-      if (nvec % tile_vecs == 0 && nvec / tile_vecs > 1 && nvec / tile_vecs <= 4096) {
+      if (c.p.cols % vec == 0 && nvec % tile_vecs == 0 && nvec / tile_vecs > 1 && nvec / tile_vecs <= 4096) {
         Shape t{64, K, false, true};
         t.CT = nvec / tile_vecs;
         shapes.push_back(t);
@@ -859,7 +860,7 @@ void fill_launch(const fs_graph& g, const Compiler& c, int vec, const Shape& s, 
 KernelCost interpreted_cost(const Compiler& c, int vec, const Shape& s, int64_t lds, int64_t bytes_min, uint32_t grid) {
   const RowProgP& base = c.p;
   const int kv = s.K * vec;
-  const uint32_t nvec = base.cols / vec;
+  const uint32_t nvec = (base.cols + vec - 1) / vec;
   const double n = (double)base.rows * base.cols;
   double in_bytes_per_elem = 0, col_bytes_per_elem = 0, narrowest = 4.0;
   for (int i = 0; i < base.n_full; ++i) {
@@ -886,7 +887,7 @@ KernelCost interpreted_cost(const Compiler& c, int vec, const Shape& s, int64_t 
   kc.lds_traffic_bytes = n * 4.0 * (c.reg_reads + c.reg_writes + base.n_full);
   kc.waves_per_block = s.block ? (int32_t)(s.L / 64) : 4;
   kc.waves = (double)grid * kc.waves_per_block;
-  kc.bytes_in_flight_per_lane = (vec == 1 ? (double)in_bytes_per_elem : std::max(16.0, (double)vec * in_bytes_per_elem)) * s.K;
+  kc.bytes_in_flight_per_lane = std::max(16.0, (double)vec * in_bytes_per_elem) * s.K;
   kc.vgpr_estimate = 40 + 3 * kv + 4 * s.K * (base.n_full <= 1 ? 1 : (base.n_full <= 2 ? 2 : 4));
   int steps = 0;
   for (uint32_t t = 1; t < std::min<uint32_t>(s.L, 64); t <<= 1) ++steps;
@@ -895,8 +896,8 @@ KernelCost interpreted_cost(const Compiler& c, int vec, const Shape& s, int64_t 
   kc.lds_bytes_per_block = (int32_t)lds;
   kc.lane_utilisation = (double)(nvec / s.CT) / ((double)s.L * s.K);
   // contiguous bytes the lanes of one row touch per access of the narrowest input
-  const double run = (double)std::min<uint32_t>(s.L, 64) * vec * narrowest;
-  kc.access_run_bytes = run >= 128.0 ? 0.0 : run;
+  kc.access_run_bytes = (double)std::min<uint32_t>(s.L, 64) * vec * narrowest;
+  kc.row_bytes = (double)base.cols * narrowest;
   kc.preamble_instr = 60;
   return kc;
 }
@@ -956,7 +957,7 @@ void make_generated(const Compiler& c, int vec, const Shape& s, Candidate* cand)
     cand->info.bytes_moved_model += (int64_t)(in_bytes * extra_passes);
     gc.valu_per_elem *= 1.0 + 0.5 * extra_passes;
     gc.trans_per_elem *= 1.0 + 0.5 * c.n_reductions;
-    gc.lane_utilisation = (double)(base.cols / vec) / ((double)s.L * s.K * s.NC);
+    gc.lane_utilisation = (double)base.cols / ((double)vec * s.L * s.K * s.NC);
     gc.serial_tail_s += d.mem_latency_s * c.n_reductions;
     // a first pass that gathers maximum and sum together issues the loads of every kept chunk before it works on the first
     if (s.kept > 0 && extra_passes < c.n_reductions) gc.bytes_in_flight_per_lane *= (double)s.kept;
@@ -971,7 +972,7 @@ void add_column_sums(const Compiler& c, int vec, const Shape& s, int64_t bytes_m
   const DeviceModel& d = device();
   Launch& ml = cand->launches.back();
   const uint32_t n_wg = ml.shape.grid[0] / s.CT;   // one row of partial sums per row block (its column tiles share the row)
-  const uint32_t width = (uint32_t)c.n_colsum * base.cols;
+  const uint32_t pitch = colsum_pitch(base.cols), width = (uint32_t)c.n_colsum * pitch;
   ml.ptr[kSlotWs].kind = BUF_WORKSPACE;
   ml.ptr[kSlotWs].offset = 0;
   cand->info.lds_bytes += s.block ? 0 : c.n_colsum * 4 * (int32_t)(s.L * kv) * 4;
@@ -981,9 +982,9 @@ void add_column_sums(const Compiler& c, int vec, const Shape& s, int64_t bytes_m
     here = (first + 1 < c.n_colsum && c.colsum_dt[first] == c.colsum_dt[first + 1]) ? 2 : 1;
     cand->launches.emplace_back();
     Launch& f = cand->launches.back();
-    make_fold_launch(&f, n_wg, (uint32_t)here * base.cols, base.cols, width, c.colsum_dt[first]);
+    make_fold_launch(&f, n_wg, (uint32_t)here * pitch, pitch, base.cols, width, c.colsum_dt[first]);
     f.ptr[0].kind = BUF_WORKSPACE;
-    f.ptr[0].offset = (int64_t)first * base.cols * 4;
+    f.ptr[0].offset = (int64_t)first * pitch * 4;
     for (int i = 0; i < here; ++i) {
       f.ptr[1 + i].kind = BUF_OUTPUT;
       f.ptr[1 + i].slot = c.colsum_slot[first + i];

@@ -40,6 +40,8 @@ __device__ __forceinline__ uint32_t pack_f16(float lo, float hi) {
   f16x2 r = {(_Float16)lo, (_Float16)hi};          // v_cvt_f16_f32: round to nearest even
   return __builtin_bit_cast(uint32_t, r);
 }
+__device__ __forceinline__ uint32_t pack2(float lo, float hi, const bf16_t*) { return pack_bf16(lo, hi); }
+__device__ __forceinline__ uint32_t pack2(float lo, float hi, const f16_t*) { return pack_f16(lo, hi); }
 __device__ __forceinline__ void unpack_f16(uint32_t w, float& lo, float& hi) {
   f16x2 h = __builtin_bit_cast(f16x2, w);
   lo = (float)h.x;

@@ -184,7 +184,7 @@ __global__ void __launch_bounds__(WAVES * 64) k_bias_gelu_dbias(const T* __restr
 // partial rows: (Q,G) = (16,16); many: (4,64), so a thread still needs one batch of loads.
 template <int Q, int G>
 __device__ __forceinline__ void fold_tile(const float* __restrict__ partials, float* __restrict__ out0, float* __restrict__ out1,
-                                          uint32_t n, uint32_t width, uint32_t stride, uint32_t split, uint32_t block,
+                                          uint32_t n, uint32_t width, uint32_t stride, uint32_t split, uint32_t out_cols, uint32_t block,
                                           f32x4* __restrict__ sm, int32_t out_dt) {
   const uint32_t q = threadIdx.x % Q, g = threadIdx.x / Q;
   const uint32_t col = (block * Q + q) * 4u;
@@ -215,10 +215,18 @@ __device__ __forceinline__ void fold_tile(const float* __restrict__ partials, fl
     // rounded here, once
     float* const base = col < split ? out0 : out1;
     const uint32_t at = col < split ? col : col - split;
-    if (out_dt == DT_F32) {
+    const float quad[4] = {v.x, v.y, v.z, v.w};
+    if (at + 4u > out_cols) {   // the last quad of a sum whose columns are no multiple of 4: the rest of it is padding
+#pragma unroll
+      for (uint32_t e = 0; e < 3u; ++e)
+        if (at + e < out_cols) {
+          if (out_dt == DT_F32) base[at + e] = quad[e];
+          else if (out_dt == DT_BF16) store1(reinterpret_cast<bf16_t*>(base) + at + e, quad[e]);
+          else store1(reinterpret_cast<f16_t*>(base) + at + e, quad[e]);
+        }
+    } else if (out_dt == DT_F32) {
       *reinterpret_cast<f32x4*>(base + at) = v;
     } else {
-      const float quad[4] = {v.x, v.y, v.z, v.w};
       if (out_dt == DT_BF16) StoreN<bf16_t, 4>::run(reinterpret_cast<bf16_t*>(base) + at, quad);
       else StoreN<f16_t, 4>::run(reinterpret_cast<f16_t*>(base) + at, quad);
     }
@@ -230,7 +238,7 @@ __global__ void __launch_bounds__(256) k_colfold(const float* __restrict__ parti
                                                  float* __restrict__ out1, GeluP p) {
   __shared__ f32x4 sm[G * Q];
   // stride >= width: a fold may take a slice of wider partial rows
-  fold_tile<Q, G>(partials, out0, out1, p.n_row_tiles, p.fold_cols, p.cols, p.fold_split, blockIdx.x, sm, p.dt);
+  fold_tile<Q, G>(partials, out0, out1, p.n_row_tiles, p.fold_cols, p.cols, p.fold_split, p.fold_out_cols, blockIdx.x, sm, p.dt);
 }
 
 // Several independent folds in one launch: workgroups [first_block[i], first_block[i+1]) run fold i.  The table
@@ -251,9 +259,9 @@ __global__ void __launch_bounds__(256) k_colfold_many(const FoldManyP table_in_k
   float* out1 = tab->out1[i];
   const uint32_t block = b - tab->first_block[i];
   if (tab->quads[i] == 4)
-    fold_tile<4, 64>(partials, out0, out1, tab->n[i], tab->width[i], tab->stride[i], tab->split[i], block, sm, tab->out_dt[i]);
+    fold_tile<4, 64>(partials, out0, out1, tab->n[i], tab->width[i], tab->stride[i], tab->split[i], tab->out_cols[i], block, sm, tab->out_dt[i]);
   else
-    fold_tile<16, 16>(partials, out0, out1, tab->n[i], tab->width[i], tab->stride[i], tab->split[i], block, sm, tab->out_dt[i]);
+    fold_tile<16, 16>(partials, out0, out1, tab->n[i], tab->width[i], tab->stride[i], tab->split[i], tab->out_cols[i], block, sm, tab->out_dt[i]);
 }
 
 }  // namespace fsk

@@ -8,9 +8,9 @@
 
 using namespace fsk;
 
-template <typename TI, typename TO, int VEC, int K, uint32_t L, bool BLOCK>
+template <typename TI, typename TO, int VEC, int K, uint32_t L, bool BLOCK, uint32_t COLS = 64u * VEC * K>
 __device__ __forceinline__ void sample_body(const GenArgs& a) {
-  typedef GenRow<1000u, 64u * VEC * K, VEC, K, L, BLOCK> Row;
+  typedef GenRow<1000u, COLS, VEC, K, L, BLOCK> Row;
   constexpr int KV = Row::KV;
   __shared__ float slots[8];
   const Row row(blockIdx.x);
@@ -34,9 +34,13 @@ extern "C" __global__ void __launch_bounds__(256) fs_gen_sample_block_bf16(const
 extern "C" __global__ void __launch_bounds__(256) fs_gen_sample_wide_f32(const GenArgs a) { sample_body<float, float, 8, 1, 8u, false>(a); }
 extern "C" __global__ void __launch_bounds__(256) fs_gen_sample_half_width_bf16(const GenArgs a) { sample_body<bf16_t, bf16_t, 4, 2, 16u, false>(a); }
 extern "C" __global__ void __launch_bounds__(256) fs_gen_sample_half_width_f16(const GenArgs a) { sample_body<f16_t, f16_t, 4, 1, 256u, true>(a); }
-extern "C" __global__ void __launch_bounds__(256) fs_gen_sample_element_f32(const GenArgs a) { sample_body<float, float, 1, 5, 64u, false>(a); }
-extern "C" __global__ void __launch_bounds__(256) fs_gen_sample_element_bf16(const GenArgs a) { sample_body<bf16_t, f16_t, 1, 3, 32u, false>(a); }
-extern "C" __global__ void __launch_bounds__(256) fs_gen_sample_element_f16(const GenArgs a) { sample_body<f16_t, bf16_t, 1, 7, 256u, true>(a); }
+extern "C" __global__ void __launch_bounds__(256) fs_gen_sample_element_f32(const GenArgs a) { sample_body<float, float, 1, 3, 1u, false, 3u>(a); }
+extern "C" __global__ void __launch_bounds__(256) fs_gen_sample_element_bf16(const GenArgs a) { sample_body<bf16_t, f16_t, 1, 1, 2u, false, 2u>(a); }
+// row lengths that are no multiple of a step: tails of 5, 7, 3 and 2 elements
+extern "C" __global__ void __launch_bounds__(256) fs_gen_sample_ragged_f16(const GenArgs a) { sample_body<f16_t, f16_t, 8, 4, 8u, false, 197u>(a); }
+extern "C" __global__ void __launch_bounds__(256) fs_gen_sample_ragged_bf16(const GenArgs a) { sample_body<bf16_t, float, 8, 2, 256u, true, 2247u>(a); }
+extern "C" __global__ void __launch_bounds__(256) fs_gen_sample_ragged_f32(const GenArgs a) { sample_body<float, bf16_t, 4, 4, 64u, false, 1003u>(a); }
+extern "C" __global__ void __launch_bounds__(256) fs_gen_sample_ragged_narrow(const GenArgs a) { sample_body<bf16_t, f16_t, 4, 1, 2u, false, 6u>(a); }
 
 // a pattern with a column sum: two rows per lane group, partial sums through LDS to the workspace
 extern "C" __global__ void __launch_bounds__(256) fs_gen_sample_colsum(const GenArgs a) {
@@ -55,5 +59,5 @@ extern "C" __global__ void __launch_bounds__(256) fs_gen_sample_colsum(const Gen
     row.store<float>(a.out[0], acc);
     row.colsum_add(acc, cs0);
   }
-  Row::colsum_flush(cs0, colred[0], static_cast<float*>(a.ws) + (size_t)blockIdx.x * 96u);
+  Row(blockIdx.x).colsum_flush(cs0, colred[0], static_cast<float*>(a.ws) + (size_t)blockIdx.x * 96u);
 }

@@ -32,96 +32,121 @@ __device__ __forceinline__ float xor_lane(float v, uint32_t mask) {
   return __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(addr, __builtin_bit_cast(int, v)));
 }
 
-// One step of one lane in storage form: VEC elements of 2 or 4 bytes are 2, 4, 8, 16 or 32 bytes.  VEC is 8 or 4
-// where the row length allows 128-bit (or, for 16-bit elements under VEC = 4, 64-bit) accesses, and 1 for rows
-// whose length is not a multiple of 4 elements: every access is then a single element, still contiguous over
-// the lanes of a row.
-template <int BYTES> struct StepBits;
-template <> struct StepBits<32> {
+// One step of one lane in storage form: VEC elements of 2 or 4 bytes are 2, 4, 8, 16 or 32 bytes.  VEC is 8 or 4, and
+// 1 for rows shorter than 4 elements.  EA: the alignment the address is known to have, in bytes -- that of a whole step
+// where the row length is a multiple of VEC elements, that of one element otherwise (a row then starts anywhere).  The
+// memory pipeline takes 64- and 128-bit accesses at any element address: a copy of 64 MB each way through 128-bit
+// accesses that all start 2 bytes off runs at 5.18 TB/s, 4 or 8 bytes off at 5.53, aligned at 5.75, and element by
+// element at 4.97 with eight times the instructions and one register per element.
+template <typename V, int EA> struct AtAlignment { typedef V type __attribute__((aligned(EA))); };
+template <int BYTES, int EA> struct StepBits;
+template <int EA> struct StepBits<32, EA> {
   u32x4 lo, hi;
   template <bool STREAM, typename T>
   __device__ __forceinline__ static StepBits load(const T* p) {
     StepBits r;
-    const u32x4* q = reinterpret_cast<const u32x4*>(p);
+    const typename AtAlignment<u32x4, EA>::type* q = reinterpret_cast<const typename AtAlignment<u32x4, EA>::type*>(p);
     r.lo = STREAM ? __builtin_nontemporal_load(q) : q[0];
     r.hi = STREAM ? __builtin_nontemporal_load(q + 1) : q[1];
     return r;
   }
 };
-template <> struct StepBits<16> {
-  u32x4 w;
+template <typename V, int EA> struct OneAccess {
   template <bool STREAM, typename T>
-  __device__ __forceinline__ static StepBits load(const T* p) {
-    StepBits r;
-    r.w = STREAM ? load_raw_nt(p) : load_raw(p);
-    return r;
+  __device__ __forceinline__ static V get(const T* p) {
+    const typename AtAlignment<V, EA>::type* q = reinterpret_cast<const typename AtAlignment<V, EA>::type*>(p);
+    return STREAM ? __builtin_nontemporal_load(q) : *q;
   }
 };
-template <> struct StepBits<8> {
-  u32x2 w;
-  template <bool STREAM, typename T>
-  __device__ __forceinline__ static StepBits load(const T* p) {
-    StepBits r;
-    const u32x2* q = reinterpret_cast<const u32x2*>(p);
-    r.w = STREAM ? __builtin_nontemporal_load(q) : *q;
-    return r;
-  }
-};
-template <> struct StepBits<4> {
-  uint32_t w;
-  template <bool STREAM, typename T>
-  __device__ __forceinline__ static StepBits load(const T* p) {
-    StepBits r;
-    const uint32_t* q = reinterpret_cast<const uint32_t*>(p);
-    r.w = STREAM ? __builtin_nontemporal_load(q) : *q;
-    return r;
-  }
-};
-template <> struct StepBits<2> {
-  uint16_t w;
-  template <bool STREAM, typename T>
-  __device__ __forceinline__ static StepBits load(const T* p) {
-    StepBits r;
-    const uint16_t* q = reinterpret_cast<const uint16_t*>(p);
-    r.w = STREAM ? __builtin_nontemporal_load(q) : *q;
-    return r;
-  }
-};
+#define FSK_STEP_BITS(BYTES, V)                                        \
+  template <int EA> struct StepBits<BYTES, EA> {                       \
+    V w;                                                               \
+    template <bool STREAM, typename T>                                 \
+    __device__ __forceinline__ static StepBits load(const T* p) {      \
+      StepBits r;                                                      \
+      r.w = OneAccess<V, EA>::template get<STREAM>(p);                 \
+      return r;                                                        \
+    }                                                                  \
+  };
+FSK_STEP_BITS(16, u32x4)
+FSK_STEP_BITS(8, u32x2)
+FSK_STEP_BITS(4, uint32_t)
+FSK_STEP_BITS(2, uint16_t)
+#undef FSK_STEP_BITS
+
 // Registers that hold a step in storage form across several passes: after this the compiler no longer knows what is
 // in them, so it cannot carry the unpacked float32 form (twice the registers of a 16-bit step) from one pass to the
 // next instead.  No instruction is emitted.
-__device__ __forceinline__ void forget_contents(StepBits<32>& s) { asm volatile("" : "+v"(s.lo), "+v"(s.hi)); }
-__device__ __forceinline__ void forget_contents(StepBits<16>& s) { asm volatile("" : "+v"(s.w)); }
-__device__ __forceinline__ void forget_contents(StepBits<8>& s) { asm volatile("" : "+v"(s.w)); }
-__device__ __forceinline__ void forget_contents(StepBits<4>& s) { asm volatile("" : "+v"(s.w)); }
-__device__ __forceinline__ void forget_contents(StepBits<2>& s) {
+template <int EA>
+__device__ __forceinline__ void forget_contents(StepBits<32, EA>& s) { asm volatile("" : "+v"(s.lo), "+v"(s.hi)); }
+template <int EA>
+__device__ __forceinline__ void forget_contents(StepBits<16, EA>& s) { asm volatile("" : "+v"(s.w)); }
+template <int EA>
+__device__ __forceinline__ void forget_contents(StepBits<8, EA>& s) { asm volatile("" : "+v"(s.w)); }
+template <int EA>
+__device__ __forceinline__ void forget_contents(StepBits<4, EA>& s) { asm volatile("" : "+v"(s.w)); }
+template <int EA>
+__device__ __forceinline__ void forget_contents(StepBits<2, EA>& s) {
   uint32_t t = s.w;
   asm volatile("" : "+v"(t));
   s.w = (uint16_t)t;
 }
 
-__device__ __forceinline__ void unpack_step(const StepBits<32>& r, float (&v)[8], const float*) {
+template <int EA>
+__device__ __forceinline__ void unpack_step(const StepBits<32, EA>& r, float (&v)[8], const float*) {
   float a[4], b[4];
   unpack(r.lo, a, (const float*)nullptr);
   unpack(r.hi, b, (const float*)nullptr);
 #pragma unroll
   for (int e = 0; e < 4; ++e) { v[e] = a[e]; v[4 + e] = b[e]; }
 }
-__device__ __forceinline__ void unpack_step(const StepBits<16>& r, float (&v)[4], const float*) { unpack(r.w, v, (const float*)nullptr); }
-template <typename T>
-__device__ __forceinline__ void unpack_step(const StepBits<16>& r, float (&v)[8], const T*) { unpack(r.w, v, (const T*)nullptr); }
-__device__ __forceinline__ void unpack_step(const StepBits<8>& r, float (&v)[4], const bf16_t*) {
+template <int EA>
+__device__ __forceinline__ void unpack_step(const StepBits<16, EA>& r, float (&v)[4], const float*) { unpack(r.w, v, (const float*)nullptr); }
+template <int EA, typename T>
+__device__ __forceinline__ void unpack_step(const StepBits<16, EA>& r, float (&v)[8], const T*) { unpack(r.w, v, (const T*)nullptr); }
+template <int EA>
+__device__ __forceinline__ void unpack_step(const StepBits<8, EA>& r, float (&v)[4], const bf16_t*) {
   v[0] = __builtin_bit_cast(float, r.w.x << 16); v[1] = __builtin_bit_cast(float, r.w.x & 0xFFFF0000u);
   v[2] = __builtin_bit_cast(float, r.w.y << 16); v[3] = __builtin_bit_cast(float, r.w.y & 0xFFFF0000u);
 }
-__device__ __forceinline__ void unpack_step(const StepBits<8>& r, float (&v)[4], const f16_t*) {
+template <int EA>
+__device__ __forceinline__ void unpack_step(const StepBits<8, EA>& r, float (&v)[4], const f16_t*) {
   unpack_f16(r.w.x, v[0], v[1]);
   unpack_f16(r.w.y, v[2], v[3]);
 }
-__device__ __forceinline__ void unpack_step(const StepBits<4>& r, float (&v)[1], const float*) { v[0] = __builtin_bit_cast(float, r.w); }
-__device__ __forceinline__ void unpack_step(const StepBits<2>& r, float (&v)[1], const bf16_t*) { v[0] = bf16_bits_to_f32(r.w); }
-__device__ __forceinline__ void unpack_step(const StepBits<2>& r, float (&v)[1], const f16_t*) {
+template <int EA>
+__device__ __forceinline__ void unpack_step(const StepBits<4, EA>& r, float (&v)[1], const float*) { v[0] = __builtin_bit_cast(float, r.w); }
+template <int EA>
+__device__ __forceinline__ void unpack_step(const StepBits<2, EA>& r, float (&v)[1], const bf16_t*) { v[0] = bf16_bits_to_f32(r.w); }
+template <int EA>
+__device__ __forceinline__ void unpack_step(const StepBits<2, EA>& r, float (&v)[1], const f16_t*) {
   v[0] = (float)__builtin_bit_cast(_Float16, r.w);
+}
+
+// Stores N float32 values as TO at an address known to be aligned to EA bytes, past the caches (see StoreN).
+template <typename TO, int N, int EA>
+__device__ __forceinline__ void store_elements(TO* p, const float (&v)[N]) {
+  if constexpr (EA >= (int)sizeof(TO) * N || N == 1) {
+    StoreN<TO, N>::run(p, v);
+  } else if constexpr (sizeof(TO) == 4) {
+    if constexpr (N == 2) {
+      const u32x2 w = {__builtin_bit_cast(uint32_t, v[0]), __builtin_bit_cast(uint32_t, v[1])};
+      __builtin_nontemporal_store(w, reinterpret_cast<typename AtAlignment<u32x2, EA>::type*>(p));
+    } else {
+#pragma unroll
+      for (int e = 0; e < N; e += 4) {
+        const f32x4 w = {v[e], v[e + 1], v[e + 2], v[e + 3]};
+        __builtin_nontemporal_store(w, reinterpret_cast<typename AtAlignment<f32x4, EA>::type*>(p + e));
+      }
+    }
+  } else {
+    uint32_t w[N / 2];
+#pragma unroll
+    for (int e = 0; e < N; e += 2) w[e / 2] = pack2(v[e], v[e + 1], (const TO*)nullptr);
+    if constexpr (N == 8) __builtin_nontemporal_store(u32x4{w[0], w[1], w[2], w[3]}, reinterpret_cast<typename AtAlignment<u32x4, EA>::type*>(p));
+    else if constexpr (N == 4) __builtin_nontemporal_store(u32x2{w[0], w[1]}, reinterpret_cast<typename AtAlignment<u32x2, EA>::type*>(p));
+    else __builtin_nontemporal_store(w[0], reinterpret_cast<typename AtAlignment<uint32_t, EA>::type*>(p));
+  }
 }
 
 // ROWS x COLS row space; VEC elements per lane and step; K steps per lane; L lanes per row: a lane group of one
@@ -130,16 +155,26 @@ __device__ __forceinline__ void unpack_step(const StepBits<2>& r, float (&v)[1],
 // workgroup indices it * gridDim.x + blockIdx.x, so that at any moment the resident workgroups sweep one band of rows).
 // ROW_STRIDE > COLS: the pattern's rows are ROW_STRIDE elements long and the kernel works on column tiles of COLS
 // elements (patterns without row reductions only: nothing ties the tiles of a row together); `tile` picks the tile.
+//
+// Row lengths that are no multiple of VEC: the row's last step slides back so that it ends where the row ends, and
+// reads some elements that the step before it holds as well (BACK of them).  Every load is then one whole access
+// inside the row.  The repeated elements count once: reductions and column sums leave them out of the last step.  Its
+// store either writes only the TAIL elements the step owns, in at most three pieces, or (AGAIN) the whole step, the
+// repeated elements a second time with the value their owner gives them: one access instead of three more (rows of 197
+// 16-bit elements, 29.8 MB: 7.6 against 8.9 us for the bare copy, 7.0 with rows padded to whole steps).
 template <uint32_t ROWS, uint32_t COLS, int VEC, int K, uint32_t L, bool BLOCK, uint32_t R = 1, uint32_t ROW_STRIDE = COLS>
 struct GenRow {
-  static constexpr uint32_t NVEC = COLS / VEC;
+  static constexpr uint32_t NVEC = (COLS + VEC - 1) / VEC;
+  static constexpr int TAIL = (int)(COLS % VEC), BACK = TAIL != 0 ? VEC - TAIL : 0;
   static constexpr uint32_t LANES = L;
   static constexpr uint32_t ROWS_PER_WG = BLOCK ? 1u : 256u / L;
-  // the row fills its lanes / the rows fill the workgroups: no clamp, no padding test
-  static constexpr bool FULL_COLS = NVEC == LANES * K;
+  // the row fills its lanes (and no element is held twice) / the rows fill the workgroups: no clamp, no padding test
+  static constexpr bool FULL_COLS = NVEC == LANES * K && TAIL == 0;
   static constexpr bool FULL_ROWS = ROWS % (ROWS_PER_WG * R) == 0;
   static constexpr int KV = K * VEC;
   static constexpr uint32_t PADDED_COLS = LANES * K * VEC;   // columns the lanes of a row cover, padding included
+  static_assert(TAIL == 0 || ROW_STRIDE >= (uint32_t)VEC, "a row holds at least one step");
+  template <typename T> static constexpr int alignment() { return (int)sizeof(T) * (ROW_STRIDE % VEC == 0 ? VEC : 1); }
 
   uint32_t lane, row, row_c, col0;
   bool row_ok;
@@ -154,14 +189,26 @@ struct GenRow {
   }
   // a chunk of a long row: COLS columns from column `first_col` on (the row itself is ROW_STRIDE elements long)
   __device__ __forceinline__ GenRow(uint32_t vblock, uint32_t tile, uint32_t first_col) : GenRow(vblock, tile) { col0 = first_col; }
-  __device__ __forceinline__ bool valid(int k) const { return FULL_COLS || lane + k * LANES < NVEC; }
-  __device__ __forceinline__ uint32_t vec_at(int k) const { return FULL_COLS ? lane + k * LANES : min(lane + k * LANES, NVEC - 1u); }
+  // only a lane's last step can be padding or the row's last one (K is the smallest that covers the row)
+  static constexpr __device__ __forceinline__ bool inner(int k) { return FULL_COLS || (uint32_t)k < (NVEC - 1u) / LANES; }
+  __device__ __forceinline__ bool valid(int k) const { return inner(k) || lane + k * LANES < NVEC; }
+  // element e of step k is the lane's own: neither padding nor a repetition of the step before
+  __device__ __forceinline__ bool own(int k, int e) const {
+    return inner(k) || lane + k * LANES < (e < BACK ? NVEC - 1u : NVEC);
+  }
+  // first column of step k (the last step's slides back; padding steps stay on the last step).  Signed: the last chunk
+  // of a long row may be shorter than a step, which then starts in the chunk before.
+  __device__ __forceinline__ int first_of(int k) const {
+    if (inner(k)) return (int)(lane + k * LANES) * VEC;
+    if constexpr (TAIL != 0) return min((int)(lane + k * LANES) * VEC, (int)COLS - VEC);
+    return (int)min(lane + k * LANES, NVEC - 1u) * VEC;
+  }
 
   // the lane's K steps of row `at_row` of a [.., COLS] tensor, in storage form; STREAM: read once, so the loads
   // carry the streaming hint and do not displace the operands that every row re-reads from cache
   template <typename T>
   struct Raw {
-    StepBits<VEC * (int)sizeof(T)> w[K];
+    StepBits<VEC * (int)sizeof(T), alignment<T>()> w[K];
     __device__ __forceinline__ void forget_contents() {
 #pragma unroll
       for (int k = 0; k < K; ++k) fsk::forget_contents(w[k]);
@@ -172,7 +219,7 @@ struct GenRow {
     Raw<T> r;
     const T* base = static_cast<const T*>(p) + at_row * ROW_STRIDE + col0;
 #pragma unroll
-    for (int k = 0; k < K; ++k) r.w[k] = StepBits<VEC * (int)sizeof(T)>::template load<STREAM>(base + (size_t)vec_at(k) * VEC);
+    for (int k = 0; k < K; ++k) r.w[k] = StepBits<VEC * (int)sizeof(T), alignment<T>()>::template load<STREAM>(base + first_of(k));
     return r;
   }
 
@@ -187,11 +234,19 @@ struct GenRow {
     }
   }
 
-  template <typename TO>
-  __device__ __forceinline__ void store(void* p, const float (&v)[KV]) const { store_at<TO>(p, (size_t)row, v); }
+  template <typename TO, bool AGAIN = false>
+  __device__ __forceinline__ void store(void* p, const float (&v)[KV]) const { store_at<TO, AGAIN>(p, (size_t)row, v); }
 
+  // N of the last step's own elements, from its element FROM on
+  template <typename TO, int FROM, int N>
+  __device__ __forceinline__ static void store_piece(TO* step, const float (&part)[VEC]) {
+    float w[N];
+#pragma unroll
+    for (int e = 0; e < N; ++e) w[e] = part[FROM + e];
+    store_elements<TO, N, (int)sizeof(TO)>(step + FROM, w);
+  }
   // the row's values to row `at_row` of the output (its own row, or the place a folded transpose gives it)
-  template <typename TO>
+  template <typename TO, bool AGAIN = false>
   __device__ __forceinline__ void store_at(void* p, size_t at_row, const float (&v)[KV]) const {
     TO* base = static_cast<TO*>(p) + at_row * ROW_STRIDE + col0;
 #pragma unroll
@@ -199,7 +254,19 @@ struct GenRow {
       float part[VEC];
 #pragma unroll
       for (int e = 0; e < VEC; ++e) part[e] = v[k * VEC + e];
-      if (row_ok && valid(k)) StoreN<TO, VEC>::run(base + (size_t)(lane + k * LANES) * VEC, part);
+      if constexpr (TAIL == 0) {
+        if (row_ok && valid(k)) store_elements<TO, VEC, alignment<TO>()>(base + (size_t)(lane + k * LANES) * VEC, part);
+      } else if constexpr (AGAIN) {
+        if (row_ok && valid(k)) store_elements<TO, VEC, alignment<TO>()>(base + first_of(k), part);
+      } else {
+        if (row_ok && own(k, 0)) store_elements<TO, VEC, alignment<TO>()>(base + (size_t)(lane + k * LANES) * VEC, part);
+        if (!inner(k) && row_ok && lane + k * LANES == NVEC - 1u) {
+          TO* const step = base + ((int)COLS - VEC);
+          if constexpr (TAIL >= 4) store_piece<TO, BACK, 4>(step, part);
+          if constexpr ((TAIL & 2) != 0) store_piece<TO, BACK + (TAIL & 4), 2>(step, part);
+          if constexpr ((TAIL & 1) != 0) store_piece<TO, VEC - 1, 1>(step, part);
+        }
+      }
     }
   }
 
@@ -223,11 +290,10 @@ struct GenRow {
     float t[KV];
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-      const bool ok = valid(k);
 #pragma unroll
       for (int e = 0; e < VEC; ++e) {
         const float x = SQUARE ? v[k * VEC + e] * v[k * VEC + e] : v[k * VEC + e];
-        t[k * VEC + e] = FULL_COLS ? x : (ok ? x : (IS_MAX ? -__builtin_huge_valf() : 0.0f));
+        t[k * VEC + e] = own(k, e) ? x : (IS_MAX ? -__builtin_huge_valf() : 0.0f);
       }
     }
 #pragma unroll
@@ -245,28 +311,30 @@ struct GenRow {
   }
 
   // ---- column sums over all rows (lane-group rows only) ----------------------------------------------------
-  // the row's values join the lane's running sums; padding lanes and rows beyond the last add nothing
+  // the row's values join the lane's running sums; padding lanes, repeated elements and rows beyond the last add nothing
   __device__ __forceinline__ void colsum_add(const float (&v)[KV], float (&sum)[KV]) const {
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-      const bool ok = row_ok && valid(k);
 #pragma unroll
-      for (int e = 0; e < VEC; ++e) sum[k * VEC + e] += ok ? v[k * VEC + e] : 0.0f;
+      for (int e = 0; e < VEC; ++e) sum[k * VEC + e] += row_ok && own(k, e) ? v[k * VEC + e] : 0.0f;
     }
   }
   // Lane-group rows: the workgroup's lane groups hold sums of the same columns: first the groups of a wavefront are folded lane to
   // lane (lane ^ L, lane ^ 2L, ...: every lane ends with the wavefront's sum), then the four wavefronts through
   // `lds` (4 * PADDED_COLS floats, used by this sum only), and one row of COLS partial sums goes to `dst`.  Fixed
   // order throughout, so the result is the same from run to run.
-  __device__ __forceinline__ static void colsum_flush(const float (&sum)[KV], float* lds, float* dst) {
+  __device__ __forceinline__ void colsum_flush(const float (&sum)[KV], float* lds, float* dst) const {
     if constexpr (BLOCK) {
       // a workgroup per row: every lane owns its columns alone, the sums over the workgroup's rows are complete
 #pragma unroll
       for (int k = 0; k < K; ++k) {
-        const uint32_t at = (threadIdx.x + k * L) * VEC;
-        if (FULL_COLS || at < COLS) {
+        const int at = first_of(k);
+        if (own(k, 0)) {
 #pragma unroll
           for (int e = 0; e < VEC; ++e) dst[at + e] = sum[k * VEC + e];
+        } else if (TAIL != 0 && own(k, VEC - 1)) {
+#pragma unroll
+          for (int e = BACK; e < VEC; ++e) dst[at + e] = sum[k * VEC + e];
         }
       }
       return;
@@ -279,12 +347,13 @@ struct GenRow {
 #pragma unroll
       for (int j = 0; j < KV; ++j) v[j] += xor_lane(v[j], s);
     }
-    const uint32_t tid = threadIdx.x, wave = tid >> 6, lane = tid & (L - 1u);
+    const uint32_t tid = threadIdx.x, wave = tid >> 6;
     if ((tid & 63u) < L) {
 #pragma unroll
       for (int k = 0; k < K; ++k)
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) lds[wave * PADDED_COLS + (lane + k * L) * VEC + e] = v[k * VEC + e];
+        for (int e = 0; e < VEC; ++e)
+          if (own(k, e)) lds[wave * PADDED_COLS + first_of(k) + e] = v[k * VEC + e];
     }
     __syncthreads();
     for (uint32_t c = tid; c < COLS; c += 256u)

@@ -124,6 +124,7 @@ struct GeluP {
   int32_t waves, unroll;            // workgroup = waves x 64 lanes; a row tile = waves * unroll rows
   int32_t fast;                     // 1: rows fill every workgroup's row tiles and cols fill the column tiles exactly
   uint32_t fold_cols, fold_split;   // K_COLFOLD: columns of the partials, first column that goes to the second output
+  uint32_t fold_out_cols;           // K_COLFOLD: columns of each output (< fold_split where a slice is padded, see colsum_pitch)
   uint32_t fold_quads;              // K_COLFOLD: column quads per workgroup (16 with 16 row groups, or 4 with 64)
 };
 struct TChainP {
@@ -257,6 +258,9 @@ struct RowProgP {
                                        // pass (the later passes do not read them again)
   ProgInstr instr[kProgMaxInstr];
 };
+// Floats between two column sums in a row of partial sums: whole quads, which the fold reads (the padding is never
+// written to an output).
+inline uint32_t colsum_pitch(uint32_t cols) { return (cols + 3u) & ~3u; }
 struct ProgArgs {
   const void* full[kProgMaxOperands];
   const void* col[kProgMaxOperands];
@@ -291,7 +295,7 @@ struct FoldManyP {
   float* out0[kFoldManyMax];
   float* out1[kFoldManyMax];
   uint32_t first_block[kFoldManyMax];   // first workgroup of each job; [0] = 0, unused entries = 0xffffffff
-  uint32_t n[kFoldManyMax], width[kFoldManyMax], stride[kFoldManyMax], split[kFoldManyMax], quads[kFoldManyMax];
+  uint32_t n[kFoldManyMax], width[kFoldManyMax], stride[kFoldManyMax], split[kFoldManyMax], out_cols[kFoldManyMax], quads[kFoldManyMax];
   int32_t out_dt[kFoldManyMax];         // dtype the sums are handed out in
 };
 int launch_fold_many(const FoldManyP& table, uint32_t n_blocks, void* stream);

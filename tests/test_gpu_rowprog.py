@@ -172,6 +172,57 @@ def test_column_sums_beside_row_work(rows, cols, dtype):
         note(f"{spec.name}: {info['kernel']}, {info['n_candidates']} shapes, worst {worst}")
 
 
+@pytest.mark.parametrize("rows,cols,dtype", [(37, 9, "bf16"), (300, 205, "f16"), (70, 1003, "f32"), (33, 2247, "bf16"), (130, 60, "f16"),
+                                             (500, 30, "f32"), (45, 4421, "f32"), (11, 3, "f32"), (3, 6, "bf16"), (64, 1554, "f16")])
+def test_column_sums_of_rows_that_end_inside_a_step(rows, cols, dtype):
+    """Row lengths that are no multiple of a step, with sums over all rows: the last step of a row slides back over
+    elements that the step before it holds, which must count once in every row reduction and column sum, and the sums'
+    last quad is padded in the workspace only.  Every launch shape; one, two and three sums."""
+    if not B.codegen_available():
+        pytest.skip("these row lengths exist as generated kernels only")
+    for make in (gelu_backward_graph, rmsnorm_backward_graph, layernorm_backward_bias_graph):
+        spec = make(rows, cols, dtype)
+        worst, info = _run(spec, repeat=2)
+        assert info["pattern"] == "row_generated" and info["n_kernels"] == 2
+        note(f"{spec.name}: {info['kernel']}, {info['n_candidates']} shapes, worst {worst}")
+
+
+@pytest.mark.parametrize("cols,dtype", [(8 + t, "bf16") for t in range(8)] + [(64 + t, "f16") for t in range(1, 8)] + [(4 + t, "f32") for t in range(4)]
+                         + [(2049, "f32"), (4099, "bf16"), (20001, "f16")])
+def test_every_tail_stays_inside_its_row(cols, dtype):
+    """Every number of elements a row can leave to its last step: results in buffers with guard bands, whose bytes stay
+    as they were, and inputs surrounded by NaN, which no result may pick up."""
+    import torch
+    if not B.codegen_available():
+        pytest.skip("these row lengths exist as generated kernels only")
+    for spec in (layernorm_stats_graph(29, cols, in_dtype=dtype, out_dtype=dtype, with_variance=True), gelu_backward_graph(29, cols, dtype, dtype)):
+        inp = make_inputs(spec, seed=3)
+        ref = O.evaluate(spec, inp)
+        floors = floors_for(spec, inp, ref)
+        plan = B.Plan(B.Graph.from_spec(spec), "auto")
+        guard = 64   # elements on either side (a multiple of 16 bytes for every dtype)
+        held, keep = [], []
+        for t in spec.inputs:
+            x = B.to_device(inp[t.name], t.dtype)
+            buf = torch.full((x.numel() + 2 * guard,), float("nan"), dtype=x.dtype, device="cuda")
+            buf[guard:guard + x.numel()] = x.reshape(-1)
+            held.append(buf)
+        for o in B.alloc_outputs(spec):
+            keep.append(torch.full((o.numel() + 2 * guard,), -7.0, dtype=o.dtype, device="cuda"))
+        ws = plan.make_workspace()
+        if ws is not None:
+            ws.fill_(0xFF)
+        size = [b.element_size() for b in held], [b.element_size() for b in keep]
+        plan.execute_ptrs([b.data_ptr() + guard * z for b, z in zip(held, size[0])], [b.data_ptr() + guard * z for b, z in zip(keep, size[1])],
+                          ws.data_ptr() if ws is not None else 0, ws.numel() if ws is not None else 0, torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        for (name, dt), b in zip(spec.outputs, keep):
+            assert bool((b[:guard] == -7.0).all()) and bool((b[-guard:] == -7.0).all()), (spec.name, plan.info["kernel"], name)
+            got = O.to_f64(B.to_host(b[guard:-guard], dt), dt).reshape(ref[name].shape)
+            err = O.max_rel_err(got, ref[name], floors.get(name, 0.0))
+            assert np.isfinite(got).all() and err <= (1e-5 if dt == "f32" else 1e-2), (spec.name, plan.info["kernel"], name, err)
+
+
 @pytest.mark.parametrize("rows,cols,dtype", [(8, 16384, "bf16"), (5, 32768, "f16"), (3, 20000, "f32"), (4, 24576, "bf16")])
 def test_long_rows_on_workgroups_of_512_and_1024_threads(rows, cols, dtype):
     """Rows beyond 256 threads x 8 vectors: generated kernels put 512 or 1024 threads on a row (reductions through LDS
