@@ -108,7 +108,7 @@ bool build_transpose(const fs_graph& g, std::vector<Candidate>* out, PackForm* p
   u.info.lds_bytes = !tile ? 0 : l.args.u.transpose.vec > 1 ? 256 * 16 * l.args.u.transpose.vec : 32 * 33 * l.args.u.transpose.elem_bytes;
   KernelCost kc;
   kc.hbm_bytes = (double)u.info.bytes_min;
-  kc.elems = (double)l.args.u.transpose.n;
+  kc.elems = (double)g.tensors[g.outputs[0]].numel();
   kc.valu_per_elem = tile ? 12 : 4;
   kc.waves_per_block = 4;
   kc.waves = (double)l.shape.grid[0] * 4;

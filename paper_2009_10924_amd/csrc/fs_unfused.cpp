@@ -34,6 +34,28 @@ struct Arena {
 
 int pick_vec(int64_t inner) { return inner % 8 == 0 ? 8 : inner % 4 == 0 ? 4 : 1; }
 
+// Units along q of the transpose's tile (256 units of vec x vec elements).  What a shape costs is the padded area, times
+// what the ends of its runs waste where they fall inside 128-byte lines -- on the writing side more than on the reading
+// one, and not where one tile spans the whole of a dense row.  Measured (us for 8 / 16 / 32 units): [64,197,768] bf16,
+// rows of 197 written, 8.6 / 12.3 / 17.2; [16,1024,1000] bf16, rows of 1000 read, 16.9 / 12.8 / 12.9; [64,49,2048] bf16,
+// area 5.2 / 2.6 / 1.3 times the tensor, 8.1 / 6.3 / 6.0; extents and rows of whole lines within 3 %.
+uint32_t transpose_units_along_q(const TransposeP& p) {
+  uint32_t best = 16;
+  double best_cost = 0;
+  for (uint32_t units : {16u, 8u, 32u}) {
+    const uint32_t side_q = units * p.vec, side_x = 256 / units * p.vec;
+    const uint32_t tq = (p.nq + side_q - 1) / side_q, tx = (p.nx + side_x - 1) / side_x;
+    const auto waste = [&](uint32_t pitch, uint32_t extent, uint32_t tiles, uint32_t side) {
+      if ((uint64_t)pitch * p.elem_bytes % 128 == 0 || (tiles == 1 && pitch == extent)) return 0.0;
+      return 128.0 / ((double)side * p.elem_bytes);
+    };
+    const double area = (double)tq * side_q / p.nq * ((double)tx * side_x / p.nx);
+    const double cost = area * (1.0 + 0.6 * waste(p.out_row, p.nx, tx, side_x) + 0.15 * waste(p.in_row, p.nq, tq, side_q));
+    if (best_cost == 0 || cost < best_cost) { best = units; best_cost = cost; }
+  }
+  return best;
+}
+
 uint32_t pow2_at_least(uint32_t v) {
   uint32_t p = 1;
   while (p < v) p <<= 1;
@@ -194,59 +216,82 @@ fs_status build_unfused(const fs_graph& g, Candidate* out) {
       }
       moved += a.numel() * dtype_bytes(dt[op.in[0]]) + n_out * dtype_bytes(dst_dt);
     } else if (opc == FS_TRANSPOSE) {
-      const int pad = FS_MAX_RANK - a.rank;
+      // the output's axes with their extents and input strides; extents of 1 dropped, axes that stay neighbours merged
       int64_t in_stride_axis[FS_MAX_RANK];   // contiguous strides of the input, by input axis
       {
         int64_t acc = 1;
         for (int k = a.rank - 1; k >= 0; --k) { in_stride_axis[k] = acc; acc *= a.dims[k]; }
       }
-      const bool keeps_inner = op.perm[a.rank - 1] == a.rank - 1;
+      int64_t ext[FS_MAX_RANK], from[FS_MAX_RANK];
+      int m = 0;
+      for (int k = 0; k < r.rank; ++k) {
+        const int64_t stride = in_stride_axis[op.perm[k]];
+        if (r.dims[k] == 1) continue;
+        if (m > 0 && from[m - 1] == stride * r.dims[k]) {
+          ext[m - 1] *= r.dims[k];
+          from[m - 1] = stride;
+        } else {
+          ext[m] = r.dims[k];
+          from[m++] = stride;
+        }
+      }
+      if (m == 0) { ext[0] = 1; from[0] = 1; m = 1; }
+      const bool keeps_inner = from[m - 1] == 1;
       Launch& l = add_launch(keeps_inner ? K_TRANSPOSE_ROWS : K_TRANSPOSE_TILE);
       TransposeP& p = l.args.u.transpose;
       p = TransposeP{};
       p.elem_bytes = dtype_bytes(a.dtype);
       p.n = (uint32_t)n_out;
-      for (int k = 0; k < FS_MAX_RANK; ++k) { p.out_dims[k] = 1; p.in_stride[k] = 0; p.out_stride[k] = 0; }
-      {
-        int64_t acc = 1;
-        for (int k = r.rank - 1; k >= 0; --k) {
-          p.out_dims[pad + k] = (uint32_t)r.dims[k];
-          p.in_stride[pad + k] = (uint32_t)in_stride_axis[op.perm[k]];
-          p.out_stride[pad + k] = (uint32_t)acc;
-          acc *= r.dims[k];
-        }
-      }
       l.ptr[0] = where[op.in[0]]; l.ptr[1] = dst;
       if (keeps_inner) {
-        const int64_t inner = r.dims[r.rank - 1];
-        const int max_vec = 16 / p.elem_bytes;
-        int vec = max_vec;
+        const int64_t inner = ext[m - 1];
+        int vec = 16 / p.elem_bytes;
         while (vec > 1 && inner % vec != 0) vec >>= 1;
         p.vec = vec;
+        uint32_t lead[3] = {1, 1, 1};
+        for (int k = 0; k < m - 1; ++k) {
+          lead[3 - (m - 1) + k] = (uint32_t)ext[k];
+          p.in_stride[3 - (m - 1) + k] = (uint32_t)from[k];
+        }
+        p.div[0] = make_fastdiv((uint32_t)inner);
+        p.div[1] = make_fastdiv(lead[2]);
+        p.div[2] = make_fastdiv(lead[1]);
         grid1d(l, n_out / vec);
       } else {
-        uint32_t q = 0;
-        for (int k = 0; k < r.rank; ++k) if (op.perm[k] == a.rank - 1) q = (uint32_t)(pad + k);
-        p.tile_in_axis_out_pos = q;
-        // both tile axes multiples of a 128-bit vector: 64x64 tile with vector accesses, else 32x32 scalar
-        const uint32_t v128 = 16 / p.elem_bytes;
-        p.vec = (p.out_dims[q] % v128 == 0 && p.out_dims[3] % v128 == 0) ? (int32_t)v128 : 1;
-        // vectorised tile: 16 x 16 units of vec x vec elements, or 8 x 32 when the moving axis is short
-        // neighbouring workgroups: when the inner axis outside the tile follows the tile's rows directly in the input
-        // ([B,S,H,D] -> [B,H,D,S]: a head's 64 x D tile is followed by the next head's), walking that axis first makes
-        // neighbours read one contiguous span (measured: 3 % on float32, nothing on 16-bit elements)
-        {
-          uint32_t ax1 = 0;
-          for (uint32_t k = 0; k < 3; ++k) if (k != q) ax1 = k;
-          p.order = (p.out_dims[ax1] > 1 && p.in_stride[ax1] == p.out_dims[q]) ? 1u : 0u;
+        int q = 0;   // the output axis that the input's innermost axis has become
+        for (int k = 0; k < m; ++k) if (from[k] == 1) q = k;
+        p.nq = (uint32_t)ext[q];
+        p.nx = (uint32_t)ext[m - 1];
+        p.in_row = (uint32_t)from[m - 1];
+        int64_t to[FS_MAX_RANK], acc = 1;
+        for (int k = m - 1; k >= 0; --k) { to[k] = acc; acc *= ext[k]; }
+        p.out_row = (uint32_t)to[q];
+        uint32_t batch[2] = {1, 1};
+        for (int k = m - 2, slot = 1; k >= 0; --k) {
+          if (k == q) continue;
+          batch[slot] = (uint32_t)ext[k];
+          p.in_batch[slot] = (uint32_t)from[k];
+          p.out_batch[slot] = (uint32_t)to[k];
+          --slot;
         }
-        p.tile_uq = p.vec > 1 ? (p.out_dims[q] > 8u * (uint32_t)p.vec ? 16u : 8u) : 0u;
-        const int64_t tile_q = p.vec > 1 ? (int64_t)p.tile_uq * p.vec : 32, tile_3 = p.vec > 1 ? (int64_t)(256 / p.tile_uq) * p.vec : 32;
-        int64_t blocks = ((int64_t)p.out_dims[q] + tile_q - 1) / tile_q * (((int64_t)p.out_dims[3] + tile_3 - 1) / tile_3);
-        for (uint32_t k = 0; k < 3; ++k) if (k != q) blocks *= p.out_dims[k];
+        const uint32_t v128 = 16 / p.elem_bytes;
+        p.vec = p.nq >= v128 && p.nx >= v128 ? (int32_t)v128 : 1;
+        p.tile_uq = p.vec > 1 ? transpose_units_along_q(p) : 0u;
+        const uint32_t side_q = p.vec > 1 ? p.tile_uq * p.vec : 32, side_x = p.vec > 1 ? 256 / p.tile_uq * p.vec : 32;
+        const uint32_t tq = (p.nq + side_q - 1) / side_q, tx = (p.nx + side_x - 1) / side_x;
+        // Neighbouring workgroups walk along q where that makes them read whole lines of one short contiguous span
+        // ([64,512,12,64] -> [64,12,64,512] float32: 36.1 against 37.4 us); along x otherwise: long or unaligned input
+        // rows lose more than that on the writing side (4096 x 4096 float32 25.2 against 29.3, 4001 x 3333 26.5 / 39.0).
+        p.q_first = (uint64_t)p.in_row * p.elem_bytes % 128 == 0 && (uint64_t)p.nq * p.elem_bytes <= 3072 ? 1 : 0;
+        p.div[0] = make_fastdiv(p.q_first ? tq : tx);
+        p.div[1] = make_fastdiv(p.q_first ? tx : tq);
+        p.div[2] = make_fastdiv(batch[1]);
+        const int64_t blocks = (int64_t)tq * tx * batch[0] * batch[1];
         if (blocks >= (int64_t(1) << 31)) return fail(FS_ERR_SHAPE, "transpose: too many tiles");
         l.shape.grid[0] = (uint32_t)blocks;
       }
+      for (const FastDiv& d : p.div)
+        if (d.d == 0) return fail(FS_ERR_SHAPE, "transpose: no exact division by one of its extents");
       moved += 2 * n_out * p.elem_bytes;
     } else {
       // unary family, convert included

@@ -19,6 +19,9 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 
+// V at addresses aligned to EA bytes only
+template <typename V, int EA> struct AtAlignment { typedef V type __attribute__((aligned(EA))); };
+
 struct bf16_t { uint16_t bits; };   // storage tag types; arithmetic is always float32
 typedef _Float16 f16_t;
 

@@ -38,7 +38,6 @@ __device__ __forceinline__ float xor_lane(float v, uint32_t mask) {
 // memory pipeline takes 64- and 128-bit accesses at any element address: a copy of 64 MB each way through 128-bit
 // accesses that all start 2 bytes off runs at 5.18 TB/s, 4 or 8 bytes off at 5.53, aligned at 5.75, and element by
 // element at 4.97 with eight times the instructions and one register per element.
-template <typename V, int EA> struct AtAlignment { typedef V type __attribute__((aligned(EA))); };
 template <int BYTES, int EA> struct StepBits;
 template <int EA> struct StepBits<32, EA> {
   u32x4 lo, hi;

@@ -83,16 +83,19 @@ struct ReduceP {
 };
 struct TransposeP {
   int32_t elem_bytes, vec;      // vec: elements per 128-bit (or narrower) access along the inner axis
-  uint32_t out_dims[4];         // output extents padded to rank 4 (leading 1s)
-  uint32_t in_stride[4];        // input stride (elements) of the axis that feeds each output axis
   uint32_t n;
-  // K_TRANSPOSE_TILE: the two axes of the tile
-  uint32_t tile_in_axis_out_pos;  // output position of the input's innermost axis
-  uint32_t out_stride[4];
-  uint32_t tile_uq;               // vectorised tile: 16-byte units along the input's innermost axis (16 or 8); the tile is
-                                  // tile_uq * vec elements along it by (256 / tile_uq) * vec along the output's innermost axis
-  uint32_t order;                 // which index neighbouring workgroups differ in: 0 the tile along the output's innermost
-                                  // axis, 1 the inner one of the two axes outside the tile
+  // Axes that stay neighbours are merged first, extents of 1 dropped.
+  // K_TRANSPOSE_ROWS: output index -> (c0, c1, c2, innermost index), each times its stride in the input
+  uint32_t in_stride[3];        // elements, of the input axis that feeds output axis 0, 1, 2
+  FastDiv div[3];               // rows: innermost extent, output extents 2 and 1
+                                // tile: tiles along the axis that neighbouring workgroups walk, along the other one, batch extent 1
+  // K_TRANSPOSE_TILE: out[b0, b1, .., q, ..] with q the input's innermost axis and x the output's
+  uint32_t nq, nx;              // extents of the tile's two axes
+  uint32_t in_row, out_row;     // input stride of x, output stride of q (elements)
+  uint32_t in_batch[2], out_batch[2];   // strides of the two axes outside the tile (0 where there is none)
+  uint32_t tile_uq;             // vectorised tile: 16-byte units along q (8, 16 or 32); the tile is tile_uq * vec elements
+                                // along q by (256 / tile_uq) * vec along x
+  uint32_t q_first;             // neighbouring workgroups walk 1: along q (they read one contiguous span), 0: along x
 };
 
 // ---- stitched -----------------------------------------------------------------

@@ -204,129 +204,117 @@ __global__ void __launch_bounds__(256) k_transpose_rows(const void* in, void* ou
   const uint32_t vi = blockIdx.x * 256u + threadIdx.x;   // vector index in the output
   const uint32_t e = vi * p.vec;
   if (e >= p.n) return;
+  // Plain divisions, measured: multiply-high ones are slower here ([64,512,12,64] -> [64,12,512,64] float32 34.6 against
+  // 35.5 us, the wavefronts then reach their loads closer together), four vectors per thread slower still (36.1).
   uint32_t rest = e;
-  const uint32_t c3 = rest % p.out_dims[3]; rest /= p.out_dims[3];
-  const uint32_t c2 = rest % p.out_dims[2]; rest /= p.out_dims[2];
-  const uint32_t c1 = rest % p.out_dims[1];
-  const uint32_t c0 = rest / p.out_dims[1];
+  const uint32_t c3 = rest % p.div[0].d; rest /= p.div[0].d;
+  const uint32_t c2 = rest % p.div[1].d; rest /= p.div[1].d;
+  const uint32_t c1 = rest % p.div[2].d, c0 = rest / p.div[2].d;
   const uint32_t src = c0 * p.in_stride[0] + c1 * p.in_stride[1] + c2 * p.in_stride[2] + c3;
   reinterpret_cast<VT*>(out)[vi] = reinterpret_cast<const VT*>(in)[src / p.vec];
 }
 
+// The tile that a workgroup moves, and where its batch entry starts in the input and in the output.
+struct TileAt {
+  uint32_t bq, bx;
+  size_t in_base, out_base;
+  __device__ __forceinline__ explicit TileAt(const TransposeP& p) {
+    uint32_t rest = blockIdx.x;
+    uint32_t r = fast_div(rest, p.div[0]);
+    const uint32_t inner = rest - r * p.div[0].d;
+    rest = r;
+    r = fast_div(rest, p.div[1]);
+    const uint32_t outer = rest - r * p.div[1].d;
+    const uint32_t b0 = fast_div(r, p.div[2]), b1 = r - b0 * p.div[2].d;
+    bq = p.q_first ? inner : outer;
+    bx = p.q_first ? outer : inner;
+    in_base = (size_t)b0 * p.in_batch[0] + (size_t)b1 * p.in_batch[1];
+    out_base = (size_t)b0 * p.out_batch[0] + (size_t)b1 * p.out_batch[1];
+  }
+};
+
 // ---- transpose, innermost axis moves: 32x32 tile through padded LDS ---------------
-// Tile rows run along the output position q that receives the input's innermost
-// axis; tile columns run along the output's innermost axis.  Reads are contiguous
-// along the input's innermost axis, writes along the output's; the 33-word pitch
-// keeps both LDS phases free of bank conflicts.
+// For tile axes shorter than a 128-bit access.  Reads are contiguous along the input's innermost axis, writes along the
+// output's; the 33-word pitch keeps both LDS phases free of bank conflicts.
 template <typename T>
 __global__ void __launch_bounds__(256) k_transpose_tile(const T* __restrict__ in, T* __restrict__ out, TransposeP p) {
   __shared__ T tile[32][33];
-  const uint32_t q = p.tile_in_axis_out_pos;
-  const uint32_t nq = p.out_dims[q], n3 = p.out_dims[3];
-  const uint32_t tq = (nq + 31u) / 32u, t3 = (n3 + 31u) / 32u;
-  uint32_t bid = blockIdx.x;
-  const uint32_t b3 = bid % t3; bid /= t3;
-  const uint32_t bq = bid % tq; bid /= tq;
-  // the two remaining output axes form the batch index
-  uint32_t ax[2], na = 0;
-  for (uint32_t k = 0; k < 3; ++k) if (k != q) ax[na++] = k;
-  const uint32_t cb1 = bid % p.out_dims[ax[1]];
-  const uint32_t cb0 = bid / p.out_dims[ax[1]];
-  const uint32_t in_base = cb0 * p.in_stride[ax[0]] + cb1 * p.in_stride[ax[1]];
-  const uint32_t out_base = cb0 * p.out_stride[ax[0]] + cb1 * p.out_stride[ax[1]];
+  const TileAt t(p);
   const uint32_t tx = threadIdx.x & 31u, ty = threadIdx.x >> 5;
-  // read: tx along input-innermost (output axis q), ty along output-innermost
   for (uint32_t j = ty; j < 32u; j += 8u) {
-    const uint32_t cq = bq * 32u + tx, c3 = b3 * 32u + j;
-    if (cq < nq && c3 < n3) tile[j][tx] = in[in_base + cq + c3 * p.in_stride[3]];
+    const uint32_t cq = t.bq * 32u + tx, cx = t.bx * 32u + j;
+    if (cq < p.nq && cx < p.nx) tile[j][tx] = in[t.in_base + cq + (size_t)cx * p.in_row];
   }
   __syncthreads();
-  // write: tx along output-innermost, ty along output axis q
   for (uint32_t i = ty; i < 32u; i += 8u) {
-    const uint32_t cq = bq * 32u + i, c3 = b3 * 32u + tx;
-    if (cq < nq && c3 < n3) out[out_base + cq * p.out_stride[q] + c3] = tile[tx][i];
+    const uint32_t cq = t.bq * 32u + i, cx = t.bx * 32u + tx;
+    if (cq < p.nq && cx < p.nx) out[t.out_base + (size_t)cq * p.out_row + cx] = tile[tx][i];
   }
 }
 
 // ---- transpose, innermost axis moves: 128-bit accesses on both HBM sides AND both LDS sides ----------------
-// The tile is UQ x U3 units of VEC x VEC elements (UQ * U3 = 256 threads, one unit each; VEC = elements in 16
-// bytes), TQ = UQ * VEC along the input's innermost axis (output axis q) by T3 = U3 * VEC along the output's.
+// The tile is UQ x UX units of VEC x VEC elements (UQ * UX = 256 threads, one unit each; VEC = elements in 16
+// bytes), TQ = UQ * VEC along the input's innermost axis q by TX = UX * VEC along the output's innermost axis x.
 // A thread loads its unit as VEC rows of 16 bytes (a wave reads runs of UQ * 16 bytes), transposes it in
 // registers (32-bit elements: a renaming; 16-bit elements: one byte-permute per pair), and parks it in LDS as VEC
-// 16-byte pieces, one per tile column, each holding VEC consecutive elements of the OUTPUT's innermost axis.
-// After the barrier a thread reads one 16-byte piece per pass and stores it: a wave writes runs of U3 * 16 bytes
-// (or several full columns).  LDS is [TQ columns][U3 pieces] of 16 bytes, unpadded; piece u of column c sits at
+// 16-byte pieces, one per tile column, each holding VEC consecutive elements of x.
+// After the barrier a thread reads one 16-byte piece per pass and stores it: a wave writes runs of UX * 16 bytes
+// (or several full columns).  LDS is [TQ columns][UX pieces] of 16 bytes, unpadded; piece u of column c sits at
 // position u ^ (c / VEC mod 8): any eight neighbouring lanes -- the lanes one LDS cycle serves for a 128-bit
 // access -- then hit eight different 16-byte bank groups, writing (same row unit, eight column units) and
 // reading (same column, eight neighbouring pieces) alike, where a padded tile with scalar accesses ran at two
 // lanes per bank (measured: conflict cycles half of the LDS-active cycles).
-// Needs both tile axes to be multiples of VEC; other shapes use the 32x32 scalar kernel.
+// Extents that are no multiple of VEC: the last unit along an axis slides back to end where the axis ends, so it moves
+// some elements that the unit before it moves as well (the same bits to the same place), and rows start at any element;
+// the memory pipeline takes 128-bit accesses at any element address.  [64,197,768] -> [64,768,197] bfloat16 (39 MB, cold)
+// 8.5 us, 25.7 as 32x32 tiles of single elements; 4001 x 3333 float32 (107 MB) 26.3 against 41.1; extents of whole units
+// as before (4096 x 4096 bfloat16 13.8 us).
 template <typename T, int UQ>
-__global__ void __launch_bounds__(256) k_transpose_tile64(const T* __restrict__ in, T* __restrict__ out, TransposeP p) {
-  constexpr uint32_t VEC = 16 / sizeof(T), U3 = 256 / UQ, TQ = UQ * VEC, T3 = U3 * VEC;
-  __shared__ u32x4 tile[TQ * U3];
-  const uint32_t q = p.tile_in_axis_out_pos;
-  const uint32_t nq = p.out_dims[q], n3 = p.out_dims[3];
-  const uint32_t tq = (nq + TQ - 1) / TQ, t3 = (n3 + T3 - 1) / T3;
-  uint32_t bid = blockIdx.x;
-  uint32_t ax[2], na = 0;
-  for (uint32_t k = 0; k < 3; ++k) if (k != q) ax[na++] = k;
-  uint32_t b3, bq, cb1, cb0;
-  if (p.order == 0) {
-    b3 = bid % t3; bid /= t3;
-    bq = bid % tq; bid /= tq;
-    cb1 = bid % p.out_dims[ax[1]];
-    cb0 = bid / p.out_dims[ax[1]];
-  } else {
-    cb1 = bid % p.out_dims[ax[1]]; bid /= p.out_dims[ax[1]];
-    b3 = bid % t3; bid /= t3;
-    bq = bid % tq;
-    cb0 = bid / tq;
-  }
-  const uint32_t in_base = cb0 * p.in_stride[ax[0]] + cb1 * p.in_stride[ax[1]];
-  const uint32_t out_base = cb0 * p.out_stride[ax[0]] + cb1 * p.out_stride[ax[1]];
-  // load: unit (uq, u3) = columns uq*VEC.. of rows u3*VEC..; padding units are clamped to valid addresses (what
-  // they park in LDS is never stored)
-  const uint32_t uq = threadIdx.x % UQ, u3 = threadIdx.x / UQ;
-  const uint32_t cq0 = min(bq * TQ + uq * VEC, nq - VEC), c30 = min(b3 * T3 + u3 * VEC, n3 - VEC);
-  u32x4 row[VEC];
+__global__ void __launch_bounds__(256) k_transpose_units(const T* __restrict__ in, T* __restrict__ out, TransposeP p) {
+  constexpr uint32_t VEC = 16 / sizeof(T), UX = 256 / UQ, TQ = UQ * VEC, TX = UX * VEC;
+  typedef typename AtAlignment<u32x4, (int)sizeof(T)>::type Unaligned;
+  __shared__ u32x4 tile[TQ * UX];
+  const TileAt t(p);
+  const uint32_t uq = threadIdx.x % UQ, ux = threadIdx.x / UQ;
+  if (t.bq * TQ + uq * VEC < p.nq && t.bx * TX + ux * VEC < p.nx) {
+    const uint32_t cq = min(t.bq * TQ + uq * VEC, p.nq - VEC), cx = min(t.bx * TX + ux * VEC, p.nx - VEC);
+    u32x4 row[VEC];
 #pragma unroll
-  for (uint32_t s = 0; s < VEC; ++s)
-    row[s] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(in + in_base + cq0 + (size_t)(c30 + s) * p.in_stride[3]));
-  // transpose in registers: col[e] = elements e of rows 0..VEC-1
-  u32x4 col[VEC];
-  if constexpr (sizeof(T) == 4) {
+    for (uint32_t s = 0; s < VEC; ++s)
+      row[s] = __builtin_nontemporal_load(reinterpret_cast<const Unaligned*>(in + t.in_base + cq + (size_t)(cx + s) * p.in_row));
+    // transpose in registers: col[e] = elements e of rows 0..VEC-1
+    u32x4 col[VEC];
+    if constexpr (sizeof(T) == 4) {
 #pragma unroll
-    for (uint32_t e = 0; e < 4; ++e) col[e] = u32x4{row[0][e], row[1][e], row[2][e], row[3][e]};
-  } else {
-    // 2x2 blocks of 16-bit elements first: for rows (2m, 2m+1) and dword k, lo = [r0.lo16, r1.lo16] is column 2k,
-    // hi = [r0.hi16, r1.hi16] column 2k+1, each holding rows 2m, 2m+1; the rest is a renaming
+      for (uint32_t e = 0; e < 4; ++e) col[e] = u32x4{row[0][e], row[1][e], row[2][e], row[3][e]};
+    } else {
+      // 2x2 blocks of 16-bit elements first: for rows (2m, 2m+1) and dword k, lo = [r0.lo16, r1.lo16] is column 2k,
+      // hi = [r0.hi16, r1.hi16] column 2k+1, each holding rows 2m, 2m+1; the rest is a renaming
 #pragma unroll
-    for (uint32_t k = 0; k < 4; ++k) {
-      uint32_t lo[4], hi[4];
+      for (uint32_t k = 0; k < 4; ++k) {
+        uint32_t lo[4], hi[4];
 #pragma unroll
-      for (uint32_t m = 0; m < 4; ++m) {
-        lo[m] = __builtin_amdgcn_perm(row[2 * m + 1][k], row[2 * m][k], 0x05040100u);   // [r0.lo, r1.lo]
-        hi[m] = __builtin_amdgcn_perm(row[2 * m + 1][k], row[2 * m][k], 0x07060302u);   // [r0.hi, r1.hi]
+        for (uint32_t m = 0; m < 4; ++m) {
+          lo[m] = __builtin_amdgcn_perm(row[2 * m + 1][k], row[2 * m][k], 0x05040100u);   // [r0.lo, r1.lo]
+          hi[m] = __builtin_amdgcn_perm(row[2 * m + 1][k], row[2 * m][k], 0x07060302u);   // [r0.hi, r1.hi]
+        }
+        col[2 * k] = u32x4{lo[0], lo[1], lo[2], lo[3]};
+        col[2 * k + 1] = u32x4{hi[0], hi[1], hi[2], hi[3]};
       }
-      col[2 * k] = u32x4{lo[0], lo[1], lo[2], lo[3]};
-      col[2 * k + 1] = u32x4{hi[0], hi[1], hi[2], hi[3]};
     }
-  }
 #pragma unroll
-  for (uint32_t e = 0; e < VEC; ++e) {
-    const uint32_t c = uq * VEC + e;
-    tile[c * U3 + (u3 ^ (uq & 7u))] = col[e];
+    for (uint32_t e = 0; e < VEC; ++e) tile[(uq * VEC + e) * UX + (ux ^ (uq & 7u))] = col[e];
   }
   __syncthreads();
-  // store: piece u of column c -> 16 bytes of output row (bq*TQ + c) at column b3*T3 + u*VEC
-  const uint32_t u = threadIdx.x % U3, c_first = threadIdx.x / U3;
+  // store: piece u of column c -> 16 bytes of the column's output row
+  const uint32_t u = threadIdx.x % UX, c_first = threadIdx.x / UX;
+  const uint32_t x0 = t.bx * TX + u * VEC, cx = min(x0, p.nx - VEC);
 #pragma unroll
   for (uint32_t s = 0; s < TQ / UQ; ++s) {
-    const uint32_t c = c_first + s * UQ;
-    const u32x4 v = tile[c * U3 + (u ^ ((c / VEC) & 7u))];
-    const uint32_t cq = bq * TQ + c, c3 = b3 * T3 + u * VEC;
-    if (cq < nq && c3 < n3) __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(out + out_base + (size_t)cq * p.out_stride[q] + c3));
+    const uint32_t c = c_first + s * UQ, unit = c / VEC, q0 = t.bq * TQ + unit * VEC;
+    const u32x4 v = tile[c * UX + (u ^ (unit & 7u))];
+    if (q0 < p.nq && x0 < p.nx)
+      __builtin_nontemporal_store(v, reinterpret_cast<Unaligned*>(out + t.out_base + (size_t)(min(q0, p.nq - VEC) + c % VEC) * p.out_row + cx));
   }
 }
 
@@ -364,9 +352,12 @@ const void* unfused_kernel_symbol(int32_t kernel, const KernelArgs& a) {
     }
     case K_TRANSPOSE_TILE:
       if (a.u.transpose.vec > 1) {
-        if (a.u.transpose.tile_uq == 8)
-          return a.u.transpose.elem_bytes == 4 ? (const void*)k_transpose_tile64<uint32_t, 8> : (const void*)k_transpose_tile64<uint16_t, 8>;
-        return a.u.transpose.elem_bytes == 4 ? (const void*)k_transpose_tile64<uint32_t, 16> : (const void*)k_transpose_tile64<uint16_t, 16>;
+        const bool wide = a.u.transpose.elem_bytes == 4;
+        switch (a.u.transpose.tile_uq) {
+          case 8: return wide ? (const void*)k_transpose_units<uint32_t, 8> : (const void*)k_transpose_units<uint16_t, 8>;
+          case 32: return wide ? (const void*)k_transpose_units<uint32_t, 32> : (const void*)k_transpose_units<uint16_t, 32>;
+          default: return wide ? (const void*)k_transpose_units<uint32_t, 16> : (const void*)k_transpose_units<uint16_t, 16>;
+        }
       }
       return a.u.transpose.elem_bytes == 4 ? (const void*)k_transpose_tile<uint32_t> : (const void*)k_transpose_tile<uint16_t>;
     case K_COPY:

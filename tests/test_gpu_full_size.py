@@ -131,3 +131,27 @@ def test_full_size_forced_lds_scheme(cfg):
     got, _, info, _ = run_spec(spec, inp, "lds", repeat=2)
     assert info["scheme"] == "lds" and info["lds_bytes"] > 0, info
     _compare(cfg, spec, got, ref, info, "lds", RMS_FLOOR[cfg])
+
+
+@pytest.mark.parametrize("dims,perm", [((3, 197, 768), (0, 2, 1)), ((2, 463, 16, 32), (0, 3, 1, 2)), ((5, 49, 1025), (0, 2, 1)), ((1001, 333), (1, 0)), ((9, 8), (1, 0)),
+                                       ((8, 9), (1, 0)), ((4, 5), (1, 0)), ((15, 257), (1, 0)), ((2, 33, 31), (0, 2, 1)), ((3, 70, 12, 80), (0, 2, 3, 1)),
+                                       ((2, 40, 3, 50), (2, 3, 0, 1)), ((6, 7, 1, 90), (3, 2, 0, 1)), ((2, 30, 20, 3), (0, 3, 1, 2)), ((130, 1, 70), (2, 1, 0)),
+                                       ((5, 1, 6, 7), (1, 0, 3, 2)), ((4, 6, 10), (1, 2, 0)), ((3, 9, 130, 17), (3, 1, 2, 0)), ((2, 9, 8, 130), (0, 2, 1, 3)), ((1, 64), (1, 0))])
+@pytest.mark.parametrize("dtype", ["f32", "f16", "i32"])
+def test_transposes_of_any_extent_move_every_bit(dims, perm, dtype):
+    """Tile edges of the transposes that move the innermost axis: extents around and between whole 16-byte units, units
+    that slide back at both ends, axes that merge, axes of extent 1 and tiles too narrow for a unit; bytes before and
+    after the output stay as they were."""
+    import torch
+    from paper_2009_10924_amd import binding as B
+    from workloads import transpose_graph
+    torch.manual_seed(1)
+    wide = dtype in ("f32", "i32")
+    x = torch.randint(-2 ** 31, 2 ** 31 - 1, dims, dtype=torch.int32, device="cuda") if wide else torch.randint(-2 ** 15, 2 ** 15 - 1, dims, dtype=torch.int16, device="cuda")
+    want = x.permute(perm).contiguous()
+    buf = torch.full((want.numel() + 128,), 77, dtype=x.dtype, device="cuda")
+    plan = B.Plan(B.Graph.from_spec(transpose_graph(dims, perm, dtype)), "auto")
+    plan.execute_ptrs([x.data_ptr()], [buf.data_ptr() + 64 * buf.element_size()], 0, 0, torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert torch.equal(buf[64:-64].reshape(want.shape), want), plan.info["kernel"]
+    assert bool((buf[:64] == 77).all()) and bool((buf[-64:] == 77).all())
