@@ -381,9 +381,11 @@ std::string body_with_entry(const RowProgP& p, const char* entry, bool member) {
     s += "  const uint32_t fs_block = blockIdx.x;\n";
   }
   const uint32_t R = p.rows_per_group > 1 ? (uint32_t)p.rows_per_group : 1u;
-  const uint32_t CT = p.col_tiles > 1 ? (uint32_t)p.col_tiles : 1u;   // column tiles of cols / CT elements
-  s += fmt("  typedef GenRow<%uu, %uu, %d, %d, %uu, %s, %uu, %uu> Row;\n", p.rows, p.cols / CT, p.vec, p.vecs_per_lane,
-           (uint32_t)p.lanes_per_row, block ? "true" : "false", R, p.cols);
+  const uint32_t CT = p.col_tiles > 1 ? (uint32_t)p.col_tiles : 1u;   // column tiles
+  // (column tiles: whole steps of every lane; the last tile may be shorter)
+  const uint32_t tile_cols = CT > 1 ? (uint32_t)(p.lanes_per_row * p.vecs_per_lane * p.vec) : p.cols;
+  s += fmt("  typedef GenRow<%uu, %uu, %d, %d, %uu, %s, %uu, %uu%s> Row;\n", p.rows, tile_cols, p.vec, p.vecs_per_lane,
+           (uint32_t)p.lanes_per_row, block ? "true" : "false", R, p.cols, CT > 1 ? fmt(", %uu", CT).c_str() : "");
   s += "  constexpr int KV = Row::KV;\n";
   const int n_waves = block ? p.lanes_per_row / 64 : 4;
   const bool looped = p.n_colsum > 0;
@@ -438,7 +440,7 @@ std::string body_with_entry(const RowProgP& p, const char* entry, bool member) {
     // loads last and whose back edge comes from a round that issued its store last, the compiler has to wait for
     // everything, the store included, in every round.  With the first round peeled both ways into the loop look
     // alike and the wait leaves the stores in flight; the last round has no row to load ahead.
-    if (!block) s += fmt("  __shared__ float colred[%d][4 * Row::PADDED_COLS];\n", p.n_colsum);
+    if (!block) s += fmt("  __shared__ __attribute__((aligned(16))) float colred[%d][4 * Row::PADDED_COLS];\n", p.n_colsum);
     for (int i = 0; i < p.n_colsum; ++i)
       s += fmt("  float cs%d[KV];\n#pragma unroll\n  for (int j = 0; j < KV; ++j) cs%d[j] = 0.0f;\n", i, i);
     // neighbouring workgroups take neighbouring column tiles of the same rows
@@ -494,10 +496,14 @@ std::string body_with_entry(const RowProgP& p, const char* entry, bool member) {
     if (R > 1u) s += "  round(0u, Yes{});\n";
     if (R > 2u) s += fmt("#pragma unroll 1\n  for (uint32_t it = 1u; it < %uu; ++it) round(it, Yes{});\n", R - 1u);
     s += fmt("  round(%uu, No{});\n", R - 1u);
+    if (!block && p.n_colsum > 0) {
+      for (int i = 0; i < p.n_colsum; ++i) s += fmt("  nrow.colsum_park(cs%d, colred[%d]);\n", i, i);
+      s += "  __syncthreads();\n";
+    }
     for (int i = 0; i < p.n_colsum; ++i)
       s += fmt("  nrow.colsum_flush(cs%d, %s, static_cast<float*>(a.ws) + (size_t)row_wg * %uu + %uu + tile * %uu);\n", i,
                block ? "nullptr" : fmt("colred[%d]", i).c_str(), (uint32_t)p.n_colsum * colsum_pitch(p.cols), (uint32_t)i * colsum_pitch(p.cols),
-               p.cols / CT);
+               tile_cols);
   }
   s += "}\n";
   return s;

@@ -55,12 +55,12 @@ CostResult evaluate(const KernelCost& k, int32_t vgprs_compiled) {
   const double in_flight = resident * 64.0 * k.bytes_in_flight_per_lane * util;
   double bw = std::min(d.hbm_peak_Bps * d.stream_fraction, in_flight / d.queue_latency_s);
   if (k.access_run_bytes > 0 && k.access_run_bytes < 128) bw /= 1.0 + (128.0 / k.access_run_bytes - 1.0);
-  if (k.access_run_bytes > 0 && k.row_bytes > 0 && std::fmod(k.row_bytes, 128.0) != 0.0) bw /= 1.0 + 1.65 * std::min(4.0, 128.0 / k.access_run_bytes);
+  if (k.access_run_bytes > 0 && k.row_bytes > 0 && std::fmod(k.row_bytes, 128.0) != 0.0 && k.rows_per_wave_loop <= 1) bw /= 1.0 + 1.65 * std::min(4.0, 128.0 / k.access_run_bytes);
   if (k.store_run_bytes > 0 && k.store_run_bytes < 512) bw *= 0.97;
   bw /= 1.0 + 0.12 * (1.0 / util - 1.0);
   bw /= 1.0 + 0.25 * (rounds / rounds_exact - 1.0);
   if (occ < 4) bw /= 1.0 + 0.04 * (4.0 - occ);   // few waves per SIMD: a wave's own stalls are not covered
-  const double t_hbm = k.hbm_bytes / bw;
+  const double t_hbm = (k.hbm_bytes + d.partial_weight * k.partial_bytes) / bw;
   const double t_cache = k.cache_bytes / d.l2_Bps;
   const double t_lds = k.lds_traffic_bytes / d.lds_Bps;
   const double t_alu = k.elems / util / 64.0 * (k.valu_per_elem * d.cycles_valu + k.trans_per_elem * d.cycles_trans) /
@@ -75,8 +75,15 @@ CostResult evaluate(const KernelCost& k, int32_t vgprs_compiled) {
   // (re-reads that the caches serve share the memory pipeline with the stream but mostly fill its gaps: a quarter
   // of their own time shows, measured on the patterns with per-column operands)
   const double t_stream = std::max(t_hbm + 0.25 * t_cache + t_lds, t_alu);
-  const double t_body = std::max(t_latency, t_stream) + 0.10 * std::min(t_latency, t_stream);
-  r.seconds = d.kernel_fixed_s + t_body + t_ramp + k.serial_tail_s;
+  double t_body = std::max(t_latency, t_stream) + 0.10 * std::min(t_latency, t_stream);
+  double t_sums = 0;
+  if (k.partial_bytes > 0) {
+    const double cus = std::min<double>(d.n_cu, std::max(1.0, k.waves / wpb));
+    t_body = std::max(t_body, (k.hbm_bytes + k.partial_bytes) / cus / d.cu_Bps);
+    t_sums = rounds * k.flush_values * (k.flush_steps < 0 ? d.flush_block_s : d.flush_value_s + k.flush_steps * d.flush_step_s) + d.fold_s +
+             d.fold_batch_s * std::ceil(k.fold_rows / 512.0);
+  }
+  r.seconds = d.kernel_fixed_s + t_body + t_ramp + t_sums + k.serial_tail_s;
   return r;
 }
 

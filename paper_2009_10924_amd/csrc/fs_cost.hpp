@@ -31,6 +31,12 @@ struct DeviceModel {
   double l2_Bps = 20.0e12;           // aggregate cache bandwidth for re-read operands
   double last_level_cache_bytes = 256.0 * 1024 * 1024;   // memory-side cache in front of HBM
   double last_level_reread = 0.45;   // time of a re-read that the memory-side cache still holds, relative to HBM (measured)
+  // column sums, fitted to every candidate of 170 patterns (bias + GELU, LayerNorm, RMS norm backward) like the rest: the
+  // candidate ranked first is 3.7 % behind the fastest one on average, 7.3 % without these terms
+  double cu_Bps = 3.3e10;            // what one compute unit streams at most (a loop over rows on few workgroups)
+  double partial_weight = 2.4;       // a byte of partial sums, relative to a streamed one (a burst at the end, then a re-read)
+  double flush_step_s = 9e-9, flush_value_s = 14e-9, flush_block_s = 30e-9;   // per value: each lane fold, LDS + store; store alone
+  double fold_s = 3.0e-6, fold_batch_s = 0.1e-6;   // the fold launch, and per 512 rows of partial sums
   double lds_Bps = 60.0e12;          // aggregate LDS bandwidth
   double barrier_s = 0.55e-6;        // one workgroup barrier incl. the LDS round trip and the wait for the slowest wave
   double cycles_valu = 4.0;          // issue cycles of one wave-wide VALU op on a 16-lane SIMD
@@ -62,6 +68,10 @@ struct KernelCost {
   double store_run_bytes = 0;           // contiguous run written by one store instruction group (0 = long)
   double preamble_instr = 40;           // VALU instructions a wave runs before it can issue its first load
   double serial_tail_s = 0;             // work done by a single workgroup after the rest finished
+  double partial_bytes = 0;             // column sums: partial sums written by the workgroups and read by the fold launch
+  double flush_values = 0;              // column sums: values of every lane that leave it at the end of its rows
+  double fold_rows = 0;                 // column sums: rows of partial sums
+  double flush_steps = -1;              // ... lane-to-lane folds before that (-1: a workgroup per row, no fold)
 };
 
 struct CostResult {

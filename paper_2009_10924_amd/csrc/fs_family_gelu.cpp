@@ -141,7 +141,11 @@ bool build_gelu(const fs_graph& g, std::vector<Candidate>* out, PackForm* pack) 
         c.info.lds_bytes = sh.waves * (int32_t)tile_cols * 4 + 4;
         c.info.bytes_moved_model = c.info.bytes_min + 2ll * n_rb * p.cols * 4;
         KernelCost kc;
-        kc.hbm_bytes = 3 * n * esz + 2.0 * n_rb * p.cols * 4;
+        kc.hbm_bytes = 3 * n * esz;
+        kc.partial_bytes = 2.0 * n_rb * p.cols * 4;
+        kc.fold_rows = n_rb;
+        kc.flush_values = VEC;
+        kc.flush_steps = 0;
         kc.elems = n;
         kc.valu_per_elem = 13 + (esz == 2 ? 1 : 0);
         kc.trans_per_elem = 2;
@@ -154,9 +158,7 @@ bool build_gelu(const fs_graph& g, std::vector<Candidate>* out, PackForm* pack) 
         kc.rows_per_wave_loop = std::max(1.0, (double)p.rows / ((double)n_rb * tile_rows));
         kc.access_run_bytes = 1024.0;   // 64 lanes of one row
         kc.row_bytes = (double)p.cols * esz;
-        kc.dep_phases = 0;   // software pipelined: only the first tile's load latency is exposed (added below)
-        // the fold: a second launch spread over the chip
-        kc.serial_tail_s = device().mem_latency_s + 0.5 * device().launch_s + device().mem_latency_s * std::ceil(n_rb / 16.0 / 8.0) * 0.5;
+        kc.dep_phases = 0;   // software pipelined: only the first tile's load latency is exposed
         char var[48];
         snprintf(var, sizeof var, "<%s,W%d,U%d,RB%u,fold>", dtype_name(p.dt), sh.waves, sh.unroll, n_rb);
         finish_candidate(&c, var, kc);

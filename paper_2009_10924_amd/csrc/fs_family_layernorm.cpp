@@ -313,7 +313,12 @@ bool build_layernorm_backward(const fs_graph& g, std::vector<Candidate>* out, Pa
         c.info.lds_bytes = (int32_t)lds_bytes;
         c.info.bytes_moved_model = c.info.bytes_min + 2 * c.info.workspace_bytes;
         KernelCost kc;
-        kc.hbm_bytes = 3 * n * esz + 2.0 * (double)c.info.workspace_bytes;
+        kc.hbm_bytes = 3 * n * esz;
+        kc.partial_bytes = 2.0 * (double)c.info.workspace_bytes;
+        kc.fold_rows = n_rb;
+        kc.flush_values = 2.0 * K * VEC;
+        kc.flush_steps = 0;
+        for (uint32_t l = L; l < 64; l <<= 1) ++kc.flush_steps;
         kc.elems = n;
         kc.valu_per_elem = 12 + (esz == 2 ? 3 : 0);
         kc.waves_per_block = sh.waves;
@@ -330,7 +335,6 @@ bool build_layernorm_backward(const fs_graph& g, std::vector<Candidate>* out, Pa
         kc.lane_utilisation = (double)nvec / ((double)L * K);
         kc.access_run_bytes = L * 16.0;
         kc.row_bytes = (double)p.cols * esz;
-        kc.serial_tail_s = device().mem_latency_s + 0.5 * device().launch_s + device().mem_latency_s * std::ceil(n_rb / 16.0 / 8.0) * 0.5;
         char var[56];
         snprintf(var, sizeof var, "<%s,K%d,L%u,W%d,R%d,RB%u>", dtype_name(p.dt), K, L, sh.waves, sh.r, n_rb);
         finish_candidate(&c, var, kc);

@@ -733,7 +733,9 @@ std::vector<int> step_widths(const RowProgP& base) {
 
 // Column sums: a workgroup's lane groups work through R rows each and leave one row of partial sums, so R trades
 // extra traffic (2 x workgroups x columns x 4 bytes) against workgroups to fill the chip with.  Every generated
-// shape is offered with R = 1, 2, 4, ... while at least one workgroup per compute unit remains.
+// shape is offered with R = 1, 2, 4, ... while at least 64 workgroups remain: wide rows are better off with a part of
+// the compute units than with partial sums as large as the tensor (LayerNorm backward over 409 x 6976 float16, us for
+// 409 / 205 / 103 workgroups: 20.7 / 16.6 / 14.6).
 std::vector<Shape> with_rows_per_group(const std::vector<Shape>& shapes, uint32_t rows) {
   std::vector<Shape> out;
   for (const Shape& sh : shapes) {
@@ -743,7 +745,7 @@ std::vector<Shape> with_rows_per_group(const std::vector<Shape>& shapes, uint32_
     std::vector<uint32_t> offered;
     bool some_moderate = false;
     for (uint32_t R : {1u, 2u, 4u, 8u, 16u, 32u, 64u}) {
-      if (R > 1 && workgroups(R) < 256) break;
+      if (R > 1 && workgroups(R) < 64) break;
       offered.push_back(R);
       some_moderate = some_moderate || workgroups(R) <= 8192;
     }
@@ -814,10 +816,10 @@ std::vector<Shape> enumerate_shapes(const Compiler& c, int vec, bool interpretab
   // vectors, so a lane keeps one or two vectors per value whatever the row length.
   if (c.n_reductions == 0 && c.n_rout == 0)
     for (int K : {1, 2}) {
-      const uint32_t tile_vecs = 64u * K;
-      if (c.p.cols % vec == 0 && nvec % tile_vecs == 0 && nvec / tile_vecs > 1 && nvec / tile_vecs <= 4096) {
+      const uint32_t tile_vecs = 64u * K, tiles = (nvec + tile_vecs - 1) / tile_vecs;
+      if (tiles > 1 && tiles <= 4096) {   // the last tile may be shorter
         Shape t{64, K, false, true};
-        t.CT = nvec / tile_vecs;
+        t.CT = tiles;
         shapes.push_back(t);
       }
     }
@@ -894,7 +896,7 @@ KernelCost interpreted_cost(const Compiler& c, int vec, const Shape& s, int64_t 
   kc.xlane_steps = steps * c.n_reductions;
   kc.barriers = s.block ? c.n_reductions : 0;
   kc.lds_bytes_per_block = (int32_t)lds;
-  kc.lane_utilisation = (double)(nvec / s.CT) / ((double)s.L * s.K);
+  kc.lane_utilisation = (double)nvec / ((double)s.L * s.K * s.CT);
   // contiguous bytes the lanes of one row touch per access of the narrowest input
   kc.access_run_bytes = (double)std::min<uint32_t>(s.L, 64) * vec * narrowest;
   kc.row_bytes = (double)base.cols * narrowest;
@@ -969,7 +971,6 @@ void make_generated(const Compiler& c, int vec, const Shape& s, Candidate* cand)
 void add_column_sums(const Compiler& c, int vec, const Shape& s, int64_t bytes_min, Candidate* cand) {
   const RowProgP& base = c.p;
   const int kv = s.K * vec;
-  const DeviceModel& d = device();
   Launch& ml = cand->launches.back();
   const uint32_t n_wg = ml.shape.grid[0] / s.CT;   // one row of partial sums per row block (its column tiles share the row)
   const uint32_t pitch = colsum_pitch(base.cols), width = (uint32_t)c.n_colsum * pitch;
@@ -1001,17 +1002,22 @@ void add_column_sums(const Compiler& c, int vec, const Shape& s, int64_t bytes_m
     snprintf(cand->info.kernel, sizeof cand->info.kernel, "row_generated<v%d,K%d,L%u,I%d,R%d,rows%u>+colfold", vec, s.K, s.L, base.n_instr,
              base.n_regs, s.R);
   KernelCost& gc = cand->cost;
-  gc.hbm_bytes += 2.0 * (double)cand->info.workspace_bytes;
+  gc.partial_bytes = 2.0 * (double)cand->info.workspace_bytes;
+  gc.fold_rows = n_wg;
+  gc.flush_values = (double)kv * c.n_colsum;
+  if (!s.block) {
+    gc.flush_steps = 0;
+    for (uint32_t l = s.L; l < 64; l <<= 1) ++gc.flush_steps;
+  }
   gc.vgpr_estimate += kv * c.n_colsum;
   gc.rows_per_wave_loop = s.R;
   if (s.R > 1) {   // software-pipelined: only the first row's load latency is exposed
     gc.dep_phases = 0;
-    gc.serial_tail_s += d.mem_latency_s;
     gc.bytes_in_flight_per_lane *= 2.0;   // this row's and the next row's loads
   }
   gc.lds_bytes_per_block = cand->info.lds_bytes;
   gc.barriers = 1;
-  gc.serial_tail_s += (d.mem_latency_s + 0.5 * d.launch_s + d.mem_latency_s * std::ceil(n_wg / 64.0 / 8.0) * 0.5) * 1.0;
+  gc.serial_tail_s = 0;
 }
 
 // One candidate: the program in shape `s`, interpreted or generated.  false: the shape does not fit (the

@@ -46,7 +46,7 @@ extern "C" __global__ void __launch_bounds__(256) fs_gen_sample_ragged_narrow(co
 extern "C" __global__ void __launch_bounds__(256) fs_gen_sample_colsum(const GenArgs a) {
   typedef GenRow<1000u, 96u, 4, 3, 8u, false, 2u> Row;
   constexpr int KV = Row::KV;
-  __shared__ float colred[1][4 * Row::PADDED_COLS];
+  __shared__ __attribute__((aligned(16))) float colred[1][4 * Row::PADDED_COLS];
   float cs0[KV];
 #pragma unroll
   for (int j = 0; j < KV; ++j) cs0[j] = 0.0f;
@@ -59,5 +59,8 @@ extern "C" __global__ void __launch_bounds__(256) fs_gen_sample_colsum(const Gen
     row.store<float>(a.out[0], acc);
     row.colsum_add(acc, cs0);
   }
-  Row(blockIdx.x).colsum_flush(cs0, colred[0], static_cast<float*>(a.ws) + (size_t)blockIdx.x * 96u);
+  const Row last(blockIdx.x);
+  last.colsum_park(cs0, colred[0]);
+  __syncthreads();
+  last.colsum_flush(cs0, colred[0], static_cast<float*>(a.ws) + (size_t)blockIdx.x * 96u);
 }

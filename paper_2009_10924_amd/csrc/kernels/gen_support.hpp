@@ -32,6 +32,22 @@ __device__ __forceinline__ float xor_lane(float v, uint32_t mask) {
   return __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(addr, __builtin_bit_cast(int, v)));
 }
 
+// value + the value 32 lanes further / in the other one of two neighbouring 16-lane rows: the swap instructions leave one
+// half in both halves of the one register and the other half in the other.  (The elements are copied out first:
+// bit-casting a vector element is miscompiled into a read of element 0, see unpack().)
+__device__ __forceinline__ float add_other_half(float v) {
+  const uint32_t b = __builtin_bit_cast(uint32_t, v);
+  const auto r = __builtin_amdgcn_permlane32_swap(b, b, false, false);
+  const uint32_t one = r[0], other = r[1];
+  return __builtin_bit_cast(float, one) + __builtin_bit_cast(float, other);
+}
+__device__ __forceinline__ float add_other_row(float v) {
+  const uint32_t b = __builtin_bit_cast(uint32_t, v);
+  const auto r = __builtin_amdgcn_permlane16_swap(b, b, false, false);
+  const uint32_t one = r[0], other = r[1];
+  return __builtin_bit_cast(float, one) + __builtin_bit_cast(float, other);
+}
+
 // One step of one lane in storage form: VEC elements of 2 or 4 bytes are 2, 4, 8, 16 or 32 bytes.  VEC is 8 or 4, and
 // 1 for rows shorter than 4 elements.  EA: the alignment the address is known to have, in bytes -- that of a whole step
 // where the row length is a multiple of VEC elements, that of one element otherwise (a row then starts anywhere).  The
@@ -154,6 +170,7 @@ __device__ __forceinline__ void store_elements(TO* p, const float (&v)[N]) {
 // workgroup indices it * gridDim.x + blockIdx.x, so that at any moment the resident workgroups sweep one band of rows).
 // ROW_STRIDE > COLS: the pattern's rows are ROW_STRIDE elements long and the kernel works on column tiles of COLS
 // elements (patterns without row reductions only: nothing ties the tiles of a row together); `tile` picks the tile.
+// TILES: their number, where the last one may be shorter than the others (1: all of COLS elements).
 //
 // Row lengths that are no multiple of VEC: the row's last step slides back so that it ends where the row ends, and
 // reads some elements that the step before it holds as well (BACK of them).  Every load is then one whole access
@@ -161,14 +178,17 @@ __device__ __forceinline__ void store_elements(TO* p, const float (&v)[N]) {
 // store either writes only the TAIL elements the step owns, in at most three pieces, or (AGAIN) the whole step, the
 // repeated elements a second time with the value their owner gives them: one access instead of three more (rows of 197
 // 16-bit elements, 29.8 MB: 7.6 against 8.9 us for the bare copy, 7.0 with rows padded to whole steps).
-template <uint32_t ROWS, uint32_t COLS, int VEC, int K, uint32_t L, bool BLOCK, uint32_t R = 1, uint32_t ROW_STRIDE = COLS>
+template <uint32_t ROWS, uint32_t COLS, int VEC, int K, uint32_t L, bool BLOCK, uint32_t R = 1, uint32_t ROW_STRIDE = COLS, uint32_t TILES = 1>
 struct GenRow {
-  static constexpr uint32_t NVEC = (COLS + VEC - 1) / VEC;
-  static constexpr int TAIL = (int)(COLS % VEC), BACK = TAIL != 0 ? VEC - TAIL : 0;
+  static constexpr bool SHORT_LAST = TILES > 1 && TILES * COLS != ROW_STRIDE;
+  static constexpr uint32_t LAST_COLS = SHORT_LAST ? ROW_STRIDE - (TILES - 1u) * COLS : COLS;
+  static constexpr uint32_t NVEC = (COLS + VEC - 1) / VEC, LAST_NVEC = (LAST_COLS + VEC - 1) / VEC;
+  static constexpr int TAIL = (int)(LAST_COLS % VEC), BACK = TAIL != 0 ? VEC - TAIL : 0;
+  static_assert(!SHORT_LAST || COLS % VEC == 0, "only the last tile ends inside a step");
   static constexpr uint32_t LANES = L;
   static constexpr uint32_t ROWS_PER_WG = BLOCK ? 1u : 256u / L;
   // the row fills its lanes (and no element is held twice) / the rows fill the workgroups: no clamp, no padding test
-  static constexpr bool FULL_COLS = NVEC == LANES * K && TAIL == 0;
+  static constexpr bool FULL_COLS = NVEC == LANES * K && TAIL == 0 && !SHORT_LAST;
   static constexpr bool FULL_ROWS = ROWS % (ROWS_PER_WG * R) == 0;
   static constexpr int KV = K * VEC;
   static constexpr uint32_t PADDED_COLS = LANES * K * VEC;   // columns the lanes of a row cover, padding included
@@ -176,11 +196,12 @@ struct GenRow {
   template <typename T> static constexpr int alignment() { return (int)sizeof(T) * (ROW_STRIDE % VEC == 0 ? VEC : 1); }
 
   uint32_t lane, row, row_c, col0;
-  bool row_ok;
+  bool row_ok, last;   // last: the tile that may be shorter than the others
 
   __device__ __forceinline__ explicit GenRow(uint32_t vblock, uint32_t tile = 0) {
     const uint32_t tid = threadIdx.x;
     col0 = tile * COLS;
+    last = tile == TILES - 1u;
     lane = BLOCK ? tid : (tid & (L - 1u));
     row = BLOCK ? vblock : vblock * ROWS_PER_WG + tid / L;
     row_ok = FULL_ROWS || row < ROWS;
@@ -189,18 +210,22 @@ struct GenRow {
   // a chunk of a long row: COLS columns from column `first_col` on (the row itself is ROW_STRIDE elements long)
   __device__ __forceinline__ GenRow(uint32_t vblock, uint32_t tile, uint32_t first_col) : GenRow(vblock, tile) { col0 = first_col; }
   // only a lane's last step can be padding or the row's last one (K is the smallest that covers the row)
-  static constexpr __device__ __forceinline__ bool inner(int k) { return FULL_COLS || (uint32_t)k < (NVEC - 1u) / LANES; }
-  __device__ __forceinline__ bool valid(int k) const { return inner(k) || lane + k * LANES < NVEC; }
+  static constexpr __device__ __forceinline__ bool inner(int k) { return FULL_COLS || (!SHORT_LAST && (uint32_t)k < (NVEC - 1u) / LANES); }
+  // steps and columns of the row (of this tile of it), and the steps that hold no repeated element
+  __device__ __forceinline__ uint32_t n_steps() const { return SHORT_LAST && last ? LAST_NVEC : NVEC; }
+  __device__ __forceinline__ uint32_t n_cols() const { return SHORT_LAST && last ? LAST_COLS : COLS; }
+  __device__ __forceinline__ uint32_t n_whole() const { return SHORT_LAST && !last ? NVEC : LAST_NVEC - (TAIL != 0 ? 1u : 0u); }
+  __device__ __forceinline__ bool valid(int k) const { return inner(k) || lane + k * LANES < n_steps(); }
   // element e of step k is the lane's own: neither padding nor a repetition of the step before
   __device__ __forceinline__ bool own(int k, int e) const {
-    return inner(k) || lane + k * LANES < (e < BACK ? NVEC - 1u : NVEC);
+    return inner(k) || lane + k * LANES < (e < BACK ? n_whole() : n_steps());
   }
   // first column of step k (the last step's slides back; padding steps stay on the last step).  Signed: the last chunk
   // of a long row may be shorter than a step, which then starts in the chunk before.
   __device__ __forceinline__ int first_of(int k) const {
     if (inner(k)) return (int)(lane + k * LANES) * VEC;
-    if constexpr (TAIL != 0) return min((int)(lane + k * LANES) * VEC, (int)COLS - VEC);
-    return (int)min(lane + k * LANES, NVEC - 1u) * VEC;
+    if constexpr (TAIL != 0) return min((int)(lane + k * LANES) * VEC, (int)n_cols() - VEC);
+    return (int)min(lane + k * LANES, n_steps() - 1u) * VEC;
   }
 
   // the lane's K steps of row `at_row` of a [.., COLS] tensor, in storage form; STREAM: read once, so the loads
@@ -259,8 +284,8 @@ struct GenRow {
         if (row_ok && valid(k)) store_elements<TO, VEC, alignment<TO>()>(base + first_of(k), part);
       } else {
         if (row_ok && own(k, 0)) store_elements<TO, VEC, alignment<TO>()>(base + (size_t)(lane + k * LANES) * VEC, part);
-        if (!inner(k) && row_ok && lane + k * LANES == NVEC - 1u) {
-          TO* const step = base + ((int)COLS - VEC);
+        if (!inner(k) && row_ok && (!SHORT_LAST || last) && lane + k * LANES == LAST_NVEC - 1u) {
+          TO* const step = base + ((int)LAST_COLS - VEC);
           if constexpr (TAIL >= 4) store_piece<TO, BACK, 4>(step, part);
           if constexpr ((TAIL & 2) != 0) store_piece<TO, BACK + (TAIL & 4), 2>(step, part);
           if constexpr ((TAIL & 1) != 0) store_piece<TO, VEC - 1, 1>(step, part);
@@ -318,11 +343,57 @@ struct GenRow {
       for (int e = 0; e < VEC; ++e) sum[k * VEC + e] += row_ok && own(k, e) ? v[k * VEC + e] : 0.0f;
     }
   }
-  // Lane-group rows: the workgroup's lane groups hold sums of the same columns: first the groups of a wavefront are folded lane to
-  // lane (lane ^ L, lane ^ 2L, ...: every lane ends with the wavefront's sum), then the four wavefronts through
-  // `lds` (4 * PADDED_COLS floats, used by this sum only), and one row of COLS partial sums goes to `dst`.  Fixed
-  // order throughout, so the result is the same from run to run.
-  __device__ __forceinline__ void colsum_flush(const float (&sum)[KV], float* lds, float* dst) const {
+  // Lane-group rows: the workgroup's lane groups hold sums of the same columns: first the groups of a wavefront are folded
+  // lane to lane (every lane of the first group ends with the wavefront's sum), then the four wavefronts through `lds`
+  // (4 * PADDED_COLS floats, used by this sum only), and one row of COLS partial sums goes to `dst`.  Fixed order
+  // throughout, so the result is the same from run to run.  In LDS a wavefront's sums lie step after step, so a lane
+  // writes 128-bit vectors (single floats, VEC apart from lane to lane, meet in the same banks).  colsum_park and
+  // colsum_flush have a barrier between them, one for all the sums of a pattern.
+  __device__ __forceinline__ void colsum_park(const float (&sum)[KV], float* lds) const {
+    if constexpr (BLOCK) return;
+    float v[KV];
+#pragma unroll
+    for (int j = 0; j < KV; ++j) v[j] = sum[j];
+    if constexpr (L <= 1u) {
+#pragma unroll
+      for (int j = 0; j < KV; ++j) v[j] += xor_lane(v[j], 1u);
+    }
+    if constexpr (L <= 2u) {
+#pragma unroll
+      for (int j = 0; j < KV; ++j) v[j] += xor_lane(v[j], 2u);
+    }
+    if constexpr (L <= 4u) {
+#pragma unroll
+      for (int j = 0; j < KV; ++j) v[j] += xor_lane(v[j], 4u);
+    }
+    if constexpr (L <= 8u) {   // row_ror:8 : the other half of the 16 lanes
+#pragma unroll
+      for (int j = 0; j < KV; ++j) v[j] += dpp_move<0x128>(v[j]);
+    }
+    if constexpr (L <= 16u) {
+#pragma unroll
+      for (int j = 0; j < KV; ++j) v[j] = add_other_row(v[j]);
+    }
+    if constexpr (L <= 32u) {
+#pragma unroll
+      for (int j = 0; j < KV; ++j) v[j] = add_other_half(v[j]);
+    }
+    const uint32_t tid = threadIdx.x;
+    if ((tid & 63u) < L) {
+      float* mine = lds + (tid >> 6) * PADDED_COLS + lane * VEC;
+#pragma unroll
+      for (int k = 0; k < K; ++k) {
+        if constexpr (VEC >= 4) {
+#pragma unroll
+          for (int e = 0; e < VEC; e += 4)
+            *reinterpret_cast<f32x4*>(mine + k * L * VEC + e) = f32x4{v[k * VEC + e], v[k * VEC + e + 1], v[k * VEC + e + 2], v[k * VEC + e + 3]};
+        } else {
+          mine[k * L] = v[k];
+        }
+      }
+    }
+  }
+  __device__ __forceinline__ void colsum_flush(const float (&sum)[KV], const float* lds, float* dst) const {
     if constexpr (BLOCK) {
       // a workgroup per row: every lane owns its columns alone, the sums over the workgroup's rows are complete
 #pragma unroll
@@ -338,25 +409,19 @@ struct GenRow {
       }
       return;
     }
-    float v[KV];
-#pragma unroll
-    for (int j = 0; j < KV; ++j) v[j] = sum[j];
-#pragma unroll
-    for (uint32_t s = L; s < 64u; s <<= 1) {
-#pragma unroll
-      for (int j = 0; j < KV; ++j) v[j] += xor_lane(v[j], s);
+    // where column c lies in LDS: the last step's own columns are the last ones of its vector
+    const auto fold4 = [&](uint32_t at) {
+      return ((lds[at] + lds[PADDED_COLS + at]) + lds[2u * PADDED_COLS + at]) + lds[3u * PADDED_COLS + at];
+    };
+    if constexpr (TAIL == 0 && VEC >= 4) {
+      for (uint32_t c = threadIdx.x * 4u; c < n_cols(); c += 1024u) {
+        const f32x4* at = reinterpret_cast<const f32x4*>(lds + c);
+        const f32x4 s = ((at[0] + at[PADDED_COLS / 4u]) + at[PADDED_COLS / 2u]) + at[PADDED_COLS / 4u * 3u];
+        *reinterpret_cast<f32x4*>(dst + c) = s;
+      }
+    } else {
+      for (uint32_t c = threadIdx.x; c < n_cols(); c += 256u) dst[c] = fold4(c < n_whole() * VEC ? c : c + BACK);
     }
-    const uint32_t tid = threadIdx.x, wave = tid >> 6;
-    if ((tid & 63u) < L) {
-#pragma unroll
-      for (int k = 0; k < K; ++k)
-#pragma unroll
-        for (int e = 0; e < VEC; ++e)
-          if (own(k, e)) lds[wave * PADDED_COLS + first_of(k) + e] = v[k * VEC + e];
-    }
-    __syncthreads();
-    for (uint32_t c = tid; c < COLS; c += 256u)
-      dst[c] = ((lds[c] + lds[PADDED_COLS + c]) + lds[2u * PADDED_COLS + c]) + lds[3u * PADDED_COLS + c];
   }
 };
 

@@ -253,7 +253,7 @@ struct RowProgP {
   int32_t n_colsum;                    // column sums over all rows (generated kernels only), at most kProgMaxColSums
   int32_t rows_per_group;              // rows each lane group works through, one after the other (> 1 only with column sums:
                                        // fewer, longer partial sums)
-  int32_t col_tiles;                   // > 1: a workgroup handles one of col_tiles column tiles of cols / col_tiles elements
+  int32_t col_tiles;                   // > 1: a workgroup handles one of col_tiles column tiles, the last possibly shorter
                                        // (generated kernels for patterns with column sums and no row reduction)
   int32_t col_chunks;                  // > 1: a row too long for the lanes' registers is worked through in col_chunks pieces of
                                        // lanes_per_row * vecs_per_lane steps, once per row reduction and once more for the stores

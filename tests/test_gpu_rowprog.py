@@ -173,7 +173,8 @@ def test_column_sums_beside_row_work(rows, cols, dtype):
 
 
 @pytest.mark.parametrize("rows,cols,dtype", [(37, 9, "bf16"), (300, 205, "f16"), (70, 1003, "f32"), (33, 2247, "bf16"), (130, 60, "f16"),
-                                             (500, 30, "f32"), (45, 4421, "f32"), (11, 3, "f32"), (3, 6, "bf16"), (64, 1554, "f16")])
+                                             (500, 30, "f32"), (45, 4421, "f32"), (11, 3, "f32"), (3, 6, "bf16"), (64, 1554, "f16"),
+                                             (300, 520, "bf16"), (90, 1025, "f16"), (70, 257, "f32")])   # column tiles, the last one a step or an element
 def test_column_sums_of_rows_that_end_inside_a_step(rows, cols, dtype):
     """Row lengths that are no multiple of a step, with sums over all rows: the last step of a row slides back over
     elements that the step before it holds, which must count once in every row reduction and column sum, and the sums'
