@@ -388,7 +388,7 @@ std::string body_with_entry(const RowProgP& p, const char* entry, bool member) {
            (uint32_t)p.lanes_per_row, block ? "true" : "false", R, p.cols, CT > 1 ? fmt(", %uu", CT).c_str() : "");
   s += "  constexpr int KV = Row::KV;\n";
   const int n_waves = block ? p.lanes_per_row / 64 : 4;
-  const bool looped = p.n_colsum > 0;
+  const bool looped = p.n_colsum > 0 || R > 1u;
   // a workgroup that walks several rows alternates between two sets of reduction slots: a wave may write the next
   // row's partial value while a slower one still reads this row's, and nobody can be two rows ahead (the next row's
   // own barrier stands in between), so no barrier is needed at a row's end

@@ -386,3 +386,26 @@ def test_random_row_patterns_with_column_sums(seed):
         assert info["pattern"] == "row_generated" and info["scheme"] == "global", (spec.name, info)
     worst = all_candidates(spec, inp, ref, floors, repeat=2)
     note(f"random pattern {seed} with column sums {rows}x{cols} {dtype}: {info['kernel']}, {info['n_candidates']} shapes, worst {worst}")
+
+
+@pytest.mark.parametrize("rows,cols,dtype", [(1024, 2051, "f32"), (1500, 4099, "bf16"), (4097, 1001, "f32"), (1031, 2056, "f16")])
+def test_workgroups_that_work_through_several_rows(rows, cols, dtype):
+    """Rows a workgroup each, with column vectors and without column sums: shapes in which a workgroup takes up to eight
+    rows one after the other, row counts that leave the last round short, and such a plan as a member of a pack (which
+    takes another shape)."""
+    if not B.codegen_available():
+        pytest.skip("these shapes exist as generated kernels only")
+    from tests.gpu_util import run_pack
+    spec = layernorm_stats_graph(rows, cols, in_dtype=dtype, out_dtype=dtype, with_variance=True)
+    names = [c["kernel"] for c in B.Plan(B.Graph.from_spec(spec), "auto").candidates()]
+    assert any(",rows" in n for n in names), names
+    worst, info = _run(spec)
+    note(f"{spec.name}: {info['kernel']}, {info['n_candidates']} shapes, worst {worst}")
+    inp = make_inputs(spec, seed=0)
+    ref = O.evaluate(spec, inp)
+    floors = floors_for(spec, inp, ref)
+    out, _ = run_pack([spec, spec], [inp, inp])
+    for member in out:
+        for name, dt in spec.outputs:
+            err = O.max_rel_err(member[name], ref[name].reshape(member[name].shape), floors.get(name, 0.0))
+            assert err <= (1e-5 if dt == "f32" else 1e-2), (spec.name, name, err)
