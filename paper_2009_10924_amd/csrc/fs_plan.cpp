@@ -90,12 +90,18 @@ static void fill_generic_form(const fs_graph& g, fs_plan* p) {
   std::vector<Candidate> cands;
   if (!build_row_program(g, &cands)) return;
   int best = -1;
+  bool best_slim = false;
   for (int i = 0; i < (int)cands.size(); ++i) {
     if (cands[i].launches.size() != 1 || cands[i].launches.front().kernel != K_ROW_GENERATED) continue;
     const RowProgP& prog = cands[i].launches.front().args.u.prog;
     if (cands[i].launches.front().shape.block[0] != 256 || prog.col_chunks > 1 || prog.rows_per_group > 1) continue;
     predict(&cands[i]);
-    if (best < 0 || cands[i].info.predicted_us < cands[best].info.predicted_us) best = i;
+    // the packed kernel has the registers of its hungriest member: shapes beyond eight wavefronts per SIMD are passed over
+    const bool slim = cands[i].cost.vgpr_estimate <= 64;
+    if (best < 0 || slim > best_slim || (slim == best_slim && cands[i].info.predicted_us < cands[best].info.predicted_us)) {
+      best = i;
+      best_slim = slim;
+    }
   }
   if (best >= 0) take(cands[best]);
 }
