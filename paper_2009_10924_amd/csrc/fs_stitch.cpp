@@ -7,7 +7,7 @@
 
 namespace fs {
 
-// Magic numbers for n / d, n < 2^31; checked on the spot against plain division.
+// Magic numbers for n / d, n < 2^31 and d < 2^31; checked on the spot against plain division.
 FastDiv make_fastdiv(uint32_t d) {
   FastDiv f = {d == 0 ? 1u : d, 0u, 0u};
   if (d <= 1) return f;
@@ -17,6 +17,7 @@ FastDiv make_fastdiv(uint32_t d) {
   f.m = (uint32_t)(((1ull << (31 + l)) / d) + 1);
   const uint32_t probes[] = {0u, 1u, d - 1, d, d + 1, 2 * d - 1, 2 * d, 0x7FFFFFFFu / d * d - 1, 0x7FFFFFFFu / d * d, 0x7FFFFFFFu};
   for (uint32_t n : probes) {
+    if (n > 0x7FFFFFFFu) continue;   // 2 d and its neighbours, for divisors beyond 2^30: outside what is promised
     const uint32_t q = (uint32_t)(((uint64_t)n * f.m) >> 32) >> f.s;
     if (q != n / d) { f.m = 0; f.s = 0; f.d = 0; break; }   // d == 0 marks "unusable"; callers then offer no candidate
   }

@@ -253,9 +253,9 @@ fs_status build_unfused(const fs_graph& g, Candidate* out) {
           lead[3 - (m - 1) + k] = (uint32_t)ext[k];
           p.in_stride[3 - (m - 1) + k] = (uint32_t)from[k];
         }
-        p.div[0] = make_fastdiv((uint32_t)inner);
-        p.div[1] = make_fastdiv(lead[2]);
-        p.div[2] = make_fastdiv(lead[1]);
+        p.out_ext[0] = lead[1];
+        p.out_ext[1] = lead[2];
+        p.out_ext[2] = (uint32_t)inner;
         grid1d(l, n_out / vec);
       } else {
         int q = 0;   // the output axis that the input's innermost axis has become
@@ -286,12 +286,12 @@ fs_status build_unfused(const fs_graph& g, Candidate* out) {
         p.div[0] = make_fastdiv(p.q_first ? tq : tx);
         p.div[1] = make_fastdiv(p.q_first ? tx : tq);
         p.div[2] = make_fastdiv(batch[1]);
+        for (const FastDiv& d : p.div)   // (both tile axes are at least 2 long, so none of these is near 2^31)
+          if (d.d == 0) return fail(FS_ERR_SHAPE, "transpose: no exact division by one of its extents");
         const int64_t blocks = (int64_t)tq * tx * batch[0] * batch[1];
         if (blocks >= (int64_t(1) << 31)) return fail(FS_ERR_SHAPE, "transpose: too many tiles");
         l.shape.grid[0] = (uint32_t)blocks;
       }
-      for (const FastDiv& d : p.div)
-        if (d.d == 0) return fail(FS_ERR_SHAPE, "transpose: no exact division by one of its extents");
       moved += 2 * n_out * p.elem_bytes;
     } else {
       // unary family, convert included

@@ -87,11 +87,11 @@ struct TransposeP {
   // Axes that stay neighbours are merged first, extents of 1 dropped.
   // K_TRANSPOSE_ROWS: output index -> (c0, c1, c2, innermost index), each times its stride in the input
   uint32_t in_stride[3];        // elements, of the input axis that feeds output axis 0, 1, 2
-  FastDiv div[3];               // rows: innermost extent, output extents 2 and 1
-                                // tile: tiles along the axis that neighbouring workgroups walk, along the other one, batch extent 1
+  uint32_t out_ext[3];          // output extents 1 and 2, innermost extent
   // K_TRANSPOSE_TILE: out[b0, b1, .., q, ..] with q the input's innermost axis and x the output's
   uint32_t nq, nx;              // extents of the tile's two axes
   uint32_t in_row, out_row;     // input stride of x, output stride of q (elements)
+  FastDiv div[3];               // tiles along the axis that neighbouring workgroups walk, along the other one, batch extent 1
   uint32_t in_batch[2], out_batch[2];   // strides of the two axes outside the tile (0 where there is none)
   uint32_t tile_uq;             // vectorised tile: 16-byte units along q (8, 16 or 32); the tile is tile_uq * vec elements
                                 // along q by (256 / tile_uq) * vec along x

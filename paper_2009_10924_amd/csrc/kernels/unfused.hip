@@ -207,9 +207,9 @@ __global__ void __launch_bounds__(256) k_transpose_rows(const void* in, void* ou
   // Plain divisions, measured: multiply-high ones are slower here ([64,512,12,64] -> [64,12,512,64] float32 34.6 against
   // 35.5 us, the wavefronts then reach their loads closer together), four vectors per thread slower still (36.1).
   uint32_t rest = e;
-  const uint32_t c3 = rest % p.div[0].d; rest /= p.div[0].d;
-  const uint32_t c2 = rest % p.div[1].d; rest /= p.div[1].d;
-  const uint32_t c1 = rest % p.div[2].d, c0 = rest / p.div[2].d;
+  const uint32_t c3 = rest % p.out_ext[2]; rest /= p.out_ext[2];
+  const uint32_t c2 = rest % p.out_ext[1]; rest /= p.out_ext[1];
+  const uint32_t c1 = rest % p.out_ext[0], c0 = rest / p.out_ext[0];
   const uint32_t src = c0 * p.in_stride[0] + c1 * p.in_stride[1] + c2 * p.in_stride[2] + c3;
   reinterpret_cast<VT*>(out)[vi] = reinterpret_cast<const VT*>(in)[src / p.vec];
 }

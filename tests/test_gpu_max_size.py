@@ -9,7 +9,7 @@ import pytest
 from oracle import oracle as O
 from tests.gpu_util import MIN_NORMAL, TOL, floors_for, note
 from workloads import (add_bias_layernorm_graph, bias_gelu_dbias_graph, make_inputs, silu_gate_graph, softmax_graph,
-                       transpose_chain_graph)
+                       transpose_chain_graph, transpose_graph)
 
 pytestmark = pytest.mark.gpu
 
@@ -129,3 +129,20 @@ def test_generated_kernel_at_the_element_limit():
     errs, info = _run_rows(lambda k: silu_gate_graph(k, 4096, "bf16"), rows, period)
     assert info["pattern"] == "row_generated"
     note(f"gated SiLU [{rows},4096]: {info['kernel']} worst {errs}")
+
+
+@pytest.mark.parametrize("dims,perm,dtype", [((2, 1, 1000000000), (1, 0, 2), "bf16"), ((1, 61000, 29000), (1, 0, 2), "f16"), ((2, 874412035), (0, 1), "f16")])
+def test_transposes_that_only_rename_axes_near_the_element_limit(dims, perm, dtype):
+    """One merged extent of more than 1.5 x 2^30 elements: a copy, every element of it compared."""
+    import torch
+    from paper_2009_10924_amd import binding as B
+    n = int(np.prod(dims))
+    x = torch.arange(n, dtype=torch.int32, device="cuda").mul_(40503).to(torch.int16)
+    out = torch.zeros(n, dtype=torch.int16, device="cuda")
+    plan = B.Plan(B.Graph.from_spec(transpose_graph(dims, perm, dtype)), "auto")
+    note(f"  {dims} {perm}: {plan.info['kernel']}, grid {plan.info['grid'][0]}")
+    plan.execute_ptrs([x.data_ptr()], [out.data_ptr()], 0, 0, torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert torch.equal(out, x)
+    del x, out
+    torch.cuda.empty_cache()

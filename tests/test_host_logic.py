@@ -209,6 +209,21 @@ def test_unfused_plan_shapes():
     assert info["workspace_bytes"] > 0 and info["scheme"] == "global"
 
 
+@pytest.mark.parametrize("dims,perm", [((2, 1, 1000000000), (1, 0, 2)), ((2, 1, 900000000), (1, 0, 2)), ((2000000000, 1), (1, 0)),
+                                       ((1, 61000, 29000), (1, 0, 2)), ((2, 874412035), (0, 1)), ((1 << 30, 1), (1, 0)),
+                                       ((3, 1, (1 << 29) + 1), (1, 0, 2)), ((1, (1 << 31) - 1), (1, 0)), ((1 << 30, 1, 1), (2, 1, 0))])
+def test_transposes_that_only_rename_axes_are_planned_at_any_extent(dims, perm):
+    """Axes that stay neighbours count as one, so the innermost extent of such a transpose is anything below 2^31: both
+    plans take it, alone and in front of another op."""
+    spec = transpose_graph(dims, perm, "bf16")
+    for scheme in ("auto", "unfused"):
+        assert B.Plan(B.Graph.from_spec(spec), scheme).info["kernel"] == "transpose_rows"
+    y = spec.ops[0].out
+    then = GraphSpec("transpose_then_exp", spec.inputs, list(spec.ops) + [OpSpec("e", "exp", [y], {})], [("e", "bf16")])
+    for scheme in ("auto", "unfused"):
+        B.Plan(B.Graph.from_spec(then), scheme)
+
+
 def test_pack_creation_and_errors(lib):
     from workloads.graphs import add_bias_layernorm_graph, rmsnorm_graph, softmax_backward_graph
     specs = [softmax_graph(64, 128, "f32"), add_bias_layernorm_graph(100, 768), rmsnorm_graph(50, 4096),
