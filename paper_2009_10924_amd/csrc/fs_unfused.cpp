@@ -276,8 +276,13 @@ fs_status build_unfused(const fs_graph& g, Candidate* out) {
         }
         const uint32_t v128 = 16 / p.elem_bytes;
         p.vec = p.nq >= v128 && p.nx >= v128 ? (int32_t)v128 : 1;
-        p.tile_uq = p.vec > 1 ? transpose_units_along_q(p) : 0u;
-        const uint32_t side_q = p.vec > 1 ? p.tile_uq * p.vec : 32, side_x = p.vec > 1 ? 256 / p.tile_uq * p.vec : 32;
+        // A small matrix per batch entry gets a wavefront's tile, not a workgroup's: with one in 256 threads and 16 to 32 KB of
+        // LDS most threads idle and few matrices are in flight.  Measured (us, a workgroup each / a wavefront each / 32x32
+        // single elements): [16384,30,30] bf16 27.2 / 15.7 / 31.9, [16384,20,20] f32 15.9 / 12.1 / 26.0, [4096,9,9]
+        // bf16 5.9 / 4.6 / 4.9, [65536,8,8] f32 36.5 / 16.9 / 49.7; full tiles ([16384,64,64] bf16) 45.0 / 43.9 / 126.
+        p.tile_units = p.nq <= 8u * p.vec && p.nx <= 8u * p.vec ? 64u : 256u;
+        p.tile_uq = p.vec == 1 ? 0u : p.tile_units == 64u ? 8u : transpose_units_along_q(p);
+        const uint32_t side_q = p.vec > 1 ? p.tile_uq * p.vec : 32, side_x = p.vec > 1 ? p.tile_units / p.tile_uq * p.vec : 32;
         const uint32_t tq = (p.nq + side_q - 1) / side_q, tx = (p.nx + side_x - 1) / side_x;
         // Neighbouring workgroups walk along q where that makes them read whole lines of one short contiguous span
         // ([64,512,12,64] -> [64,12,64,512] float32: 36.1 against 37.4 us); along x otherwise: long or unaligned input
@@ -290,7 +295,9 @@ fs_status build_unfused(const fs_graph& g, Candidate* out) {
           if (d.d == 0) return fail(FS_ERR_SHAPE, "transpose: no exact division by one of its extents");
         const int64_t blocks = (int64_t)tq * tx * batch[0] * batch[1];
         if (blocks >= (int64_t(1) << 31)) return fail(FS_ERR_SHAPE, "transpose: too many tiles");
-        l.shape.grid[0] = (uint32_t)blocks;
+        p.n_tiles = (uint32_t)blocks;
+        const int64_t per_workgroup = p.vec > 1 && p.tile_units == 64u ? 4 : 1;
+        l.shape.grid[0] = (uint32_t)((blocks + per_workgroup - 1) / per_workgroup);
       }
       moved += 2 * n_out * p.elem_bytes;
     } else {

@@ -93,9 +93,10 @@ struct TransposeP {
   uint32_t in_row, out_row;     // input stride of x, output stride of q (elements)
   FastDiv div[3];               // tiles along the axis that neighbouring workgroups walk, along the other one, batch extent 1
   uint32_t in_batch[2], out_batch[2];   // strides of the two axes outside the tile (0 where there is none)
-  uint32_t tile_uq;             // vectorised tile: 16-byte units along q (8, 16 or 32); the tile is tile_uq * vec elements
-                                // along q by (256 / tile_uq) * vec along x
-  uint32_t q_first;             // neighbouring workgroups walk 1: along q (they read one contiguous span), 0: along x
+  uint32_t tile_units, tile_uq; // vectorised tile: 16-byte units in all (256, or 64: a tile per wavefront) and along q (8, 16 or
+                                // 32); the tile is tile_uq * vec elements along q by (tile_units / tile_uq) * vec along x
+  uint32_t n_tiles;
+  uint32_t q_first;             // neighbouring tiles follow one another 1: along q (they read one contiguous span), 0: along x
 };
 
 // ---- stitched -----------------------------------------------------------------

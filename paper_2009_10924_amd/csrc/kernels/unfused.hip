@@ -214,12 +214,12 @@ __global__ void __launch_bounds__(256) k_transpose_rows(const void* in, void* ou
   reinterpret_cast<VT*>(out)[vi] = reinterpret_cast<const VT*>(in)[src / p.vec];
 }
 
-// The tile that a workgroup moves, and where its batch entry starts in the input and in the output.
+// Tile `index` of a transpose, and where its batch entry starts in the input and in the output.
 struct TileAt {
   uint32_t bq, bx;
   size_t in_base, out_base;
-  __device__ __forceinline__ explicit TileAt(const TransposeP& p) {
-    uint32_t rest = blockIdx.x;
+  __device__ __forceinline__ TileAt(const TransposeP& p, uint32_t index) {
+    uint32_t rest = index;
     uint32_t r = fast_div(rest, p.div[0]);
     const uint32_t inner = rest - r * p.div[0].d;
     rest = r;
@@ -239,7 +239,7 @@ struct TileAt {
 template <typename T>
 __global__ void __launch_bounds__(256) k_transpose_tile(const T* __restrict__ in, T* __restrict__ out, TransposeP p) {
   __shared__ T tile[32][33];
-  const TileAt t(p);
+  const TileAt t(p, blockIdx.x);
   const uint32_t tx = threadIdx.x & 31u, ty = threadIdx.x >> 5;
   for (uint32_t j = ty; j < 32u; j += 8u) {
     const uint32_t cq = t.bq * 32u + tx, cx = t.bx * 32u + j;
@@ -253,7 +253,7 @@ __global__ void __launch_bounds__(256) k_transpose_tile(const T* __restrict__ in
 }
 
 // ---- transpose, innermost axis moves: 128-bit accesses on both HBM sides AND both LDS sides ----------------
-// The tile is UQ x UX units of VEC x VEC elements (UQ * UX = 256 threads, one unit each; VEC = elements in 16
+// The tile is UQ x UX units of VEC x VEC elements (UQ * UX = UNITS threads, one unit each; VEC = elements in 16
 // bytes), TQ = UQ * VEC along the input's innermost axis q by TX = UX * VEC along the output's innermost axis x.
 // A thread loads its unit as VEC rows of 16 bytes (a wave reads runs of UQ * 16 bytes), transposes it in
 // registers (32-bit elements: a renaming; 16-bit elements: one byte-permute per pair), and parks it in LDS as VEC
@@ -269,14 +269,18 @@ __global__ void __launch_bounds__(256) k_transpose_tile(const T* __restrict__ in
 // the memory pipeline takes 128-bit accesses at any element address.  [64,197,768] -> [64,768,197] bfloat16 (39 MB, cold)
 // 8.5 us, 25.7 as 32x32 tiles of single elements; 4001 x 3333 float32 (107 MB) 26.3 against 41.1; extents of whole units
 // as before (4096 x 4096 bfloat16 13.8 us).
-template <typename T, int UQ>
+// UNITS = 64, for matrices of at most 8 x 8 units: a tile per wavefront, four batch entries per workgroup.
+template <typename T, int UQ, int UNITS = 256>
 __global__ void __launch_bounds__(256) k_transpose_units(const T* __restrict__ in, T* __restrict__ out, TransposeP p) {
-  constexpr uint32_t VEC = 16 / sizeof(T), UX = 256 / UQ, TQ = UQ * VEC, TX = UX * VEC;
+  constexpr uint32_t VEC = 16 / sizeof(T), UX = UNITS / UQ, TQ = UQ * VEC, TX = UX * VEC;
   typedef typename AtAlignment<u32x4, (int)sizeof(T)>::type Unaligned;
-  __shared__ u32x4 tile[TQ * UX];
-  const TileAt t(p);
-  const uint32_t uq = threadIdx.x % UQ, ux = threadIdx.x / UQ;
-  if (t.bq * TQ + uq * VEC < p.nq && t.bx * TX + ux * VEC < p.nx) {
+  __shared__ u32x4 tiles[256 / UNITS][TQ * UX];
+  u32x4* const tile = tiles[threadIdx.x / UNITS];
+  const uint32_t tid = threadIdx.x % UNITS, index = blockIdx.x * (256u / UNITS) + threadIdx.x / UNITS;
+  const bool there = UNITS == 256 || index < p.n_tiles;
+  const TileAt t(p, there ? index : 0u);
+  const uint32_t uq = tid % UQ, ux = tid / UQ;
+  if (there && t.bq * TQ + uq * VEC < p.nq && t.bx * TX + ux * VEC < p.nx) {
     const uint32_t cq = min(t.bq * TQ + uq * VEC, p.nq - VEC), cx = min(t.bx * TX + ux * VEC, p.nx - VEC);
     u32x4 row[VEC];
 #pragma unroll
@@ -307,13 +311,13 @@ __global__ void __launch_bounds__(256) k_transpose_units(const T* __restrict__ i
   }
   __syncthreads();
   // store: piece u of column c -> 16 bytes of the column's output row
-  const uint32_t u = threadIdx.x % UX, c_first = threadIdx.x / UX;
+  const uint32_t u = tid % UX, c_first = tid / UX;
   const uint32_t x0 = t.bx * TX + u * VEC, cx = min(x0, p.nx - VEC);
 #pragma unroll
   for (uint32_t s = 0; s < TQ / UQ; ++s) {
     const uint32_t c = c_first + s * UQ, unit = c / VEC, q0 = t.bq * TQ + unit * VEC;
     const u32x4 v = tile[c * UX + (u ^ (unit & 7u))];
-    if (q0 < p.nq && x0 < p.nx)
+    if (there && q0 < p.nq && x0 < p.nx)
       __builtin_nontemporal_store(v, reinterpret_cast<Unaligned*>(out + t.out_base + (size_t)(min(q0, p.nq - VEC) + c % VEC) * p.out_row + cx));
   }
 }
@@ -353,6 +357,8 @@ const void* unfused_kernel_symbol(int32_t kernel, const KernelArgs& a) {
     case K_TRANSPOSE_TILE:
       if (a.u.transpose.vec > 1) {
         const bool wide = a.u.transpose.elem_bytes == 4;
+        if (a.u.transpose.tile_units == 64)
+          return wide ? (const void*)k_transpose_units<uint32_t, 8, 64> : (const void*)k_transpose_units<uint16_t, 8, 64>;
         switch (a.u.transpose.tile_uq) {
           case 8: return wide ? (const void*)k_transpose_units<uint32_t, 8> : (const void*)k_transpose_units<uint16_t, 8>;
           case 32: return wide ? (const void*)k_transpose_units<uint32_t, 32> : (const void*)k_transpose_units<uint16_t, 32>;

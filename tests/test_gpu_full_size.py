@@ -155,3 +155,12 @@ def test_transposes_of_any_extent_move_every_bit(dims, perm, dtype):
     torch.cuda.synchronize()
     assert torch.equal(buf[64:-64].reshape(want.shape), want), plan.info["kernel"]
     assert bool((buf[:64] == 77).all()) and bool((buf[-64:] == 77).all())
+
+
+@pytest.mark.parametrize("dims,perm", [((n, *m), (0, 2, 1)) for n in (1, 4, 7, 130) for m in ((4, 4), (9, 9), (32, 32), (31, 8), (33, 32), (32, 33))]
+                         + [((5, 64, 64), (0, 2, 1)), ((3, 65, 64), (0, 2, 1)), ((6, 64, 65), (0, 2, 1)), ((2, 3, 17, 20), (0, 1, 3, 2)), ((3, 2, 20, 9), (1, 0, 3, 2))])
+@pytest.mark.parametrize("dtype", ["f32", "f16"])
+def test_transposes_of_small_matrices(dims, perm, dtype):
+    """A tile per wavefront (matrices of at most 8 x 8 units of 16 bytes, batches that leave a workgroup's last wavefronts
+    without one) and its neighbours with a tile per workgroup."""
+    test_transposes_of_any_extent_move_every_bit(dims, perm, dtype)

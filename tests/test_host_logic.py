@@ -224,6 +224,13 @@ def test_transposes_that_only_rename_axes_are_planned_at_any_extent(dims, perm):
         B.Plan(B.Graph.from_spec(then), scheme)
 
 
+@pytest.mark.parametrize("dims,dtype,workgroups", [((4096, 20, 20), "bf16", 1024), ((4097, 20, 20), "bf16", 1025), ((4096, 64, 64), "f16", 1024),
+                                                   ((4096, 65, 64), "f16", 4096), ((4096, 32, 32), "f32", 1024), ((4096, 32, 33), "f32", 4096)])
+def test_transposes_of_small_matrices_share_workgroups(dims, dtype, workgroups):
+    info = B.Plan(B.Graph.from_spec(transpose_graph(dims, (0, 2, 1), dtype)), "auto").info
+    assert info["grid"][0] == workgroups and info["block"][0] == 256, info
+
+
 def test_pack_creation_and_errors(lib):
     from workloads.graphs import add_bias_layernorm_graph, rmsnorm_graph, softmax_backward_graph
     specs = [softmax_graph(64, 128, "f32"), add_bias_layernorm_graph(100, 768), rmsnorm_graph(50, 4096),
