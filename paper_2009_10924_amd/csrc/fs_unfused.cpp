@@ -287,9 +287,16 @@ fs_status build_unfused(const fs_graph& g, Candidate* out) {
         // Neighbouring workgroups walk along q where that makes them read whole lines of one short contiguous span
         // ([64,512,12,64] -> [64,12,64,512] float32: 36.1 against 37.4 us); along x otherwise: long or unaligned input
         // rows lose more than that on the writing side (4096 x 4096 float32 25.2 against 29.3, 4001 x 3333 26.5 / 39.0).
-        p.q_first = (uint64_t)p.in_row * p.elem_bytes % 128 == 0 && (uint64_t)p.nq * p.elem_bytes <= 3072 ? 1 : 0;
-        p.div[0] = make_fastdiv(p.q_first ? tq : tx);
-        p.div[1] = make_fastdiv(p.q_first ? tx : tq);
+        // Longer rows that are written out as rows of 1 to 2 KB take every other tile along q first, then the next x, then
+        // the tiles in between (us along x / along q / every other one, float32 to [.., h*d, s]): s 512 of 4 KB rows 49.7 /
+        // 48.8 / 46.5, of 8 KB rows 96.0 / 92.6 / 89.4, s 500 of 8 KB rows 61.5 / 54.2 / 51.0, s 256 25.3 / 24.4 / 23.9, s 384
+        // level; outside that span it loses: s 256 of 4 KB rows in bf16 13.0 / 13.2 / 13.7, s 2048 23.9 / 24.8 / 24.4.
+        const uint64_t read_row = (uint64_t)p.nq * p.elem_bytes, written_row = (uint64_t)p.out_row * p.elem_bytes;
+        if ((uint64_t)p.in_row * p.elem_bytes % 128 != 0) p.q_step = 0;
+        else if (read_row <= 3072) p.q_step = 1;
+        else p.q_step = tq % 2 == 0 && written_row >= 1024 && written_row <= 2048 ? 2 : 0;
+        p.div[0] = make_fastdiv(p.q_step ? tq / p.q_step : tx);
+        p.div[1] = make_fastdiv(p.q_step ? tx : tq);
         p.div[2] = make_fastdiv(batch[1]);
         for (const FastDiv& d : p.div)   // (both tile axes are at least 2 long, so none of these is near 2^31)
           if (d.d == 0) return fail(FS_ERR_SHAPE, "transpose: no exact division by one of its extents");

@@ -96,7 +96,8 @@ struct TransposeP {
   uint32_t tile_units, tile_uq; // vectorised tile: 16-byte units in all (256, or 64: a tile per wavefront) and along q (8, 16 or
                                 // 32); the tile is tile_uq * vec elements along q by (tile_units / tile_uq) * vec along x
   uint32_t n_tiles;
-  uint32_t q_first;             // neighbouring tiles follow one another 1: along q (they read one contiguous span), 0: along x
+  uint32_t q_step;              // neighbouring tiles follow one another 1: along q (they read one contiguous span), 2: along q,
+                                // every other one first, then along x, 0: along x
 };
 
 // ---- stitched -----------------------------------------------------------------

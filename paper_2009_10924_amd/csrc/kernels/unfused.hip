@@ -225,9 +225,14 @@ struct TileAt {
     rest = r;
     r = fast_div(rest, p.div[1]);
     const uint32_t outer = rest - r * p.div[1].d;
+    uint32_t phase = 0;
+    if (p.q_step == 2u) {
+      phase = r & 1u;
+      r >>= 1;
+    }
     const uint32_t b0 = fast_div(r, p.div[2]), b1 = r - b0 * p.div[2].d;
-    bq = p.q_first ? inner : outer;
-    bx = p.q_first ? outer : inner;
+    bq = p.q_step ? inner * p.q_step + phase : outer;
+    bx = p.q_step ? outer : inner;
     in_base = (size_t)b0 * p.in_batch[0] + (size_t)b1 * p.in_batch[1];
     out_base = (size_t)b0 * p.out_batch[0] + (size_t)b1 * p.out_batch[1];
   }

@@ -158,9 +158,10 @@ def test_transposes_of_any_extent_move_every_bit(dims, perm, dtype):
 
 
 @pytest.mark.parametrize("dims,perm", [((n, *m), (0, 2, 1)) for n in (1, 4, 7, 130) for m in ((4, 4), (9, 9), (32, 32), (31, 8), (33, 32), (32, 33))]
-                         + [((5, 64, 64), (0, 2, 1)), ((3, 65, 64), (0, 2, 1)), ((6, 64, 65), (0, 2, 1)), ((2, 3, 17, 20), (0, 1, 3, 2)), ((3, 2, 20, 9), (1, 0, 3, 2))])
+                         + [((5, 64, 64), (0, 2, 1)), ((3, 65, 64), (0, 2, 1)), ((6, 64, 65), (0, 2, 1)), ((2, 3, 17, 20), (0, 1, 3, 2)), ((3, 2, 20, 9), (1, 0, 3, 2))]
+                         + [((2, 300, 16, 128), (0, 2, 3, 1)), ((3, 512, 11, 128), (0, 2, 3, 1)), ((2, 256, 13, 96), (0, 2, 3, 1)), ((257, 4096), (1, 0))])
 @pytest.mark.parametrize("dtype", ["f32", "f16"])
-def test_transposes_of_small_matrices(dims, perm, dtype):
+def test_transposes_of_small_matrices_and_of_long_rows(dims, perm, dtype):
     """A tile per wavefront (matrices of at most 8 x 8 units of 16 bytes, batches that leave a workgroup's last wavefronts
-    without one) and its neighbours with a tile per workgroup."""
+    without one) and its neighbours with a tile per workgroup; rows whose tiles are walked every other one first."""
     test_transposes_of_any_extent_move_every_bit(dims, perm, dtype)
