@@ -409,3 +409,30 @@ def test_workgroups_that_work_through_several_rows(rows, cols, dtype):
         for name, dt in spec.outputs:
             err = O.max_rel_err(member[name], ref[name].reshape(member[name].shape), floors.get(name, 0.0))
             assert err <= (1e-5 if dt == "f32" else 1e-2), (spec.name, name, err)
+
+
+@pytest.mark.parametrize("rows", [2, 15, 16, 17, 113, 128, 129, 513, 641])
+def test_folds_of_any_number_of_partial_rows(rows):
+    """A row of partial sums per row of the pattern: numbers that leave the fold's row groups without a row, with a partial
+    batch of loads and with a whole one; the workspace holds NaN wherever no partial sum is written."""
+    import torch
+    if not B.codegen_available():
+        pytest.skip("patterns with column sums exist as generated kernels only")
+    spec = rmsnorm_backward_graph(rows, 516, "f32")
+    inp = make_inputs(spec, seed=5)
+    ref = O.evaluate(spec, inp)
+    floors = floors_for(spec, inp, ref)
+    graph = B.Graph.from_spec(spec)
+    which = [i for i, c in enumerate(B.Plan(graph, "auto").candidates()) if "L256" in c["kernel"] and "rows1>" in c["kernel"]]
+    assert which
+    for i in which:
+        plan = B.Plan(graph, "auto", candidate=i)
+        assert plan.info["grid"][0] == rows
+        held = [B.to_device(inp[t.name], t.dtype) for t in spec.inputs]
+        out = B.alloc_outputs(spec)
+        ws = torch.full((plan.info["workspace_bytes"] + 4096,), 0xFF, dtype=torch.uint8, device="cuda")
+        plan.execute_ptrs([t.data_ptr() for t in held], [t.data_ptr() for t in out], ws.data_ptr(), plan.info["workspace_bytes"], torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        for (name, dt), got in zip(spec.outputs, out):
+            err = O.max_rel_err(O.to_f64(B.to_host(got, dt), dt).reshape(ref[name].shape), ref[name], floors.get(name, 0.0))
+            assert err <= 1e-5, (rows, plan.info["kernel"], name, err)
