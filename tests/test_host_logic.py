@@ -8,7 +8,8 @@ import pytest
 
 from paper_2009_10924_amd import binding as B
 from workloads import (FULL_CONFIGS, add_bias_layernorm_graph, attention_scores_graph, bias_gelu_dbias_graph,
-                       bias_gelu_graph, softmax_graph, transpose_chain_graph, transpose_graph)
+                       bias_gelu_graph, gelu_backward_graph, layernorm_backward_bias_graph, layernorm_backward_graph,
+                       rmsnorm_backward_graph, softmax_graph, transpose_chain_graph, transpose_graph)
 from workloads.graphs import GraphSpec, OpSpec, TensorSpec
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -229,6 +230,19 @@ def test_transposes_that_only_rename_axes_are_planned_at_any_extent(dims, perm):
 def test_transposes_of_small_matrices_share_workgroups(dims, dtype, workgroups):
     info = B.Plan(B.Graph.from_spec(transpose_graph(dims, (0, 2, 1), dtype)), "auto").info
     assert info["grid"][0] == workgroups and info["block"][0] == 256, info
+
+
+@pytest.mark.parametrize("make,rows,cols,dtype", [(layernorm_backward_graph, 6617, 1088, "bf16"), (layernorm_backward_graph, 17807, 1408, "bf16"),
+                                                 (layernorm_backward_graph, 12343, 1120, "bf16"), (layernorm_backward_graph, 60000, 1024, "f32"),
+                                                 (rmsnorm_backward_graph, 16679, 1544, "bf16"), (rmsnorm_backward_graph, 30011, 2048, "f16"),
+                                                 (layernorm_backward_bias_graph, 18756, 368, "bf16"), (layernorm_backward_bias_graph, 33102, 744, "bf16"),
+                                                 (bias_gelu_dbias_graph, 65536, 4096, "f16"), (gelu_backward_graph, 30000, 3333, "f32")])
+def test_partial_sums_that_can_fit_the_static_scratch_do(make, rows, cols, dtype):
+    """Whatever the rows: the plan that AUTO makes is one that fs_execute_static takes."""
+    plan = B.Plan(B.Graph.from_spec(make(rows, cols, dtype)), "auto")
+    if plan.info["scheme"] == "unfused":
+        pytest.skip("needs the run-time compiler")
+    assert 0 < plan.info["workspace_bytes"] <= B.FS_STATIC_SCRATCH_BYTES, plan.info
 
 
 def test_pack_creation_and_errors(lib):
