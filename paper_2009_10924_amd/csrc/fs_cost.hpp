@@ -39,6 +39,7 @@ struct DeviceModel {
   double fold_s = 3.0e-6, fold_batch_s = 0.1e-6;   // the fold launch, and per 512 rows of partial sums
   double lds_Bps = 60.0e12;          // aggregate LDS bandwidth
   double barrier_s = 0.55e-6;        // one workgroup barrier incl. the LDS round trip and the wait for the slowest wave
+  double first_load_s = 0.6e-6;      // a software-pipelined loop over rows: the part of the first row's load latency that shows
   double cycles_valu = 4.0;          // issue cycles of one wave-wide VALU op on a 16-lane SIMD
   double cycles_trans = 16.0;        // quarter-rate transcendental
   double cycles_xlane = 12.0;        // DPP / permute step incl. its dependency stall
@@ -57,7 +58,8 @@ struct KernelCost {
   int32_t waves_per_block = 4;
   double bytes_in_flight_per_lane = 16; // independent load bytes a lane has outstanding
   double rows_per_wave_loop = 1;        // sequential trips of the kernel's outer loop per wave
-  int32_t dep_phases = 1;               // dependent global-memory phases per trip
+  double dep_phases = 1;                // dependent global-memory phases per trip (a part of one: partly hidden)
+  bool first_load = false;              // the first trip's loads are waited for before the loop
   int32_t xlane_steps = 0;              // cross-lane steps per trip
   int32_t barriers = 0;                 // workgroup barriers per trip
   int32_t vgpr_estimate = 32;
