@@ -55,7 +55,13 @@ CostResult evaluate(const KernelCost& k, int32_t vgprs_compiled) {
   const double in_flight = resident * 64.0 * k.bytes_in_flight_per_lane * util;
   double bw = std::min(d.hbm_peak_Bps * d.stream_fraction, in_flight / d.queue_latency_s);
   if (k.access_run_bytes > 0 && k.access_run_bytes < 128) bw /= 1.0 + (128.0 / k.access_run_bytes - 1.0);
-  if (k.access_run_bytes > 0 && k.row_bytes > 0 && std::fmod(k.row_bytes, 128.0) != 0.0 && k.rows_per_wave_loop <= 1) bw /= 1.0 + 1.65 * std::min(4.0, 128.0 / k.access_run_bytes);
+  if (k.access_run_bytes > 0 && k.row_bytes > 0 && std::fmod(k.row_bytes, 128.0) != 0.0) {
+    // (fitted for each of the three kinds of loop; a workgroup that works through several rows finds the line that two of
+    // them share in its caches more often, and column sums are bound by other things first)
+    const double shared_lines = k.rows_per_wave_loop <= 1 ? 1.65 : k.partial_bytes > 0 ? 0.3 : 1.07;
+    bw /= 1.0 + shared_lines * std::min(4.0, 128.0 / k.access_run_bytes);
+  }
+  bw /= 1.0 + k.stream_penalty;
   if (k.store_run_bytes > 0 && k.store_run_bytes < 512) bw *= 0.97;
   bw /= 1.0 + 0.12 * (1.0 / util - 1.0);
   bw /= 1.0 + 0.25 * (rounds / rounds_exact - 1.0);

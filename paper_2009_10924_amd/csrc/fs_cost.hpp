@@ -67,6 +67,7 @@ struct KernelCost {
   double lane_utilisation = 1.0;        // fraction of lanes holding data
   double access_run_bytes = 0;          // contiguous bytes one row group touches per load (0 = long)
   double row_bytes = 0;                 // from one row to the next, in the narrowest row operand (0 = not row by row)
+  double stream_penalty = 0;            // the streaming rate falls to 1 / (1 + this) for reasons of the kernel's own
   double store_run_bytes = 0;           // contiguous run written by one store instruction group (0 = long)
   double preamble_instr = 40;           // VALU instructions a wave runs before it can issue its first load
   double serial_tail_s = 0;             // work done by a single workgroup after the rest finished

@@ -952,6 +952,15 @@ void make_generated(const Compiler& c, int vec, const Shape& s, Candidate* cand)
     gc.serial_tail_s += d.mem_latency_s;
     gc.bytes_in_flight_per_lane *= 2.0;
     gc.vgpr_estimate += 2 * s.K * base.n_full;
+    // Several rows per workgroup lose where more is written than read (stores and loads of one loop wait for each other:
+    // normalisation with a float32 copy of a row scalar, 72 pairs of shapes, 9 % on average) and where few workgroups with
+    // little to do each are left (LayerNorm with statistics 31 MB on 588 workgroups 22 %, 67 MB on 512 gains 11 %).
+    double read = 0, written = 0;
+    for (int i = 0; i < base.n_full; ++i)
+      if (!((base.full_bcast >> i) & 1u)) read += dtype_bytes(base.full_dt[i]);
+    for (int i = 0; i < base.n_instr; ++i)
+      if (base.instr[i].op == PO_STORE) written += dtype_bytes(base.instr[i].aux);
+    if (written > read || (gl.shape.grid[0] < 896 && gc.hbm_bytes < 60e6)) gc.stream_penalty = 0.15;
   }
   if (s.NC > 1) {
     // a pass over the row per reduction re-reads the operands (counted as device-memory traffic: the rows in flight

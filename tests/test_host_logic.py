@@ -9,6 +9,7 @@ import pytest
 from paper_2009_10924_amd import binding as B
 from workloads import (FULL_CONFIGS, add_bias_layernorm_graph, attention_scores_graph, bias_gelu_dbias_graph,
                        bias_gelu_graph, gelu_backward_graph, layernorm_backward_bias_graph, layernorm_backward_graph,
+                       layernorm_stats_graph, normalize_from_stats_graph, rmsnorm_graph,
                        rmsnorm_backward_graph, softmax_graph, transpose_chain_graph, transpose_graph)
 from workloads.graphs import GraphSpec, OpSpec, TensorSpec
 
@@ -250,6 +251,18 @@ def test_layernorm_backward_loads_one_row_at_a_time(rows, cols):
     """Several rows loaded together were ranked first and measured 10 to 18 % slower."""
     kernel = B.Plan(B.Graph.from_spec(layernorm_backward_graph(rows, cols, "f16")), "auto").info["kernel"]
     assert ",R1," in kernel, kernel
+
+
+@pytest.mark.parametrize("spec,several", [(normalize_from_stats_graph(3000, 1000), False), (normalize_from_stats_graph(16384, 520), False),
+                                          (normalize_from_stats_graph(8192, 2056), False), (normalize_from_stats_graph(22701, 920, "bf16"), False),
+                                          (layernorm_stats_graph(2145, 1342, in_dtype="bf16", out_dtype="bf16"), False),
+                                          (rmsnorm_graph(8192, 4099), True),
+                                          (layernorm_stats_graph(4096, 2051, in_dtype="f32", out_dtype="f32", with_variance=True), True)])
+def test_several_rows_per_workgroup_only_where_they_gain(spec, several):
+    if not B.codegen_available():
+        pytest.skip("these shapes exist as generated kernels only")
+    kernel = B.Plan(B.Graph.from_spec(spec), "auto").info["kernel"]
+    assert (",rows" in kernel) == several, kernel
 
 
 def test_pack_creation_and_errors(lib):
