@@ -42,7 +42,8 @@ CostResult evaluate(const KernelCost& k, int32_t vgprs_compiled) {
   // two or three waves on a SIMD do not cover each other's instruction latencies
   const double issue_stall = r.waves_per_simd < 4 ? 1.0 + 0.6 * (4 - r.waves_per_simd) : 1.0;
   const double t_issue = cycles * simd_share * issue_stall / d.clock_hz;
-  const double t_trip = k.dep_phases * d.mem_latency_s + k.barriers * d.barrier_s + t_issue;
+  const double t_barrier = d.barrier_idle_s + (d.barrier_s - d.barrier_idle_s) * std::min(1.0, resident / (d.n_cu * d.simd_per_cu));
+  const double t_trip = k.dep_phases * d.mem_latency_s + k.barriers * t_barrier + t_issue;
   const double t_latency = rounds * (k.rows_per_wave_loop * t_trip + (k.first_load ? d.first_load_s : 0.0));
 
   // Streaming floor.  Achievable bandwidth = the measured copy rate, derated for

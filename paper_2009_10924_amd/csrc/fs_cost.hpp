@@ -38,7 +38,9 @@ struct DeviceModel {
   double flush_step_s = 9e-9, flush_value_s = 14e-9, flush_block_s = 30e-9;   // per value: each lane fold, LDS + store; store alone
   double fold_s = 3.0e-6, fold_batch_s = 0.1e-6;   // the fold launch, and per 512 rows of partial sums
   double lds_Bps = 60.0e12;          // aggregate LDS bandwidth
-  double barrier_s = 0.55e-6;        // one workgroup barrier incl. the LDS round trip and the wait for the slowest wave
+  // One workgroup barrier incl. the LDS round trip and the wait for the slowest wave: by itself, and where every SIMD has
+  // wavefronts of its own to wait for (LayerNorm of 72 rows x 1888: wave form 4.7 us, block form 3.8; of 3000 x 1000: 7.9, 8.4).
+  double barrier_idle_s = 0.15e-6, barrier_s = 0.65e-6;
   double first_load_s = 0.6e-6;      // a software-pipelined loop over rows: the part of the first row's load latency that shows
   double cycles_valu = 4.0;          // issue cycles of one wave-wide VALU op on a 16-lane SIMD
   double cycles_trans = 16.0;        // quarter-rate transcendental

@@ -172,8 +172,8 @@ bool build_softmax(const fs_graph& g, std::vector<Candidate>* out, PackForm* pac
       kc.barriers = 2;
       kc.lds_bytes_per_block = 32;
       kc.lane_utilisation = (double)nvec / ((double)T * K);
-      kc.access_run_bytes = 1024.0;
       kc.row_bytes = (double)p.cols * esz;
+      kc.access_run_bytes = std::min(1024.0, kc.row_bytes);
       char var[32];
       snprintf(var, sizeof var, "<%s,K%d,T%u>", dtype_name(p.in_dt), K, T);
       finish_candidate(&c, var, kc);

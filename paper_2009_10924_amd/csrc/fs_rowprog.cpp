@@ -1048,6 +1048,7 @@ void add_column_sums(const Compiler& c, int vec, const Shape& s, int64_t bytes_m
   gc.rows_per_wave_loop = s.R;
   if (s.R > 1) {   // software-pipelined: only the first row's load latency is exposed
     gc.dep_phases = 0;
+    gc.first_load = true;
     gc.bytes_in_flight_per_lane *= 2.0;   // this row's and the next row's loads
   }
   gc.lds_bytes_per_block = cand->info.lds_bytes;

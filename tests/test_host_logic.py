@@ -265,6 +265,15 @@ def test_several_rows_per_workgroup_only_where_they_gain(spec, several):
     assert (",rows" in kernel) == several, kernel
 
 
+@pytest.mark.parametrize("spec,form", [(layernorm_stats_graph(72, 1888), "layernorm_block"), (add_bias_layernorm_graph(65, 2880, in_dtype="bf16"), "layernorm_block"),
+                                       (add_bias_layernorm_graph(8192, 768), "layernorm_wave"), (softmax_graph(3831, 16, "bf16"), "softmax_wave"),
+                                       (attention_scores_graph(20, 16, 16, 16), "softmax_wave")])
+def test_wavefront_or_workgroup_per_row(spec, form):
+    """A few long rows take a workgroup each (a barrier with nobody to wait for is cheap); tiny rows never do."""
+    kernel = B.Plan(B.Graph.from_spec(spec), "auto").info["kernel"]
+    assert kernel.startswith(form + "<"), kernel
+
+
 def test_pack_creation_and_errors(lib):
     from workloads.graphs import add_bias_layernorm_graph, rmsnorm_graph, softmax_backward_graph
     specs = [softmax_graph(64, 128, "f32"), add_bias_layernorm_graph(100, 768), rmsnorm_graph(50, 4096),
