@@ -10,6 +10,48 @@ const DeviceModel& device() {
   return d;
 }
 
+// What the streaming rate is divided by for the runs in which rows are accessed, see evaluate().
+static double run_derating(const KernelCost& k) {
+  double f = 1.0;
+  if (k.access_run_bytes > 0 && k.access_run_bytes < 128) f *= 1.0 + (128.0 / k.access_run_bytes - 1.0);
+  if (k.access_run_bytes > 0 && k.row_bytes > 0 && std::fmod(k.row_bytes, 128.0) != 0.0) {
+    // (fitted for each of the three kinds of loop; a workgroup that works through several rows finds the line that two of
+    // them share in its caches more often, and column sums are bound by other things first)
+    const double shared_lines = k.rows_per_wave_loop <= 1 ? 1.65 : k.partial_bytes > 0 ? 0.3 : 1.07;
+    f *= 1.0 + shared_lines * std::min(4.0, 128.0 / k.access_run_bytes);
+  }
+  return f;
+}
+
+KernelCost together(const std::vector<const KernelCost*>& members) {
+  KernelCost t;
+  t.hbm_bytes = t.elems = t.waves = 0;
+  double valu = 0, trans = 0, bif = 0, lanes = 0, xlane = 0, barriers = 0;
+  t.vgpr_estimate = 0;
+  for (const KernelCost* m : members) {
+    t.hbm_bytes += m->hbm_bytes * run_derating(*m);
+    t.cache_bytes += m->cache_bytes;
+    t.elems += m->elems;
+    t.waves += m->waves;
+    valu += m->valu_per_elem * m->elems;
+    trans += m->trans_per_elem * m->elems;
+    bif += m->bytes_in_flight_per_lane * m->waves;
+    lanes += m->elems / std::max(0.05, m->lane_utilisation);
+    xlane += m->xlane_steps * m->waves;
+    barriers += m->barriers * m->waves;
+    t.vgpr_estimate = std::max(t.vgpr_estimate, m->vgpr_estimate);
+    t.lds_bytes_per_block = std::max(t.lds_bytes_per_block, m->lds_bytes_per_block);
+    t.serial_tail_s = std::max(t.serial_tail_s, m->serial_tail_s);
+  }
+  t.valu_per_elem = valu / t.elems;
+  t.trans_per_elem = trans / t.elems;
+  t.bytes_in_flight_per_lane = bif / t.waves;
+  t.lane_utilisation = t.elems / lanes;
+  t.xlane_steps = (int32_t)std::lround(xlane / t.waves);
+  t.barriers = (int32_t)std::lround(barriers / t.waves);
+  return t;
+}
+
 CostResult evaluate(const KernelCost& k, int32_t vgprs_compiled) {
   const DeviceModel& d = device();
   CostResult r;
@@ -55,13 +97,7 @@ CostResult evaluate(const KernelCost& k, int32_t vgprs_compiled) {
   //   * a last, partly filled round of wavefronts.
   const double in_flight = resident * 64.0 * k.bytes_in_flight_per_lane * util;
   double bw = std::min(d.hbm_peak_Bps * d.stream_fraction, in_flight / d.queue_latency_s);
-  if (k.access_run_bytes > 0 && k.access_run_bytes < 128) bw /= 1.0 + (128.0 / k.access_run_bytes - 1.0);
-  if (k.access_run_bytes > 0 && k.row_bytes > 0 && std::fmod(k.row_bytes, 128.0) != 0.0) {
-    // (fitted for each of the three kinds of loop; a workgroup that works through several rows finds the line that two of
-    // them share in its caches more often, and column sums are bound by other things first)
-    const double shared_lines = k.rows_per_wave_loop <= 1 ? 1.65 : k.partial_bytes > 0 ? 0.3 : 1.07;
-    bw /= 1.0 + shared_lines * std::min(4.0, 128.0 / k.access_run_bytes);
-  }
+  bw /= run_derating(k);
   bw /= 1.0 + k.stream_penalty;
   if (k.store_run_bytes > 0 && k.store_run_bytes < 512) bw *= 0.97;
   bw /= 1.0 + 0.12 * (1.0 / util - 1.0);

@@ -5,6 +5,7 @@
 // kernels run at the memory roofline, not at the instruction-issue limit.
 #pragma once
 #include <cstdint>
+#include <vector>
 
 namespace fs {
 
@@ -85,5 +86,7 @@ struct CostResult {
   int32_t vgprs = 0;
 };
 CostResult evaluate(const KernelCost& k, int32_t vgprs_compiled);
+// Several kernels without loops over rows or column sums as one launch with the registers of the hungriest.
+KernelCost together(const std::vector<const KernelCost*>& members);
 
 }  // namespace fs

@@ -109,17 +109,18 @@ struct Candidate {
 }  // namespace fs
 
 namespace fs {
-// A plan's pattern as a row program with a launch shape: the form in which it can join a generated packed kernel.
+// A plan's pattern as a row program with a launch shape: a form in which it can join a generated packed kernel.
 struct GenericForm {
-  bool valid = false;
   RowProgP prog;
   BufRef ptr[kMaxPtrs];
   uint32_t blocks = 0;
+  KernelCost cost;
+  double predicted_us = 0;   // by itself
 };
 }  // namespace fs
 
 struct fs_plan {
-  fs::GenericForm generic;
+  std::vector<fs::GenericForm> generic;   // the faster by itself first, each later one with fewer registers; empty: none
   std::vector<fs::Candidate> candidates;
   int32_t chosen = 0;
   int32_t n_inputs = 0, n_outputs = 0;

@@ -5,6 +5,7 @@
 // the kernel arguments, so nothing is allocated or copied on the device side.
 #include <algorithm>
 #include <cstring>
+#include <functional>
 
 #include "fs_internal.hpp"
 
@@ -58,42 +59,105 @@ bool shape_member(const PackForm& f, PackEntry* e, uint32_t* blocks) {
   return true;
 }
 
+// Which form each of `n` members takes, the most promising assignment first.  The packed kernel has the registers of its
+// hungriest member, and every other one runs at that occupancy: for each register count that some form has, every member
+// takes its fastest form with no more (or its leanest), and the evaluator ranks the launches that this makes.  Measured
+// (us, every member's fastest form / at most 64 registers wherever there are any / this): 32 members of 114 rows up to 5568
+// long 16.1 / 12.1 / 12.1, two each of four kinds of 1000 rows 15.7 / 17.1 / 12.9, 32 LayerNorms 128 x 768 7.6 / 9.4 / 7.6,
+// two of 8192 x 768 with statistics 22.5 / 23.2 / 22.6.
+std::vector<std::vector<const GenericForm*>> form_assignments(const fs_plan* const* plans, int32_t n) {
+  std::vector<int32_t> caps;
+  for (int i = 0; i < n; ++i)
+    for (const GenericForm& f : plans[i]->generic) caps.push_back(f.cost.vgpr_estimate);
+  std::sort(caps.begin(), caps.end(), std::greater<int32_t>());
+  caps.erase(std::unique(caps.begin(), caps.end()), caps.end());
+  std::vector<std::pair<double, std::vector<const GenericForm*>>> ranked;
+  for (int32_t cap : caps) {
+    std::vector<const GenericForm*> forms;
+    std::vector<const KernelCost*> costs;
+    for (int i = 0; i < n; ++i) {
+      const std::vector<GenericForm>& all = plans[i]->generic;
+      size_t k = 0;
+      while (k + 1 < all.size() && all[k].cost.vgpr_estimate > cap) ++k;
+      forms.push_back(&all[k]);
+      costs.push_back(&all[k].cost);
+    }
+    if (!ranked.empty() && ranked.back().second == forms) continue;
+    const KernelCost all_together = together(costs);
+    double t = evaluate(all_together, 0).seconds;
+    for (const KernelCost* c : costs) t = std::max(t, evaluate(*c, all_together.vgpr_estimate).seconds);   // no sooner than the slowest member
+    ranked.emplace_back(t, std::move(forms));
+  }
+  std::stable_sort(ranked.begin(), ranked.end(), [](const auto& a, const auto& b) { return a.first < b.first; });
+  std::vector<std::vector<const GenericForm*>> out;
+  for (auto& r : ranked) out.push_back(std::move(r.second));
+  return out;
+}
+
+// The packed kernel of `n` members in the given forms; false: it does not compile, or spills registers.
+bool compile_packed(const std::vector<const GenericForm*>& forms, fs_pack::GenLaunch* gl, std::vector<std::vector<int>>* slots, int32_t* vgprs) {
+  std::vector<RowProgP> progs;
+  std::vector<uint32_t> blocks;
+  uint64_t total = 0;
+  for (const GenericForm* f : forms) {
+    progs.push_back(f->prog);
+    blocks.push_back(f->blocks);
+    total += f->blocks;
+  }
+  if (total >= (1ull << 31)) return false;
+  std::string entry;
+  const std::string source = embedded_prelude() + generate_pack_kernel(progs, blocks, slots, &entry);
+  std::string log;
+  if (gen_compile(source, entry.c_str(), &gl->kernel, &log) != 0) return false;
+  const GenResources res = gen_resources(gl->kernel.get());
+  if (res.scratch_bytes > 0 || gen_preload(gl->kernel.get()) != 0) {
+    gl->kernel.reset();
+    return false;
+  }
+  *vgprs = res.vgprs;
+  gl->blocks = (uint32_t)total;
+  return true;
+}
+
 // The pack as generated kernels, one per 32 members, each made for exactly its members (a device function per
 // member, dispatched on the workgroup index; the operand pointers travel in one table in the kernel arguments).
-// false if some member has no row-program form or a kernel does not compile: the caller then tries the fixed
-// packed kernel.
+// A kernel over many members may spill registers although each member's own does not: then the next assignment of forms
+// is tried, the leanest at the latest.  false if some member has no row-program form or no kernel serves: the caller then
+// tries the fixed packed kernel.
 bool build_generated_pack(const fs_plan* const* plans, int32_t n, fs_pack* pk) {
   if (!codegen_enabled()) return false;
   for (int i = 0; i < n; ++i)
-    if (!plans[i] || !plans[i]->generic.valid) return false;
+    if (!plans[i] || plans[i]->generic.empty()) return false;
   int32_t first_input = 0, first_output = 0;
   int32_t vgprs = 0;
   for (int begin = 0; begin < n; begin += kPackMaxMembers) {
     const int end = std::min(n, begin + kPackMaxMembers);
-    std::vector<RowProgP> progs;
-    std::vector<uint32_t> blocks;
-    uint64_t total = 0;
-    for (int i = begin; i < end; ++i) {
-      progs.push_back(plans[i]->generic.prog);
-      blocks.push_back(plans[i]->generic.blocks);
-      total += plans[i]->generic.blocks;
+    std::vector<std::vector<const GenericForm*>> tries = form_assignments(plans + begin, end - begin);
+    if (tries.size() > 3) {   // two by rank, then the one with the fewest registers
+      const auto registers = [](const std::vector<const GenericForm*>& forms) {
+        int32_t most = 0;
+        for (const GenericForm* f : forms) most = std::max(most, f->cost.vgpr_estimate);
+        return most;
+      };
+      auto leanest = std::min_element(tries.begin() + 2, tries.end(), [&](const auto& a, const auto& b) { return registers(a) < registers(b); });
+      std::swap(tries[2], *leanest);
+      tries.resize(3);
     }
-    if (total >= (1ull << 31)) return false;
-    std::vector<std::vector<int>> slots;
-    std::string entry;
-    const std::string source = embedded_prelude() + generate_pack_kernel(progs, blocks, &slots, &entry);
     fs_pack::GenLaunch gl;
-    std::string log;
-    if (gen_compile(source, entry.c_str(), &gl.kernel, &log) != 0) return false;
-    const GenResources res = gen_resources(gl.kernel.get());
-    if (res.scratch_bytes > 0) return false;
-    if (gen_preload(gl.kernel.get()) != 0) return false;
-    vgprs = std::max(vgprs, res.vgprs);
-    gl.blocks = (uint32_t)total;
+    std::vector<std::vector<int>> slots;
+    const std::vector<const GenericForm*>* forms = nullptr;
+    for (const auto& t : tries) {
+      int32_t used = 0;
+      if (!compile_packed(t, &gl, &slots, &used)) continue;
+      forms = &t;
+      vgprs = std::max(vgprs, used);
+      break;
+    }
+    if (!forms) return false;
     for (int i = begin; i < end; ++i) {
       const fs_plan* p = plans[i];
       for (int slot : slots[i - begin]) {
-        const BufRef& r = p->generic.ptr[slot];
+        const BufRef& r = (*forms)[i - begin]->ptr[slot];
         fs_pack::PtrRef pr;
         pr.kind = r.kind;
         pr.index = (r.kind == BUF_INPUT ? first_input : first_output) + r.slot;
@@ -104,7 +168,7 @@ bool build_generated_pack(const fs_plan* const* plans, int32_t n, fs_pack* pk) {
       first_output += p->n_outputs;
     }
     if (gl.ptrs.size() > 480) return false;   // the table travels in 4 KB of kernel arguments
-    pk->info.grid += (int32_t)total;
+    pk->info.grid += (int32_t)gl.blocks;
     pk->generated.push_back(gl);
   }
   pk->info.vgprs = vgprs;

@@ -95,42 +95,52 @@ bool codegen_enabled() {
   return v != 0 && gen_available();
 }
 
-// The pattern as a row program with a launch shape, for packed launches generated over several plans: the chosen
-// candidate's own program if it runs one, else (a hand-written family) the best generated shape of the same pattern.
+// The pattern as a row program with a launch shape, for packed launches generated over several plans: every generated
+// shape of the pattern that no other one beats in both time and registers (the packed kernel has the registers of its
+// hungriest member, so which of them serves best is for the pack to say); where the caller has asked for a shape, or no
+// generated one is offered, the chosen candidate's own program.
 // Patterns with column sums stay out: their fold is a launch of its own.
-static void fill_generic_form(const fs_graph& g, fs_plan* p) {
-  auto take = [&](const Candidate& c) {
+static void fill_generic_forms(const fs_graph& g, fs_plan* p) {
+  // a packed kernel's workgroups have 256 threads; rows worked through in chunks, or several by one workgroup, take a
+  // launch of their own
+  auto packs = [](const Candidate& c) {
     if (c.launches.size() != 1) return false;
     const Launch& l = c.launches.front();
-    if ((l.kernel != K_ROW_GENERATED && l.kernel != K_ROW_PROGRAM) || l.args.u.prog.n_colsum > 0) return false;
-    if (l.shape.block[0] != 256) return false;   // a packed kernel's workgroups have 256 threads
-    // rows worked through in chunks, or several by one workgroup: a launch of its own
-    if (l.args.u.prog.col_chunks > 1 || l.args.u.prog.rows_per_group > 1) return false;
-    p->generic.valid = true;
-    p->generic.prog = l.args.u.prog;
-    for (int k = 0; k < kMaxPtrs; ++k) p->generic.ptr[k] = l.ptr[k];
-    p->generic.blocks = l.shape.grid[0];
-    return true;
+    if ((l.kernel != K_ROW_GENERATED && l.kernel != K_ROW_PROGRAM) || l.shape.block[0] != 256) return false;
+    const RowProgP& q = l.args.u.prog;
+    return q.n_colsum == 0 && q.col_chunks <= 1 && q.rows_per_group <= 1;
   };
-  if (take(p->candidates[p->chosen])) return;
-  if (p->candidates[p->chosen].info.scheme == FS_SCHEME_UNFUSED) return;
-  std::vector<Candidate> cands;
-  if (!build_row_program(g, &cands)) return;
-  int best = -1;
-  bool best_slim = false;
-  for (int i = 0; i < (int)cands.size(); ++i) {
-    if (cands[i].launches.size() != 1 || cands[i].launches.front().kernel != K_ROW_GENERATED) continue;
-    const RowProgP& prog = cands[i].launches.front().args.u.prog;
-    if (cands[i].launches.front().shape.block[0] != 256 || prog.col_chunks > 1 || prog.rows_per_group > 1) continue;
-    predict(&cands[i]);
-    // the packed kernel has the registers of its hungriest member: shapes beyond eight wavefronts per SIMD are passed over
-    const bool slim = cands[i].cost.vgpr_estimate <= 64;
-    if (best < 0 || slim > best_slim || (slim == best_slim && cands[i].info.predicted_us < cands[best].info.predicted_us)) {
-      best = i;
-      best_slim = slim;
-    }
+  auto add = [&](const Candidate& c) {
+    const Launch& l = c.launches.front();
+    p->generic.emplace_back();
+    GenericForm& f = p->generic.back();
+    f.prog = l.args.u.prog;
+    for (int k = 0; k < kMaxPtrs; ++k) f.ptr[k] = l.ptr[k];
+    f.blocks = l.shape.grid[0];
+    f.cost = c.cost;
+    f.predicted_us = c.info.predicted_us;
+  };
+  const Candidate& own = p->candidates[p->chosen];
+  const bool asked = p->opts.candidate >= 0 || p->opts.block_threads > 0 || p->opts.lanes_per_row > 0 || p->opts.vecs_per_lane > 0;
+  if (packs(own) && (asked || own.launches.front().kernel == K_ROW_PROGRAM)) return add(own);
+  if (own.info.scheme == FS_SCHEME_UNFUSED) return;
+  std::vector<Candidate> built;
+  const bool row_program = own.launches.front().kernel == K_ROW_GENERATED;
+  if (!row_program && !build_row_program(g, &built)) return;
+  std::vector<Candidate>& cands = row_program ? p->candidates : built;
+  std::vector<Candidate*> order;
+  for (Candidate& c : cands) {
+    if (!packs(c) || c.launches.front().kernel != K_ROW_GENERATED) continue;
+    if (!row_program) predict(&c);
+    order.push_back(&c);
   }
-  if (best >= 0) take(cands[best]);
+  std::stable_sort(order.begin(), order.end(), [](const Candidate* a, const Candidate* b) { return a->info.predicted_us < b->info.predicted_us; });
+  int32_t fewest = INT32_MAX;
+  for (const Candidate* c : order)
+    if (c->cost.vgpr_estimate < fewest) {
+      fewest = c->cost.vgpr_estimate;
+      add(*c);
+    }
 }
 
 fs_status complete_plan(fs_plan* p) {
@@ -324,7 +334,7 @@ fs_status fs::create_plan(const fs_graph* g, int32_t scheme, const fs_plan_opts*
   p->n_outputs = (int32_t)g->outputs.size();
   for (int t : g->inputs) p->input_bytes.push_back(g->tensors[t].numel() * dtype_bytes(g->tensors[t].dtype));
   for (int t : g->outputs) p->output_bytes.push_back(g->tensors[t].numel() * dtype_bytes(g->tensors[t].store_as));
-  if (scheme != FS_SCHEME_UNFUSED && codegen_enabled()) fill_generic_form(*g, p);
+  if (scheme != FS_SCHEME_UNFUSED && codegen_enabled()) fill_generic_forms(*g, p);
   if (complete) {
     const fs_status s = complete_plan(p);
     if (s != FS_OK) {

@@ -103,3 +103,15 @@ def test_pack_layer_norm_variant_without_residual():
     plain = dataclasses.replace(full, inputs=[t for t in full.inputs if t.name in ("x", "gamma", "beta")], ops=ops)
     worst, _ = _check_members([plain, full], seeds=[4, 5])
     note(f"plain + full LayerNorm members: worst {worst:.3f} of the bar")
+
+
+@pytest.mark.parametrize("rows,cols", [(20, 231), (9, 203), (11, 90), (16, 232), (5, 1386)])
+def test_pack_of_many_members_of_odd_widths(pack_form, rows, cols):
+    """Eight members of each of four kinds, in the forms the pack chooses for them together."""
+    if pack_form == "fixed":
+        pytest.skip("odd row lengths are members of generated packs only")
+    specs = ([softmax_graph(rows, cols, "f32")] * 2 + [add_bias_layernorm_graph(rows, cols)] * 2 + [softmax_backward_graph(rows, cols, "f16")] * 2
+             + [rmsnorm_graph(rows, 2 * cols)] * 2) * 4
+    worst, info = _check_members(specs, seeds=range(len(specs)))
+    assert info["generated"] == 1 and info["n_kernels"] == 1
+    note(f"pack of {len(specs)} members {rows}x{cols}: {info['grid']} workgroups, vgprs {info['vgprs']}, worst {worst:.2f} of the bar")

@@ -10,7 +10,7 @@ from paper_2009_10924_amd import binding as B
 from workloads import (FULL_CONFIGS, add_bias_layernorm_graph, attention_scores_graph, bias_gelu_dbias_graph,
                        bias_gelu_graph, gelu_backward_graph, layernorm_backward_bias_graph, layernorm_backward_graph,
                        layernorm_stats_graph, normalize_from_stats_graph, rmsnorm_graph,
-                       rmsnorm_backward_graph, softmax_graph, transpose_chain_graph, transpose_graph)
+                       rmsnorm_backward_graph, softmax_backward_graph, softmax_graph, transpose_chain_graph, transpose_graph)
 from workloads.graphs import GraphSpec, OpSpec, TensorSpec
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -340,6 +340,18 @@ def test_generated_pack_takes_any_row_local_member(lib):
     with pytest.raises(B.FsError) as e:       # per-op plans carry no pattern
         B.Pack([B.Plan(B.Graph.from_spec(softmax_graph(8, 64)), "unfused")])
     assert e.value.code == -5
+
+
+@pytest.mark.parametrize("rows,cols", [(120, 231), (83, 203), (46, 90), (114, 232)])
+def test_pack_members_take_forms_that_fit_one_kernel(lib, rows, cols):
+    """A kernel over many members may need more registers than any of them by itself; members then take leaner forms."""
+    if not B.codegen_available():
+        pytest.skip("needs the run-time compiler")
+    plans = [B.Plan(B.Graph.from_spec(s), "auto") for s in (softmax_graph(rows, cols, "f32"), add_bias_layernorm_graph(2 * rows, 6 * cols),
+                                                            softmax_backward_graph(6 * rows, cols, "f16"), rmsnorm_graph(rows, 8 * cols),
+                                                            bias_gelu_graph(rows, 24 * cols, "bf16"))]
+    info = B.Pack([p for p, n in zip(plans, (8, 8, 8, 4, 4)) for _ in range(n)]).info
+    assert info["generated"] == 1 and info["n_kernels"] == 1 and info["n_members"] == 32
 
 
 def test_zero_initialised_plan_opts_ask_for_nothing(lib):
