@@ -292,11 +292,11 @@ fs_status build_unfused(const fs_graph& g, Candidate* out) {
         // 48.8 / 46.5, of 8 KB rows 96.0 / 92.6 / 89.4, s 500 of 8 KB rows 61.5 / 54.2 / 51.0, s 256 25.3 / 24.4 / 23.9, s 384
         // level; outside that span it loses: s 256 of 4 KB rows in bf16 13.0 / 13.2 / 13.7, s 2048 23.9 / 24.8 / 24.4.
         const uint64_t read_row = (uint64_t)p.nq * p.elem_bytes, written_row = (uint64_t)p.out_row * p.elem_bytes;
-        if ((uint64_t)p.in_row * p.elem_bytes % 128 != 0) p.q_step = 0;
-        else if (read_row <= 3072) p.q_step = 1;
-        else p.q_step = tq % 2 == 0 && written_row >= 1024 && written_row <= 2048 ? 2 : 0;
-        p.div[0] = make_fastdiv(p.q_step ? tq / p.q_step : tx);
-        p.div[1] = make_fastdiv(p.q_step ? tx : tq);
+        const bool whole_lines = (uint64_t)p.in_row * p.elem_bytes % 128 == 0;
+        p.every_other = whole_lines && read_row > 3072 && tq % 2 == 0 && written_row >= 1024 && written_row <= 2048 ? 1 : 0;
+        p.walk_q = whole_lines && (read_row <= 3072 || p.every_other) ? 1 : 0;
+        p.div[0] = make_fastdiv(p.walk_q ? tq >> p.every_other : tx);
+        p.div[1] = make_fastdiv(p.walk_q ? tx : tq);
         p.div[2] = make_fastdiv(batch[1]);
         for (const FastDiv& d : p.div)   // (both tile axes are at least 2 long, so none of these is near 2^31)
           if (d.d == 0) return fail(FS_ERR_SHAPE, "transpose: no exact division by one of its extents");

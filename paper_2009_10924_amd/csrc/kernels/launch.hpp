@@ -82,22 +82,23 @@ struct ReduceP {
   float post_scale;             // 1/red for mean on the final pass, else 1
 };
 struct TransposeP {
-  int32_t elem_bytes, vec;      // vec: elements per 128-bit (or narrower) access along the inner axis
-  uint32_t n;
   // Axes that stay neighbours are merged first, extents of 1 dropped.
-  // K_TRANSPOSE_ROWS: output index -> (c0, c1, c2, innermost index), each times its stride in the input
-  uint32_t in_stride[3];        // elements, of the input axis that feeds output axis 0, 1, 2
-  uint32_t out_ext[3];          // output extents 1 and 2, innermost extent
-  // K_TRANSPOSE_TILE: out[b0, b1, .., q, ..] with q the input's innermost axis and x the output's
+  // K_TRANSPOSE_TILE: out[b0, b1, .., q, ..] with q the input's innermost axis and x the output's.  What the kernel reads
+  // comes first and together: arguments are fetched line by line, and every line more is a wait before the first load.
+  FastDiv div[3];               // tiles along the axis that neighbouring workgroups walk, along the other one, batch extent 1
   uint32_t nq, nx;              // extents of the tile's two axes
   uint32_t in_row, out_row;     // input stride of x, output stride of q (elements)
-  FastDiv div[3];               // tiles along the axis that neighbouring workgroups walk, along the other one, batch extent 1
   uint32_t in_batch[2], out_batch[2];   // strides of the two axes outside the tile (0 where there is none)
+  uint32_t walk_q, every_other; // neighbouring tiles follow one another along q (1: they read one contiguous span) or x (0);
+                                // along q every other one first, then along x, then the ones in between (1)
+  uint32_t n_tiles;
   uint32_t tile_units, tile_uq; // vectorised tile: 16-byte units in all (256, or 64: a tile per wavefront) and along q (8, 16 or
                                 // 32); the tile is tile_uq * vec elements along q by (tile_units / tile_uq) * vec along x
-  uint32_t n_tiles;
-  uint32_t q_step;              // neighbouring tiles follow one another 1: along q (they read one contiguous span), 2: along q,
-                                // every other one first, then along x, 0: along x
+  int32_t elem_bytes, vec;      // vec: elements per 128-bit (or narrower) access along the inner axis
+  // K_TRANSPOSE_ROWS: output index -> (c0, c1, c2, innermost index), each times its stride in the input
+  uint32_t n;
+  uint32_t in_stride[3];        // elements, of the input axis that feeds output axis 0, 1, 2
+  uint32_t out_ext[3];          // output extents 1 and 2, innermost extent
 };
 
 // ---- stitched -----------------------------------------------------------------

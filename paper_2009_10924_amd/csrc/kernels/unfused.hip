@@ -225,14 +225,11 @@ struct TileAt {
     rest = r;
     r = fast_div(rest, p.div[1]);
     const uint32_t outer = rest - r * p.div[1].d;
-    uint32_t phase = 0;
-    if (p.q_step == 2u) {
-      phase = r & 1u;
-      r >>= 1;
-    }
+    const uint32_t phase = r & p.every_other;
+    r >>= p.every_other;
     const uint32_t b0 = fast_div(r, p.div[2]), b1 = r - b0 * p.div[2].d;
-    bq = p.q_step ? inner * p.q_step + phase : outer;
-    bx = p.q_step ? outer : inner;
+    bq = p.walk_q ? (inner << p.every_other) + phase : outer;
+    bx = p.walk_q ? outer : inner;
     in_base = (size_t)b0 * p.in_batch[0] + (size_t)b1 * p.in_batch[1];
     out_base = (size_t)b0 * p.out_batch[0] + (size_t)b1 * p.out_batch[1];
   }
@@ -280,8 +277,9 @@ __global__ void __launch_bounds__(256) k_transpose_units(const T* __restrict__ i
   constexpr uint32_t VEC = 16 / sizeof(T), UX = UNITS / UQ, TQ = UQ * VEC, TX = UX * VEC;
   typedef typename AtAlignment<u32x4, (int)sizeof(T)>::type Unaligned;
   __shared__ u32x4 tiles[256 / UNITS][TQ * UX];
-  u32x4* const tile = tiles[threadIdx.x / UNITS];
-  const uint32_t tid = threadIdx.x % UNITS, index = blockIdx.x * (256u / UNITS) + threadIdx.x / UNITS;
+  const uint32_t part = UNITS == 256 ? 0u : threadIdx.x / UNITS, tid = UNITS == 256 ? threadIdx.x : threadIdx.x % UNITS;
+  u32x4* const tile = tiles[part];
+  const uint32_t index = blockIdx.x * (256u / UNITS) + part;
   const bool there = UNITS == 256 || index < p.n_tiles;
   const TileAt t(p, there ? index : 0u);
   const uint32_t uq = tid % UQ, ux = tid / UQ;
