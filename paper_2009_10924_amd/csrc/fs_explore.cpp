@@ -710,7 +710,7 @@ void decide_packs(const fs_graph& g, fs_program* prog, std::vector<int>* pos) {
   std::map<std::pair<int, int>, std::vector<int>> by_level;   // (stage, level): members of a pack are issued together
   for (int s = 0; s < ns; ++s) {
     const fs_plan* p = prog->steps[s].plan;
-    if ((p->pack.spec >= 0 || !p->generic.empty()) && p->candidates[p->chosen].info.predicted_us <= tiny_us)
+    if ((p->pack.spec >= 0 || !p->generic.forms.empty()) && p->candidates[p->chosen].info.predicted_us <= tiny_us)
       by_level[{prog->steps[s].stage, level[s]}].push_back(s);
   }
   for (auto& kv : by_level) {

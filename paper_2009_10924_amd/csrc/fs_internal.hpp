@@ -109,18 +109,29 @@ struct Candidate {
 }  // namespace fs
 
 namespace fs {
-// A plan's pattern as a row program with a launch shape: a form in which it can join a generated packed kernel.
+// A plan's pattern as a row program, and the launch shapes in which it can join a generated packed kernel.
 struct GenericForm {
-  RowProgP prog;
-  BufRef ptr[kMaxPtrs];
-  uint32_t blocks = 0;
+  int32_t vec, lanes_per_row, lanes_log2, vecs_per_lane;   // as in RowProgP
+  uint32_t blocks;
   KernelCost cost;
-  double predicted_us = 0;   // by itself
+};
+struct GenericProgram {
+  RowProgP prog;                    // in the shape of the first form
+  BufRef ptr[kMaxPtrs];
+  std::vector<GenericForm> forms;   // the faster by itself first, each later one with fewer registers; empty: none
+  RowProgP in_form(const GenericForm& f) const {
+    RowProgP p = prog;
+    p.vec = f.vec;
+    p.lanes_per_row = f.lanes_per_row;
+    p.lanes_log2 = f.lanes_log2;
+    p.vecs_per_lane = f.vecs_per_lane;
+    return p;
+  }
 };
 }  // namespace fs
 
 struct fs_plan {
-  std::vector<fs::GenericForm> generic;   // the faster by itself first, each later one with fewer registers; empty: none
+  fs::GenericProgram generic;
   std::vector<fs::Candidate> candidates;
   int32_t chosen = 0;
   int32_t n_inputs = 0, n_outputs = 0;

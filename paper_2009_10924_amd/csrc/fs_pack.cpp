@@ -68,7 +68,7 @@ bool shape_member(const PackForm& f, PackEntry* e, uint32_t* blocks) {
 std::vector<std::vector<const GenericForm*>> form_assignments(const fs_plan* const* plans, int32_t n) {
   std::vector<int32_t> caps;
   for (int i = 0; i < n; ++i)
-    for (const GenericForm& f : plans[i]->generic) caps.push_back(f.cost.vgpr_estimate);
+    for (const GenericForm& f : plans[i]->generic.forms) caps.push_back(f.cost.vgpr_estimate);
   std::sort(caps.begin(), caps.end(), std::greater<int32_t>());
   caps.erase(std::unique(caps.begin(), caps.end()), caps.end());
   std::vector<std::pair<double, std::vector<const GenericForm*>>> ranked;
@@ -76,7 +76,7 @@ std::vector<std::vector<const GenericForm*>> form_assignments(const fs_plan* con
     std::vector<const GenericForm*> forms;
     std::vector<const KernelCost*> costs;
     for (int i = 0; i < n; ++i) {
-      const std::vector<GenericForm>& all = plans[i]->generic;
+      const std::vector<GenericForm>& all = plans[i]->generic.forms;
       size_t k = 0;
       while (k + 1 < all.size() && all[k].cost.vgpr_estimate > cap) ++k;
       forms.push_back(&all[k]);
@@ -95,14 +95,15 @@ std::vector<std::vector<const GenericForm*>> form_assignments(const fs_plan* con
 }
 
 // The packed kernel of `n` members in the given forms; false: it does not compile, or spills registers.
-bool compile_packed(const std::vector<const GenericForm*>& forms, fs_pack::GenLaunch* gl, std::vector<std::vector<int>>* slots, int32_t* vgprs) {
+bool compile_packed(const fs_plan* const* plans, const std::vector<const GenericForm*>& forms, fs_pack::GenLaunch* gl,
+                    std::vector<std::vector<int>>* slots, int32_t* vgprs) {
   std::vector<RowProgP> progs;
   std::vector<uint32_t> blocks;
   uint64_t total = 0;
-  for (const GenericForm* f : forms) {
-    progs.push_back(f->prog);
-    blocks.push_back(f->blocks);
-    total += f->blocks;
+  for (size_t i = 0; i < forms.size(); ++i) {
+    progs.push_back(plans[i]->generic.in_form(*forms[i]));
+    blocks.push_back(forms[i]->blocks);
+    total += forms[i]->blocks;
   }
   if (total >= (1ull << 31)) return false;
   std::string entry;
@@ -127,7 +128,7 @@ bool compile_packed(const std::vector<const GenericForm*>& forms, fs_pack::GenLa
 bool build_generated_pack(const fs_plan* const* plans, int32_t n, fs_pack* pk) {
   if (!codegen_enabled()) return false;
   for (int i = 0; i < n; ++i)
-    if (!plans[i] || plans[i]->generic.empty()) return false;
+    if (!plans[i] || plans[i]->generic.forms.empty()) return false;
   int32_t first_input = 0, first_output = 0;
   int32_t vgprs = 0;
   for (int begin = 0; begin < n; begin += kPackMaxMembers) {
@@ -145,19 +146,19 @@ bool build_generated_pack(const fs_plan* const* plans, int32_t n, fs_pack* pk) {
     }
     fs_pack::GenLaunch gl;
     std::vector<std::vector<int>> slots;
-    const std::vector<const GenericForm*>* forms = nullptr;
+    bool built = false;
     for (const auto& t : tries) {
       int32_t used = 0;
-      if (!compile_packed(t, &gl, &slots, &used)) continue;
-      forms = &t;
+      if (!compile_packed(plans + begin, t, &gl, &slots, &used)) continue;
       vgprs = std::max(vgprs, used);
+      built = true;
       break;
     }
-    if (!forms) return false;
+    if (!built) return false;
     for (int i = begin; i < end; ++i) {
       const fs_plan* p = plans[i];
       for (int slot : slots[i - begin]) {
-        const BufRef& r = (*forms)[i - begin]->ptr[slot];
+        const BufRef& r = p->generic.ptr[slot];
         fs_pack::PtrRef pr;
         pr.kind = r.kind;
         pr.index = (r.kind == BUF_INPUT ? first_input : first_output) + r.slot;

@@ -112,13 +112,12 @@ static void fill_generic_forms(const fs_graph& g, fs_plan* p) {
   };
   auto add = [&](const Candidate& c) {
     const Launch& l = c.launches.front();
-    p->generic.emplace_back();
-    GenericForm& f = p->generic.back();
-    f.prog = l.args.u.prog;
-    for (int k = 0; k < kMaxPtrs; ++k) f.ptr[k] = l.ptr[k];
-    f.blocks = l.shape.grid[0];
-    f.cost = c.cost;
-    f.predicted_us = c.info.predicted_us;
+    const RowProgP& q = l.args.u.prog;
+    if (p->generic.forms.empty()) {
+      p->generic.prog = q;
+      for (int k = 0; k < kMaxPtrs; ++k) p->generic.ptr[k] = l.ptr[k];
+    }
+    p->generic.forms.push_back({q.vec, q.lanes_per_row, q.lanes_log2, q.vecs_per_lane, l.shape.grid[0], c.cost});
   };
   const Candidate& own = p->candidates[p->chosen];
   const bool asked = p->opts.candidate >= 0 || p->opts.block_threads > 0 || p->opts.lanes_per_row > 0 || p->opts.vecs_per_lane > 0;
