@@ -49,13 +49,14 @@ __device__ __forceinline__ float add_other_row(float v) {
 }
 
 // One step of one lane in storage form: VEC elements of 2 or 4 bytes are 2, 4, 8, 16 or 32 bytes.  VEC is 8 or 4, and
-// 1 for rows shorter than 4 elements.  EA: the alignment the address is known to have, in bytes -- that of a whole step
-// where the row length is a multiple of VEC elements, that of one element otherwise (a row then starts anywhere).  The
+// 1 for rows shorter than 4 elements.  EA: the alignment the address is known to have, in bytes -- that of a whole step, 16
+// at most, where the row length is a multiple of VEC elements, that of one element otherwise (a row then starts anywhere).  The
 // memory pipeline takes 64- and 128-bit accesses at any element address: a copy of 64 MB each way through 128-bit
 // accesses that all start 2 bytes off runs at 5.18 TB/s, 4 or 8 bytes off at 5.53, aligned at 5.75, and element by
 // element at 4.97 with eight times the instructions and one register per element.
 template <int BYTES, int EA> struct StepBits;
 template <int EA> struct StepBits<32, EA> {
+  static_assert(EA <= 16, "callers' pointers are aligned to 16 bytes, and the second half starts 16 behind the first");
   u32x4 lo, hi;
   template <bool STREAM, typename T>
   __device__ __forceinline__ static StepBits load(const T* p) {
@@ -141,7 +142,7 @@ __device__ __forceinline__ void unpack_step(const StepBits<2, EA>& r, float (&v)
 // Stores N float32 values as TO at an address known to be aligned to EA bytes, past the caches (see StoreN).
 template <typename TO, int N, int EA>
 __device__ __forceinline__ void store_elements(TO* p, const float (&v)[N]) {
-  if constexpr (EA >= (int)sizeof(TO) * N || N == 1) {
+  if constexpr (EA >= 16 || EA >= (int)sizeof(TO) * N || N == 1) {
     StoreN<TO, N>::run(p, v);
   } else if constexpr (sizeof(TO) == 4) {
     if constexpr (N == 2) {
@@ -193,7 +194,10 @@ struct GenRow {
   static constexpr int KV = K * VEC;
   static constexpr uint32_t PADDED_COLS = LANES * K * VEC;   // columns the lanes of a row cover, padding included
   static_assert(TAIL == 0 || ROW_STRIDE >= (uint32_t)VEC, "a row holds at least one step");
-  template <typename T> static constexpr int alignment() { return (int)sizeof(T) * (ROW_STRIDE % VEC == 0 ? VEC : 1); }
+  template <typename T> static constexpr int alignment() {
+    constexpr int step = (int)sizeof(T) * (ROW_STRIDE % VEC == 0 ? VEC : 1);
+    return step < 16 ? step : 16;
+  }
 
   uint32_t lane, row, row_c, col0;
   bool row_ok, last;   // last: the tile that may be shorter than the others
