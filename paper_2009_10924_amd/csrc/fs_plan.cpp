@@ -441,7 +441,9 @@ int64_t fs_plan_describe(const fs_plan* p, char* text, size_t capacity) try {
                                             std::to_string(q.oms[i][2]) : std::string()) + "\n";
     for (int i = 0; i < kProgMaxOperands; ++i)
       if (l.ptr[kSlotRout + i].kind != BUF_NONE) s += "  routput " + std::to_string(i) + " " + buf_name(l.ptr[kSlotRout + i]) + "\n";
-    if (q.n_colsum > 0)   // partial sums: one row of n_colsum * cols floats per workgroup, folded by the next launch
+    if (q.n_colsum == 0 && q.rows_per_group > 1)   // a workgroup works through that many rows, one after the other
+      s += "  rows_per_group " + std::to_string(q.rows_per_group) + "\n";
+    if (q.n_colsum > 0)   // partial sums: a row of n_colsum * colsum_pitch(cols) floats per workgroup, folded by the next launch
       s += "  colsums " + std::to_string(q.n_colsum) + " partials " + buf_name(l.ptr[kSlotWs]) + " rows_per_group " +
            std::to_string(q.rows_per_group) + " col_tiles " + std::to_string(q.col_tiles > 1 ? q.col_tiles : 1) + "\n";
     if (q.col_chunks > 1)   // the row in pieces of lanes * vecs steps, a pass per row reduction and one for the stores

@@ -705,8 +705,8 @@ struct Compiler {
 // ---- launch shapes and candidates ------------------------------------------------------------------------
 
 // How a row program is laid over the device: L lanes of a wavefront (or the whole 256-thread workgroup) per row, K
-// steps of `vec` elements per lane; generated kernels with column sums also R rows per lane group, one after the
-// other, and CT column tiles.
+// steps of `vec` elements per lane; generated kernels also R rows per lane group, one after the other (with column sums, or
+// a workgroup per row and column vectors), and with column sums CT column tiles.
 struct Shape {
   uint32_t L;
   int K;
@@ -929,7 +929,8 @@ void make_generated(const Compiler& c, int vec, const Shape& s, Candidate* cand)
   Launch& gl = cand->launches.back();
   gl.kernel = K_ROW_GENERATED;
   gl.shape.lds_bytes = 0;
-  const int32_t slots = s.block ? (int32_t)(s.L / 64) * 4 * c.n_reductions : 0;
+  // (a loop over rows alternates between two sets of reduction slots)
+  const int32_t slots = s.block ? (int32_t)(s.L / 64) * 4 * c.n_reductions * (s.R > 1 || c.n_colsum > 0 ? 2 : 1) : 0;
   cand->info.lds_bytes = slots;
   snprintf(cand->info.pattern, sizeof cand->info.pattern, "row_generated");
   snprintf(cand->info.kernel, sizeof cand->info.kernel, "row_generated<v%d,K%d,L%u,I%d,R%d>", vec, s.K, s.L, base.n_instr, base.n_regs);

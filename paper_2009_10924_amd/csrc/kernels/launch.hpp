@@ -254,8 +254,9 @@ struct RowProgP {
   uint32_t oms[kProgMaxOperands][3];
   uint8_t rscal_sreg[kProgMaxOperands], rscal_dt[kProgMaxOperands];
   int32_t n_colsum;                    // column sums over all rows (generated kernels only), at most kProgMaxColSums
-  int32_t rows_per_group;              // rows each lane group works through, one after the other (> 1 only with column sums:
-                                       // fewer, longer partial sums)
+  int32_t rows_per_group;              // rows each lane group works through, one after the other (> 1 in generated kernels with
+                                       // column sums: fewer, longer partial sums; and with a workgroup per row and column
+                                       // vectors: those are loaded once for all the rows)
   int32_t col_tiles;                   // > 1: a workgroup handles one of col_tiles column tiles, the last possibly shorter
                                        // (generated kernels for patterns with column sums and no row reduction)
   int32_t col_chunks;                  // > 1: a row too long for the lanes' registers is worked through in col_chunks pieces of

@@ -6,7 +6,7 @@ import pytest
 
 from paper_2009_10924_amd import binding as B
 from workloads import (layernorm_stats_graph, masked_scores_gate_graph, random_multi_pattern, random_row_pattern,
-                       silu_gate_graph, softmax_graph)
+                       rmsnorm_backward_graph, rmsnorm_graph, silu_gate_graph, softmax_graph)
 from workloads.graphs import GraphSpec, OpSpec, TensorSpec
 
 pytestmark = pytest.mark.skipif(not B.codegen_available(), reason="the HIP run-time compiler is not installed here")
@@ -236,3 +236,17 @@ def test_plans_can_be_made_from_several_threads_at_once():
     for name, _, entry in results:
         by_name.setdefault(name, set()).add(entry)
     assert all(len(v) == 1 for v in by_name.values())
+
+
+@pytest.mark.parametrize("spec", [layernorm_stats_graph(4096, 2051, in_dtype="f32", out_dtype="f32", with_variance=True), rmsnorm_graph(8192, 4099),
+                                  rmsnorm_backward_graph(3000, 4096, "bf16"), softmax_graph(64, 20000, "f32")])
+def test_listing_tells_rows_per_workgroup_and_shared_memory(spec):
+    """A loop over rows shows in the listing, with and without column sums, and every shared array of the source counts."""
+    plan = _plan(spec)
+    assert "row_generated" in plan.info["kernel"]
+    rows = re.search(r",rows(\d+)", plan.info["kernel"])
+    told = re.search(r"rows_per_group (\d+)", plan.describe())
+    assert (told.group(1) if told else "1") == (rows.group(1) if rows else "1"), plan.describe()
+    floats = re.findall(r"__shared__ (?:__attribute__\(\(aligned\(16\)\)\) )?float (\w+)\[(\d+)\](\[[^\]]*\])?", plan.source())
+    if all(not rest for _, _, rest in floats):
+        assert plan.info["lds_bytes"] == 4 * sum(int(n) for _, n, _ in floats), (plan.info, floats)
