@@ -436,3 +436,26 @@ def test_folds_of_any_number_of_partial_rows(rows):
         for (name, dt), got in zip(spec.outputs, out):
             err = O.max_rel_err(O.to_f64(B.to_host(got, dt), dt).reshape(ref[name].shape), ref[name], floors.get(name, 0.0))
             assert err <= 1e-5, (rows, plan.info["kernel"], name, err)
+
+
+@pytest.mark.parametrize("cols,dtype", [(2051, "f32"), (2056, "f16"), (4099, "bf16")])
+def test_several_rows_per_workgroup_with_every_kind_of_operand(cols, dtype):
+    """The loop over rows of a workgroup, without column sums: operands stretched along leading axes, per-row scalars (one
+    stretched), an input and an output through transposes of the leading axes, next to the column vector that asks for it."""
+    if not B.codegen_available():
+        pytest.skip("these shapes exist as generated kernels only")
+    from workloads.graphs import GraphSpec, OpSpec, TensorSpec
+    b, h, q = 2, 3, 179   # 1074 rows, which two per workgroup leave with a short last round
+    ops = [OpSpec("xt", "transpose", ("x",), {"perm": (0, 2, 1, 3)}), OpSpec("t", "mul", ("xt", "gain")), OpSpec("a", "add", ("t", "mask")),
+           OpSpec("s", "mul", ("a", "r_head")), OpSpec("mx", "reduce_max", ("s",), {"axis": 3}), OpSpec("d", "sub", ("s", "mx")), OpSpec("e", "exp", ("d",)),
+           OpSpec("sum", "reduce_sum", ("e",), {"axis": 3}), OpSpec("y", "div", ("e", "sum")), OpSpec("z", "mul", ("y", "r_row"))]
+    if dtype != "f32":
+        ops.append(OpSpec("zc", "convert", ("z",), {"dtype": dtype}))
+    ops.append(OpSpec("out", "transpose", (ops[-1].out,), {"perm": (0, 2, 1, 3)}))
+    spec = GraphSpec(f"several_rows_operands_{dtype}_{cols}",
+                     [TensorSpec("x", dtype, (b, q, h, cols)), TensorSpec("gain", "f32", (cols,)), TensorSpec("mask", dtype, (b, 1, 1, cols)),
+                      TensorSpec("r_head", "f32", (h, 1, 1)), TensorSpec("r_row", "f32", (b, h, q, 1))], ops, [("out", dtype), ("mx", "f32")])
+    names = [c["kernel"] for c in B.Plan(B.Graph.from_spec(spec), "auto").candidates()]
+    assert any(",rows" in n for n in names), names
+    worst, info = _run(spec)
+    note(f"{spec.name}: {info['kernel']}, {info['n_candidates']} shapes, worst {worst}")
