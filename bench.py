@@ -13,8 +13,9 @@ input read once + each output written once) over the whole step, plus `roofline`
 carries `per_config`, the same measurement for all five configurations (C2 and C5 both as the
 evaluator's choice and with the LDS scheme forced), each beside the per-op GPU baseline and
 beside streaming probes of the same bytes and read : write mix -- and `cpu_baseline` (the
-float64 per-op oracle timed on this machine's host).  Further context (backward patterns, packed
-launches, explored programs, generated kernels) follows in extra keys.
+float64 per-op oracle timed on this machine's host).  Further context (the configurations' full
+records, backward patterns, packed launches, explored programs, generated kernels) goes to stderr,
+one JSON line too: some 30 KB, more than a reader of the last lines of stdout keeps.
 """
 from __future__ import annotations
 
@@ -409,6 +410,15 @@ def _row(m, tag):
     return row
 
 
+LINE_KEYS = ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "higher_is_better", "scaling", "vs_baseline", "dtype",
+             "data", "config", "roofline", "wall_ms_per_step", "cpu_baseline")
+
+
+def split_line(result):
+    """(what the line on stdout holds, the rest)"""
+    return ({k: v for k, v in result.items() if k in LINE_KEYS}, {k: v for k, v in result.items() if k not in LINE_KEYS})
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -545,7 +555,10 @@ def main():
             del r
             torch.cuda.empty_cache()
         result["generic_patterns"] = generic
-    print(json.dumps(result))
+    line, context = split_line(result)
+    if context:
+        print(json.dumps(context), file=sys.stderr, flush=True)
+    print(json.dumps(line))
 
 
 if __name__ == "__main__":
