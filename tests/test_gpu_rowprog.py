@@ -142,8 +142,8 @@ def test_several_leading_axis_moves_as_one_kernel():
 @pytest.mark.parametrize("rows,cols,dtype", [(10, 50, "f32"), (9, 1001, "bf16"), (13, 36, "f16"), (70, 127, "f16"), (3, 3003, "f32"),
                                              (300, 6, "bf16")])
 def test_row_lengths_that_allow_no_128_bit_access(rows, cols, dtype):
-    """Rows that are no multiple of 8 (16-bit) or 4 elements: the generated kernels step by 4 elements with 64-bit
-    accesses for the 16-bit operands, or by single elements; before, such patterns ran per op."""
+    """Rows that are no multiple of 8 (16-bit) or 4 elements: the generated kernels' steps start at any element and the row's
+    last one slides back to end with the row (rows shorter than 4 elements step by single ones)."""
     if not B.codegen_available():
         pytest.skip("these step widths exist as generated kernels only")
     for make in (lambda: layernorm_stats_graph(rows, cols, in_dtype=dtype, out_dtype=dtype, with_variance=True),
@@ -452,7 +452,7 @@ def test_several_rows_per_workgroup_with_every_kind_of_operand(cols, dtype):
     if dtype != "f32":
         ops.append(OpSpec("zc", "convert", ("z",), {"dtype": dtype}))
     ops.append(OpSpec("out", "transpose", (ops[-1].out,), {"perm": (0, 2, 1, 3)}))
-    spec = GraphSpec(f"several_rows_operands_{dtype}_{cols}",
+    spec = GraphSpec(f"pattern_several_rows_operands_{dtype}_{cols}",
                      [TensorSpec("x", dtype, (b, q, h, cols)), TensorSpec("gain", "f32", (cols,)), TensorSpec("mask", dtype, (b, 1, 1, cols)),
                       TensorSpec("r_head", "f32", (h, 1, 1)), TensorSpec("r_row", "f32", (b, h, q, 1))], ops, [("out", dtype), ("mx", "f32")])
     names = [c["kernel"] for c in B.Plan(B.Graph.from_spec(spec), "auto").candidates()]
