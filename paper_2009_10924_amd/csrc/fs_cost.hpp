@@ -19,9 +19,9 @@ struct DeviceModel {
   uint32_t lds_per_cu = 160 * 1024;
   double clock_hz = 2.4e9;
   double hbm_peak_Bps = 8.0e12;
-  // measured / calibrated on one MI355X: every candidate of 400 row patterns (nine kinds, rows of 16 to 131072 elements,
-  // three dtypes, 2 MB to 2 GB) timed; the candidate ranked first is on average 3.4 % behind the fastest one (24 % at
-  // worst).  With terms that only knew rows of whole 128-byte lines it was 6.3 % and 55 %: attention rows of 392 16-bit
+  // measured / calibrated on one MI355X: every candidate of about 1900 row patterns (rows of 16 to 131072 elements, three
+  // dtypes, 0.2 MB to 2 GB) timed; over 1000 of them the candidate ranked first is on average 3.6 % behind the fastest one.
+  // With terms that only knew rows of whole 128-byte lines it was 6.3 % over 400 of them: attention rows of 392 16-bit
   // elements ran on 8 lanes in 48.8 us where 64 lanes take 32.4.
   double stream_fraction = 0.84;     // one-shot kernels with three or more independent streams, fraction of hbm_peak
                                      // (the grid-stride copy kernel reaches 0.78)
@@ -32,8 +32,8 @@ struct DeviceModel {
   double l2_Bps = 20.0e12;           // aggregate cache bandwidth for re-read operands
   double last_level_cache_bytes = 256.0 * 1024 * 1024;   // memory-side cache in front of HBM
   double last_level_reread = 0.45;   // time of a re-read that the memory-side cache still holds, relative to HBM (measured)
-  // column sums, fitted to every candidate of 170 patterns (bias + GELU, LayerNorm, RMS norm backward) like the rest: the
-  // candidate ranked first is 3.7 % behind the fastest one on average, 7.3 % without these terms
+  // column sums, fitted to every candidate of bias + GELU, LayerNorm and RMS norm backward patterns like the rest: over the
+  // first 170 of them the candidate ranked first was 3.7 % behind the fastest one on average, 7.3 % without these terms
   double cu_Bps = 3.3e10;            // what one compute unit streams at most (a loop over rows on few workgroups)
   double partial_weight = 2.4;       // a byte of partial sums, relative to a streamed one (a burst at the end, then a re-read)
   double flush_step_s = 9e-9, flush_value_s = 14e-9, flush_block_s = 30e-9;   // per value: each lane fold, LDS + store; store alone
