@@ -252,8 +252,9 @@ std::string chunked_body(const RowProgP& p, const char* entry) {
   std::string s = "using namespace fsk;\n";
   s += fmt("extern \"C\" __global__ void __launch_bounds__(%u) %s(const GenArgs a) {\n", L, entry);
   s += "  const uint32_t fs_block = blockIdx.x;\n";
-  s += fmt("  typedef GenRow<%uu, %uu, %d, %d, %uu, true, 1u, %uu> Row;       // a whole chunk\n", p.rows, chunk, p.vec, p.vecs_per_lane, L, p.cols);
-  s += fmt("  typedef GenRow<%uu, %uu, %d, %d, %uu, true, 1u, %uu> TailRow;   // the row's last chunk\n", p.rows, tail, p.vec, p.vecs_per_lane, L, p.cols);
+  const char* past_caches = p.stream ? ", 1u, true" : "";
+  s += fmt("  typedef GenRow<%uu, %uu, %d, %d, %uu, true, 1u, %uu%s> Row;       // a whole chunk\n", p.rows, chunk, p.vec, p.vecs_per_lane, L, p.cols, past_caches);
+  s += fmt("  typedef GenRow<%uu, %uu, %d, %d, %uu, true, 1u, %uu%s> TailRow;   // the row's last chunk\n", p.rows, tail, p.vec, p.vecs_per_lane, L, p.cols, past_caches);
   s += "  constexpr int KV = Row::KV;\n";
   if (n_red > 0) s += fmt("  __shared__ float slots[%d];\n", n_waves * n_red);
   for (int q = 0; q < n_red; ++q) s += fmt("  float red%d;\n", q);
@@ -385,7 +386,7 @@ std::string body_with_entry(const RowProgP& p, const char* entry, bool member) {
   // (column tiles: whole steps of every lane; the last tile may be shorter)
   const uint32_t tile_cols = CT > 1 ? (uint32_t)(p.lanes_per_row * p.vecs_per_lane * p.vec) : p.cols;
   s += fmt("  typedef GenRow<%uu, %uu, %d, %d, %uu, %s, %uu, %uu%s> Row;\n", p.rows, tile_cols, p.vec, p.vecs_per_lane,
-           (uint32_t)p.lanes_per_row, block ? "true" : "false", R, p.cols, CT > 1 ? fmt(", %uu", CT).c_str() : "");
+           (uint32_t)p.lanes_per_row, block ? "true" : "false", R, p.cols, CT > 1 || p.stream ? fmt(", %uu%s", CT, p.stream ? ", true" : "").c_str() : "");
   s += "  constexpr int KV = Row::KV;\n";
   const int n_waves = block ? p.lanes_per_row / 64 : 4;
   const bool looped = p.n_colsum > 0 || R > 1u;
@@ -405,7 +406,7 @@ std::string body_with_entry(const RowProgP& p, const char* entry, bool member) {
     std::string t;
     for (int i = 0; i < p.n_full; ++i) {
       // an input stretched along leading axes is read by many rows: it goes through the caches like a column vector;
-      // the others are read once and stream past them
+      // the others are read once and stream past them (if they are too large for the caches, see GenRow)
       const bool stretched = ((p.full_bcast >> i) & 1u) != 0;
       const std::string at = stretched ? stretched_row(p.ms[i], pre) : fmt("(size_t)%s.row_c", rv);
       t += fmt("  %s%sraw_full%d = %s.load<%s, %s>(a.full[%d], %s);\n", decl_raw, pre, i, rv, storage_type(p.full_dt[i]),

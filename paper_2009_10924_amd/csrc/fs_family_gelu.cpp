@@ -52,6 +52,7 @@ bool build_gelu(const fs_graph& g, std::vector<Candidate>* out, PackForm* pack) 
   p.cols = (uint32_t)x.dims[x.rank - 1];
   p.rows = (uint32_t)(x.numel() / p.cols);
   p.dt = x.dtype;
+  p.stream = streams_inputs(g) ? 1 : 0;
   p.bias_dt = g.tensors[tb].dtype;
   const Tensor& y = g.tensors[st.tensors["__y"]];
   if (!is_row_vector(g.tensors[tb], p.cols) || p.bias_dt != p.dt || y.store_as != p.dt) return true;

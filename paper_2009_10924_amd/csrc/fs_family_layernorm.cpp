@@ -56,6 +56,7 @@ bool build_layernorm(const fs_graph& g, std::vector<Candidate>* out, PackForm* p
   const int32_t tg = affine ? st.tensors["G"] : -1, tbt = affine ? st.tensors["Bt"] : -1;
   if (affine && (!is_row_vector(g.tensors[tg], p.cols) || !is_row_vector(g.tensors[tbt], p.cols))) return true;
   p.in_dt = x.dtype;
+  p.stream = streams_inputs(g) ? 1 : 0;
   p.par_dt = x.dtype;
   p.out_dt = g.tensors[root].store_as;
   // the other outputs: the row mean (the reduction whose result is subtracted) and the reciprocal standard
@@ -247,6 +248,7 @@ bool build_layernorm_backward(const fs_graph& g, std::vector<Candidate>* out, Pa
   p.rows = (uint32_t)h.dims[0];
   p.cols = (uint32_t)h.dims[1];
   p.dt = h.dtype;
+  p.stream = streams_inputs(g) ? 1 : 0;
   p.inv_cols = (float)(1.0 / (double)p.cols);
   const Tensor& mu = g.tensors[tmu];
   const Tensor& rs = g.tensors[trs];

@@ -28,6 +28,7 @@ void emit_row_candidates(const fs_graph& g, const RowMatch& m, std::vector<Candi
   RowP p{};
   p.pattern = m.pattern;
   p.dt = x.dtype;
+  p.stream = streams_inputs(g) ? 1 : 0;
   p.cols = (uint32_t)x.dims[x.rank - 1];
   p.rows = (uint32_t)(x.numel() / p.cols);
   for (int i = 0; i < 4; ++i) p.f[i] = m.f[i];

@@ -27,6 +27,7 @@ bool build_softmax(const fs_graph& g, std::vector<Candidate>* out, PackForm* pac
   const bool has_mask = st.tensors.count("M") != 0;
   SoftmaxP p{};
   p.in_dt = x.dtype;
+  p.stream = streams_inputs(g) ? 1 : 0;
   p.out_dt = y.store_as;
   p.cols = (uint32_t)x.dims[x.rank - 1];
   p.rows = (uint32_t)(x.numel() / p.cols);

@@ -20,6 +20,7 @@ bool build_tchain(const fs_graph& g, std::vector<Candidate>* out, PackForm* pack
   // scale must be one value per head: [H,1,1] (or [1,H,1,1])
   if (s.numel() != (int64_t)p.H || s.rank < 3 || s.dims[s.rank - 3] != (int64_t)p.H) return true;
   p.dt = x.dtype;
+  p.stream = streams_inputs(g) ? 1 : 0;
   p.scale_dt = s.dtype;
   p.eps = (float)st.scalars[0];
   if (s.dtype != x.dtype || g.tensors[g.outputs[0]].store_as != x.dtype) return true;

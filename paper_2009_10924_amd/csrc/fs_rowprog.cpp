@@ -697,6 +697,7 @@ struct Compiler {
     p.col_tiles = 1;
     p.col_chunks = 1;
     p.col_kept = 0;
+    p.stream = streams_inputs(g) ? 1 : 0;
     if (n_colsum > 0) interpretable = false;
     return n_out + n_rout + n_colsum == (int)g.outputs.size();
   }

@@ -242,6 +242,7 @@ fs_status build_unfused(const fs_graph& g, Candidate* out) {
       p = TransposeP{};
       p.elem_bytes = dtype_bytes(a.dtype);
       p.n = (uint32_t)n_out;
+      p.stream = streams_inputs(g) ? 1 : 0;
       l.ptr[0] = where[op.in[0]]; l.ptr[1] = dst;
       if (keeps_inner) {
         const int64_t inner = ext[m - 1];
@@ -373,6 +374,24 @@ fs_status build_unfused(const fs_graph& g, Candidate* out) {
     snprintf(info.kernel, sizeof info.kernel, "%s", kernel_name(L[dom].kernel));
   }
   return FS_OK;
+}
+
+// Up to 96 MiB of inputs are read through the caches, more past them.  A hinted read takes no place in the 256 MB memory-side
+// cache: a later read of the same tensor, by this kernel or another, goes to device memory again, and a read of lines that
+// the kernel before has just written is slower too.  Measured (us, hinted / plain), inputs written by the kernel before:
+// softmax f16 160 MB moved 30.4 / 26.6, LayerNorm f32 80 MB 20.4 / 16.7, its backward 120 MB 32.6 / 25.0, 24 MB of
+// either level; three sets of buffers in turn: softmax f16 48 MB 7.8 / 7.6, 80 MB 15.0 / 13.0, LayerNorm bf16 48 MB 11.0 / 8.6,
+// scores f16 120 MB 20.8 / 17.3, transpose bf16 24 MB 5.3 / 4.3, bias + GELU backward f32 80 MB 18.9 / 15.6.  Inputs that no
+// cache can hold are better off without taking a place there: the same turns level out at 100 MB of inputs and lose 3 to 7 %
+// from 130 MB on, and where each pass reads other memory (700 MB in turn) the plain read loses 2 to 5 % at any size, more
+// right behind a kernel that left the cache full of unwritten lines.
+//
+// The parts of a larger graph keep hinted reads: what one step hands to the next was stored past the caches, and the inputs of
+// all steps together use up the place (block backward of 53 MB 29.4 / 30.1, of 201 MB 51.7 / 56.0).
+bool streams_inputs(const fs_graph& g) {
+  int64_t b = 0;
+  for (int t : g.inputs) b += g.tensors[t].numel() * dtype_bytes(g.tensors[t].dtype);
+  return g.cut_out || b > (int64_t(96) << 20);
 }
 
 int64_t graph_bytes_min(const fs_graph& g) {

@@ -103,6 +103,11 @@ template <typename T>
 __device__ __forceinline__ u32x4 load_raw(const T* p) {
   return *reinterpret_cast<const u32x4*>(p);
 }
+// STREAM: past the caches, for inputs too large to be in them (see streams_inputs() for where the line lies)
+template <bool STREAM, typename T>
+__device__ __forceinline__ u32x4 load_input(const T* p) {
+  return STREAM ? load_raw_nt(p) : load_raw(p);
+}
 __device__ __forceinline__ void unpack(u32x4 t, float (&v)[4], const float*) {
   // the whole vector is re-typed first: bit-casting a single vector element (an lvalue
   // like t.y) is miscompiled by this toolchain into a read of element 0

@@ -23,7 +23,7 @@ namespace fsk {
 using namespace fs;
 
 // ---- bias + GELU only ------------------------------------------------------------
-template <typename T>
+template <typename T, bool STREAM>
 __global__ void __launch_bounds__(256) k_bias_gelu(const T* __restrict__ x, const T* __restrict__ bias,
                                                    T* __restrict__ y, GeluP p) {
   constexpr int VEC = Elem<T>::VEC;
@@ -32,7 +32,7 @@ __global__ void __launch_bounds__(256) k_bias_gelu(const T* __restrict__ x, cons
   const uint32_t vi = blockIdx.x * 256u + threadIdx.x;
   if (vi >= n_vec) return;
   const uint32_t cv = vi % vecs_per_row;
-  const u32x4 rx = load_raw_nt(x + (size_t)vi * VEC);
+  const u32x4 rx = load_input<STREAM>(x + (size_t)vi * VEC);
   const u32x4 rb = load_raw(bias + cv * VEC);
   float v[VEC], b[VEC];
   unpack(rx, v, (const T*)nullptr);
@@ -70,7 +70,7 @@ __device__ __forceinline__ float gelu_and_grad(float z, float g, float& acc) {
 // loads it waits for, so it waits for everything -- every round of the loop then ends
 // with the wave idle until its own y stores are acknowledged.  With unconditional stores
 // the wait before the next tile's data leaves the UNROLL stores of this tile in flight.
-template <typename T, int WAVES, int UNROLL, bool FAST>
+template <typename T, int WAVES, int UNROLL, bool FAST, bool STREAM>
 __global__ void __launch_bounds__(WAVES * 64) k_bias_gelu_dbias(const T* __restrict__ x, const T* __restrict__ bias,
                                                                 const T* __restrict__ grad, T* __restrict__ y,
                                                                 float* __restrict__ partials, GeluP p) {
@@ -98,8 +98,8 @@ __global__ void __launch_bounds__(WAVES * 64) k_bias_gelu_dbias(const T* __restr
     for (int u = 0; u < UNROLL; ++u) {
       const uint32_t r = r0 + wave + u * WAVES;
       const size_t off = (size_t)(FAST ? r : min(r, p.rows - 1)) * p.cols + col;
-      nx[u] = load_raw_nt(x + off);
-      ng[u] = load_raw_nt(grad + off);
+      nx[u] = load_input<STREAM>(x + off);
+      ng[u] = load_input<STREAM>(grad + off);
     }
   };
   auto compute = [&](uint32_t r0, const u32x4 (&rx)[UNROLL], const u32x4 (&rg)[UNROLL]) {
@@ -281,18 +281,22 @@ namespace fs {
 using namespace fsk;
 
 namespace {
-template <typename T, bool FAST>
+template <typename T, bool FAST, bool S>
 const void* dbias_sym(int waves, int unroll) {
-  if (waves == 4 && unroll == 2) return (const void*)k_bias_gelu_dbias<T, 4, 2, FAST>;
-  if (waves == 4 && unroll == 4) return (const void*)k_bias_gelu_dbias<T, 4, 4, FAST>;
-  if (waves == 8 && unroll == 2) return (const void*)k_bias_gelu_dbias<T, 8, 2, FAST>;
-  if (waves == 8 && unroll == 4) return (const void*)k_bias_gelu_dbias<T, 8, 4, FAST>;
+  if (waves == 4 && unroll == 2) return (const void*)k_bias_gelu_dbias<T, 4, 2, FAST, S>;
+  if (waves == 4 && unroll == 4) return (const void*)k_bias_gelu_dbias<T, 4, 4, FAST, S>;
+  if (waves == 8 && unroll == 2) return (const void*)k_bias_gelu_dbias<T, 8, 2, FAST, S>;
+  if (waves == 8 && unroll == 4) return (const void*)k_bias_gelu_dbias<T, 8, 4, FAST, S>;
   return nullptr;
+}
+template <typename T, bool S>
+const void* gelu_sym_s(int32_t kernel, const GeluP& p) {
+  if (kernel == K_BIAS_GELU) return (const void*)k_bias_gelu<T, S>;
+  return p.fast ? dbias_sym<T, true, S>(p.waves, p.unroll) : dbias_sym<T, false, S>(p.waves, p.unroll);
 }
 template <typename T>
 const void* gelu_sym(int32_t kernel, const GeluP& p) {
-  if (kernel == K_BIAS_GELU) return (const void*)k_bias_gelu<T>;
-  return p.fast ? dbias_sym<T, true>(p.waves, p.unroll) : dbias_sym<T, false>(p.waves, p.unroll);
+  return p.stream ? gelu_sym_s<T, true>(kernel, p) : gelu_sym_s<T, false>(kernel, p);
 }
 }  // namespace
 

@@ -172,6 +172,7 @@ __device__ __forceinline__ void store_elements(TO* p, const float (&v)[N]) {
 // ROW_STRIDE > COLS: the pattern's rows are ROW_STRIDE elements long and the kernel works on column tiles of COLS
 // elements (patterns without row reductions only: nothing ties the tiles of a row together); `tile` picks the tile.
 // TILES: their number, where the last one may be shorter than the others (1: all of COLS elements).
+// PAST_CACHES: operands that are read once carry the streaming hint (inputs too large for the caches, see streams_inputs()).
 //
 // Row lengths that are no multiple of VEC: the row's last step slides back so that it ends where the row ends, and
 // reads some elements that the step before it holds as well (BACK of them).  Every load is then one whole access
@@ -179,7 +180,8 @@ __device__ __forceinline__ void store_elements(TO* p, const float (&v)[N]) {
 // store either writes only the TAIL elements the step owns, in at most three pieces, or (AGAIN) the whole step, the
 // repeated elements a second time with the value their owner gives them: one access instead of three more (rows of 197
 // 16-bit elements, 29.8 MB: 7.6 against 8.9 us for the bare copy, 7.0 with rows padded to whole steps).
-template <uint32_t ROWS, uint32_t COLS, int VEC, int K, uint32_t L, bool BLOCK, uint32_t R = 1, uint32_t ROW_STRIDE = COLS, uint32_t TILES = 1>
+template <uint32_t ROWS, uint32_t COLS, int VEC, int K, uint32_t L, bool BLOCK, uint32_t R = 1, uint32_t ROW_STRIDE = COLS, uint32_t TILES = 1,
+          bool PAST_CACHES = false>
 struct GenRow {
   static constexpr bool SHORT_LAST = TILES > 1 && TILES * COLS != ROW_STRIDE;
   static constexpr uint32_t LAST_COLS = SHORT_LAST ? ROW_STRIDE - (TILES - 1u) * COLS : COLS;
@@ -232,8 +234,8 @@ struct GenRow {
     return (int)min(lane + k * LANES, n_steps() - 1u) * VEC;
   }
 
-  // the lane's K steps of row `at_row` of a [.., COLS] tensor, in storage form; STREAM: read once, so the loads
-  // carry the streaming hint and do not displace the operands that every row re-reads from cache
+  // the lane's K steps of row `at_row` of a [.., COLS] tensor, in storage form; STREAM: read once, so the loads may
+  // carry the streaming hint and then do not displace the operands that every row re-reads from cache
   template <typename T>
   struct Raw {
     StepBits<VEC * (int)sizeof(T), alignment<T>()> w[K];
@@ -247,7 +249,7 @@ struct GenRow {
     Raw<T> r;
     const T* base = static_cast<const T*>(p) + at_row * ROW_STRIDE + col0;
 #pragma unroll
-    for (int k = 0; k < K; ++k) r.w[k] = StepBits<VEC * (int)sizeof(T), alignment<T>()>::template load<STREAM>(base + first_of(k));
+    for (int k = 0; k < K; ++k) r.w[k] = StepBits<VEC * (int)sizeof(T), alignment<T>()>::template load<STREAM && PAST_CACHES>(base + first_of(k));
     return r;
   }
 

@@ -99,6 +99,7 @@ struct TransposeP {
   uint32_t n;
   uint32_t in_stride[3];        // elements, of the input axis that feeds output axis 0, 1, 2
   uint32_t out_ext[3];          // output extents 1 and 2, innermost extent
+  int32_t stream;               // vectorised tile: 1 = the input is read past the caches
 };
 
 // ---- stitched -----------------------------------------------------------------
@@ -112,6 +113,7 @@ struct SoftmaxP {
   int32_t lanes_per_row, vecs_per_lane;
   int32_t lanes_log2;               // log2(lanes_per_row) for the wave variant
   int32_t fast;                     // 1: the row fills the lanes and the rows fill the workgroups exactly
+  int32_t stream;                   // here and below: 1 = row inputs are read past the caches (see streams_inputs)
 };
 struct LayerNormP {
   int32_t in_dt, out_dt, par_dt;    // x/res dtype, output dtype, bias/gamma/beta dtype
@@ -122,6 +124,7 @@ struct LayerNormP {
   int32_t lanes_per_row, vecs_per_lane, rows_per_block;
   int32_t lanes_log2;
   int32_t fast;                     // 1: all operands present, row and row count fill lanes / workgroups exactly
+  int32_t stream;
 };
 struct GeluP {
   int32_t dt, bias_dt;              // x / grad / y share dt; K_COLFOLD: dt = dtype the sums are handed out in
@@ -132,6 +135,7 @@ struct GeluP {
   uint32_t fold_cols, fold_split;   // K_COLFOLD: columns of the partials, first column that goes to the second output
   uint32_t fold_out_cols;           // K_COLFOLD: columns of each output (< fold_split where a slice is padded, see colsum_pitch)
   uint32_t fold_quads;              // K_COLFOLD: column quads per workgroup (16 with 16 row groups, or 4 with 64)
+  int32_t stream;
 };
 struct TChainP {
   int32_t dt, scale_dt;
@@ -141,6 +145,7 @@ struct TChainP {
   int32_t passes;                   // rows each lane group handles = ceil(s_tile * H / groups), 1..4
   int32_t lanes_log2;
   FastDiv div_h, div_s_tiles;       // division by H and by the number of s tiles per batch entry
+  int32_t stream;
 };
 
 struct LnBwdP {
@@ -150,6 +155,7 @@ struct LnBwdP {
   int32_t lanes_per_row, lanes_log2, vecs_per_lane;
   int32_t waves, rows_per_group;    // workgroup = waves x 64 lanes; rows each lane group loads up front
   int32_t fast;                     // 1: the row fills the lanes exactly, the tiles fill the workgroups' rounds exactly
+  int32_t stream;
 };
 enum RowPattern : int32_t { ROW_SOFTMAX_BWD = 0, ROW_RMSNORM = 1 };
 struct RowP {
@@ -157,6 +163,7 @@ struct RowP {
   uint32_t rows, cols;
   float f[4];                       // pattern scalars
   int32_t lanes_per_row, lanes_log2, vecs_per_lane, fast;
+  int32_t stream;
 };
 
 // ---- packed launch: many independent row patterns in one kernel -----------------------
@@ -263,6 +270,7 @@ struct RowProgP {
                                        // lanes_per_row * vecs_per_lane steps, once per row reduction and once more for the stores
   int32_t col_kept;                    // of those chunks, the first col_kept stay in registers in storage form after the first
                                        // pass (the later passes do not read them again)
+  int32_t stream;                      // generated kernels: 1 = row inputs are read past the caches (see streams_inputs)
   ProgInstr instr[kProgMaxInstr];
 };
 // Floats between two column sums in a row of partial sums: whole quads, which the fold reads (the padding is never

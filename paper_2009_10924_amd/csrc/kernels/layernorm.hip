@@ -22,7 +22,7 @@ using namespace fs;
 // FAST: residual, bias and affine all present, the row fills the lanes exactly and the
 // row count fills the workgroups exactly, so every flag test, clamp and padding mask
 // folds away at compile time (the shape of the benchmarked configuration).
-template <typename TI, typename TO, int K, bool FAST>
+template <typename TI, typename TO, int K, bool FAST, bool STREAM>
 struct LnRow {
   static constexpr int VEC = Elem<TI>::VEC;
   float h[K][VEC];
@@ -40,10 +40,10 @@ struct LnRow {
     auto vec_at = [&](int k) { return FAST ? lane + k * stride : min(lane + k * stride, nvec - 1); };
     u32x4 rx[K], rr[K], rb[K];
 #pragma unroll
-    for (int k = 0; k < K; ++k) rx[k] = load_raw_nt(x + base + vec_at(k) * VEC);
+    for (int k = 0; k < K; ++k) rx[k] = load_input<STREAM>(x + base + vec_at(k) * VEC);
     if (has_res) {
 #pragma unroll
-      for (int k = 0; k < K; ++k) rr[k] = load_raw_nt(res + base + vec_at(k) * VEC);
+      for (int k = 0; k < K; ++k) rr[k] = load_input<STREAM>(res + base + vec_at(k) * VEC);
     }
     if (has_bias) {
 #pragma unroll
@@ -123,7 +123,7 @@ struct LnRow {
 
 // STATS: the pattern also hands out the per-row mean and reciprocal standard deviation.  A template flag, not a
 // run-time test of the pointers: the kernel without statistics must stay one basic block (see the file header).
-template <typename TI, typename TO, int K, bool FAST, bool STATS>
+template <typename TI, typename TO, int K, bool FAST, bool STATS, bool STREAM>
 __global__ void __launch_bounds__(256) k_layernorm_wave(const TI* __restrict__ x, const TI* __restrict__ res,
                                                         const TI* __restrict__ bias, const TI* __restrict__ gamma,
                                                         const TI* __restrict__ beta, TO* __restrict__ out,
@@ -135,7 +135,7 @@ __global__ void __launch_bounds__(256) k_layernorm_wave(const TI* __restrict__ x
   const uint32_t row = blockIdx.x * (256u >> p.lanes_log2) + group;
   const bool row_ok = row < p.rows;
   const float inv_n = p.inv_cols;
-  LnRow<TI, TO, K, FAST> r;
+  LnRow<TI, TO, K, FAST, STREAM> r;
   const float mean = group_allreduce<OpSum>(r.load(x, res, bias, gamma, beta, p, row, lane, L), L) * inv_n;
   const float var = group_allreduce<OpSum>(r.center(p, mean, lane, L), L) * inv_n;
   const float rstd = fast_rsqrt(var + p.eps);
@@ -148,7 +148,7 @@ __global__ void __launch_bounds__(256) k_layernorm_wave(const TI* __restrict__ x
   }
 }
 
-template <typename TI, typename TO, int K, bool FAST>
+template <typename TI, typename TO, int K, bool FAST, bool STREAM>
 __global__ void __launch_bounds__(256) k_layernorm_block(const TI* __restrict__ x, const TI* __restrict__ res,
                                                          const TI* __restrict__ bias, const TI* __restrict__ gamma,
                                                          const TI* __restrict__ beta, TO* __restrict__ out,
@@ -159,7 +159,7 @@ __global__ void __launch_bounds__(256) k_layernorm_block(const TI* __restrict__ 
   const float inv_n = p.inv_cols;
   uint32_t it = 0;
   for (uint32_t row = blockIdx.x; row < p.rows; row += gridDim.x, ++it) {
-    LnRow<TI, TO, K, FAST> r;
+    LnRow<TI, TO, K, FAST, STREAM> r;
     // two slot sets alternate between rows: a wave may start row i+1 while a slower
     // one still reads the slots of row i.
     const float mean = block_allreduce<OpSum>(r.load(x, res, bias, gamma, beta, p, row, threadIdx.x, blockDim.x),
@@ -193,7 +193,7 @@ __global__ void __launch_bounds__(256) k_layernorm_block(const TI* __restrict__ 
 // FAST: the row fills the lanes exactly and the tiles fill the workgroups' rounds exactly.  Then nothing in the
 // row loop is conditional, the next tile's loads are issued before this tile's arithmetic (software pipeline),
 // and -- because the stores sit in no branch -- the wait for those loads leaves this tile's stores in flight.
-template <typename T, int K, int R, int WAVES, bool FAST>
+template <typename T, int K, int R, int WAVES, bool FAST, bool STREAM>
 __global__ void __launch_bounds__(WAVES * 64) k_layernorm_bwd(const T* __restrict__ h, const T* __restrict__ dy,
                                                               const T* __restrict__ gamma, const float* __restrict__ mu,
                                                               const float* __restrict__ rstd, T* __restrict__ dx,
@@ -234,8 +234,8 @@ __global__ void __launch_bounds__(WAVES * 64) k_layernorm_bwd(const T* __restric
       const size_t base = (size_t)rc * p.cols;
 #pragma unroll
       for (int k = 0; k < K; ++k) {
-        w.h[r][k] = load_raw_nt(h + base + vec_at(k) * VEC);
-        w.d[r][k] = load_raw_nt(dy + base + vec_at(k) * VEC);
+        w.h[r][k] = load_input<STREAM>(h + base + vec_at(k) * VEC);
+        w.d[r][k] = load_input<STREAM>(dy + base + vec_at(k) * VEC);
       }
       w.mu[r] = mu[rc];
       w.rs[r] = rstd[rc];
@@ -327,47 +327,53 @@ namespace fs {
 using namespace fsk;
 
 namespace {
-template <typename T, int R, int WAVES, bool FAST>
+template <typename T, int R, int WAVES, bool FAST, bool S>
 const void* ln_bwd_sym_k(int K) {
   switch (K) {
-    case 1: return (const void*)k_layernorm_bwd<T, 1, R, WAVES, FAST>;
-    case 2: return (const void*)k_layernorm_bwd<T, 2, R, WAVES, FAST>;
-    case 3: return (const void*)k_layernorm_bwd<T, 3, R, WAVES, FAST>;
-    case 4: return (const void*)k_layernorm_bwd<T, 4, R, WAVES, FAST>;
-    case 6: return (const void*)k_layernorm_bwd<T, 6, R, WAVES, FAST>;
+    case 1: return (const void*)k_layernorm_bwd<T, 1, R, WAVES, FAST, S>;
+    case 2: return (const void*)k_layernorm_bwd<T, 2, R, WAVES, FAST, S>;
+    case 3: return (const void*)k_layernorm_bwd<T, 3, R, WAVES, FAST, S>;
+    case 4: return (const void*)k_layernorm_bwd<T, 4, R, WAVES, FAST, S>;
+    case 6: return (const void*)k_layernorm_bwd<T, 6, R, WAVES, FAST, S>;
     default: return nullptr;
   }
 }
-template <typename T, bool FAST>
+template <typename T, bool FAST, bool S>
 const void* ln_bwd_sym_f(const LnBwdP& b) {
-  if (b.waves == 4 && b.rows_per_group == 1) return ln_bwd_sym_k<T, 1, 4, FAST>(b.vecs_per_lane);
-  if (b.waves == 4 && b.rows_per_group == 2) return ln_bwd_sym_k<T, 2, 4, FAST>(b.vecs_per_lane);
-  if (b.waves == 4 && b.rows_per_group == 4) return ln_bwd_sym_k<T, 4, 4, FAST>(b.vecs_per_lane);
-  if (b.waves == 8 && b.rows_per_group == 1) return ln_bwd_sym_k<T, 1, 8, FAST>(b.vecs_per_lane);
-  if (b.waves == 8 && b.rows_per_group == 2) return ln_bwd_sym_k<T, 2, 8, FAST>(b.vecs_per_lane);
+  if (b.waves == 4 && b.rows_per_group == 1) return ln_bwd_sym_k<T, 1, 4, FAST, S>(b.vecs_per_lane);
+  if (b.waves == 4 && b.rows_per_group == 2) return ln_bwd_sym_k<T, 2, 4, FAST, S>(b.vecs_per_lane);
+  if (b.waves == 4 && b.rows_per_group == 4) return ln_bwd_sym_k<T, 4, 4, FAST, S>(b.vecs_per_lane);
+  if (b.waves == 8 && b.rows_per_group == 1) return ln_bwd_sym_k<T, 1, 8, FAST, S>(b.vecs_per_lane);
+  if (b.waves == 8 && b.rows_per_group == 2) return ln_bwd_sym_k<T, 2, 8, FAST, S>(b.vecs_per_lane);
   return nullptr;
 }
 template <typename T>
 const void* ln_bwd_sym(const LnBwdP& b) {
-  return b.fast ? ln_bwd_sym_f<T, true>(b) : ln_bwd_sym_f<T, false>(b);
+  if (b.stream) return b.fast ? ln_bwd_sym_f<T, true, true>(b) : ln_bwd_sym_f<T, false, true>(b);
+  return b.fast ? ln_bwd_sym_f<T, true, false>(b) : ln_bwd_sym_f<T, false, false>(b);
 }
-template <typename TI, typename TO>
-const void* ln_sym(int32_t kernel, int K, bool fast, bool stats) {
+template <typename TI, typename TO, bool S>
+const void* ln_sym_s(int32_t kernel, int K, bool fast, bool stats) {
 #define FS_LN_CASE(KK)                                                                                     \
   case KK:                                                                                                 \
     if (kernel == K_LAYERNORM_WAVE) {                                                                      \
-      if (stats) return fast ? (const void*)k_layernorm_wave<TI, TO, KK, true, true>                       \
-                             : (const void*)k_layernorm_wave<TI, TO, KK, false, true>;                     \
-      return fast ? (const void*)k_layernorm_wave<TI, TO, KK, true, false>                                 \
-                  : (const void*)k_layernorm_wave<TI, TO, KK, false, false>;                               \
+      if (stats) return fast ? (const void*)k_layernorm_wave<TI, TO, KK, true, true, S>                       \
+                             : (const void*)k_layernorm_wave<TI, TO, KK, false, true, S>;                     \
+      return fast ? (const void*)k_layernorm_wave<TI, TO, KK, true, false, S>                                 \
+                  : (const void*)k_layernorm_wave<TI, TO, KK, false, false, S>;                               \
     }                                                                                                      \
-    return fast && !stats ? (const void*)k_layernorm_block<TI, TO, KK, true>                               \
-                          : (const void*)k_layernorm_block<TI, TO, KK, false>;
+    return fast && !stats ? (const void*)k_layernorm_block<TI, TO, KK, true, S>                               \
+                          : (const void*)k_layernorm_block<TI, TO, KK, false, S>;
   switch (K) {
     FS_LN_CASE(1) FS_LN_CASE(2) FS_LN_CASE(3) FS_LN_CASE(4) FS_LN_CASE(6) FS_LN_CASE(8)
     default: return nullptr;
   }
 #undef FS_LN_CASE
+}
+template <typename TI, typename TO>
+const void* ln_sym(int32_t kernel, const LayerNormP& p) {
+  return p.stream ? ln_sym_s<TI, TO, true>(kernel, p.vecs_per_lane, p.fast != 0, p.stats != 0)
+                  : ln_sym_s<TI, TO, false>(kernel, p.vecs_per_lane, p.fast != 0, p.stats != 0);
 }
 }  // namespace
 
@@ -381,12 +387,11 @@ const void* layernorm_kernel_symbol(int32_t kernel, const KernelArgs& a) {
     }
   }
   const LayerNormP& p = a.u.layernorm;
-  const int K = p.vecs_per_lane;
-  if (p.in_dt == DT_F32 && p.out_dt == DT_F32) return ln_sym<float, float>(kernel, K, p.fast != 0, p.stats != 0);
-  if (p.in_dt == DT_F32 && p.out_dt == DT_BF16) return ln_sym<float, bf16_t>(kernel, K, p.fast != 0, p.stats != 0);
-  if (p.in_dt == DT_F32 && p.out_dt == DT_F16) return ln_sym<float, f16_t>(kernel, K, p.fast != 0, p.stats != 0);
-  if (p.in_dt == DT_BF16 && p.out_dt == DT_BF16) return ln_sym<bf16_t, bf16_t>(kernel, K, p.fast != 0, p.stats != 0);
-  if (p.in_dt == DT_F16 && p.out_dt == DT_F16) return ln_sym<f16_t, f16_t>(kernel, K, p.fast != 0, p.stats != 0);
+  if (p.in_dt == DT_F32 && p.out_dt == DT_F32) return ln_sym<float, float>(kernel, p);
+  if (p.in_dt == DT_F32 && p.out_dt == DT_BF16) return ln_sym<float, bf16_t>(kernel, p);
+  if (p.in_dt == DT_F32 && p.out_dt == DT_F16) return ln_sym<float, f16_t>(kernel, p);
+  if (p.in_dt == DT_BF16 && p.out_dt == DT_BF16) return ln_sym<bf16_t, bf16_t>(kernel, p);
+  if (p.in_dt == DT_F16 && p.out_dt == DT_F16) return ln_sym<f16_t, f16_t>(kernel, p);
   return nullptr;
 }
 

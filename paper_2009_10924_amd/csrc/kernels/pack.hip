@@ -16,7 +16,7 @@ namespace fsk {
 
 template <typename Spec, typename T, typename TO, int K>
 __device__ __forceinline__ void run_member(const PackEntry& e, float* slots, uint32_t vblock) {
-  RowCtx<T, TO, Spec::NI, Spec::NV, K, false, MODE_RUNTIME> c(e.p, slots, vblock);
+  RowCtx<T, TO, Spec::NI, Spec::NV, K, false, MODE_RUNTIME, false> c(e.p, slots, vblock);
   const T* in[Spec::NI];
   const T* vec[Spec::NV > 0 ? Spec::NV : 1] = {nullptr};
 #pragma unroll

@@ -22,7 +22,7 @@ using namespace fs;
 //               where one kernel serves members of either form).
 enum RowMode : int { MODE_WAVE = 0, MODE_BLOCK = 1, MODE_RUNTIME = 2 };
 
-template <typename T, typename TO, int NI, int NV, int K, bool FAST, int MODE>
+template <typename T, typename TO, int NI, int NV, int K, bool FAST, int MODE, bool STREAM>
 struct RowCtx {
   static constexpr int VEC = Elem<T>::VEC;
   float x[NI][K][VEC];                 // row inputs, padding slots hold 0
@@ -58,7 +58,7 @@ struct RowCtx {
 #pragma unroll
     for (int i = 0; i < NI; ++i)
 #pragma unroll
-      for (int k = 0; k < K; ++k) raw[i][k] = load_raw_nt(in[i] + base + vec_at(k) * VEC);
+      for (int k = 0; k < K; ++k) raw[i][k] = load_input<STREAM>(in[i] + base + vec_at(k) * VEC);
 #pragma unroll
     for (int i = 0; i < NV; ++i)
 #pragma unroll

@@ -22,20 +22,20 @@ __device__ __forceinline__ void run_row_pattern(Ctx& c, const T* in0, const T* i
   Spec::run(c, out0);
 }
 
-template <typename Spec, typename T, int K, bool FAST>
+template <typename Spec, typename T, int K, bool FAST, bool STREAM>
 __global__ void __launch_bounds__(256) k_row_wave(const T* __restrict__ in0, const T* __restrict__ in1,
                                                   const T* __restrict__ vec0, const T* __restrict__ vec1,
                                                   T* __restrict__ out0, T* __restrict__ out1, RowP p) {
-  RowCtx<T, T, Spec::NI, Spec::NV, K, FAST, MODE_WAVE> c(p, nullptr, blockIdx.x);
+  RowCtx<T, T, Spec::NI, Spec::NV, K, FAST, MODE_WAVE, STREAM> c(p, nullptr, blockIdx.x);
   run_row_pattern<Spec, T>(c, in0, in1, vec0, vec1, out0);
 }
 
-template <typename Spec, typename T, int K, bool FAST>
+template <typename Spec, typename T, int K, bool FAST, bool STREAM>
 __global__ void __launch_bounds__(256) k_row_block(const T* __restrict__ in0, const T* __restrict__ in1,
                                                    const T* __restrict__ vec0, const T* __restrict__ vec1,
                                                    T* __restrict__ out0, T* __restrict__ out1, RowP p) {
   __shared__ float slots[16];
-  RowCtx<T, T, Spec::NI, Spec::NV, K, FAST, MODE_BLOCK> c(p, slots, blockIdx.x);
+  RowCtx<T, T, Spec::NI, Spec::NV, K, FAST, MODE_BLOCK, STREAM> c(p, slots, blockIdx.x);
   run_row_pattern<Spec, T>(c, in0, in1, vec0, vec1, out0);
 }
 
@@ -45,30 +45,30 @@ namespace fs {
 using namespace fsk;
 
 namespace {
-template <typename Spec, typename T>
+template <typename Spec, typename T, bool S>
 const void* row_sym(int32_t kernel, int K, bool fast) {
   if (kernel == K_ROW_BLOCK) {
     switch (K) {
-      case 1: return fast ? (const void*)k_row_block<Spec, T, 1, true> : (const void*)k_row_block<Spec, T, 1, false>;
-      case 2: return fast ? (const void*)k_row_block<Spec, T, 2, true> : (const void*)k_row_block<Spec, T, 2, false>;
-      case 4: return fast ? (const void*)k_row_block<Spec, T, 4, true> : (const void*)k_row_block<Spec, T, 4, false>;
+      case 1: return fast ? (const void*)k_row_block<Spec, T, 1, true, S> : (const void*)k_row_block<Spec, T, 1, false, S>;
+      case 2: return fast ? (const void*)k_row_block<Spec, T, 2, true, S> : (const void*)k_row_block<Spec, T, 2, false, S>;
+      case 4: return fast ? (const void*)k_row_block<Spec, T, 4, true, S> : (const void*)k_row_block<Spec, T, 4, false, S>;
       default: return nullptr;
     }
   }
 #define FS_ROW_CASE(KK) \
-  case KK: return fast ? (const void*)k_row_wave<Spec, T, KK, true> : (const void*)k_row_wave<Spec, T, KK, false>;
+  case KK: return fast ? (const void*)k_row_wave<Spec, T, KK, true, S> : (const void*)k_row_wave<Spec, T, KK, false, S>;
   switch (K) {
     FS_ROW_CASE(1) FS_ROW_CASE(2) FS_ROW_CASE(4) FS_ROW_CASE(8)
     default: return nullptr;
   }
 #undef FS_ROW_CASE
 }
-template <typename Spec>
+template <typename Spec, bool S>
 const void* row_sym_dt(int32_t kernel, const RowP& p) {
   switch (p.dt) {
-    case DT_F32: return row_sym<Spec, float>(kernel, p.vecs_per_lane, p.fast != 0);
-    case DT_F16: return row_sym<Spec, f16_t>(kernel, p.vecs_per_lane, p.fast != 0);
-    default: return row_sym<Spec, bf16_t>(kernel, p.vecs_per_lane, p.fast != 0);
+    case DT_F32: return row_sym<Spec, float, S>(kernel, p.vecs_per_lane, p.fast != 0);
+    case DT_F16: return row_sym<Spec, f16_t, S>(kernel, p.vecs_per_lane, p.fast != 0);
+    default: return row_sym<Spec, bf16_t, S>(kernel, p.vecs_per_lane, p.fast != 0);
   }
 }
 }  // namespace
@@ -76,8 +76,8 @@ const void* row_sym_dt(int32_t kernel, const RowP& p) {
 const void* rowops_kernel_symbol(int32_t kernel, const KernelArgs& a) {
   const RowP& p = a.u.row;
   switch (p.pattern) {
-    case ROW_SOFTMAX_BWD: return row_sym_dt<SoftmaxBwdSpec>(kernel, p);
-    case ROW_RMSNORM: return row_sym_dt<RmsNormSpec>(kernel, p);
+    case ROW_SOFTMAX_BWD: return p.stream ? row_sym_dt<SoftmaxBwdSpec, true>(kernel, p) : row_sym_dt<SoftmaxBwdSpec, false>(kernel, p);
+    case ROW_RMSNORM: return p.stream ? row_sym_dt<RmsNormSpec, true>(kernel, p) : row_sym_dt<RmsNormSpec, false>(kernel, p);
     default: return nullptr;
   }
 }

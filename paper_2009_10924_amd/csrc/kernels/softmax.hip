@@ -23,7 +23,7 @@ using namespace fs;
 // so no branch separates the loads and all of them are in flight together.
 // FAST: the row fills the lanes exactly, the rows fill the workgroups exactly and a mask,
 // if any, varies along the row: clamps, padding masks and flag tests fold away.
-template <typename T, int K, bool HAS_MASK, bool FAST>
+template <typename T, int K, bool HAS_MASK, bool FAST, bool STREAM>
 __device__ __forceinline__ void softmax_load(const T* __restrict__ x, const T* __restrict__ mask, const SoftmaxP& p,
                                              uint32_t row, uint32_t lane, uint32_t stride,
                                              float (&v)[K][Elem<T>::VEC]) {
@@ -36,7 +36,7 @@ __device__ __forceinline__ void softmax_load(const T* __restrict__ x, const T* _
   u32x4 raw[K], rawm[K];
   float mscalar = 0.0f;
 #pragma unroll
-  for (int k = 0; k < K; ++k) raw[k] = load_raw_nt(xr + vec_at(k) * VEC);
+  for (int k = 0; k < K; ++k) raw[k] = load_input<STREAM>(xr + vec_at(k) * VEC);
   if constexpr (HAS_MASK) {
     const uint32_t r1 = fast_div(r, p.od[2]);
     const uint32_t c2 = r - r1 * p.od[2].d;
@@ -116,7 +116,7 @@ __device__ __forceinline__ void softmax_store(T* __restrict__ out, const Softmax
 }
 
 // ---- wave variant ------------------------------------------------------------------
-template <typename T, int K, bool HAS_MASK, bool FAST>
+template <typename T, int K, bool HAS_MASK, bool FAST, bool STREAM>
 __global__ void __launch_bounds__(256) k_softmax_wave(const T* __restrict__ x, const T* __restrict__ mask,
                                                       T* __restrict__ out, SoftmaxP p) {
   constexpr int VEC = Elem<T>::VEC;
@@ -126,14 +126,14 @@ __global__ void __launch_bounds__(256) k_softmax_wave(const T* __restrict__ x, c
   const uint32_t row = blockIdx.x * (256u >> p.lanes_log2) + group;
   const bool row_ok = row < p.rows;
   float v[K][VEC];
-  softmax_load<T, K, HAS_MASK, FAST>(x, mask, p, row, lane, L, v);
+  softmax_load<T, K, HAS_MASK, FAST, STREAM>(x, mask, p, row, lane, L, v);
   const float m = group_allreduce<OpMax>(local_max<K, VEC>(v), L);
   const float s = group_allreduce<OpSum>(exp_and_sum<K, VEC>(v, m), L);
   softmax_store<T, K, FAST>(out, p, row, row_ok, lane, L, v, fast_rcp(s));
 }
 
 // ---- block variant -----------------------------------------------------------------
-template <typename T, int K, bool HAS_MASK, bool FAST>
+template <typename T, int K, bool HAS_MASK, bool FAST, bool STREAM>
 __global__ void __launch_bounds__(256) k_softmax_block(const T* __restrict__ x, const T* __restrict__ mask,
                                                        T* __restrict__ out, SoftmaxP p) {
   constexpr int VEC = Elem<T>::VEC;
@@ -141,7 +141,7 @@ __global__ void __launch_bounds__(256) k_softmax_block(const T* __restrict__ x, 
   const uint32_t row = blockIdx.x;
   const uint32_t n_waves = blockDim.x >> 6;
   float v[K][VEC];
-  softmax_load<T, K, HAS_MASK, FAST>(x, mask, p, row, threadIdx.x, blockDim.x, v);
+  softmax_load<T, K, HAS_MASK, FAST, STREAM>(x, mask, p, row, threadIdx.x, blockDim.x, v);
   const float m = block_allreduce<OpMax>(local_max<K, VEC>(v), slot_max, n_waves);
   const float s = block_allreduce<OpSum>(exp_and_sum<K, VEC>(v, m), slot_sum, n_waves);
   softmax_store<T, K, FAST>(out, p, row, true, threadIdx.x, blockDim.x, v, fast_rcp(s));
@@ -182,33 +182,37 @@ namespace fs {
 using namespace fsk;
 
 namespace {
-template <typename T, bool M, bool F>
+template <typename T, bool M, bool F, bool S>
 const void* wave_sym(int K) {
   switch (K) {
-    case 1: return (const void*)k_softmax_wave<T, 1, M, F>;
-    case 2: return (const void*)k_softmax_wave<T, 2, M, F>;
-    case 4: return (const void*)k_softmax_wave<T, 4, M, F>;
-    default: return (const void*)k_softmax_wave<T, 8, M, F>;
+    case 1: return (const void*)k_softmax_wave<T, 1, M, F, S>;
+    case 2: return (const void*)k_softmax_wave<T, 2, M, F, S>;
+    case 4: return (const void*)k_softmax_wave<T, 4, M, F, S>;
+    default: return (const void*)k_softmax_wave<T, 8, M, F, S>;
   }
 }
-template <typename T, bool M, bool F>
+template <typename T, bool M, bool F, bool S>
 const void* block_sym(int K) {
   switch (K) {
-    case 1: return (const void*)k_softmax_block<T, 1, M, F>;
-    case 2: return (const void*)k_softmax_block<T, 2, M, F>;
-    case 4: return (const void*)k_softmax_block<T, 4, M, F>;
-    default: return (const void*)k_softmax_block<T, 8, M, F>;
+    case 1: return (const void*)k_softmax_block<T, 1, M, F, S>;
+    case 2: return (const void*)k_softmax_block<T, 2, M, F, S>;
+    case 4: return (const void*)k_softmax_block<T, 4, M, F, S>;
+    default: return (const void*)k_softmax_block<T, 8, M, F, S>;
   }
 }
-template <typename T, bool M>
+template <typename T, bool M, bool S>
 const void* sym_mf(int32_t kernel, const SoftmaxP& p) {
-  if (kernel == K_SOFTMAX_WAVE) return p.fast ? wave_sym<T, M, true>(p.vecs_per_lane) : wave_sym<T, M, false>(p.vecs_per_lane);
-  return p.fast ? block_sym<T, M, true>(p.vecs_per_lane) : block_sym<T, M, false>(p.vecs_per_lane);
+  if (kernel == K_SOFTMAX_WAVE) return p.fast ? wave_sym<T, M, true, S>(p.vecs_per_lane) : wave_sym<T, M, false, S>(p.vecs_per_lane);
+  return p.fast ? block_sym<T, M, true, S>(p.vecs_per_lane) : block_sym<T, M, false, S>(p.vecs_per_lane);
+}
+template <typename T, bool M>
+const void* sym_m(int32_t kernel, const SoftmaxP& p) {
+  return p.stream ? sym_mf<T, M, true>(kernel, p) : sym_mf<T, M, false>(kernel, p);
 }
 template <typename T>
 const void* sym_for(int32_t kernel, const SoftmaxP& p) {
   if (p.vecs_per_lane == 0) return (const void*)k_softmax_generic<T>;
-  return p.has_mask ? sym_mf<T, true>(kernel, p) : sym_mf<T, false>(kernel, p);
+  return p.has_mask ? sym_m<T, true>(kernel, p) : sym_m<T, false>(kernel, p);
 }
 }  // namespace
 

@@ -20,7 +20,7 @@ using namespace fs;
 // g, g + groups, ... (input order, so a wavefront reads consecutive rows).  PASSES rows
 // per lane group are loaded up front so that all loads are in flight together; rows
 // past the slab are clamped to its last row and dropped at the store.
-template <typename T, int K, int PASSES>
+template <typename T, int K, int PASSES, bool STREAM>
 struct TChainTile {
   static constexpr int VEC = Elem<T>::VEC;
   float v[PASSES][K][VEC];
@@ -42,7 +42,7 @@ struct TChainTile {
       h[it] = cidx - sl[it] * p.H;
       const T* xrow = x + ((size_t)(b * p.S + s0 + sl[it]) * p.H + h[it]) * p.D;
 #pragma unroll
-      for (int k = 0; k < K; ++k) raw[it][k] = load_raw_nt(xrow + min(lane + k * L, nvec - 1) * VEC);
+      for (int k = 0; k < K; ++k) raw[it][k] = load_input<STREAM>(xrow + min(lane + k * L, nvec - 1) * VEC);
       sc[it] = load1(scale + h[it]);
     }
 #pragma unroll
@@ -68,7 +68,7 @@ struct TChainTile {
   }
 };
 
-template <typename T, int K, int PASSES>
+template <typename T, int K, int PASSES, bool STREAM>
 __global__ void __launch_bounds__(256) k_tchain_wave(const T* __restrict__ x, const T* __restrict__ scale,
                                                      T* __restrict__ out, TChainP p) {
   constexpr int VEC = Elem<T>::VEC;
@@ -79,7 +79,7 @@ __global__ void __launch_bounds__(256) k_tchain_wave(const T* __restrict__ x, co
   const uint32_t b = fast_div(blockIdx.x, p.div_s_tiles);
   const uint32_t s0 = (blockIdx.x - b * p.div_s_tiles.d) * p.s_tile;
   const uint32_t s_cnt = min((uint32_t)p.s_tile, p.S - s0);
-  TChainTile<T, K, PASSES> t;
+  TChainTile<T, K, PASSES, STREAM> t;
   t.run(x, scale, p, b, s0, s_cnt * p.H, group, groups, lane, L);
 #pragma unroll
   for (int it = 0; it < PASSES; ++it) {
@@ -92,7 +92,7 @@ __global__ void __launch_bounds__(256) k_tchain_wave(const T* __restrict__ x, co
   }
 }
 
-template <typename T, int K, int PASSES>
+template <typename T, int K, int PASSES, bool STREAM>
 __global__ void __launch_bounds__(256) k_tchain_lds(const T* __restrict__ x, const T* __restrict__ scale,
                                                     T* __restrict__ out, TChainP p) {
   constexpr int VEC = Elem<T>::VEC;
@@ -106,7 +106,7 @@ __global__ void __launch_bounds__(256) k_tchain_lds(const T* __restrict__ x, con
   const uint32_t s0 = (blockIdx.x - b * p.div_s_tiles.d) * p.s_tile;
   const uint32_t s_cnt = min((uint32_t)p.s_tile, p.S - s0);
   {
-    TChainTile<T, K, PASSES> t;
+    TChainTile<T, K, PASSES, STREAM> t;
     t.run(x, scale, p, b, s0, s_cnt * p.H, group, groups, lane, L);
 #pragma unroll
     for (int it = 0; it < PASSES; ++it) {
@@ -147,33 +147,37 @@ namespace fs {
 using namespace fsk;
 
 namespace {
-template <typename T, int K>
+template <typename T, int K, bool S>
 const void* tc_sym_kp(int32_t kernel, int passes) {
 #define FS_TC_CASE(PP) \
-  case PP: return kernel == K_TCHAIN_WAVE ? (const void*)k_tchain_wave<T, K, PP> : (const void*)k_tchain_lds<T, K, PP>;
+  case PP: return kernel == K_TCHAIN_WAVE ? (const void*)k_tchain_wave<T, K, PP, S> : (const void*)k_tchain_lds<T, K, PP, S>;
   switch (passes) {
     FS_TC_CASE(1) FS_TC_CASE(2) FS_TC_CASE(3) FS_TC_CASE(4)
     default: return nullptr;
   }
 #undef FS_TC_CASE
 }
-template <typename T>
-const void* tc_sym(int32_t kernel, int K, int passes) {
+template <typename T, bool S>
+const void* tc_sym_s(int32_t kernel, int K, int passes) {
   switch (K) {
-    case 1: return tc_sym_kp<T, 1>(kernel, passes);
-    case 2: return tc_sym_kp<T, 2>(kernel, passes);
-    case 4: return tc_sym_kp<T, 4>(kernel, passes);
+    case 1: return tc_sym_kp<T, 1, S>(kernel, passes);
+    case 2: return tc_sym_kp<T, 2, S>(kernel, passes);
+    case 4: return tc_sym_kp<T, 4, S>(kernel, passes);
     default: return nullptr;
   }
+}
+template <typename T>
+const void* tc_sym(int32_t kernel, const TChainP& p) {
+  return p.stream ? tc_sym_s<T, true>(kernel, p.vecs_per_lane, p.passes) : tc_sym_s<T, false>(kernel, p.vecs_per_lane, p.passes);
 }
 }  // namespace
 
 const void* tchain_kernel_symbol(int32_t kernel, const KernelArgs& a) {
   const TChainP& p = a.u.tchain;
   switch (p.dt) {
-    case DT_F32: return tc_sym<float>(kernel, p.vecs_per_lane, p.passes);
-    case DT_F16: return tc_sym<f16_t>(kernel, p.vecs_per_lane, p.passes);
-    default: return tc_sym<bf16_t>(kernel, p.vecs_per_lane, p.passes);
+    case DT_F32: return tc_sym<float>(kernel, p);
+    case DT_F16: return tc_sym<f16_t>(kernel, p);
+    default: return tc_sym<bf16_t>(kernel, p);
   }
 }
 

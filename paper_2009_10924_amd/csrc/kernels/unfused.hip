@@ -272,7 +272,7 @@ __global__ void __launch_bounds__(256) k_transpose_tile(const T* __restrict__ in
 // 8.5 us, 25.7 as 32x32 tiles of single elements; 4001 x 3333 float32 (107 MB) 26.3 against 41.1; extents of whole units
 // as before (4096 x 4096 bfloat16 13.8 us).
 // UNITS = 64, for matrices of at most 8 x 8 units: a tile per wavefront, four batch entries per workgroup.
-template <typename T, int UQ, int UNITS = 256>
+template <typename T, int UQ, bool STREAM, int UNITS = 256>
 __global__ void __launch_bounds__(256) k_transpose_units(const T* __restrict__ in, T* __restrict__ out, TransposeP p) {
   constexpr uint32_t VEC = 16 / sizeof(T), UX = UNITS / UQ, TQ = UQ * VEC, TX = UX * VEC;
   typedef typename AtAlignment<u32x4, (int)sizeof(T)>::type Unaligned;
@@ -287,8 +287,10 @@ __global__ void __launch_bounds__(256) k_transpose_units(const T* __restrict__ i
     const uint32_t cq = min(t.bq * TQ + uq * VEC, p.nq - VEC), cx = min(t.bx * TX + ux * VEC, p.nx - VEC);
     u32x4 row[VEC];
 #pragma unroll
-    for (uint32_t s = 0; s < VEC; ++s)
-      row[s] = __builtin_nontemporal_load(reinterpret_cast<const Unaligned*>(in + t.in_base + cq + (size_t)(cx + s) * p.in_row));
+    for (uint32_t s = 0; s < VEC; ++s) {
+      const Unaligned* const at = reinterpret_cast<const Unaligned*>(in + t.in_base + cq + (size_t)(cx + s) * p.in_row);
+      row[s] = STREAM ? __builtin_nontemporal_load(at) : *at;
+    }
     // transpose in registers: col[e] = elements e of rows 0..VEC-1
     u32x4 col[VEC];
     if constexpr (sizeof(T) == 4) {
@@ -342,6 +344,18 @@ __global__ void __launch_bounds__(256) k_copy(const u32x4* __restrict__ src, u32
 namespace fs {
 using namespace fsk;
 
+namespace {
+template <typename T, bool STREAM>
+const void* units_symbol(const TransposeP& p) {
+  if (p.tile_units == 64) return (const void*)k_transpose_units<T, 8, STREAM, 64>;
+  switch (p.tile_uq) {
+    case 8: return (const void*)k_transpose_units<T, 8, STREAM>;
+    case 32: return (const void*)k_transpose_units<T, 32, STREAM>;
+    default: return (const void*)k_transpose_units<T, 16, STREAM>;
+  }
+}
+}  // namespace
+
 const void* unfused_kernel_symbol(int32_t kernel, const KernelArgs& a) {
   switch (kernel) {
     case K_UNARY:
@@ -360,13 +374,8 @@ const void* unfused_kernel_symbol(int32_t kernel, const KernelArgs& a) {
     case K_TRANSPOSE_TILE:
       if (a.u.transpose.vec > 1) {
         const bool wide = a.u.transpose.elem_bytes == 4;
-        if (a.u.transpose.tile_units == 64)
-          return wide ? (const void*)k_transpose_units<uint32_t, 8, 64> : (const void*)k_transpose_units<uint16_t, 8, 64>;
-        switch (a.u.transpose.tile_uq) {
-          case 8: return wide ? (const void*)k_transpose_units<uint32_t, 8> : (const void*)k_transpose_units<uint16_t, 8>;
-          case 32: return wide ? (const void*)k_transpose_units<uint32_t, 32> : (const void*)k_transpose_units<uint16_t, 32>;
-          default: return wide ? (const void*)k_transpose_units<uint32_t, 16> : (const void*)k_transpose_units<uint16_t, 16>;
-        }
+        if (a.u.transpose.stream) return wide ? units_symbol<uint32_t, true>(a.u.transpose) : units_symbol<uint16_t, true>(a.u.transpose);
+        return wide ? units_symbol<uint32_t, false>(a.u.transpose) : units_symbol<uint16_t, false>(a.u.transpose);
       }
       return a.u.transpose.elem_bytes == 4 ? (const void*)k_transpose_tile<uint32_t> : (const void*)k_transpose_tile<uint16_t>;
     case K_COPY:
