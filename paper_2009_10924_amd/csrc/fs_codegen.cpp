@@ -100,9 +100,30 @@ int online_reduction_pairs(const RowProgP& p, std::vector<char>* online) {
 }
 
 namespace {
-// member = false: an extern "C" kernel `entry(const GenArgs a)`.  member = true: a device function
-// `entry(const GenArgs& a, uint32_t fs_block)` that a packed kernel calls for the member's range of workgroups.
+// member = false: an extern "C" kernel `entry(p0, p1, ..)` over the pointers of generated_ptr_slots().  member = true: a
+// device function `entry(const GenArgs& a, uint32_t fs_block)` that a packed kernel calls for the member's range of workgroups.
 std::string body_with_entry(const RowProgP& p, const char* entry, bool member = false);
+// `a.<field>[i]` of the pointer slot `slot` (kSlot*)
+std::string arg_field(int slot) {
+  if (slot == kSlotWs) return "a.ws";
+  const char* field = slot >= kSlotRout ? "rout" : slot >= kSlotOut ? "out" : slot >= kSlotRscal ? "rscal" : slot >= kSlotCol ? "col" : "full";
+  return fmt("a.%s[%d]", field, slot % 8);
+}
+// The head of a generated kernel.  Its parameters are the pointers that it uses and nothing else, one by one: the compiler
+// preloads the first seven of them into scalar registers (see gen_compile), so a wavefront issues its first loads without
+// waiting for its arguments, which no cache holds when a kernel starts.  Measured (us per call, a block of all 41 pointer slots
+// over five cache lines / this): softmax bf16 [1006,5902] 5.1 / 4.6, attention rows f16 [16,12,197,197] 7.1 / 6.9, RMS norm f32
+// [1832,990] 4.05 / 3.54, the seven dependent launches of a block's backward pass 51.7 / 51.1 at 201 MB and 26.2 / 22.3 at 1.6 MB.
+std::string kernel_head(const RowProgP& p, const char* entry, int threads) {
+  const std::vector<int> slots = generated_ptr_slots(p);
+  std::string params, fields;
+  for (size_t k = 0; k < slots.size(); ++k) {
+    params += fmt("%svoid* p%zu", k ? ", " : "", k);
+    fields += fmt("  %s = p%zu;\n", arg_field(slots[k]).c_str(), k);
+  }
+  return fmt("extern \"C\" __global__ void __launch_bounds__(%d) %s(%s) {\n  GenArgs a{};\n", threads, entry, params.c_str()) + fields +
+         "  const uint32_t fs_block = blockIdx.x;\n";
+}
 const char kEntryPlaceholder[] = "@ENTRY@";
 uint32_t fnv1a(const std::string& text) {
   uint32_t h = 2166136261u;
@@ -110,6 +131,19 @@ uint32_t fnv1a(const std::string& text) {
   return h;
 }
 }  // namespace
+
+std::vector<int> generated_ptr_slots(const RowProgP& p) {
+  std::vector<int> slots;
+  for (int i = 0; i < p.n_full; ++i) slots.push_back(kSlotFull + i);
+  for (int i = 0; i < p.n_col; ++i) slots.push_back(kSlotCol + i);
+  for (int i = 0; i < p.n_rscal; ++i) slots.push_back(kSlotRscal + i);
+  for (int i = 0; i < p.n_instr; ++i) {
+    if (p.instr[i].op == PO_STORE) slots.push_back(kSlotOut + p.instr[i].dst);
+    if (p.instr[i].op == PO_STORE_SCAL) slots.push_back(kSlotRout + p.instr[i].dst);
+  }
+  if (p.n_colsum > 0) slots.push_back(kSlotWs);
+  return slots;
+}
 
 // The kernel's name carries a hash of its own source (pattern, extents and launch shape), so that kernel traces
 // tell the generated kernels of a process apart.
@@ -250,8 +284,7 @@ std::string chunked_body(const RowProgP& p, const char* entry) {
   std::vector<char> online(n_red + 1, 0);
   online_reduction_pairs(p, &online);
   std::string s = "using namespace fsk;\n";
-  s += fmt("extern \"C\" __global__ void __launch_bounds__(%u) %s(const GenArgs a) {\n", L, entry);
-  s += "  const uint32_t fs_block = blockIdx.x;\n";
+  s += kernel_head(p, entry, (int)L);
   const char* past_caches = p.stream ? ", 1u, true" : "";
   s += fmt("  typedef GenRow<%uu, %uu, %d, %d, %uu, true, 1u, %uu%s> Row;       // a whole chunk\n", p.rows, chunk, p.vec, p.vecs_per_lane, L, p.cols, past_caches);
   s += fmt("  typedef GenRow<%uu, %uu, %d, %d, %uu, true, 1u, %uu%s> TailRow;   // the row's last chunk\n", p.rows, tail, p.vec, p.vecs_per_lane, L, p.cols, past_caches);
@@ -378,8 +411,7 @@ std::string body_with_entry(const RowProgP& p, const char* entry, bool member) {
     s += fmt("static __device__ __forceinline__ void %s(const GenArgs& a, const uint32_t fs_block) {\n", entry);
   } else {
     s += "using namespace fsk;\n";
-    s += fmt("extern \"C\" __global__ void __launch_bounds__(%d) %s(const GenArgs a) {\n", block ? p.lanes_per_row : 256, entry);
-    s += "  const uint32_t fs_block = blockIdx.x;\n";
+    s += kernel_head(p, entry, block ? p.lanes_per_row : 256);
   }
   const uint32_t R = p.rows_per_group > 1 ? (uint32_t)p.rows_per_group : 1u;
   const uint32_t CT = p.col_tiles > 1 ? (uint32_t)p.col_tiles : 1u;   // column tiles
@@ -524,13 +556,7 @@ std::string generate_pack_kernel(const std::vector<RowProgP>& members, const std
   for (size_t m = 0; m < members.size(); ++m) {
     const RowProgP& p = members[m];
     std::vector<int>& slots = (*ptr_slots)[m];
-    for (int i = 0; i < p.n_full; ++i) slots.push_back(kSlotFull + i);
-    for (int i = 0; i < p.n_col; ++i) slots.push_back(kSlotCol + i);
-    for (int i = 0; i < p.n_rscal; ++i) slots.push_back(kSlotRscal + i);
-    for (int i = 0; i < p.n_instr; ++i) {
-      if (p.instr[i].op == PO_STORE) slots.push_back(kSlotOut + p.instr[i].dst);
-      if (p.instr[i].op == PO_STORE_SCAL) slots.push_back(kSlotRout + p.instr[i].dst);
-    }
+    slots = generated_ptr_slots(p);   // no column sums, so no workspace
     n_ptrs += slots.size();
     body += body_with_entry(p, fmt("fs_member_%zu", m).c_str(), true);
   }
@@ -542,10 +568,7 @@ std::string generate_pack_kernel(const std::vector<RowProgP>& members, const std
   uint32_t first = 0;
   for (size_t m = 0; m < members.size(); ++m) {
     k += fmt("  if (b < %uu) {\n    GenArgs a{};\n", first + blocks[m]);
-    for (int slot : (*ptr_slots)[m]) {
-      const char* field = slot >= kSlotRout ? "rout" : slot >= kSlotOut ? "out" : slot >= kSlotRscal ? "rscal" : slot >= kSlotCol ? "col" : "full";
-      k += fmt("    a.%s[%d] = t.p[%zu];\n", field, slot % 8, at++);
-    }
+    for (int slot : (*ptr_slots)[m]) k += fmt("    %s = t.p[%zu];\n", arg_field(slot).c_str(), at++);
     k += fmt("    fs_member_%zu(a, b - %uu);\n    return;\n  }\n", m, first);
     first += blocks[m];
   }

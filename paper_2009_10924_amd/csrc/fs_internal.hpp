@@ -85,6 +85,7 @@ struct Launch {
   BufRef ptr[kMaxPtrs];          // which buffer each pointer slot takes
   LaunchShape shape;
   std::shared_ptr<GenKernel> gen;   // K_ROW_GENERATED: the compiled kernel, once the plan that chose it is complete
+  std::vector<int32_t> gen_slots;   // and the pointer slots it takes, in the order of its parameters
 };
 
 // Form in which a matched pattern can join a packed launch (one kernel over many
@@ -176,6 +177,8 @@ bool build_row_program(const fs_graph& g, std::vector<Candidate>* out);
 // launch shape; the body alone (without the embedded device headers) for listings.
 std::string generate_row_kernel(const RowProgP& p);
 std::string generate_row_kernel_body(const RowProgP& p);
+// The pointer slots (kSlot*) that the generated kernel of `p` takes, in the order of its parameters.
+std::vector<int> generated_ptr_slots(const RowProgP& p);
 std::string generated_kernel_entry(const RowProgP& p);   // fs_gen_row_<hash of the source>
 // Source (without the embedded device headers, see embedded_prelude) of one kernel that runs several row programs,
 // member m on workgroups [sum of blocks before m, + blocks[m]); ptr_slots[m]: the members' pointer slots in the

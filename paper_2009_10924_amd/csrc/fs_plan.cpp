@@ -164,6 +164,7 @@ fs_status complete_plan(fs_plan* p) {
       }
     }
     if (usable) {
+      gen->gen_slots = generated_ptr_slots(gen->args.u.prog);
       const int e = gen_preload(gen->gen.get());
       if (e != 0) return fail(FS_ERR_HIP, "fs_plan_create: loading the generated kernel failed: %s", hip_error_text(e));
       predict(&c);   // with the compiled kernel's own register count
@@ -241,7 +242,10 @@ fs_status fs::run_launches(const fs_plan* p, const void* const* inputs, void* co
     int err;
     if (l.kernel == K_ROW_GENERATED) {
       if (!l.gen) return fail(FS_ERR_INVALID_ARG, "fs_execute: the plan's generated kernel was never compiled");
-      err = gen_launch(l.gen.get(), a.p, sizeof(void*) * kGenArgPtrs, l.shape, hip_stream);
+      void* ptrs[kGenArgPtrs];
+      size_t n = 0;
+      for (int32_t slot : l.gen_slots) ptrs[n++] = address(l.ptr[slot]);
+      err = gen_launch(l.gen.get(), ptrs, sizeof(void*) * n, l.shape, hip_stream);
     } else {
       err = launch_kernel(l.kernel, a, l.shape, hip_stream);
     }

@@ -111,7 +111,7 @@ std::string cache_path(const std::string& source) {
   if (!dir || !dir[0]) return std::string();
   char name[64];
   // the compiler settings are part of the key (the source alone would survive a change of them)
-  snprintf(name, sizeof name, "/fs_gfx950_%016llx.co", (unsigned long long)fnv1a64("gfx950|O3|c++17|no-packed-fp32|" + source));
+  snprintf(name, sizeof name, "/fs_gfx950_%016llx.co", (unsigned long long)fnv1a64("gfx950|O3|c++17|no-packed-fp32|preload16|" + source));
   return std::string(dir) + name;
 }
 bool cache_read(const std::string& source, std::string* code) {
@@ -229,8 +229,10 @@ int gen_compile(const std::string& source, const char* entry, std::shared_ptr<Ge
     if (log) *log = r.error_string(rc);
     return (int)hipErrorUnknown;
   }
-  // same code generation settings as the library's own kernels; packed-fp32 VALU ops stay off
-  const char* opts[] = {"--offload-arch=gfx950", "-O3", "-std=c++17", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"};
+  // same code generation settings as the library's own kernels; packed-fp32 VALU ops stay off, leading kernel arguments are
+  // preloaded into scalar registers
+  const char* opts[] = {"--offload-arch=gfx950", "-O3", "-std=c++17", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+                        "-mllvm", "-amdgpu-kernarg-preload-count=16"};
   rc = r.compile(prog, (int)(sizeof opts / sizeof opts[0]), opts);
   if (log) {
     size_t n = 0;
