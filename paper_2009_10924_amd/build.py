@@ -27,9 +27,10 @@ EMBEDDED = [("kernels/device_utils.hpp", "kEmbeddedDeviceUtils"), ("kernels/gen_
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 COMMON = ["-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function"]
-# packed-fp32 VALU ops stay off (some of their forms misbehave on the test machines)
+# packed-fp32 VALU ops stay off (some of their forms misbehave on these parts); leading kernel arguments are preloaded into
+# scalar registers
 DEVICE = ["--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-          "-Wno-unused-command-line-argument"]
+          "-mllvm", "-amdgpu-kernarg-preload-count=16", "-Wno-unused-command-line-argument"]
 
 
 def _compile(src: str, verbose: bool) -> str:

@@ -477,8 +477,10 @@ std::string body_with_entry(const RowProgP& p, const char* entry, bool member) {
     for (int i = 0; i < p.n_colsum; ++i)
       s += fmt("  float cs%d[KV];\n#pragma unroll\n  for (int j = 0; j < KV; ++j) cs%d[j] = 0.0f;\n", i, i);
     // neighbouring workgroups take neighbouring column tiles of the same rows
-    if (CT > 1) s += fmt("  const uint32_t tile = blockIdx.x %% %uu, row_wg = blockIdx.x / %uu, n_row_wgs = gridDim.x / %uu;\n", CT, CT, CT);
-    else s += "  const uint32_t tile = 0, row_wg = blockIdx.x, n_row_wgs = gridDim.x;\n";
+    const uint32_t rows_per_wg = (block ? 1u : 256u / (uint32_t)p.lanes_per_row) * R;
+    if (CT > 1) s += fmt("  const uint32_t tile = blockIdx.x %% %uu, row_wg = blockIdx.x / %uu;\n", CT, CT);
+    else s += "  const uint32_t tile = 0, row_wg = blockIdx.x;\n";
+    s += fmt("  constexpr uint32_t n_row_wgs = %uu;\n", (p.rows + rows_per_wg - 1u) / rows_per_wg);   // the grid's (a constant: nothing to fetch)
     s += "  Row nrow(row_wg, tile);\n";
     s += col_loads("nrow");
     if (needs_lead) s += "  uint32_t nq1, nlead0, nlead1, nlead2;\n" + lead_of("nrow", "n", false);

@@ -193,7 +193,8 @@ template <> struct StoreN<bf16_t, 8> {
 // ---- division by a run-time constant (see fs::FastDiv) -------------------------------
 template <typename FD>
 __device__ __forceinline__ uint32_t fast_div(uint32_t n, const FD& f) {
-  return f.d == 1 ? n : (__umulhi(n, f.m) >> f.s);
+  // no branch (m = 0 where d = 1): at a branch the compiler waits for the constants, and for loads already on their way
+  return (__umulhi(n, f.m) >> f.s) + (f.d == 1 ? n : 0u);
 }
 
 // ---- math ---------------------------------------------------------------------

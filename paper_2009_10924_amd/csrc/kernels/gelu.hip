@@ -25,10 +25,10 @@ using namespace fs;
 // ---- bias + GELU only ------------------------------------------------------------
 template <typename T, bool STREAM>
 __global__ void __launch_bounds__(256) k_bias_gelu(const T* __restrict__ x, const T* __restrict__ bias,
-                                                   T* __restrict__ y, GeluP p) {
+                                                   T* __restrict__ y, uint32_t rows, uint32_t cols) {
   constexpr int VEC = Elem<T>::VEC;
-  const uint32_t vecs_per_row = p.cols / VEC;
-  const uint32_t n_vec = p.rows * vecs_per_row;
+  const uint32_t vecs_per_row = cols / VEC;
+  const uint32_t n_vec = rows * vecs_per_row;
   const uint32_t vi = blockIdx.x * 256u + threadIdx.x;
   if (vi >= n_vec) return;
   const uint32_t cv = vi % vecs_per_row;
@@ -73,17 +73,18 @@ __device__ __forceinline__ float gelu_and_grad(float z, float g, float& acc) {
 template <typename T, int WAVES, int UNROLL, bool FAST, bool STREAM>
 __global__ void __launch_bounds__(WAVES * 64) k_bias_gelu_dbias(const T* __restrict__ x, const T* __restrict__ bias,
                                                                 const T* __restrict__ grad, T* __restrict__ y,
-                                                                float* __restrict__ partials, GeluP p) {
+                                                                float* __restrict__ partials, uint32_t rows, uint32_t cols,
+                                                                uint32_t n_row_tiles) {
   constexpr int VEC = Elem<T>::VEC;
   constexpr int TILE_COLS = 64 * VEC, NT = WAVES * 64, TILE_ROWS = WAVES * UNROLL;
   __shared__ __align__(16) float red[WAVES][TILE_COLS];
-  const uint32_t n_col_tiles = (p.cols + TILE_COLS - 1) / TILE_COLS;
+  const uint32_t n_col_tiles = (cols + TILE_COLS - 1) / TILE_COLS;
   const uint32_t rb = blockIdx.x / n_col_tiles;
   const uint32_t ct = blockIdx.x - rb * n_col_tiles;
   const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
   const uint32_t col = FAST ? ct * TILE_COLS + lane * VEC
-                            : min(ct * TILE_COLS + lane * VEC, p.cols - VEC);   // clamped lanes of a ragged tile redo valid columns
-  const bool col_ok = FAST || ct * TILE_COLS + lane * VEC < p.cols;
+                            : min(ct * TILE_COLS + lane * VEC, cols - VEC);   // clamped lanes of a ragged tile redo valid columns
+  const bool col_ok = FAST || ct * TILE_COLS + lane * VEC < cols;
 
   float acc[VEC], b[VEC];
 #pragma unroll
@@ -97,7 +98,7 @@ __global__ void __launch_bounds__(WAVES * 64) k_bias_gelu_dbias(const T* __restr
 #pragma unroll
     for (int u = 0; u < UNROLL; ++u) {
       const uint32_t r = r0 + wave + u * WAVES;
-      const size_t off = (size_t)(FAST ? r : min(r, p.rows - 1)) * p.cols + col;
+      const size_t off = (size_t)(FAST ? r : min(r, rows - 1)) * cols + col;
       nx[u] = load_input<STREAM>(x + off);
       ng[u] = load_input<STREAM>(grad + off);
     }
@@ -116,23 +117,23 @@ __global__ void __launch_bounds__(WAVES * 64) k_bias_gelu_dbias(const T* __restr
         for (int e = 0; e < VEC; ++e) out[u][e] = gelu_and_grad(out[u][e] + b[e], gv[e], acc[e]);
       }
 #pragma unroll
-      for (int u = 0; u < UNROLL; ++u) store_vec_nt(y + (size_t)(r0 + wave + u * WAVES) * p.cols + col, out[u]);
+      for (int u = 0; u < UNROLL; ++u) store_vec_nt(y + (size_t)(r0 + wave + u * WAVES) * cols + col, out[u]);
     } else {
 #pragma unroll
       for (int u = 0; u < UNROLL; ++u) {
         const uint32_t r = r0 + wave + u * WAVES;
-        if (r < p.rows) {
+        if (r < rows) {
           float xv[VEC], gv[VEC];
           unpack(rx[u], xv, (const T*)nullptr);
           unpack(rg[u], gv, (const T*)nullptr);
 #pragma unroll
           for (int e = 0; e < VEC; ++e) xv[e] = gelu_and_grad(xv[e] + b[e], gv[e], acc[e]);
-          if (col_ok) store_vec_nt(y + (size_t)r * p.cols + col, xv);
+          if (col_ok) store_vec_nt(y + (size_t)r * cols + col, xv);
         }
       }
     }
   };
-  const uint32_t stride = p.n_row_tiles * TILE_ROWS;
+  const uint32_t stride = n_row_tiles * TILE_ROWS;
   uint32_t r0 = rb * TILE_ROWS;
   if constexpr (FAST) {
     // every workgroup makes the same number of rounds (rows / stride >= 1), none with a test around its loads or
@@ -147,19 +148,19 @@ __global__ void __launch_bounds__(WAVES * 64) k_bias_gelu_dbias(const T* __restr
       compute(at, rx, rg);
     };
     issue(r0);
-    if (r0 + stride < p.rows) {
+    if (r0 + stride < rows) {
       round(r0);
       r0 += stride;
-      for (; r0 + stride < p.rows; r0 += stride) round(r0);
+      for (; r0 + stride < rows; r0 += stride) round(r0);
     }
     compute(r0, nx, ng);
   } else {
-    if (r0 < p.rows) issue(r0);
-    for (; r0 < p.rows; r0 += stride) {
+    if (r0 < rows) issue(r0);
+    for (; r0 < rows; r0 += stride) {
       u32x4 rx[UNROLL], rg[UNROLL];
 #pragma unroll
       for (int u = 0; u < UNROLL; ++u) { rx[u] = nx[u]; rg[u] = ng[u]; }
-      if (r0 + stride < p.rows) issue(r0 + stride);
+      if (r0 + stride < rows) issue(r0 + stride);
       compute(r0, rx, rg);
     }
   }
@@ -174,7 +175,7 @@ __global__ void __launch_bounds__(WAVES * 64) k_bias_gelu_dbias(const T* __restr
 #pragma unroll
     for (int w = 1; w < WAVES; ++w) s += red[w][c];
     const uint32_t gc = ct * TILE_COLS + c;
-    if (gc < p.cols) partials[(size_t)rb * p.cols + gc] = s;
+    if (gc < cols) partials[(size_t)rb * cols + gc] = s;
   }
 }
 
@@ -246,10 +247,11 @@ __device__ __forceinline__ void fold_tile(const float* __restrict__ partials, fl
 
 template <int Q, int G>
 __global__ void __launch_bounds__(256) k_colfold(const float* __restrict__ partials, float* __restrict__ out0,
-                                                 float* __restrict__ out1, GeluP p) {
+                                                 float* __restrict__ out1, uint32_t n, uint32_t width, uint32_t stride,
+                                                 uint32_t split, uint32_t out_cols, int32_t out_dt) {
   __shared__ f32x4 sm[G * Q];
   // stride >= width: a fold may take a slice of wider partial rows
-  fold_tile<Q, G>(partials, out0, out1, p.n_row_tiles, p.fold_cols, p.cols, p.fold_split, p.fold_out_cols, blockIdx.x, sm, p.dt);
+  fold_tile<Q, G>(partials, out0, out1, n, width, stride, split, out_cols, blockIdx.x, sm, out_dt);
 }
 
 // Several independent folds in one launch: workgroups [first_block[i], first_block[i+1]) run fold i.  The table

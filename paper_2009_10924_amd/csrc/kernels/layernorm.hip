@@ -121,14 +121,29 @@ struct LnRow {
   }
 };
 
+#define LN_PARAMS(TI, TO)                                                                                                       \
+  const TI *__restrict__ x, const TI *__restrict__ res, const TI *__restrict__ bias, uint32_t rows, uint32_t word,              \
+      const TI *__restrict__ gamma, const TI *__restrict__ beta, TO *__restrict__ out, float eps, float inv_cols
+#define LN_ARGS x, res, bias, rows, word, gamma, beta, out, eps, inv_cols
+
+// What a kernel's arguments say (row_word; the launcher packs them).
+__device__ __forceinline__ LayerNormP layernorm_params(bool block, uint32_t rows, uint32_t word, float eps, float inv_cols) {
+  LayerNormP p{};
+  p.rows = rows;
+  p.cols = word & 0xFFFFFFu;
+  p.lanes_log2 = (int32_t)((word >> 24) & 7u);
+  p.lanes_per_row = block ? p.lanes_log2 * 64 : 1 << p.lanes_log2;
+  p.has_res = (int32_t)((word >> 27) & 1u), p.has_bias = (int32_t)((word >> 28) & 1u), p.has_affine = (int32_t)((word >> 29) & 1u);
+  p.eps = eps;
+  p.inv_cols = inv_cols;
+  return p;
+}
+
 // STATS: the pattern also hands out the per-row mean and reciprocal standard deviation.  A template flag, not a
 // run-time test of the pointers: the kernel without statistics must stay one basic block (see the file header).
 template <typename TI, typename TO, int K, bool FAST, bool STATS, bool STREAM>
-__global__ void __launch_bounds__(256) k_layernorm_wave(const TI* __restrict__ x, const TI* __restrict__ res,
-                                                        const TI* __restrict__ bias, const TI* __restrict__ gamma,
-                                                        const TI* __restrict__ beta, TO* __restrict__ out,
-                                                        float* __restrict__ mean_out, float* __restrict__ rstd_out,
-                                                        LayerNormP p) {
+__device__ __forceinline__ void layernorm_wave(LN_PARAMS(TI, TO), float* __restrict__ mean_out, float* __restrict__ rstd_out) {
+  const LayerNormP p = layernorm_params(false, rows, word, eps, inv_cols);
   const uint32_t L = p.lanes_per_row;
   const uint32_t group = threadIdx.x >> p.lanes_log2;
   const uint32_t lane = threadIdx.x & (L - 1);
@@ -147,34 +162,47 @@ __global__ void __launch_bounds__(256) k_layernorm_wave(const TI* __restrict__ x
     }
   }
 }
-
 template <typename TI, typename TO, int K, bool FAST, bool STREAM>
-__global__ void __launch_bounds__(256) k_layernorm_block(const TI* __restrict__ x, const TI* __restrict__ res,
-                                                         const TI* __restrict__ bias, const TI* __restrict__ gamma,
-                                                         const TI* __restrict__ beta, TO* __restrict__ out,
-                                                         float* __restrict__ mean_out, float* __restrict__ rstd_out,
-                                                         LayerNormP p) {
+__global__ void __launch_bounds__(256) k_layernorm_wave(LN_PARAMS(TI, TO)) {
+  layernorm_wave<TI, TO, K, FAST, false, STREAM>(LN_ARGS, nullptr, nullptr);
+}
+template <typename TI, typename TO, int K, bool FAST, bool STREAM>
+__global__ void __launch_bounds__(256) k_layernorm_wave_stats(LN_PARAMS(TI, TO), float* __restrict__ mean_out, float* __restrict__ rstd_out) {
+  layernorm_wave<TI, TO, K, FAST, true, STREAM>(LN_ARGS, mean_out, rstd_out);
+}
+
+template <typename TI, typename TO, int K, bool FAST, bool STATS, bool STREAM>
+__device__ __forceinline__ void layernorm_block(LN_PARAMS(TI, TO), float* __restrict__ mean_out, float* __restrict__ rstd_out) {
   __shared__ float slot_sum[2][4], slot_sq[2][4];
-  const uint32_t n_waves = blockDim.x >> 6;
+  const LayerNormP p = layernorm_params(true, rows, word, eps, inv_cols);
+  const uint32_t T = p.lanes_per_row, n_waves = T >> 6;
   const float inv_n = p.inv_cols;
   uint32_t it = 0;
   for (uint32_t row = blockIdx.x; row < p.rows; row += gridDim.x, ++it) {
     LnRow<TI, TO, K, FAST, STREAM> r;
     // two slot sets alternate between rows: a wave may start row i+1 while a slower
     // one still reads the slots of row i.
-    const float mean = block_allreduce<OpSum>(r.load(x, res, bias, gamma, beta, p, row, threadIdx.x, blockDim.x),
+    const float mean = block_allreduce<OpSum>(r.load(x, res, bias, gamma, beta, p, row, threadIdx.x, T),
                                               slot_sum[it & 1], n_waves) * inv_n;
-    const float var = block_allreduce<OpSum>(r.center(p, mean, threadIdx.x, blockDim.x),
+    const float var = block_allreduce<OpSum>(r.center(p, mean, threadIdx.x, T),
                                              slot_sq[it & 1], n_waves) * inv_n;
     const float rstd = fast_rsqrt(var + p.eps);
-    r.finish(out, p, row, true, threadIdx.x, blockDim.x, rstd);
-    if constexpr (!FAST) {   // patterns with statistics use the general form of this kernel
+    r.finish(out, p, row, true, threadIdx.x, T, rstd);
+    if constexpr (STATS) {
       if (threadIdx.x == 0) {
         if (mean_out) mean_out[row] = mean;
         if (rstd_out) rstd_out[row] = rstd;
       }
     }
   }
+}
+template <typename TI, typename TO, int K, bool FAST, bool STREAM>
+__global__ void __launch_bounds__(256) k_layernorm_block(LN_PARAMS(TI, TO)) {
+  layernorm_block<TI, TO, K, FAST, false, STREAM>(LN_ARGS, nullptr, nullptr);
+}
+template <typename TI, typename TO, int K, bool STREAM>   // patterns with statistics use the general form of this kernel
+__global__ void __launch_bounds__(256) k_layernorm_block_stats(LN_PARAMS(TI, TO), float* __restrict__ mean_out, float* __restrict__ rstd_out) {
+  layernorm_block<TI, TO, K, false, true, STREAM>(LN_ARGS, mean_out, rstd_out);
 }
 
 // ---- LayerNorm backward ------------------------------------------------------------------
@@ -196,8 +224,16 @@ __global__ void __launch_bounds__(256) k_layernorm_block(const TI* __restrict__ 
 template <typename T, int K, int R, int WAVES, bool FAST, bool STREAM>
 __global__ void __launch_bounds__(WAVES * 64) k_layernorm_bwd(const T* __restrict__ h, const T* __restrict__ dy,
                                                               const T* __restrict__ gamma, const float* __restrict__ mu,
-                                                              const float* __restrict__ rstd, T* __restrict__ dx,
-                                                              float* __restrict__ partials, LnBwdP p) {
+                                                              const float* __restrict__ rstd, uint32_t rows, uint32_t word,
+                                                              T* __restrict__ dx, float* __restrict__ partials) {
+  LnBwdP p{};
+  p.rows = rows;
+  p.cols = word & 0x1FFFu;
+  p.lanes_log2 = (int32_t)((word >> 13) & 7u);
+  p.lanes_per_row = 1 << p.lanes_log2;
+  const uint32_t n_wg = word >> 16;
+  // as the host would round it: for whole numbers below 2^24 the quotient in float and the one in double, rounded, agree
+  p.inv_cols = 1.0f / (float)p.cols;
   constexpr int VEC = Elem<T>::VEC;
   constexpr uint32_t NT = WAVES * 64;
   extern __shared__ __align__(16) float lds[];         // [groups][2][cols]
@@ -277,24 +313,24 @@ __global__ void __launch_bounds__(WAVES * 64) k_layernorm_bwd(const T* __restric
     }
   };
   if constexpr (FAST) {
-    // n_tiles / gridDim.x rounds for every workgroup; first and last stand outside the loop so that the loop is
+    // n_tiles / n_wg rounds for every workgroup; first and last stand outside the loop so that the loop is
     // entered with the same loads and stores in flight that its own rounds leave behind
     Raw next;
     uint32_t tile = blockIdx.x;
     auto round = [&](uint32_t at) {
       const Raw cur = next;
-      issue(at + gridDim.x, next);
+      issue(at + n_wg, next);
       compute(at, cur);
     };
     issue(tile, next);
-    if (tile + gridDim.x < n_tiles) {
+    if (tile + n_wg < n_tiles) {
       round(tile);
-      tile += gridDim.x;
-      for (; tile + gridDim.x < n_tiles; tile += gridDim.x) round(tile);
+      tile += n_wg;
+      for (; tile + n_wg < n_tiles; tile += n_wg) round(tile);
     }
     compute(tile, next);
   } else {
-    for (uint32_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
+    for (uint32_t tile = blockIdx.x; tile < n_tiles; tile += n_wg) {
       Raw w;
       issue(tile, w);
       compute(tile, w);
@@ -357,13 +393,13 @@ const void* ln_sym_s(int32_t kernel, int K, bool fast, bool stats) {
 #define FS_LN_CASE(KK)                                                                                     \
   case KK:                                                                                                 \
     if (kernel == K_LAYERNORM_WAVE) {                                                                      \
-      if (stats) return fast ? (const void*)k_layernorm_wave<TI, TO, KK, true, true, S>                       \
-                             : (const void*)k_layernorm_wave<TI, TO, KK, false, true, S>;                     \
-      return fast ? (const void*)k_layernorm_wave<TI, TO, KK, true, false, S>                                 \
-                  : (const void*)k_layernorm_wave<TI, TO, KK, false, false, S>;                               \
+      if (stats) return fast ? (const void*)k_layernorm_wave_stats<TI, TO, KK, true, S>                       \
+                             : (const void*)k_layernorm_wave_stats<TI, TO, KK, false, S>;                     \
+      return fast ? (const void*)k_layernorm_wave<TI, TO, KK, true, S>                                 \
+                  : (const void*)k_layernorm_wave<TI, TO, KK, false, S>;                               \
     }                                                                                                      \
-    return fast && !stats ? (const void*)k_layernorm_block<TI, TO, KK, true, S>                               \
-                          : (const void*)k_layernorm_block<TI, TO, KK, false, S>;
+    if (stats) return (const void*)k_layernorm_block_stats<TI, TO, KK, S>;                                    \
+    return fast ? (const void*)k_layernorm_block<TI, TO, KK, true, S> : (const void*)k_layernorm_block<TI, TO, KK, false, S>;
   switch (K) {
     FS_LN_CASE(1) FS_LN_CASE(2) FS_LN_CASE(3) FS_LN_CASE(4) FS_LN_CASE(6) FS_LN_CASE(8)
     default: return nullptr;

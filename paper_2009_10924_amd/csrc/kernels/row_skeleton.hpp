@@ -38,7 +38,7 @@ struct RowCtx {
       : p(params), slots(lds_slots) {
     block_mode = MODE == MODE_BLOCK || (MODE == MODE_RUNTIME && params.lanes_per_row > 64);
     if (block_mode) {
-      L = blockDim.x;
+      L = p.lanes_per_row;   // the whole workgroup
       lane = threadIdx.x;
       row = vblock;
     } else {
@@ -80,8 +80,8 @@ struct RowCtx {
   }
   template <typename OP>
   __device__ __forceinline__ float reduce(float s) {
-    if (MODE == MODE_BLOCK) return block_allreduce<OP>(s, slots + 4 * (next_slot++), (int)(blockDim.x >> 6));
-    if (MODE == MODE_RUNTIME && block_mode) return block_allreduce<OP>(s, slots + 4 * (next_slot++), (int)(blockDim.x >> 6));
+    if (MODE == MODE_BLOCK) return block_allreduce<OP>(s, slots + 4 * (next_slot++), (int)(L >> 6));
+    if (MODE == MODE_RUNTIME && block_mode) return block_allreduce<OP>(s, slots + 4 * (next_slot++), (int)(L >> 6));
     return group_allreduce<OP>(s, (int)L);
   }
   // sum over the row of f(k, e); padding slots must contribute 0 (inputs there are 0)

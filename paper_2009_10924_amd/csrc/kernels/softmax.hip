@@ -38,6 +38,7 @@ __device__ __forceinline__ void softmax_load(const T* __restrict__ x, const T* _
 #pragma unroll
   for (int k = 0; k < K; ++k) raw[k] = load_input<STREAM>(xr + vec_at(k) * VEC);
   if constexpr (HAS_MASK) {
+    __builtin_amdgcn_sched_barrier(0);   // the row's loads first: finding the mask's row takes longer
     const uint32_t r1 = fast_div(r, p.od[2]);
     const uint32_t c2 = r - r1 * p.od[2].d;
     const uint32_t c0 = fast_div(r1, p.od[1]);
@@ -115,10 +116,28 @@ __device__ __forceinline__ void softmax_store(T* __restrict__ out, const Softmax
   }
 }
 
+// What a kernel's arguments say (softmax_word; the launcher packs them).
+#define SOFTMAX_PARAMS uint32_t rows, uint32_t word, float scale, uint32_t d1, uint32_t m1, uint32_t d2, uint32_t m2, uint32_t ms0, uint32_t ms1, uint32_t ms2
+#define SOFTMAX_ARGS rows, word, scale, d1, m1, d2, m2, ms0, ms1, ms2
+__device__ __forceinline__ SoftmaxP softmax_params(bool block, SOFTMAX_PARAMS) {
+  SoftmaxP p{};
+  p.rows = rows;
+  p.cols = word & 0x3FFFFu;
+  p.lanes_log2 = (int32_t)((word >> 18) & 7u);
+  p.lanes_per_row = block ? p.lanes_log2 * 64 : 1 << p.lanes_log2;
+  p.mask_inner = (int32_t)((word >> 21) & 1u);
+  p.scale = scale;
+  p.od[1] = FastDiv{d1, m1, (word >> 22) & 31u};
+  p.od[2] = FastDiv{d2, m2, word >> 27};
+  p.ms[0] = ms0, p.ms[1] = ms1, p.ms[2] = ms2;
+  return p;
+}
+
 // ---- wave variant ------------------------------------------------------------------
 template <typename T, int K, bool HAS_MASK, bool FAST, bool STREAM>
 __global__ void __launch_bounds__(256) k_softmax_wave(const T* __restrict__ x, const T* __restrict__ mask,
-                                                      T* __restrict__ out, SoftmaxP p) {
+                                                      T* __restrict__ out, SOFTMAX_PARAMS) {
+  const SoftmaxP p = softmax_params(false, SOFTMAX_ARGS);
   constexpr int VEC = Elem<T>::VEC;
   const uint32_t L = p.lanes_per_row;            // power of two, <= 64
   const uint32_t group = threadIdx.x >> p.lanes_log2;
@@ -135,45 +154,50 @@ __global__ void __launch_bounds__(256) k_softmax_wave(const T* __restrict__ x, c
 // ---- block variant -----------------------------------------------------------------
 template <typename T, int K, bool HAS_MASK, bool FAST, bool STREAM>
 __global__ void __launch_bounds__(256) k_softmax_block(const T* __restrict__ x, const T* __restrict__ mask,
-                                                       T* __restrict__ out, SoftmaxP p) {
+                                                       T* __restrict__ out, SOFTMAX_PARAMS) {
+  const SoftmaxP p = softmax_params(true, SOFTMAX_ARGS);
   constexpr int VEC = Elem<T>::VEC;
   __shared__ float slot_max[4], slot_sum[4];
   const uint32_t row = blockIdx.x;
-  const uint32_t n_waves = blockDim.x >> 6;
+  const uint32_t n_waves = p.lanes_per_row >> 6;
   float v[K][VEC];
-  softmax_load<T, K, HAS_MASK, FAST, STREAM>(x, mask, p, row, threadIdx.x, blockDim.x, v);
+  softmax_load<T, K, HAS_MASK, FAST, STREAM>(x, mask, p, row, threadIdx.x, p.lanes_per_row, v);
   const float m = block_allreduce<OpMax>(local_max<K, VEC>(v), slot_max, n_waves);
   const float s = block_allreduce<OpSum>(exp_and_sum<K, VEC>(v, m), slot_sum, n_waves);
-  softmax_store<T, K, FAST>(out, p, row, true, threadIdx.x, blockDim.x, v, fast_rcp(s));
+  softmax_store<T, K, FAST>(out, p, row, true, threadIdx.x, p.lanes_per_row, v, fast_rcp(s));
 }
 
 // ---- generic variant ---------------------------------------------------------------
 template <typename T>
 __global__ void __launch_bounds__(256) k_softmax_generic(const T* __restrict__ x, const T* __restrict__ mask,
-                                                         T* __restrict__ out, SoftmaxP p) {
+                                                         T* __restrict__ out, SOFTMAX_PARAMS) {
+  // rows of any length: `rows` holds the columns, of which the word has none
+  const uint32_t cols = rows;
+  const SoftmaxP p = softmax_params(true, SOFTMAX_ARGS);
+  const bool has_mask = mask != nullptr;
   __shared__ float slot_max[4], slot_sum[4];
   const uint32_t row = blockIdx.x;
   uint32_t moff = 0;
-  if (p.has_mask) {
+  if (has_mask) {
     const uint32_t r1 = fast_div(row, p.od[2]);
     const uint32_t c0 = fast_div(r1, p.od[1]);
     moff = c0 * p.ms[0] + (r1 - c0 * p.od[1].d) * p.ms[1] + (row - r1 * p.od[2].d) * p.ms[2];
   }
-  const T* xr = x + (size_t)row * p.cols;
+  const T* xr = x + (size_t)row * cols;
   auto value = [&](uint32_t c) {
     float a = load1(xr + c) * p.scale;
-    if (p.has_mask) a += load1(mask + moff + (p.mask_inner ? c : 0u));
+    if (has_mask) a += load1(mask + moff + (p.mask_inner ? c : 0u));
     return a;
   };
   float m = -INFINITY;
-  for (uint32_t c = threadIdx.x; c < p.cols; c += 256u) m = fmaxf(m, value(c));
+  for (uint32_t c = threadIdx.x; c < cols; c += 256u) m = fmaxf(m, value(c));
   m = block_allreduce<OpMax>(m, slot_max, 4);
   float s = 0.0f;
-  for (uint32_t c = threadIdx.x; c < p.cols; c += 256u) s += fast_exp(value(c) - m);
+  for (uint32_t c = threadIdx.x; c < cols; c += 256u) s += fast_exp(value(c) - m);
   s = block_allreduce<OpSum>(s, slot_sum, 4);
   const float inv = fast_rcp(s);
-  T* orow = out + (size_t)row * p.cols;
-  for (uint32_t c = threadIdx.x; c < p.cols; c += 256u) store1(orow + c, fast_exp(value(c) - m) * inv);
+  T* orow = out + (size_t)row * cols;
+  for (uint32_t c = threadIdx.x; c < cols; c += 256u) store1(orow + c, fast_exp(value(c) - m) * inv);
 }
 
 }  // namespace fsk

@@ -38,11 +38,16 @@ struct TChainTile {
       const uint32_t idx = it * groups + group;
       ok[it] = idx < n_rows;
       const uint32_t cidx = min(idx, n_rows - 1);
-      sl[it] = fast_div(cidx, p.div_h);
-      h[it] = cidx - sl[it] * p.H;
-      const T* xrow = x + ((size_t)(b * p.S + s0 + sl[it]) * p.H + h[it]) * p.D;
+      const T* xrow = x + ((size_t)(b * p.S + s0) * p.H + cidx) * p.D;
 #pragma unroll
       for (int k = 0; k < K; ++k) raw[it][k] = load_input<STREAM>(xrow + min(lane + k * L, nvec - 1) * VEC);
+    }
+    __builtin_amdgcn_sched_barrier(0);   // the rows' loads first: finding their heads takes longer
+#pragma unroll
+    for (int it = 0; it < PASSES; ++it) {
+      const uint32_t cidx = min(it * groups + group, n_rows - 1);
+      sl[it] = fast_div(cidx, p.div_h);
+      h[it] = cidx - sl[it] * p.H;
       sc[it] = load1(scale + h[it]);
     }
 #pragma unroll
@@ -68,9 +73,26 @@ struct TChainTile {
   }
 };
 
+// What a kernel's arguments say (tchain_word; the launcher packs them).
+#define TCHAIN_PARAMS uint32_t word, uint32_t S, uint32_t H, uint32_t s_tile, uint32_t tiles_d, uint32_t tiles_m, uint32_t h_m, float eps
+#define TCHAIN_ARGS word, S, H, s_tile, tiles_d, tiles_m, h_m, eps
+__device__ __forceinline__ TChainP tchain_params(TCHAIN_PARAMS) {
+  TChainP p{};
+  p.S = S, p.H = H;
+  p.D = word & 0xFFFFu;
+  p.lanes_log2 = (int32_t)((word >> 16) & 7u);
+  p.lanes_per_row = 1 << p.lanes_log2;
+  p.s_tile = (int32_t)s_tile;
+  p.div_s_tiles = FastDiv{tiles_d, tiles_m, (word >> 19) & 31u};
+  p.div_h = FastDiv{H, h_m, (word >> 24) & 31u};
+  p.eps = eps;
+  return p;
+}
+
 template <typename T, int K, int PASSES, bool STREAM>
 __global__ void __launch_bounds__(256) k_tchain_wave(const T* __restrict__ x, const T* __restrict__ scale,
-                                                     T* __restrict__ out, TChainP p) {
+                                                     T* __restrict__ out, TCHAIN_PARAMS) {
+  const TChainP p = tchain_params(TCHAIN_ARGS);
   constexpr int VEC = Elem<T>::VEC;
   const uint32_t L = p.lanes_per_row;
   const uint32_t groups = 256u >> p.lanes_log2;
@@ -94,7 +116,8 @@ __global__ void __launch_bounds__(256) k_tchain_wave(const T* __restrict__ x, co
 
 template <typename T, int K, int PASSES, bool STREAM>
 __global__ void __launch_bounds__(256) k_tchain_lds(const T* __restrict__ x, const T* __restrict__ scale,
-                                                    T* __restrict__ out, TChainP p) {
+                                                    T* __restrict__ out, TCHAIN_PARAMS) {
+  const TChainP p = tchain_params(TCHAIN_ARGS);
   constexpr int VEC = Elem<T>::VEC;
   extern __shared__ float slab[];                          // [H][s_tile][pitch] float32, output order
   const uint32_t L = p.lanes_per_row;

@@ -200,18 +200,19 @@ __global__ void __launch_bounds__(256) k_reduce_mid(const void* in, void* out, R
 
 // ---- transpose, innermost axis kept: rows of contiguous elements are re-ordered ----
 template <typename VT>
-__global__ void __launch_bounds__(256) k_transpose_rows(const void* in, void* out, TransposeP p) {
+__global__ void __launch_bounds__(256) k_transpose_rows(const void* in, void* out, uint32_t n, uint32_t vec, uint32_t is0, uint32_t is1,
+                                                        uint32_t is2, uint32_t oe0, uint32_t oe1, uint32_t oe2) {
   const uint32_t vi = blockIdx.x * 256u + threadIdx.x;   // vector index in the output
-  const uint32_t e = vi * p.vec;
-  if (e >= p.n) return;
+  const uint32_t e = vi * vec;
+  if (e >= n) return;
   // Plain divisions, measured: multiply-high ones are slower here ([64,512,12,64] -> [64,12,512,64] float32 34.6 against
   // 35.5 us, the wavefronts then reach their loads closer together), four vectors per thread slower still (36.1).
   uint32_t rest = e;
-  const uint32_t c3 = rest % p.out_ext[2]; rest /= p.out_ext[2];
-  const uint32_t c2 = rest % p.out_ext[1]; rest /= p.out_ext[1];
-  const uint32_t c1 = rest % p.out_ext[0], c0 = rest / p.out_ext[0];
-  const uint32_t src = c0 * p.in_stride[0] + c1 * p.in_stride[1] + c2 * p.in_stride[2] + c3;
-  reinterpret_cast<VT*>(out)[vi] = reinterpret_cast<const VT*>(in)[src / p.vec];
+  const uint32_t c3 = rest % oe2; rest /= oe2;
+  const uint32_t c2 = rest % oe1; rest /= oe1;
+  const uint32_t c1 = rest % oe0, c0 = rest / oe0;
+  const uint32_t src = c0 * is0 + c1 * is1 + c2 * is2 + c3;
+  reinterpret_cast<VT*>(out)[vi] = reinterpret_cast<const VT*>(in)[src / vec];
 }
 
 // Tile `index` of a transpose, and where its batch entry starts in the input and in the output.
