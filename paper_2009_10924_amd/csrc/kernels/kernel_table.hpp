@@ -24,6 +24,11 @@ inline uint32_t tchain_word(uint32_t D, uint32_t lanes_log2, uint32_t s_tiles, u
 // columns (below 2^13), log2 of the lanes per row, workgroups in the grid (the grid's size from the hardware's own arguments
 // would put 256 bytes of them behind the kernel's)
 inline uint32_t lnbwd_word(uint32_t cols, uint32_t lanes_log2, uint32_t grid) { return cols | lanes_log2 << 13 | grid << 16; }
+// a tiled transpose: the shifts of three divisions, walk_q, every_other
+inline uint32_t transpose_word(const TransposeP& t) {
+  return t.div[0].s | t.div[1].s << 5 | t.div[2].s << 10 | (t.walk_q ? 1u << 15 : 0u) | (t.every_other ? 1u << 16 : 0u);
+}
+inline bool transpose_two_batch_axes(const TransposeP& t) { return t.in_batch[0] != 0 || t.out_batch[0] != 0; }
 
 const void* unfused_kernel_symbol(int32_t kernel, const KernelArgs& a);
 const void* softmax_kernel_symbol(int32_t kernel, const KernelArgs& a);

@@ -43,7 +43,16 @@ bool list_arguments(int32_t kernel, const KernelArgs& a, uint32_t grid, ArgList*
     case K_UNARY: case K_COPY: l->add(p[0], p[1], a.u.unary); return true;
     case K_BINARY: l->add(p[0], p[1], p[2], a.u.binary); return true;
     case K_REDUCE_ROW: case K_REDUCE_MID: l->add(p[0], p[1], a.u.reduce); return true;
-    case K_TRANSPOSE_TILE: l->add(p[0], p[1], a.u.transpose); return true;
+    case K_TRANSPOSE_TILE: {
+      const TransposeP& t = a.u.transpose;
+      if (t.vec == 1) {   // 32x32 single elements
+        l->add(p[0], p[1], t);
+        return true;
+      }
+      l->add(p[0], p[1], t.div[0].m, t.div[1].m, transpose_word(t), t.nq, t.nx, t.in_row, t.in_batch[1], t.n_tiles, t.out_row, t.out_batch[1]);
+      if (transpose_two_batch_axes(t)) l->add(t.div[2].d, t.div[2].m, t.in_batch[0], t.out_batch[0]);
+      return true;
+    }
     case K_TRANSPOSE_ROWS: {
       const TransposeP& t = a.u.transpose;
       l->add(p[0], p[1], t.n, t.vec, t.in_stride[0], t.in_stride[1], t.in_stride[2], t.out_ext[0], t.out_ext[1], t.out_ext[2]);

@@ -215,7 +215,9 @@ __global__ void __launch_bounds__(256) k_transpose_rows(const void* in, void* ou
   reinterpret_cast<VT*>(out)[vi] = reinterpret_cast<const VT*>(in)[src / vec];
 }
 
-// Tile `index` of a transpose, and where its batch entry starts in the input and in the output.
+// Tile `index` of a transpose, and where its batch entry starts in the input and in the output.  TWO: there are two axes
+// outside the tile (with one, it is the second of TransposeP's).
+template <bool TWO>
 struct TileAt {
   uint32_t bq, bx;
   size_t in_base, out_base;
@@ -228,11 +230,19 @@ struct TileAt {
     const uint32_t outer = rest - r * p.div[1].d;
     const uint32_t phase = r & p.every_other;
     r >>= p.every_other;
-    const uint32_t b0 = fast_div(r, p.div[2]), b1 = r - b0 * p.div[2].d;
+    uint32_t b0 = 0, b1 = r;
+    if constexpr (TWO) {
+      b0 = fast_div(r, p.div[2]);
+      b1 = r - b0 * p.div[2].d;
+    }
     bq = p.walk_q ? (inner << p.every_other) + phase : outer;
     bx = p.walk_q ? outer : inner;
-    in_base = (size_t)b0 * p.in_batch[0] + (size_t)b1 * p.in_batch[1];
-    out_base = (size_t)b0 * p.out_batch[0] + (size_t)b1 * p.out_batch[1];
+    in_base = (size_t)b1 * p.in_batch[1];
+    out_base = (size_t)b1 * p.out_batch[1];
+    if constexpr (TWO) {
+      in_base += (size_t)b0 * p.in_batch[0];
+      out_base += (size_t)b0 * p.out_batch[0];
+    }
   }
 };
 
@@ -242,7 +252,7 @@ struct TileAt {
 template <typename T>
 __global__ void __launch_bounds__(256) k_transpose_tile(const T* __restrict__ in, T* __restrict__ out, TransposeP p) {
   __shared__ T tile[32][33];
-  const TileAt t(p, blockIdx.x);
+  const TileAt<true> t(p, blockIdx.x);
   const uint32_t tx = threadIdx.x & 31u, ty = threadIdx.x >> 5;
   for (uint32_t j = ty; j < 32u; j += 8u) {
     const uint32_t cq = t.bq * 32u + tx, cx = t.bx * 32u + j;
@@ -273,8 +283,8 @@ __global__ void __launch_bounds__(256) k_transpose_tile(const T* __restrict__ in
 // 8.5 us, 25.7 as 32x32 tiles of single elements; 4001 x 3333 float32 (107 MB) 26.3 against 41.1; extents of whole units
 // as before (4096 x 4096 bfloat16 13.8 us).
 // UNITS = 64, for matrices of at most 8 x 8 units: a tile per wavefront, four batch entries per workgroup.
-template <typename T, int UQ, bool STREAM, int UNITS = 256>
-__global__ void __launch_bounds__(256) k_transpose_units(const T* __restrict__ in, T* __restrict__ out, TransposeP p) {
+template <typename T, int UQ, bool STREAM, int UNITS, bool TWO>
+__device__ __forceinline__ void transpose_units(const T* __restrict__ in, T* __restrict__ out, const TransposeP& p) {
   constexpr uint32_t VEC = 16 / sizeof(T), UX = UNITS / UQ, TQ = UQ * VEC, TX = UX * VEC;
   typedef typename AtAlignment<u32x4, (int)sizeof(T)>::type Unaligned;
   __shared__ u32x4 tiles[256 / UNITS][TQ * UX];
@@ -282,7 +292,7 @@ __global__ void __launch_bounds__(256) k_transpose_units(const T* __restrict__ i
   u32x4* const tile = tiles[part];
   const uint32_t index = blockIdx.x * (256u / UNITS) + part;
   const bool there = UNITS == 256 || index < p.n_tiles;
-  const TileAt t(p, there ? index : 0u);
+  const TileAt<TWO> t(p, there ? index : 0u);
   const uint32_t uq = tid % UQ, ux = tid / UQ;
   if (there && t.bq * TQ + uq * VEC < p.nq && t.bx * TX + ux * VEC < p.nx) {
     const uint32_t cq = min(t.bq * TQ + uq * VEC, p.nq - VEC), cx = min(t.bx * TX + ux * VEC, p.nx - VEC);
@@ -328,6 +338,41 @@ __global__ void __launch_bounds__(256) k_transpose_units(const T* __restrict__ i
   }
 }
 
+// What a kernel's arguments say (transpose_word; the launcher packs them).  The numbers of tiles follow from the extents.
+// Measured against a by-value block of 128 bytes (us, before / after): [64,197,768] -> [64,768,197] bf16 7.2 / 6.9, [8,64,792] ->
+// [8,792,64] bf16 4.1 / 3.6, [59,220,8,64] -> [59,8,64,220] f16 5.1 / 4.8.
+#define UNITS_PARAMS uint32_t m0, uint32_t m1, uint32_t word, uint32_t nq, uint32_t nx, uint32_t in_row, uint32_t in_batch, uint32_t n_tiles, \
+                     uint32_t out_row, uint32_t out_batch
+#define UNITS_ARGS m0, m1, word, nq, nx, in_row, in_batch, n_tiles, out_row, out_batch
+__device__ __forceinline__ TransposeP units_params(uint32_t TQ, uint32_t TX, UNITS_PARAMS) {
+  TransposeP p{};
+  p.walk_q = (word >> 15) & 1u;
+  p.every_other = (word >> 16) & 1u;
+  const uint32_t tq = (nq + TQ - 1u) / TQ, tx = (nx + TX - 1u) / TX;
+  p.div[0] = FastDiv{p.walk_q ? tq >> p.every_other : tx, m0, word & 31u};
+  p.div[1] = FastDiv{p.walk_q ? tx : tq, m1, (word >> 5) & 31u};
+  p.nq = nq, p.nx = nx, p.in_row = in_row, p.out_row = out_row;
+  p.in_batch[1] = in_batch, p.out_batch[1] = out_batch;
+  p.n_tiles = n_tiles;
+  return p;
+}
+template <typename T, int UQ, bool STREAM, int UNITS = 256>
+__global__ void __launch_bounds__(256) k_transpose_units(const T* __restrict__ in, T* __restrict__ out, UNITS_PARAMS) {
+  constexpr uint32_t VEC = 16 / sizeof(T);
+  const TransposeP p = units_params(UQ * VEC, UNITS / UQ * VEC, UNITS_ARGS);
+  transpose_units<T, UQ, STREAM, UNITS, false>(in, out, p);
+}
+// two axes outside the tile
+template <typename T, int UQ, bool STREAM, int UNITS = 256>
+__global__ void __launch_bounds__(256) k_transpose_units2(const T* __restrict__ in, T* __restrict__ out, UNITS_PARAMS, uint32_t d2, uint32_t m2,
+                                                          uint32_t in_batch0, uint32_t out_batch0) {
+  constexpr uint32_t VEC = 16 / sizeof(T);
+  TransposeP p = units_params(UQ * VEC, UNITS / UQ * VEC, UNITS_ARGS);
+  p.div[2] = FastDiv{d2, m2, (word >> 10) & 31u};
+  p.in_batch[0] = in_batch0, p.out_batch[0] = out_batch0;
+  transpose_units<T, UQ, STREAM, UNITS, true>(in, out, p);
+}
+
 // ---- streaming copy (the measured HBM ceiling) ------------------------------------
 __global__ void __launch_bounds__(256) k_copy(const u32x4* __restrict__ src, u32x4* __restrict__ dst, UnaryP p) {
   const uint32_t n_vec = p.n;   // 128-bit vectors
@@ -348,11 +393,12 @@ using namespace fsk;
 namespace {
 template <typename T, bool STREAM>
 const void* units_symbol(const TransposeP& p) {
-  if (p.tile_units == 64) return (const void*)k_transpose_units<T, 8, STREAM, 64>;
+  const bool two = transpose_two_batch_axes(p);
+  if (p.tile_units == 64) return two ? (const void*)k_transpose_units2<T, 8, STREAM, 64> : (const void*)k_transpose_units<T, 8, STREAM, 64>;
   switch (p.tile_uq) {
-    case 8: return (const void*)k_transpose_units<T, 8, STREAM>;
-    case 32: return (const void*)k_transpose_units<T, 32, STREAM>;
-    default: return (const void*)k_transpose_units<T, 16, STREAM>;
+    case 8: return two ? (const void*)k_transpose_units2<T, 8, STREAM> : (const void*)k_transpose_units<T, 8, STREAM>;
+    case 32: return two ? (const void*)k_transpose_units2<T, 32, STREAM> : (const void*)k_transpose_units<T, 32, STREAM>;
+    default: return two ? (const void*)k_transpose_units2<T, 16, STREAM> : (const void*)k_transpose_units<T, 16, STREAM>;
   }
 }
 }  // namespace
