@@ -345,7 +345,7 @@ typedef struct fs_program_info {
   int32_t n_packs;        /* packed launches among the steps                               */
   int32_t beam_plans;     /* candidate plans the final choice was made among               */
   int32_t n_joint_folds;  /* column-sum folds moved behind the last step and issued as one launch (per 8): sums over
-                             all rows that nothing in the graph reads need only be complete when the program ends */
+                             all rows that nothing in the graph reads need only be complete when the program ends (in the last step's own launch where its kernel can take them along) */
   int64_t workspace_bytes;   /* device scratch fs_program_execute needs                    */
   int64_t bytes_min;         /* graph inputs read once + graph outputs written once        */
   int64_t bytes_moved_model; /* bytes the plan's kernels move, tensors between patterns included */
@@ -395,7 +395,8 @@ fs_status fs_program_pattern(const fs_program *p, int32_t index, int32_t *ops, i
  * `out<k>` of the graph, or `ws+<offset>` in the program's workspace) and the plan's own
  * scratch (`scratch ws+<offset> <bytes>`); then one line per packed launch (`pack <j>
  * launches=<n> members=<steps>`) and per joint fold launch (`joint_fold <j> folds=<n>
- * of_steps=<steps whose column sums it finishes>`).  Errors: FS_ERR_INVALID_ARG.         */
+ * of_steps=<steps whose column sums it finishes>`, with `with_step=<i>` where the last step's
+ * kernel runs them too: one launch for both, counted here and not at the step).  Errors: FS_ERR_INVALID_ARG.         */
 int64_t fs_program_describe(const fs_program *p, char *text, size_t capacity);
 /* Enqueues the whole program on `hip_stream` and returns without waiting.  inputs /
  * outputs: DEVICE pointers in the graph's declaration order, 16-byte aligned.  `workspace`:

@@ -23,7 +23,8 @@ SOURCES = [
 ]
 
 # device headers the run-time compiler gets as text in front of a generated kernel: (file, name of the C string)
-EMBEDDED = [("kernels/device_utils.hpp", "kEmbeddedDeviceUtils"), ("kernels/gen_support.hpp", "kEmbeddedGenSupport")]
+EMBEDDED = [("kernels/device_utils.hpp", "kEmbeddedDeviceUtils"), ("kernels/gen_support.hpp", "kEmbeddedGenSupport"),
+            ("kernels/fold.hpp", "kEmbeddedFold")]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 COMMON = ["-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function"]

@@ -582,6 +582,38 @@ std::string generate_pack_kernel(const std::vector<RowProgP>& members, const std
   return out;
 }
 
+// The kernel of `p` that also runs folds of column sums: workgroups [0, sum of blocks) take the folds one after the other, the
+// others the rows.  Everything about a fold but its three pointers is a constant.
+std::string generate_kernel_with_folds(const RowProgP& p, const std::vector<Launch>& folds, std::string* entry) {
+  std::string body = body_with_entry(p, "fs_rows", true);
+  const std::vector<int> slots = generated_ptr_slots(p);
+  std::string params, fields, jobs;
+  size_t n = 0;
+  for (size_t k = 0; k < slots.size(); ++k, ++n) {
+    params += fmt("%svoid* p%zu", n ? ", " : "", n);
+    fields += fmt("    %s = p%zu;\n", arg_field(slots[k]).c_str(), n);
+  }
+  uint32_t first = 0;
+  for (const Launch& f : folds) {
+    const GeluP& q = f.args.u.gelu;
+    for (int i = 0; i < 3; ++i) params += fmt("%svoid* p%zu", n + i ? ", " : "", n + i);
+    jobs += fmt("  if (b < %uu) {\n    fold_tile<%s>(static_cast<const float*>(p%zu), static_cast<float*>(p%zu), static_cast<float*>(p%zu), %uu, %uu, %uu, %uu, "
+                "%uu, b - %uu, sm, %d);\n    return;\n  }\n",
+                first + f.shape.grid[0], q.fold_quads == 4 ? "4, 64" : "16, 16", n, n + 1, n + 2, q.n_row_tiles, q.fold_cols, q.cols, q.fold_split,
+                q.fold_out_cols, first, q.dt);
+    first += f.shape.grid[0];
+    n += 3;
+  }
+  std::string k = fmt("extern \"C\" __global__ void __launch_bounds__(256) %s(%s) {\n", kEntryPlaceholder, params.c_str());
+  k += "  __shared__ f32x4 sm[256];\n  const uint32_t b = blockIdx.x;\n";
+  k += fmt("  if (b >= %uu) {\n    GenArgs a{};\n", first) + fields + fmt("    fs_rows(a, b - %uu);\n    return;\n  }\n", first) + jobs + "}\n";
+  const std::string text = "using namespace fsk;\n" + body + k;
+  *entry = fmt("fs_gen_folds_%08x", fnv1a(text));
+  std::string out = kEmbeddedFold + text;
+  out.replace(out.find(kEntryPlaceholder), sizeof kEntryPlaceholder - 1, *entry);
+  return out;
+}
+
 std::string embedded_prelude() { return std::string(kEmbeddedDeviceUtils) + kEmbeddedGenSupport; }
 
 std::string generate_row_kernel(const RowProgP& p) {

@@ -60,7 +60,7 @@ int64_t fs_program_describe(const fs_program* p, char* text, size_t capacity) tr
     std::string ops;
     for (int o : st.ops) ops += (ops.empty() ? "" : ",") + std::to_string(o);
     snprintf(line, sizeof line, "step %zu ops=%s pattern=%s kernel=%s launches=%zu f_us=%.3f", i, ops.c_str(), pi.pattern, pi.kernel,
-             st.pack >= 0 ? (size_t)0 : launches_issued(st.plan, st.own_launches), st.f);
+             st.pack >= 0 || (int)i == p->carrier.step ? (size_t)0 : launches_issued(st.plan, st.own_launches), st.f);
     s += line;
     if (st.pack >= 0) s += " pack=" + std::to_string(st.pack);
     if (p->info.n_stages > 1) s += " stage=" + std::to_string(st.stage);
@@ -78,7 +78,9 @@ int64_t fs_program_describe(const fs_program* p, char* text, size_t capacity) tr
   for (size_t j = 0; j < p->joint_folds.size(); ++j) {
     std::string of;
     for (const fs_program::JointFold& f : p->joint_folds[j]) of += (of.empty() ? "" : ",") + std::to_string(f.step);
-    s += "joint_fold " + std::to_string(j) + " folds=" + std::to_string(p->joint_folds[j].size()) + " of_steps=" + of + "\n";
+    s += "joint_fold " + std::to_string(j) + " folds=" + std::to_string(p->joint_folds[j].size()) + " of_steps=" + of;
+    if (p->carrier.step >= 0) s += " with_step=" + std::to_string(p->carrier.step);   // one launch for both, counted here
+    s += "\n";
   }
   const size_t need = s.size() + 1;
   if (capacity > 0) {
@@ -117,11 +119,35 @@ static fs_status run_program(const fs_program* p, int32_t first_stage, int32_t l
     if (r.kind == BUF_OUTPUT) return outputs[r.slot];
     return ws + r.offset;
   };
+  // an operand of one of a step's launches
+  auto operand = [&](const fs_program::Step& s, const BufRef& r) -> void* {
+    switch (r.kind) {
+      case BUF_INPUT: return address(s.in[r.slot]);
+      case BUF_OUTPUT: return address(s.out[r.slot]);
+      case BUF_WORKSPACE: return ws + s.plan_ws_offset + r.offset;
+      default: return nullptr;
+    }
+  };
   std::vector<char> pack_done(p->packs.size(), 0);
   std::vector<const void*> in;
   std::vector<void*> out;
-  for (const fs_program::Step& s : p->steps) {
+  for (size_t si = 0; si < p->steps.size(); ++si) {
+    const fs_program::Step& s = p->steps[si];
     if (s.stage < first_stage || s.stage > last_stage) continue;
+    if ((int)si == p->carrier.step) {   // the program's last step, and the joint folds with it
+      const Launch& own = s.plan->candidates[s.plan->chosen].launches[0];
+      void* ptrs[kGenArgPtrs + 3 * kFoldManyMax];
+      size_t n = 0;
+      for (int32_t slot : own.gen_slots) ptrs[n++] = operand(s, own.ptr[slot]);
+      for (const fs_program::JointFold& f : p->joint_folds[0]) {
+        const fs_program::Step& of = p->steps[f.step];
+        const Launch& l = of.plan->candidates[of.plan->chosen].launches[f.launch];
+        for (int a = 0; a < 3; ++a) ptrs[n++] = operand(of, l.ptr[a]);
+      }
+      const int err = gen_launch(p->carrier.kernel.get(), ptrs, sizeof(void*) * n, p->carrier.shape, hip_stream);
+      if (err != 0) return fail(FS_ERR_HIP, "fs_program_execute: launching a step with the joint folds failed: %s", hip_error_text(err));
+      continue;
+    }
     if (s.pack >= 0) {
       if (pack_done[s.pack]) continue;
       pack_done[s.pack] = 1;
@@ -143,7 +169,7 @@ static fs_status run_program(const fs_program* p, int32_t first_stage, int32_t l
     const fs_status st = run_launches(s.plan, in.data(), out.data(), need > 0 ? ws + s.plan_ws_offset : nullptr, hip_stream, s.own_launches);
     if (st != FS_OK) return st;
   }
-  if (last_stage < p->info.n_stages - 1) return FS_OK;
+  if (last_stage < p->info.n_stages - 1 || p->carrier.step >= 0) return FS_OK;
   for (const std::vector<fs_program::JointFold>& joint : p->joint_folds) {
     FoldManyP t{};
     uint32_t blocks = 0;
@@ -152,11 +178,7 @@ static fs_status run_program(const fs_program* p, int32_t first_stage, int32_t l
       const fs_program::Step& s = p->steps[joint[k].step];
       const Launch& l = s.plan->candidates[s.plan->chosen].launches[joint[k].launch];
       void* ptr[3];
-      for (int a = 0; a < 3; ++a) {
-        const BufRef& r = l.ptr[a];
-        ptr[a] = r.kind == BUF_INPUT ? address(s.in[r.slot]) : r.kind == BUF_OUTPUT ? address(s.out[r.slot])
-                 : r.kind == BUF_WORKSPACE ? (void*)(ws + s.plan_ws_offset + r.offset) : nullptr;
-      }
+      for (int a = 0; a < 3; ++a) ptr[a] = operand(s, l.ptr[a]);
       const GeluP& f = l.args.u.gelu;
       t.partials[k] = static_cast<const float*>(ptr[0]);
       t.out0[k] = static_cast<float*>(ptr[1]);

@@ -32,6 +32,12 @@ struct fs_program {
   std::vector<Step> steps;              // dependence order
   std::vector<Pack> packs;
   std::vector<std::vector<JointFold>> joint_folds;   // one launch each, at most kFoldManyMax folds in it
+  // the last step's kernel carries the joint folds along (see carry_folds): they have no launch of their own
+  struct Carrier {
+    int step = -1;
+    std::shared_ptr<GenKernel> kernel;
+    LaunchShape shape;
+  } carrier;
   fs_program_info info{};
   int32_t n_inputs = 0, n_outputs = 0;
   ~fs_program() {
