@@ -64,8 +64,8 @@ __device__ __forceinline__ float gelu_and_grad(float z, float g, float& acc) {
 // rows w, w+WAVES, ... of a row tile, so every wave-wide access is one contiguous
 // 1 KB piece, and at any moment the resident workgroups sweep one band of rows
 // (DRAM pages stay open) while each keeps its column sums in registers.
-// FAST: the rows fill every workgroup's row tiles exactly and the columns fill the column
-// tiles, so the row loop has no test inside.  That matters beyond the saved compares: the
+// The row loop has no test inside (but for ragged float32 shapes; FAST: nothing is clamped either, the rows fill every workgroup's row tiles exactly and the
+// columns fill the column tiles).  That matters beyond the saved compares: the
 // memory counter of this part counts loads and stores alike, in issue order, and when a
 // store sits inside a branch the compiler can no longer tell how many stores follow the
 // loads it waits for, so it waits for everything -- every round of the loop then ends
@@ -85,7 +85,6 @@ __global__ void __launch_bounds__(WAVES * 64) k_bias_gelu_dbias(const T* __restr
   const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
   const uint32_t col = FAST ? ct * TILE_COLS + lane * VEC
                             : min(ct * TILE_COLS + lane * VEC, cols - VEC);   // clamped lanes of a ragged tile redo valid columns
-  const bool col_ok = FAST || ct * TILE_COLS + lane * VEC < cols;
 
   float acc[VEC], b[VEC];
 #pragma unroll
@@ -104,67 +103,62 @@ __global__ void __launch_bounds__(WAVES * 64) k_bias_gelu_dbias(const T* __restr
       ng[u] = load_input<STREAM>(grad + off);
     }
   };
+  // all rows of the tile first, then their stores in one burst (measured: 0.5 us of 50 against a store
+  // after every row; the memory system takes a run of writes better than writes sprinkled between reads)
   auto compute = [&](uint32_t r0, const u32x4 (&rx)[UNROLL], const u32x4 (&rg)[UNROLL]) {
-    if constexpr (FAST) {
-      // all rows of the tile first, then their stores in one burst (measured: 0.5 us of 50 against a store
-      // after every row; the memory system takes a run of writes better than writes sprinkled between reads)
-      float out[UNROLL][VEC];
+    float out[UNROLL][VEC];
 #pragma unroll
-      for (int u = 0; u < UNROLL; ++u) {
-        float gv[VEC];
-        unpack(rx[u], out[u], (const T*)nullptr);
+    for (int u = 0; u < UNROLL; ++u) {
+      float gv[VEC];
+      unpack(rx[u], out[u], (const T*)nullptr);
+      unpack(rg[u], gv, (const T*)nullptr);
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) out[u][e] = gelu_and_grad(out[u][e] + b[e], gv[e], acc[e]);
+    }
+    // (a clamped lane writes what the owner of its columns writes, to the same place)
+#pragma unroll
+    for (int u = 0; u < UNROLL; ++u) store_vec_nt(y + (size_t)(r0 + wave + u * WAVES) * cols + col, out[u]);
+  };
+  // the rows' last tile, where it is a partial one
+  auto compute_some = [&](uint32_t r0, const u32x4 (&rx)[UNROLL], const u32x4 (&rg)[UNROLL]) {
+#pragma unroll
+    for (int u = 0; u < UNROLL; ++u) {
+      const uint32_t r = r0 + wave + u * WAVES;
+      if (r < rows) {
+        float xv[VEC], gv[VEC];
+        unpack(rx[u], xv, (const T*)nullptr);
         unpack(rg[u], gv, (const T*)nullptr);
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) out[u][e] = gelu_and_grad(out[u][e] + b[e], gv[e], acc[e]);
-      }
-#pragma unroll
-      for (int u = 0; u < UNROLL; ++u) store_vec_nt(y + (size_t)(r0 + wave + u * WAVES) * cols + col, out[u]);
-    } else {
-#pragma unroll
-      for (int u = 0; u < UNROLL; ++u) {
-        const uint32_t r = r0 + wave + u * WAVES;
-        if (r < rows) {
-          float xv[VEC], gv[VEC];
-          unpack(rx[u], xv, (const T*)nullptr);
-          unpack(rg[u], gv, (const T*)nullptr);
-#pragma unroll
-          for (int e = 0; e < VEC; ++e) xv[e] = gelu_and_grad(xv[e] + b[e], gv[e], acc[e]);
-          if (col_ok) store_vec_nt(y + (size_t)r * cols + col, xv);
-        }
+        for (int e = 0; e < VEC; ++e) xv[e] = gelu_and_grad(xv[e] + b[e], gv[e], acc[e]);
+        store_vec_nt(y + (size_t)r * cols + col, xv);
       }
     }
   };
   const uint32_t stride = n_row_tiles * TILE_ROWS;
   uint32_t r0 = rb * TILE_ROWS;
-  if constexpr (FAST) {
-    // every workgroup makes the same number of rounds (rows / stride >= 1), none with a test around its loads or
-    // its stores.  First and last round stand outside the loop: the loop is then entered with the same sequence of
-    // loads and stores in flight that its own rounds leave behind, which is what lets the wait at its head be
-    // "all but the last stores" on both ways in.
-    auto round = [&](uint32_t at) {
-      u32x4 rx[UNROLL], rg[UNROLL];
+  // Only the rows' very last tile can be partial, and it is the last one of its workgroup: no other round has a test around its
+  // loads or its stores.  First and last round stand outside the loop: the loop is then entered with the same sequence of
+  // loads and stores in flight that its own rounds leave behind, which is what lets the wait at its head be
+  // "all but the last stores" on both ways in.  Measured, rounds with tests / without (us): bf16 [8191,3072] 28.4 / 27.8, f16
+  // [2001,4096] 11.1 / 10.5, bf16 [4097,768] 7.4 / 7.2, bf16 [30001,520] 24.9 / 24.1; f32 [12345,1544] 49.5 / 50.7, so ragged
+  // float32 shapes keep the tests (and gain by the rounds outside the loop: [4001,3072] 28.7 / 26.2, [20001,520] 26.7 / 25.1).
+  constexpr bool UNTESTED = FAST || VEC == 8;
+  auto round = [&](uint32_t at) {
+    u32x4 rx[UNROLL], rg[UNROLL];
 #pragma unroll
-      for (int u = 0; u < UNROLL; ++u) { rx[u] = nx[u]; rg[u] = ng[u]; }
-      issue(at + stride);
-      compute(at, rx, rg);
-    };
-    issue(r0);
-    if (r0 + stride < rows) {
-      round(r0);
-      r0 += stride;
-      for (; r0 + stride < rows; r0 += stride) round(r0);
-    }
-    compute(r0, nx, ng);
-  } else {
-    if (r0 < rows) issue(r0);
-    for (; r0 < rows; r0 += stride) {
-      u32x4 rx[UNROLL], rg[UNROLL];
-#pragma unroll
-      for (int u = 0; u < UNROLL; ++u) { rx[u] = nx[u]; rg[u] = ng[u]; }
-      if (r0 + stride < rows) issue(r0 + stride);
-      compute(r0, rx, rg);
-    }
+    for (int u = 0; u < UNROLL; ++u) { rx[u] = nx[u]; rg[u] = ng[u]; }
+    issue(at + stride);
+    if constexpr (UNTESTED) compute(at, rx, rg);
+    else compute_some(at, rx, rg);
+  };
+  issue(r0);   // (every workgroup has a row tile)
+  if (r0 + stride < rows) {
+    round(r0);
+    r0 += stride;
+    for (; r0 + stride < rows; r0 += stride) round(r0);
   }
+  if (FAST || (UNTESTED && r0 + TILE_ROWS <= rows)) compute(r0, nx, ng);
+  else compute_some(r0, nx, ng);
 
   // regional step: fold the waves of this workgroup through LDS, in wave order
 #pragma unroll
