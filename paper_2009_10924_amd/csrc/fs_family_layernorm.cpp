@@ -159,6 +159,11 @@ bool build_layernorm(const fs_graph& g, std::vector<Candidate>* out, PackForm* p
     kc.lane_utilisation = (double)nvec / ((double)L * K);
     kc.access_run_bytes = L * 16.0;
     kc.row_bytes = (double)p.cols * in_b;
+    // A lane's own chain between its loads and its stores: with nothing to fetch before the first load, shorter lanes measure
+    // faster (us, f32 unless said, many / few vectors per lane): [8192,1024] 13.8 / 12.9, [4096,768] 6.4 / 5.9, [16000,512] 13.4 /
+    // 12.6, [7000,704] 9.7 / 9.2, bf16 [8192,768] 6.7 / 6.3, [8192,768] from cold memory 13.1 / 11.9.
+    const DeviceModel& dm = device();
+    kc.serial_tail_s = 2.0 * K * VEC * kc.valu_per_elem * dm.cycles_valu / dm.clock_hz;
     char var[40];
     snprintf(var, sizeof var, "<%s,%s,K%d,L%u>", dtype_name(p.in_dt), dtype_name(p.out_dt), K, L);
     finish_candidate(&c, var, kc);
