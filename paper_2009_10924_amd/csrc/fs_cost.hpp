@@ -73,7 +73,7 @@ struct KernelCost {
   double stream_penalty = 0;            // the streaming rate falls to 1 / (1 + this) for reasons of the kernel's own
   double store_run_bytes = 0;           // contiguous run written by one store instruction group (0 = long)
   double preamble_instr = 40;           // VALU instructions a wave runs before it can issue its first load
-  double serial_tail_s = 0;             // work done by a single workgroup after the rest finished
+  double serial_tail_s = 0;             // what no other wavefront covers: a lane's own chain from its loads to its stores
   double partial_bytes = 0;             // column sums: partial sums written by the workgroups and read by the fold launch
   double flush_values = 0;              // column sums: values of every lane that leave it at the end of its rows
   double fold_rows = 0;                 // column sums: rows of partial sums

@@ -127,6 +127,17 @@ bool build_layernorm(const fs_graph& g, std::vector<Candidate>* out, PackForm* p
     if (t_rstd >= 0) l.ptr[7] = out_ref(g.tensors[t_rstd].output_slot);
   };
 
+  // A lane's own chain of instructions between its loads and its stores, issued once.  The first and the last wavefronts of a
+  // launch run it with the memory system idle, lanes of a workgroup-per-row shape longer: they wait for each other at two barriers.
+  // What is charged of it is fitted to 515 shapes of 64 to 65536 rows x 256 to 6144 columns in three dtypes, every candidate timed on
+  // three sets of buffers in turn and on inputs from cold memory.  The shape taken is behind the fastest one by (%, geometric means,
+  // in turn / cold): 2 chains for lane groups and 3 for workgroups 1.4 / 1.6; 2 and 2 1.5 / 1.6; 1.5 and 1.5 1.5 / 1.6; 1 and 1 1.6 / 1.8;
+  // no charge 2.4 / 2.8; 2 for lane groups alone 2.4 / 2.2, which moves shapes to a workgroup per row that are up to 27 % slower
+  // there (us, lane groups / workgroup: f32 [20044,712] 26.1 / 29.9, [2048,1000] 4.9 / 5.7, bf16 [512,2048] 3.5 / 4.3).
+  auto chain_s = [&](int K, const KernelCost& kc) {
+    const DeviceModel& dm = device();
+    return (double)K * VEC * kc.valu_per_elem * dm.cycles_valu / dm.clock_hz;
+  };
   for (int K : {1, 2, 3, 4, 6, 8}) {
     const uint32_t L = pow2_at_least((nvec + K - 1) / K);
     if (L > 64) continue;
@@ -159,11 +170,7 @@ bool build_layernorm(const fs_graph& g, std::vector<Candidate>* out, PackForm* p
     kc.lane_utilisation = (double)nvec / ((double)L * K);
     kc.access_run_bytes = L * 16.0;
     kc.row_bytes = (double)p.cols * in_b;
-    // A lane's own chain between its loads and its stores: with nothing to fetch before the first load, shorter lanes measure
-    // faster (us, f32 unless said, many / few vectors per lane): [8192,1024] 13.8 / 12.9, [4096,768] 6.4 / 5.9, [16000,512] 13.4 /
-    // 12.6, [7000,704] 9.7 / 9.2, bf16 [8192,768] 6.7 / 6.3, [8192,768] from cold memory 13.1 / 11.9.
-    const DeviceModel& dm = device();
-    kc.serial_tail_s = 2.0 * K * VEC * kc.valu_per_elem * dm.cycles_valu / dm.clock_hz;
+    kc.serial_tail_s = 2.0 * chain_s(K, kc);
     char var[40];
     snprintf(var, sizeof var, "<%s,%s,K%d,L%u>", dtype_name(p.in_dt), dtype_name(p.out_dt), K, L);
     finish_candidate(&c, var, kc);
@@ -216,6 +223,7 @@ bool build_layernorm(const fs_graph& g, std::vector<Candidate>* out, PackForm* p
     kc.lane_utilisation = (double)nvec / ((double)T * K);
     kc.access_run_bytes = 1024.0;
     kc.row_bytes = (double)p.cols * in_b;
+    kc.serial_tail_s = 3.0 * chain_s(K, kc);
     char var[40];
     snprintf(var, sizeof var, "<%s,%s,K%d,T%u>", dtype_name(p.in_dt), dtype_name(p.out_dt), K, T);
     finish_candidate(&c, var, kc);
