@@ -397,6 +397,24 @@ fs_status fs_plan_candidate(const fs_plan* p, int32_t index, fs_plan_info* out) 
   return fs::fail_caught("fs_plan_candidate");
 }
 
+namespace {
+// How a launch reads its row inputs (see streams_inputs): 1 past the caches, 0 through them, -1 where its kernel has one form.
+int streamed_loads(const Launch& l) {
+  const KernelArgs& a = l.args;
+  switch (l.kernel) {
+    case K_TRANSPOSE_TILE: return a.u.transpose.vec > 1 ? a.u.transpose.stream : -1;
+    case K_SOFTMAX_WAVE: case K_SOFTMAX_BLOCK: return a.u.softmax.vecs_per_lane > 0 ? a.u.softmax.stream : -1;
+    case K_LAYERNORM_WAVE: case K_LAYERNORM_BLOCK: return a.u.layernorm.stream;
+    case K_LAYERNORM_BWD: return a.u.lnbwd.stream;
+    case K_BIAS_GELU: case K_BIAS_GELU_DBIAS: return a.u.gelu.stream;
+    case K_TCHAIN_WAVE: case K_TCHAIN_LDS: return a.u.tchain.stream;
+    case K_ROW_WAVE: case K_ROW_BLOCK: return a.u.row.stream;
+    case K_ROW_GENERATED: return a.u.prog.stream;
+    default: return -1;
+  }
+}
+}  // namespace
+
 int64_t fs_plan_describe(const fs_plan* p, char* text, size_t capacity) try {
   clear_error();
   if (!p || (!text && capacity > 0)) return fail(FS_ERR_INVALID_ARG, "fs_plan_describe: null argument");
@@ -417,6 +435,7 @@ int64_t fs_plan_describe(const fs_plan* p, char* text, size_t capacity) try {
     snprintf(line, sizeof line, "launch %s grid=%u block=%u lds=%u\n", kernel_name(l.kernel), l.shape.grid[0] * l.shape.grid[1] * l.shape.grid[2],
              l.shape.block[0] * l.shape.block[1] * l.shape.block[2], l.shape.lds_bytes);
     s += line;
+    if (const int streamed = streamed_loads(l); streamed >= 0) s += streamed ? "  loads streamed\n" : "  loads cached\n";
     if (l.kernel == K_ROW_GENERATED) s += "  entry " + generated_kernel_entry(l.args.u.prog) + "\n";
     if (l.kernel != K_ROW_PROGRAM && l.kernel != K_ROW_GENERATED) {
       for (int k = 0; k < kMaxPtrs; ++k)

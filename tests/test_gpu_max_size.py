@@ -34,7 +34,7 @@ def _device_err(got, want_block, floor, torch):
     return worst
 
 
-def _run_rows(make, n, period, scheme="auto"):
+def _run_rows(make, n, period, scheme="auto", **opts):
     """`make(k)`: the descriptor with leading extent k.  Builds the inputs for extent n by repeating those of extent
     `period`, runs `scheme`, compares every output; returns ({output: error}, plan info)."""
     import torch
@@ -52,7 +52,7 @@ def _run_rows(make, n, period, scheme="auto"):
             d = d.repeat((-(-n // period),) + (1,) * (d.dim() - 1))[:n].contiguous()
         assert tuple(d.shape) == big_dims[t.name]
         dev_in.append(d)
-    plan = B.Plan(B.Graph.from_spec(big_spec), scheme)
+    plan = B.Plan(B.Graph.from_spec(big_spec), scheme, **opts)
     info = plan.info
     dev_out = B.alloc_outputs(big_spec)
     for t in dev_out:
