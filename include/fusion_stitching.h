@@ -393,7 +393,8 @@ fs_status fs_program_pattern(const fs_program *p, int32_t index, int32_t *ops, i
  * including the NUL, or a negative error.  One line per step in execution order (`step <i>
  * ops=<graph op indices> pattern=<name> kernel=<name> launches=<issued at the step> f_us=<score>`,
  * with `pack=<j>` for members of a packed launch, which is issued where its first member
- * stands, and `stage=<k>` when the program has more than one stage), indented under it where each of the plan's inputs and outputs lives (`in<k>` /
+ * stands, `stage=<k>` when the program has more than one stage, and `loads=cached|streamed` as in
+ * fs_plan_describe), indented under it where each of the plan's inputs and outputs lives (`in<k>` /
  * `out<k>` of the graph, or `ws+<offset>` in the program's workspace) and the plan's own
  * scratch (`scratch ws+<offset> <bytes>`); then one line per packed launch (`pack <j>
  * launches=<n> members=<steps>`) and per joint fold launch (`joint_fold <j> folds=<n>

@@ -126,7 +126,7 @@ struct Explorer {
     std::vector<char> inside(n, 0);
     for (int o : p) inside[o] = 1;
     if (fs_graph_create(&sub->g) != FS_OK) return FS_ERR_INVALID_ARG;
-    sub->g->cut_out = true;
+    sub->g->cut_out = (int)p.size() < n;   // (a program of one pattern hands nothing from step to step)
     std::map<int32_t, fs_tensor> local;   // big-graph tensor -> sub tensor
     for (int o : p) {
       const Op& op = g.ops[o];

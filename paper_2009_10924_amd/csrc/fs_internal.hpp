@@ -60,7 +60,7 @@ struct fs_graph {
   // (from, input): graph input `input` is computed outside the graph (say, by a matrix product) from the graph output
   // `from`.  Whatever reads `input` runs after `from` is complete, and never in the kernel that makes `from`.
   std::vector<std::pair<int32_t, int32_t>> external;
-  bool cut_out = false;   // a part of a larger graph, cut out by the explorer
+  bool cut_out = false;   // a part of a larger graph, cut out by the explorer (a pattern that is the whole graph is none)
   bool finalized = false;
   // per op: the ops whose results it waits for through external computations (sorted, distinct)
   std::vector<std::vector<int>> external_producers() const;
@@ -210,6 +210,8 @@ fs_status complete_plan(fs_plan* p);
 int64_t graph_bytes_min(const fs_graph& g);
 // Whether a kernel whose inputs are that large reads them past the caches (with the streaming hint) or through them.
 bool streams_inputs(const fs_graph& g);
+// How a launch reads its row inputs: 1 past the caches, 0 through them, -1 where its kernel has one form.
+int streamed_loads(const Launch& l);
 // Multiply-high constants for n / d with n < 2^31 (d == 0 in the result marks "no usable constants").
 FastDiv make_fastdiv(uint32_t d);
 void predict(Candidate* c);  // fills info.predicted_us, waves_per_simd, vgprs, lds

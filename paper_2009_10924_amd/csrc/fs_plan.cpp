@@ -356,6 +356,21 @@ fs_status fs::create_plan(const fs_graph* g, int32_t scheme, const fs_plan_opts*
   return FS_OK;
 }
 
+int fs::streamed_loads(const Launch& l) {
+  const KernelArgs& a = l.args;
+  switch (l.kernel) {
+    case K_TRANSPOSE_TILE: return a.u.transpose.vec > 1 ? a.u.transpose.stream : -1;
+    case K_SOFTMAX_WAVE: case K_SOFTMAX_BLOCK: return a.u.softmax.vecs_per_lane > 0 ? a.u.softmax.stream : -1;
+    case K_LAYERNORM_WAVE: case K_LAYERNORM_BLOCK: return a.u.layernorm.stream;
+    case K_LAYERNORM_BWD: return a.u.lnbwd.stream;
+    case K_BIAS_GELU: case K_BIAS_GELU_DBIAS: return a.u.gelu.stream;
+    case K_TCHAIN_WAVE: case K_TCHAIN_LDS: return a.u.tchain.stream;
+    case K_ROW_WAVE: case K_ROW_BLOCK: return a.u.row.stream;
+    case K_ROW_GENERATED: return a.u.prog.stream;
+    default: return -1;
+  }
+}
+
 extern "C" {
 
 fs_status fs_plan_create(const fs_graph* g, int32_t scheme, const fs_plan_opts* opts, fs_plan** out) try {
@@ -396,24 +411,6 @@ fs_status fs_plan_candidate(const fs_plan* p, int32_t index, fs_plan_info* out) 
 } catch (...) {
   return fs::fail_caught("fs_plan_candidate");
 }
-
-namespace {
-// How a launch reads its row inputs (see streams_inputs): 1 past the caches, 0 through them, -1 where its kernel has one form.
-int streamed_loads(const Launch& l) {
-  const KernelArgs& a = l.args;
-  switch (l.kernel) {
-    case K_TRANSPOSE_TILE: return a.u.transpose.vec > 1 ? a.u.transpose.stream : -1;
-    case K_SOFTMAX_WAVE: case K_SOFTMAX_BLOCK: return a.u.softmax.vecs_per_lane > 0 ? a.u.softmax.stream : -1;
-    case K_LAYERNORM_WAVE: case K_LAYERNORM_BLOCK: return a.u.layernorm.stream;
-    case K_LAYERNORM_BWD: return a.u.lnbwd.stream;
-    case K_BIAS_GELU: case K_BIAS_GELU_DBIAS: return a.u.gelu.stream;
-    case K_TCHAIN_WAVE: case K_TCHAIN_LDS: return a.u.tchain.stream;
-    case K_ROW_WAVE: case K_ROW_BLOCK: return a.u.row.stream;
-    case K_ROW_GENERATED: return a.u.prog.stream;
-    default: return -1;
-  }
-}
-}  // namespace
 
 int64_t fs_plan_describe(const fs_plan* p, char* text, size_t capacity) try {
   clear_error();

@@ -64,6 +64,8 @@ int64_t fs_program_describe(const fs_program* p, char* text, size_t capacity) tr
     s += line;
     if (st.pack >= 0) s += " pack=" + std::to_string(st.pack);
     if (p->info.n_stages > 1) s += " stage=" + std::to_string(st.stage);
+    if (const int streamed = streamed_loads(st.plan->candidates[st.plan->chosen].launches[0]); st.pack < 0 && streamed >= 0)
+      s += streamed ? " loads=streamed" : " loads=cached";
     s += "\n";
     for (size_t k = 0; k < st.in.size(); ++k) s += "  input " + std::to_string(k) + " " + where(st.in[k]) + "\n";
     for (size_t k = 0; k < st.out.size(); ++k) s += "  output " + std::to_string(k) + " " + where(st.out[k]) + "\n";

@@ -233,6 +233,14 @@ def test_backward_block_folds_its_column_sums_in_one_launch_at_the_end():
     assert len(sums) >= 2 and all(s["info"]["n_kernels"] >= 2 for s in sums)                  # a plan alone keeps its folds
 
 
+@pytest.mark.parametrize("make", [lambda: softmax_graph(640, 1024, "f16"), lambda: layernorm_backward_graph(512, 768, "f32")])
+def test_a_program_of_one_pattern_reads_its_inputs_like_the_plan(make):
+    graph = B.Graph.from_spec(make())
+    prog, plan = B.Program(graph), B.Plan(graph, "auto")
+    assert prog.info["n_patterns"] == 1 and "loads cached" in plan.describe()
+    assert " loads=cached" in prog.describe() and "loads=streamed" not in prog.describe()
+
+
 def test_program_listing_names_steps_buffers_and_joint_folds():
     from workloads import transformer_block_backward_graph
     spec = transformer_block_backward_graph(3, 40, 4, 32, 256, "bf16")
