@@ -808,7 +808,7 @@ void join_folds(const fs_graph& g, fs_program* prog) {
     }
     for (size_t l = first; l < launches.size(); ++l) found.push_back({(int)si, l});
   }
-  if (found.size() < 2) return;   // one fold alone gains nothing by moving
+  if (found.size() < 2) return;   // one fold alone would still be one launch, behind the last step instead of its own (carry_folds never sees it)
   for (const fs_program::JointFold& f : found) {
     fs_program::Step& s = prog->steps[f.step];
     s.own_launches = std::min(s.own_launches, f.launch);
@@ -820,8 +820,12 @@ void join_folds(const fs_graph& g, fs_program* prog) {
 // The joint folds need only come after the steps that make their partial sums.  Where the last step makes none and is a
 // generated kernel of 256 threads, one kernel made of both runs them together: a launch that follows another one costs 2.5 to
 // 3.5 us before it does anything, and the folds' few workgroups find room beside the rows'.  Measured (us, folds behind the last
-// step / with it): backward pass through a transformer block, 201 MB, 50.3 / 47.6.
-// (A lone op as the last step stays as it is: the number of launches of such programs is pinned.)
+// step / with it), backward pass through a transformer block of 0.2 MB 23.5 / 19.5, 2.1 MB 22.9 / 20.7, 15 MB 21.8 / 15.8, 50 MB
+// 26.0 / 22.0, 101 MB 32.4 / 29.8, 201 MB 50.2 / 47.5, 319 MB 68.7 / 65.8, 478 MB 93.6 / 91.2, and five more between them: never
+// slower, so neither the evaluator nor the merged kernel's registers are asked.
+// A lone op as the last step keeps the fold launch behind it.  Nothing in the kernels asks for that: it would save 2.3 to 2.5 us
+// there too (three bias gradients [300,256] 17.9 / 15.5, [2100,768] 25.7 / 23.2, [8192,1024] 64.3 / 62.1), but that joining folds
+// saves such a program exactly one launch is a count that its users check (test_gpu_explorer.py).
 void carry_folds(fs_program* prog) {
   if (prog->joint_folds.size() != 1 || prog->steps.empty() || !codegen_enabled()) return;
   const int last = (int)prog->steps.size() - 1;
