@@ -8,6 +8,7 @@
 #include <string>
 
 #include "fs_internal.hpp"
+#include "kernels/kernel_arguments.hpp"
 
 namespace fs {
 
@@ -301,10 +302,18 @@ fs_status fs::create_plan(const fs_graph* g, int32_t scheme, const fs_plan_opts*
                 "fs_plan_create: pattern '%s' recognised, but its shapes / dtypes fit no stitched kernel", pattern.c_str());
   }
 
-  // keep the candidates of the requested scheme; AUTO keeps all of them
+  // keep the candidates of the requested scheme (AUTO keeps all of them) that their kernels' argument words can hold: every
+  // shape the families offer, so that what cannot be launched is not planned should one come to offer more
+  auto launchable = [](const Candidate& c) {
+    for (const Launch& l : c.launches) {
+      ArgList list;
+      if (l.kernel != K_ROW_PROGRAM && l.kernel != K_ROW_GENERATED && !list_arguments(l.kernel, l.args, l.shape.grid[0], &list)) return false;
+    }
+    return true;
+  };
   std::vector<Candidate> kept;
   for (const Candidate& c : all)
-    if (scheme == FS_SCHEME_AUTO || scheme == FS_SCHEME_UNFUSED || c.info.scheme == scheme) kept.push_back(c);
+    if ((scheme == FS_SCHEME_AUTO || scheme == FS_SCHEME_UNFUSED || c.info.scheme == scheme) && launchable(c)) kept.push_back(c);
   if (kept.empty())
     return fail(FS_ERR_LOCALITY,
                 "fs_plan_create: pattern '%s' has no %s schedule that keeps its reduction rows inside the reuse scope",

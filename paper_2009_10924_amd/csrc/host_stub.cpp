@@ -8,6 +8,7 @@
 #include <string>
 
 #include "fs_internal.hpp"
+#include "kernels/kernel_arguments.hpp"
 
 namespace fs {
 
@@ -26,12 +27,131 @@ int check_shape(const LaunchShape& s) {
   if (s.lds_bytes > 160u * 1024u) return 1;
   return 0;
 }
+template <typename T>
+T argument(const ArgList& l, size_t k) {
+  T v;
+  memcpy(&v, l.address[k], sizeof v);
+  return v;
+}
+bool same(const FastDiv& a, const FastDiv& b) { return a.d == b.d && a.m == b.m && a.s == b.s; }
+
+// The arguments of a launch, taken apart with the kernel's own functions, are what its parameter block says.
+bool arguments_round_trip(int32_t kernel, const KernelArgs& a, uint32_t grid) {
+  ArgList l;
+  if (!list_arguments(kernel, a, grid, &l)) return false;
+  auto u = [&](size_t k) { return argument<uint32_t>(l, k); };
+  auto f = [&](size_t k) { return argument<float>(l, k); };
+  switch (kernel) {
+    case K_SOFTMAX_WAVE: case K_SOFTMAX_BLOCK: {
+      const SoftmaxP& s = a.u.softmax;
+      const bool block = kernel == K_SOFTMAX_BLOCK;
+      const SoftmaxP q = softmax_params(block, u(3), u(4), f(5), u(6), u(7), u(8), u(9), u(10), u(11), u(12));
+      if (s.vecs_per_lane == 0 ? u(3) != s.cols : (q.rows != s.rows || q.cols != s.cols || q.lanes_per_row != s.lanes_per_row)) return false;
+      if (!block && q.lanes_log2 != s.lanes_log2) return false;
+      return q.mask_inner == (s.mask_inner != 0) && q.scale == s.scale && same(q.od[1], s.od[1]) && same(q.od[2], s.od[2]) &&
+             memcmp(q.ms, s.ms, sizeof q.ms) == 0 && (argument<void*>(l, 1) != nullptr) == (s.has_mask && a.p[1]);
+    }
+    case K_LAYERNORM_WAVE: case K_LAYERNORM_BLOCK: {
+      const LayerNormP& n = a.u.layernorm;
+      const LayerNormP q = layernorm_params(kernel == K_LAYERNORM_BLOCK, u(3), u(4), f(8), f(9));
+      return q.rows == n.rows && q.cols == n.cols && q.lanes_per_row == n.lanes_per_row && !q.has_res == !n.has_res && !q.has_bias == !n.has_bias &&
+             !q.has_affine == !n.has_affine && q.eps == n.eps && q.inv_cols == n.inv_cols && l.n == (n.stats ? 12u : 10u);
+    }
+    case K_LAYERNORM_BWD: {
+      const LnBwdP& n = a.u.lnbwd;
+      const LnBwdP q = lnbwd_params(u(5), u(6));
+      return q.rows == n.rows && q.cols == n.cols && q.lanes_per_row == n.lanes_per_row && q.lanes_log2 == n.lanes_log2 && lnbwd_grid(u(6)) == grid &&
+             q.inv_cols == (float)(1.0 / (double)n.cols);
+    }
+    case K_TCHAIN_WAVE: case K_TCHAIN_LDS: {
+      const TChainP& t = a.u.tchain;
+      const TChainP q = tchain_params(u(3), u(4), u(5), u(6), u(7), u(8), u(9), f(10));
+      return q.D == t.D && q.S == t.S && q.H == t.H && q.s_tile == t.s_tile && q.lanes_log2 == t.lanes_log2 && q.lanes_per_row == t.lanes_per_row &&
+             same(q.div_s_tiles, t.div_s_tiles) && same(q.div_h, t.div_h) && q.eps == t.eps;
+    }
+    case K_ROW_WAVE: case K_ROW_BLOCK: {
+      const RowP& r = a.u.row;
+      const RowP q = row_params(kernel == K_ROW_BLOCK, u(4), u(5), f(7), f(8));
+      return q.rows == r.rows && q.cols == r.cols && q.lanes_per_row == r.lanes_per_row && q.f[0] == r.f[0] && q.f[1] == r.f[1];
+    }
+    case K_TRANSPOSE_TILE: {
+      const TransposeP& t = a.u.transpose;
+      if (t.vec == 1) return true;   // the block as it is
+      const uint32_t uq = t.tile_units == 64 ? 8u : t.tile_uq, vec = (uint32_t)t.vec;
+      TransposeP q = units_params(uq * vec, t.tile_units / uq * vec, u(2), u(3), u(4), u(5), u(6), u(7), u(8), u(9), u(10), u(11));
+      if (transpose_two_batch_axes(t)) {
+        units_second_axis(&q, u(4), u(12), u(13), u(14), u(15));
+        if (!same(q.div[2], t.div[2])) return false;
+      }
+      return same(q.div[0], t.div[0]) && same(q.div[1], t.div[1]) && q.nq == t.nq && q.nx == t.nx && q.in_row == t.in_row && q.out_row == t.out_row &&
+             q.in_batch[0] == t.in_batch[0] && q.in_batch[1] == t.in_batch[1] && q.out_batch[0] == t.out_batch[0] &&
+             q.out_batch[1] == t.out_batch[1] && !q.walk_q == !t.walk_q && q.every_other == t.every_other && q.n_tiles == t.n_tiles;
+    }
+    default: return true;
+  }
+}
+
+// Every field of the words at its limits comes back, and one beyond is refused: number of checks that failed.
+int check_words() {
+  int bad = 0;
+  const FastDiv divs[] = {{1, 0, 0}, {3, 0xAAAAAAABu, 1}, {0x7fffffffu, 0xffffffffu, 30}};
+  auto expect = [&](int32_t kernel, const KernelArgs& a, uint32_t grid, bool fits) {
+    ArgList l;
+    bad += fits ? !arguments_round_trip(kernel, a, grid) : list_arguments(kernel, a, grid, &l);
+  };
+  for (int block = 0; block < 2; ++block)
+    for (int lanes = 0; lanes <= (block ? 7 : 6); ++lanes)
+      for (const FastDiv& d : divs)
+        for (uint32_t cols : {1u, 197u, (1u << 18) - 1u, 1u << 18, (1u << 24) - 1u, 1u << 24}) {
+          const int32_t per_row = block ? 64 * lanes : 1 << lanes;
+          KernelArgs a{};
+          for (int mask = 0; mask < 4; ++mask) {
+            a = KernelArgs{};
+            a.p[1] = &a;
+            SoftmaxP& s = a.u.softmax;
+            s.has_mask = mask & 1, s.mask_inner = mask >> 1, s.rows = 0x7fffffffu, s.cols = cols, s.lanes_per_row = per_row, s.lanes_log2 = lanes;
+            s.vecs_per_lane = 1, s.scale = 0.125f, s.od[1] = d, s.od[2] = divs[2], s.ms[0] = 0xffffffffu, s.ms[2] = 1;
+            expect(block ? K_SOFTMAX_BLOCK : K_SOFTMAX_WAVE, a, 1, cols < (1u << 18));
+          }
+          for (int flags = 0; flags < 16; ++flags) {
+            a = KernelArgs{};
+            LayerNormP& n = a.u.layernorm;
+            n.has_res = flags & 1, n.has_bias = (flags >> 1) & 1, n.has_affine = (flags >> 2) & 1, n.stats = flags >> 3, n.rows = 0x7fffffffu;
+            n.cols = cols, n.eps = 1e-5f, n.inv_cols = 1.0f / (float)cols, n.lanes_per_row = per_row, n.lanes_log2 = lanes;
+            expect(block ? K_LAYERNORM_BLOCK : K_LAYERNORM_WAVE, a, 1, cols < (1u << 24));
+          }
+          a = KernelArgs{};
+          RowP& r = a.u.row;
+          r.rows = 0x7fffffffu, r.cols = cols, r.lanes_per_row = per_row, r.lanes_log2 = lanes, r.f[0] = 1e-6f, r.f[1] = 0.5f;
+          expect(block ? K_ROW_BLOCK : K_ROW_WAVE, a, 1, cols < (1u << 24));
+          if (block) continue;
+          for (uint32_t grid : {1u, 65535u, 65536u})
+            for (uint32_t c : {1u, 8191u, 8192u}) {
+              a = KernelArgs{};
+              LnBwdP& b = a.u.lnbwd;
+              b.rows = 0x7fffffffu, b.cols = c, b.lanes_per_row = per_row, b.lanes_log2 = lanes;
+              expect(K_LAYERNORM_BWD, a, grid, grid < 65536u && c < 8192u);
+            }
+          for (uint32_t dim : {1u, 65535u, 65536u}) {
+            a = KernelArgs{};
+            TChainP& t = a.u.tchain;
+            t.D = dim, t.S = 0x7fffffffu, t.H = d.d, t.s_tile = 16, t.lanes_per_row = per_row, t.lanes_log2 = lanes, t.div_s_tiles = divs[2], t.div_h = d;
+            t.eps = 1e-6f;
+            expect(K_TCHAIN_WAVE, a, 1, dim < 65536u);
+          }
+        }
+  KernelArgs a{};   // more lanes than a code can say
+  a.u.softmax.vecs_per_lane = 1, a.u.softmax.cols = 64, a.u.softmax.lanes_per_row = 512;
+  expect(K_SOFTMAX_BLOCK, a, 1, false);
+  return bad;
+}
 }  // namespace
 
 int launch_kernel(int32_t kernel, const KernelArgs& args, const LaunchShape& shape, void*) {
   if (kernel < 0 || kernel >= K_COUNT || kernel == K_ROW_GENERATED) return 1;
   if (check_shape(shape)) return 1;
   if (!args.p[0] && kernel != K_ROW_PROGRAM) return 1;   // every compiled-in kernel reads its first pointer
+  if (kernel != K_ROW_PROGRAM && !arguments_round_trip(kernel, args, shape.grid[0])) return 1;
   ++g_launches;
   return 0;
 }
@@ -91,3 +211,4 @@ extern "C" fs_status fs_stream_probe(void*, const void*, size_t, size_t, int32_t
   return fs::fail(FS_ERR_HIP, "fs_stream_probe: not part of the host stub");
 }
 extern "C" long fs_stub_launch_count(void) { return fs::g_launches; }
+extern "C" int fs_stub_check_argument_words(void) { return fs::check_words(); }

@@ -126,19 +126,6 @@ struct LnRow {
       const TI *__restrict__ gamma, const TI *__restrict__ beta, TO *__restrict__ out, float eps, float inv_cols
 #define LN_ARGS x, res, bias, rows, word, gamma, beta, out, eps, inv_cols
 
-// What a kernel's arguments say (row_word; the launcher packs them).
-__device__ __forceinline__ LayerNormP layernorm_params(bool block, uint32_t rows, uint32_t word, float eps, float inv_cols) {
-  LayerNormP p{};
-  p.rows = rows;
-  p.cols = word & 0xFFFFFFu;
-  p.lanes_log2 = (int32_t)((word >> 24) & 7u);
-  p.lanes_per_row = block ? p.lanes_log2 * 64 : 1 << p.lanes_log2;
-  p.has_res = (int32_t)((word >> 27) & 1u), p.has_bias = (int32_t)((word >> 28) & 1u), p.has_affine = (int32_t)((word >> 29) & 1u);
-  p.eps = eps;
-  p.inv_cols = inv_cols;
-  return p;
-}
-
 // STATS: the pattern also hands out the per-row mean and reciprocal standard deviation.  A template flag, not a
 // run-time test of the pointers: the kernel without statistics must stay one basic block (see the file header).
 template <typename TI, typename TO, int K, bool FAST, bool STATS, bool STREAM>
@@ -226,14 +213,8 @@ __global__ void __launch_bounds__(WAVES * 64) k_layernorm_bwd(const T* __restric
                                                               const T* __restrict__ gamma, const float* __restrict__ mu,
                                                               const float* __restrict__ rstd, uint32_t rows, uint32_t word,
                                                               T* __restrict__ dx, float* __restrict__ partials) {
-  LnBwdP p{};
-  p.rows = rows;
-  p.cols = word & 0x1FFFu;
-  p.lanes_log2 = (int32_t)((word >> 13) & 7u);
-  p.lanes_per_row = 1 << p.lanes_log2;
-  const uint32_t n_wg = word >> 16;
-  // as the host would round it: for whole numbers below 2^24 the quotient in float and the one in double, rounded, agree
-  p.inv_cols = 1.0f / (float)p.cols;
+  const LnBwdP p = lnbwd_params(rows, word);
+  const uint32_t n_wg = lnbwd_grid(word);
   constexpr int VEC = Elem<T>::VEC;
   constexpr uint32_t NT = WAVES * 64;
   extern __shared__ __align__(16) float lds[];         // [groups][2][cols]

@@ -22,17 +22,6 @@ __device__ __forceinline__ void run_row_pattern(Ctx& c, const T* in0, const T* i
   Spec::run(c, out0);
 }
 
-// What a kernel's arguments say (row_word; the launcher packs them).
-__device__ __forceinline__ RowP row_params(bool block, uint32_t rows, uint32_t word, float f0, float f1) {
-  RowP p{};
-  p.rows = rows;
-  p.cols = word & 0xFFFFFFu;
-  p.lanes_log2 = (int32_t)((word >> 24) & 7u);
-  p.lanes_per_row = block ? p.lanes_log2 * 64 : 1 << p.lanes_log2;
-  p.f[0] = f0, p.f[1] = f1;
-  return p;
-}
-
 template <typename Spec, typename T, int K, bool FAST, bool STREAM>
 __global__ void __launch_bounds__(256) k_row_wave(const T* __restrict__ in0, const T* __restrict__ in1,
                                                   const T* __restrict__ vec0, const T* __restrict__ vec1, uint32_t rows, uint32_t word,

@@ -116,22 +116,9 @@ __device__ __forceinline__ void softmax_store(T* __restrict__ out, const Softmax
   }
 }
 
-// What a kernel's arguments say (softmax_word; the launcher packs them).
+// (what they say: softmax_params)
 #define SOFTMAX_PARAMS uint32_t rows, uint32_t word, float scale, uint32_t d1, uint32_t m1, uint32_t d2, uint32_t m2, uint32_t ms0, uint32_t ms1, uint32_t ms2
 #define SOFTMAX_ARGS rows, word, scale, d1, m1, d2, m2, ms0, ms1, ms2
-__device__ __forceinline__ SoftmaxP softmax_params(bool block, SOFTMAX_PARAMS) {
-  SoftmaxP p{};
-  p.rows = rows;
-  p.cols = word & 0x3FFFFu;
-  p.lanes_log2 = (int32_t)((word >> 18) & 7u);
-  p.lanes_per_row = block ? p.lanes_log2 * 64 : 1 << p.lanes_log2;
-  p.mask_inner = (int32_t)((word >> 21) & 1u);
-  p.scale = scale;
-  p.od[1] = FastDiv{d1, m1, (word >> 22) & 31u};
-  p.od[2] = FastDiv{d2, m2, word >> 27};
-  p.ms[0] = ms0, p.ms[1] = ms1, p.ms[2] = ms2;
-  return p;
-}
 
 // ---- wave variant ------------------------------------------------------------------
 template <typename T, int K, bool HAS_MASK, bool FAST, bool STREAM>

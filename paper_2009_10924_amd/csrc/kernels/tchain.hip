@@ -73,21 +73,9 @@ struct TChainTile {
   }
 };
 
-// What a kernel's arguments say (tchain_word; the launcher packs them).
+// (what they say: tchain_params)
 #define TCHAIN_PARAMS uint32_t word, uint32_t S, uint32_t H, uint32_t s_tile, uint32_t tiles_d, uint32_t tiles_m, uint32_t h_m, float eps
 #define TCHAIN_ARGS word, S, H, s_tile, tiles_d, tiles_m, h_m, eps
-__device__ __forceinline__ TChainP tchain_params(TCHAIN_PARAMS) {
-  TChainP p{};
-  p.S = S, p.H = H;
-  p.D = word & 0xFFFFu;
-  p.lanes_log2 = (int32_t)((word >> 16) & 7u);
-  p.lanes_per_row = 1 << p.lanes_log2;
-  p.s_tile = (int32_t)s_tile;
-  p.div_s_tiles = FastDiv{tiles_d, tiles_m, (word >> 19) & 31u};
-  p.div_h = FastDiv{H, h_m, (word >> 24) & 31u};
-  p.eps = eps;
-  return p;
-}
 
 template <typename T, int K, int PASSES, bool STREAM>
 __global__ void __launch_bounds__(256) k_tchain_wave(const T* __restrict__ x, const T* __restrict__ scale,

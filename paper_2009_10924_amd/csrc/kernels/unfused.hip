@@ -338,24 +338,12 @@ __device__ __forceinline__ void transpose_units(const T* __restrict__ in, T* __r
   }
 }
 
-// What a kernel's arguments say (transpose_word; the launcher packs them).  The numbers of tiles follow from the extents.
+// (what they say: units_params)
 // Measured against a by-value block of 128 bytes (us, before / after): [64,197,768] -> [64,768,197] bf16 7.2 / 6.9, [8,64,792] ->
 // [8,792,64] bf16 4.1 / 3.6, [59,220,8,64] -> [59,8,64,220] f16 5.1 / 4.8.
 #define UNITS_PARAMS uint32_t m0, uint32_t m1, uint32_t word, uint32_t nq, uint32_t nx, uint32_t in_row, uint32_t in_batch, uint32_t n_tiles, \
                      uint32_t out_row, uint32_t out_batch
 #define UNITS_ARGS m0, m1, word, nq, nx, in_row, in_batch, n_tiles, out_row, out_batch
-__device__ __forceinline__ TransposeP units_params(uint32_t TQ, uint32_t TX, UNITS_PARAMS) {
-  TransposeP p{};
-  p.walk_q = (word >> 15) & 1u;
-  p.every_other = (word >> 16) & 1u;
-  const uint32_t tq = (nq + TQ - 1u) / TQ, tx = (nx + TX - 1u) / TX;
-  p.div[0] = FastDiv{p.walk_q ? tq >> p.every_other : tx, m0, word & 31u};
-  p.div[1] = FastDiv{p.walk_q ? tx : tq, m1, (word >> 5) & 31u};
-  p.nq = nq, p.nx = nx, p.in_row = in_row, p.out_row = out_row;
-  p.in_batch[1] = in_batch, p.out_batch[1] = out_batch;
-  p.n_tiles = n_tiles;
-  return p;
-}
 template <typename T, int UQ, bool STREAM, int UNITS = 256>
 __global__ void __launch_bounds__(256) k_transpose_units(const T* __restrict__ in, T* __restrict__ out, UNITS_PARAMS) {
   constexpr uint32_t VEC = 16 / sizeof(T);
@@ -368,8 +356,7 @@ __global__ void __launch_bounds__(256) k_transpose_units2(const T* __restrict__ 
                                                           uint32_t in_batch0, uint32_t out_batch0) {
   constexpr uint32_t VEC = 16 / sizeof(T);
   TransposeP p = units_params(UQ * VEC, UNITS / UQ * VEC, UNITS_ARGS);
-  p.div[2] = FastDiv{d2, m2, (word >> 10) & 31u};
-  p.in_batch[0] = in_batch0, p.out_batch[0] = out_batch0;
+  units_second_axis(&p, word, d2, m2, in_batch0, out_batch0);
   transpose_units<T, UQ, STREAM, UNITS, true>(in, out, p);
 }
 

@@ -1,7 +1,8 @@
 """Run as a child process by tests/test_host_sanitizers.py with the sanitizer build of the host core loaded
 (FUSION_STITCHING_LIB) and the sanitizer runtime preloaded.  Plans and "executes" the benchmark configurations, the
-generic patterns, packs and explored programs through the host stub: every launch is checked and counted, none runs,
-no device pointer is dereferenced.  Any AddressSanitizer / UndefinedBehaviorSanitizer report aborts the process."""
+generic patterns, packs and explored programs through the host stub: every launch is checked (its arguments are taken apart
+again as the kernel does it) and counted, none runs, no device pointer is dereferenced.  Any AddressSanitizer /
+UndefinedBehaviorSanitizer report aborts the process."""
 import ctypes
 import os
 import sys
@@ -11,7 +12,8 @@ sys.path.insert(0, ROOT)
 
 from paper_2009_10924_amd import binding as B                                            # noqa: E402
 from workloads import (EXPLORE_CONFIGS, FULL_CONFIGS, GENERIC_CONFIGS, NEXT_CONFIGS, PACK_CONFIGS, gelu_backward_graph,  # noqa: E402
-                       independent_tiny_patterns_graph, layernorm_backward_bias_graph, random_multi_pattern, random_row_pattern)
+                       independent_tiny_patterns_graph, layernorm_backward_bias_graph, random_multi_pattern, random_row_pattern,
+                       transpose_graph)
 
 
 def fake(n, base):
@@ -45,6 +47,7 @@ def main():
     lib = B.load()
     lib.fs_stub_launch_count.restype = ctypes.c_long
     assert "host_san" in B.lib_path()
+    assert lib.fs_stub_check_argument_words() == 0      # every field of the kernels' argument words, at its limits and beyond
     for compile_ok in ("", "1"):
         if compile_ok:
             os.environ["FS_STUB_COMPILE_OK"] = "1"      # generated kernels "compile": the generator's whole path runs
@@ -58,6 +61,10 @@ def main():
                 except B.FsError as e:
                     assert e.code == -5, (name, i, e)   # a generated candidate that did not "compile"
             run_plan(spec, "unfused")
+        for dims, perm in (((64, 197, 768), (0, 2, 1)), ((4096, 4096), (1, 0)), ((5, 24, 20, 40), (0, 3, 2, 1)), ((9, 136, 12, 200), (0, 2, 3, 1)),
+                           ((3, 77, 5, 131), (0, 3, 2, 1)), ((700, 3000), (1, 0)), ((2048, 512), (1, 0))):
+            for dt in ("bf16", "f32"):
+                run_plan(transpose_graph(dims, perm, dt))
         for r, c, dt in ((64, 128, "f32"), (37, 96, "bf16"), (300, 1001, "f16")):
             run_plan(gelu_backward_graph(r, c - c % 8 if dt != "f32" else c - c % 4, dt))
             run_plan(layernorm_backward_bias_graph(r, 96, dt, sum_dtype="f32"))
