@@ -72,7 +72,7 @@ bool list_arguments(int32_t kernel, const KernelArgs& a, uint32_t grid, ArgList*
       const RowP& r = a.u.row;
       const uint32_t lanes = kernel == K_ROW_WAVE ? (uint32_t)r.lanes_log2 : (uint32_t)r.lanes_per_row / 64u;
       if (r.cols >= cols24 || lanes > 7u) return false;
-      l->add(p[0], p[1], p[2], p[3], r.rows, row_word(r.cols, lanes), p[4], r.f[0], r.f[1]);
+      l->add(p[0], p[1], p[2], r.rows, row_word(r.cols, lanes), p[4], r.f[0], r.f[1]);
       return true;
     }
     default: return false;

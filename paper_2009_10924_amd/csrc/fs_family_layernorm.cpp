@@ -262,7 +262,6 @@ bool build_layernorm_backward(const fs_graph& g, std::vector<Candidate>* out, Pa
   p.cols = (uint32_t)h.dims[1];
   p.dt = h.dtype;
   p.stream = streams_inputs(g) ? 1 : 0;
-  p.inv_cols = (float)(1.0 / (double)p.cols);
   const Tensor& mu = g.tensors[tmu];
   const Tensor& rs = g.tensors[trs];
   auto per_row = [&](const Tensor& t) { return t.rank == 2 && t.dims[0] == (int64_t)p.rows && t.dims[1] == 1 && t.dtype == FS_F32; };

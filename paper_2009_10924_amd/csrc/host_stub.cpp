@@ -71,7 +71,7 @@ bool arguments_round_trip(int32_t kernel, const KernelArgs& a, uint32_t grid) {
     }
     case K_ROW_WAVE: case K_ROW_BLOCK: {
       const RowP& r = a.u.row;
-      const RowP q = row_params(kernel == K_ROW_BLOCK, u(4), u(5), f(7), f(8));
+      const RowP q = row_params(kernel == K_ROW_BLOCK, u(3), u(4), f(6), f(7));
       return q.rows == r.rows && q.cols == r.cols && q.lanes_per_row == r.lanes_per_row && q.f[0] == r.f[0] && q.f[1] == r.f[1];
     }
     case K_TRANSPOSE_TILE: {

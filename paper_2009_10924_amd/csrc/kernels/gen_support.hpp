@@ -168,7 +168,7 @@ __device__ __forceinline__ void store_elements(TO* p, const float (&v)[N]) {
 // ROWS x COLS row space; VEC elements per lane and step; K steps per lane; L lanes per row: a lane group of one
 // wavefront in a 256-thread workgroup, or, when BLOCK, the whole workgroup of L = 256, 512 or 1024 threads.
 // R: rows each lane group works through, one after the other (the kernel body runs R times with virtual
-// workgroup indices it * gridDim.x + blockIdx.x, so that at any moment the resident workgroups sweep one band of rows).
+// workgroup indices it * (workgroups over the rows, a constant) + its own, so that at any moment the resident workgroups sweep one band of rows).
 // ROW_STRIDE > COLS: the pattern's rows are ROW_STRIDE elements long and the kernel works on column tiles of COLS
 // elements (patterns without row reductions only: nothing ties the tiles of a row together); `tile` picks the tile.
 // TILES: their number, where the last one may be shorter than the others (1: all of COLS elements).

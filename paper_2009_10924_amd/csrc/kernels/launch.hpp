@@ -36,7 +36,7 @@ enum KernelId : int32_t {
   K_COLFOLD,           // p0 partials [n_row_tiles, fold_cols] f32, p1 out0 (columns < fold_split), p2 out1 (the rest), both of dtype dt
   K_TCHAIN_WAVE,       // p0 x, p1 scale, p2 out
   K_TCHAIN_LDS,
-  K_ROW_WAVE,          // p0,p1 row inputs, p2,p3 column vectors, p4 out0, p5 out1 : generic row-stitched skeleton
+  K_ROW_WAVE,          // p0,p1 row inputs, p2 column vector, p4 out : generic row-stitched skeleton
   K_ROW_BLOCK,         // same operands as K_ROW_WAVE, one workgroup per row, reduced values through LDS
   K_ROW_PROGRAM,       // interpreted row program: p0-7 full inputs, p8-15 column vectors, p16-23 per-row scalar
                        // inputs, p24-31 full outputs, p32-39 per-row scalar outputs (kSlot*)
@@ -151,7 +151,7 @@ struct TChainP {
 struct LnBwdP {
   int32_t dt;                       // h / dy / gamma / dx share dt; mu, rstd, dgamma, dbeta are float32
   uint32_t rows, cols;
-  float inv_cols;
+  float inv_cols;                   // the kernel's own (lnbwd_params)
   int32_t lanes_per_row, lanes_log2, vecs_per_lane;
   int32_t waves, rows_per_group;    // workgroup = waves x 64 lanes; rows each lane group loads up front
   int32_t fast;                     // 1: the row fills the lanes exactly, the tiles fill the workgroups' rounds exactly

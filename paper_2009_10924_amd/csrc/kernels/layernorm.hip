@@ -165,7 +165,7 @@ __device__ __forceinline__ void layernorm_block(LN_PARAMS(TI, TO), float* __rest
   const uint32_t T = p.lanes_per_row, n_waves = T >> 6;
   const float inv_n = p.inv_cols;
   uint32_t it = 0;
-  for (uint32_t row = blockIdx.x; row < p.rows; row += gridDim.x, ++it) {
+  for (uint32_t row = blockIdx.x; row < p.rows; row += gridDim.x, ++it) {   // (the one loop here that asks the hardware's own arguments)
     LnRow<TI, TO, K, FAST, STREAM> r;
     // two slot sets alternate between rows: a wave may start row i+1 while a slower
     // one still reads the slots of row i.

@@ -9,36 +9,36 @@
 namespace fsk {
 
 template <typename Spec, typename T, typename Ctx>
-__device__ __forceinline__ void run_row_pattern(Ctx& c, const T* in0, const T* in1, const T* vec0, const T* vec1, T* out0) {
+__device__ __forceinline__ void run_row_pattern(Ctx& c, const T* in0, const T* in1, const T* vec0, T* out0) {
+  static_assert(Spec::NV <= 1, "the kernels take one column vector");
   const T* all_in[2] = {in0, in1};
-  const T* all_vec[2] = {vec0, vec1};
   const T* in[Spec::NI];
   const T* vec[Spec::NV > 0 ? Spec::NV : 1] = {nullptr};
 #pragma unroll
   for (int i = 0; i < Spec::NI; ++i) in[i] = all_in[i];
 #pragma unroll
-  for (int i = 0; i < Spec::NV; ++i) vec[i] = all_vec[i];
+  for (int i = 0; i < Spec::NV; ++i) vec[i] = vec0;
   c.load(in, vec);
   Spec::run(c, out0);
 }
 
 template <typename Spec, typename T, int K, bool FAST, bool STREAM>
 __global__ void __launch_bounds__(256) k_row_wave(const T* __restrict__ in0, const T* __restrict__ in1,
-                                                  const T* __restrict__ vec0, const T* __restrict__ vec1, uint32_t rows, uint32_t word,
+                                                  const T* __restrict__ vec0, uint32_t rows, uint32_t word,
                                                   T* __restrict__ out0, float f0, float f1) {
   const RowP p = row_params(false, rows, word, f0, f1);
   RowCtx<T, T, Spec::NI, Spec::NV, K, FAST, MODE_WAVE, STREAM> c(p, nullptr, blockIdx.x);
-  run_row_pattern<Spec, T>(c, in0, in1, vec0, vec1, out0);
+  run_row_pattern<Spec, T>(c, in0, in1, vec0, out0);
 }
 
 template <typename Spec, typename T, int K, bool FAST, bool STREAM>
 __global__ void __launch_bounds__(256) k_row_block(const T* __restrict__ in0, const T* __restrict__ in1,
-                                                   const T* __restrict__ vec0, const T* __restrict__ vec1, uint32_t rows, uint32_t word,
-                                                  T* __restrict__ out0, float f0, float f1) {
+                                                   const T* __restrict__ vec0, uint32_t rows, uint32_t word,
+                                                   T* __restrict__ out0, float f0, float f1) {
   const RowP p = row_params(true, rows, word, f0, f1);
   __shared__ float slots[16];
   RowCtx<T, T, Spec::NI, Spec::NV, K, FAST, MODE_BLOCK, STREAM> c(p, slots, blockIdx.x);
-  run_row_pattern<Spec, T>(c, in0, in1, vec0, vec1, out0);
+  run_row_pattern<Spec, T>(c, in0, in1, vec0, out0);
 }
 
 }  // namespace fsk
