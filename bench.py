@@ -5,8 +5,8 @@ Headline workload: the largest of the five benchmark configurations, C4 = bias +
 forward fused with the bias-gradient column sum, x, grad bf16 [16384,3072] (302 MB of minimum
 traffic; two launches per step: the stitched kernel and the fold of its column partial sums).
 A step is one pass of the whole subgraph over one batch.  Inputs are resident in HBM before
-the timed region; the step rotates through enough independent buffer sets that no set is still
-in the 256 MB Infinity Cache when its turn comes again (cold-HBM rule).
+the timed region; the step rotates through enough independent buffer sets that no set's inputs are
+still in the 256 MB Infinity Cache when its turn comes again (cold-HBM rule; outputs are stored past it).
 
 Prints ONE JSON line: metric/value = achieved GB/s on the subgraph's minimum traffic (each
 input read once + each output written once) over the whole step, plus `roofline` -- which
@@ -30,7 +30,7 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBPS = 8000.0          # MI355X published HBM3E peak
-CACHE_BYTES = 256 << 20         # Infinity Cache; rotation footprint must be >= 2x this
+CACHE_BYTES = 256 << 20         # Infinity Cache; the inputs of a rotation must be >= 2x this
 
 
 TRAFFIC_PROFILE = "profiles/stitched_kernels_hbm_traffic_pmc.md"
@@ -41,22 +41,24 @@ def _profiled_traffic(tag: str, kernel: str = ""):
     known size, summed over the step's launches).  NOT measured in this run: read from the committed counter
     summary, whose lines `TRAFFIC_BYTES_PER_STEP <config> <kernels> <bytes>` were written from such a run.
     None when the summary was taken on another kernel than the one this run times (`kernel`: the plan's name of
-    its stitched kernel, which starts with the profiled kernel's name less its `k_`)."""
+    its stitched kernel, launch shape included)."""
     try:
         for line in open(os.path.join(ROOT, TRAFFIC_PROFILE)):
             parts = line.split()
             if len(parts) == 4 and parts[0] == "TRAFFIC_BYTES_PER_STEP" and parts[1] == tag:
-                profiled = parts[2].split("+")[0]
-                if kernel and not kernel.startswith(profiled[2:] if profiled.startswith("k_") else profiled):
-                    return None
-                return float(parts[3])
+                return float(parts[3]) if not kernel or kernel == parts[2] else None
     except OSError:
         pass
     return None
 
 
-def _sets_needed(footprint: int) -> int:
-    return max(2, -(-2 * (CACHE_BYTES + (32 << 20)) // max(1, footprint)))
+def _sets_needed(input_bytes: int) -> int:
+    """Buffer sets that a cold rotation takes.  Inputs alone count: they may stay in the cache, what is stored does not."""
+    return max(2, -(-2 * (CACHE_BYTES + (32 << 20)) // max(1, input_bytes)))
+
+
+def rotation_sets(spec, most: int) -> int:
+    return min(_sets_needed(traffic_split(spec)[0]), most)
 
 
 class Runner:
@@ -72,8 +74,7 @@ class Runner:
         self.info = self.plan.info
         self.host_inputs = host_inputs if host_inputs is not None else make_inputs(spec, seed)
         first = [B.to_device(self.host_inputs[t.name], t.dtype) for t in spec.inputs]
-        footprint = self.info["bytes_min"] + self.info["workspace_bytes"]
-        self.n_sets = n_sets or min(_sets_needed(footprint), 4096)
+        self.n_sets = n_sets or rotation_sets(spec, 4096)
         self.inputs = [first] + [[t.clone() for t in first] for _ in range(self.n_sets - 1)]
         self.outputs = [B.alloc_outputs(spec) for _ in range(self.n_sets)]
         self.workspaces = [self.plan.make_workspace() for _ in range(self.n_sets)]
@@ -206,7 +207,7 @@ def probe_us(total_bytes, reads, writes, vecs_per_lane=2, steps=200):
     import torch
     from paper_2009_10924_amd import binding as B
     stream_bytes = max(16, (total_bytes // (reads + writes)) // 16 * 16)
-    n_sets = min(_sets_needed((reads + writes) * stream_bytes), 4096)
+    n_sets = min(_sets_needed((reads or writes) * stream_bytes), 4096)
     srcs = [torch.empty(max(16, reads * stream_bytes), dtype=torch.uint8, device="cuda").fill_(3) for _ in range(n_sets)]
     dsts = [torch.empty(max(16, writes * stream_bytes), dtype=torch.uint8, device="cuda") for _ in range(n_sets)]
     stream = torch.cuda.current_stream().cuda_stream
@@ -341,7 +342,7 @@ def measure_program(name, steps, warmup):
     info = prog.info
     host = make_inputs(spec, 0)
     first = [B.to_device(host[t.name], t.dtype) for t in spec.inputs]
-    n_sets = min(_sets_needed(info["bytes_min"] + info["workspace_bytes"]), 64)
+    n_sets = rotation_sets(spec, 64)
     inputs = [first] + [[t.clone() for t in first] for _ in range(n_sets - 1)]
     outputs = [B.alloc_outputs(spec) for _ in range(n_sets)]
     stream = torch.cuda.current_stream().cuda_stream
@@ -463,7 +464,7 @@ def main():
         "dtype": "f32", "data": "synthetic",
         "config": {"workload": HEADLINE_TEXT, "pattern": r.info["pattern"], "scheme": r.info["scheme"], "kernel": r.info["kernel"],
                    "launches_per_step": r.info["n_kernels"], "block": r.info["block"], "grid": r.info["grid"], "vgprs": r.info["vgprs"],
-                   "buffer_sets": r.n_sets, "cold_hbm_rotation_bytes": r.n_sets * bytes_min},
+                   "buffer_sets": r.n_sets, "cold_hbm_rotation_bytes": r.n_sets * traffic_split(r.spec)[0]},
         "roofline": roofline,
         "wall_ms_per_step": wall / args.steps * 1e3,
     }

@@ -19,3 +19,22 @@ def test_the_line_holds_the_measurement_and_stays_short():
     line, context = bench.split_line(result)
     assert set(line) == set(bench.LINE_KEYS) and set(context) == {"per_config_details", "generic_patterns"}
     assert len(json.dumps(line)) < 8000, len(json.dumps(line))
+
+
+def test_rotations_count_what_can_stay_in_the_cache():
+    """Inputs are read through the cache and outputs are stored past it: the inputs of a rotation have to exceed it twice."""
+    from workloads import FULL_CONFIGS
+    for config in ("C2", "C3", "C4", "C5"):
+        bytes_in, _ = bench.traffic_split(FULL_CONFIGS[config]())
+        sets = bench.rotation_sets(FULL_CONFIGS[config](), 4096)
+        assert sets * bytes_in >= 2 * bench.CACHE_BYTES and (sets - 1) * bytes_in < 2 * bench.CACHE_BYTES + (64 << 20), config
+
+
+def test_profiled_traffic_is_that_of_the_kernel_itself(tmp_path, monkeypatch):
+    assert bench._profiled_traffic("C2", "layernorm_wave<f32,bf16,K99,L64>") is None   # a shape that no profile names
+    (tmp_path / "p.md").write_text("TRAFFIC_BYTES_PER_STEP C2 layernorm_wave<f32,bf16,K3,L64> 63038332\n")
+    monkeypatch.setattr(bench, "ROOT", str(tmp_path))
+    monkeypatch.setattr(bench, "TRAFFIC_PROFILE", "p.md")
+    assert bench._profiled_traffic("C2", "layernorm_wave<f32,bf16,K3,L64>") == 63038332.0
+    assert bench._profiled_traffic("C2", "layernorm_wave<f32,bf16,K6,L32>") is None
+    assert bench._profiled_traffic("C3", "softmax_wave<f16,K2,L8>") is None
