@@ -249,7 +249,7 @@ def measure_config(name, spec, steps, warmup, with_unfused=True, scheme="auto", 
     import torch
     torch.cuda.empty_cache()
     if with_unfused:
-        u = Runner(spec, "unfused", host_inputs=host, n_sets=2)
+        u = Runner(spec, "unfused", host_inputs=host, n_sets=out["buffer_sets"])   # inputs as cold as the stitched plan's
         _, evu = u.time_region(max(10, steps // 4), max(3, warmup // 4))
         secu = evu / max(10, steps // 4)
         out.update({"unfused_us": secu * 1e6, "unfused_kernels": u.info["n_kernels"],
@@ -355,8 +355,8 @@ def measure_program(name, steps, warmup):
     unf = B.Plan(B.Graph.from_spec(dataclasses.replace(spec, external=[])), "unfused")
     uws = [unf.make_workspace() for _ in range(2)]
     ucalls = [unf.bind([t.data_ptr() for t in inputs[k]], [t.data_ptr() for t in outputs[k]],
-                       uws[k].data_ptr() if uws[k] is not None else 0, uws[k].numel() if uws[k] is not None else 0, stream)
-              for k in range(2)]
+                       uws[k % 2].data_ptr() if uws[0] is not None else 0, uws[0].numel() if uws[0] is not None else 0, stream)
+              for k in range(n_sets)]
 
     def timed(fns, n):
         for k in range(warmup):
