@@ -1,5 +1,5 @@
 // Kernel dispatch: the symbol that serves a (kernel id, parameter block), launched with the arguments that it takes
-// (fs_arguments.cpp).
+// (kernel_arguments.hpp).
 #include <hip/hip_runtime.h>
 
 #include "kernel_table.hpp"
