@@ -99,6 +99,37 @@ int online_reduction_pairs(const RowProgP& p, std::vector<char>* online) {
   return pairs;
 }
 
+// Rows that end inside a step may store their last step whole (GenRow, AGAIN) where every element has been read before
+// any is stored: behind a row reduction, unless a later pass reads the row again.
+static bool stores_again(const RowProgP& p) {
+  if (p.cols % (uint32_t)p.vec == 0 || (p.col_chunks > 1 && p.col_kept < p.col_chunks)) return false;
+  for (int i = 0; i < p.n_instr; ++i) {
+    if (p.instr[i].op == PO_STORE) return false;
+    if (p.instr[i].op == PO_RSUM || p.instr[i].op == PO_RMAX || p.instr[i].op == PO_RSUMSQ) return true;
+  }
+  return false;
+}
+
+// Rows that end inside a step lie on the tensor's steps (GenRow, EDGES) where
+//   * their operands are 16-bit elements and their length is odd: what costs is a 128-bit access that starts off a 4-byte
+//     boundary (us, every step unaligned / on the grid: log-softmax bf16 [2048,50257] 89.0 / 76.5, [809,9269] 6.86 / 5.69, f16
+//     [34,88897] 12.4 / 9.4; float32 and even lengths gain nothing),
+//   * a workgroup works on a row, or a wavefront's lanes on several steps of rows with a stretched operand beside them (attention
+//     rows f16 [7,8,587,587] 14.0 / 12.3; softmax without a mask on a wavefront bf16 [30000,210] 4.98 / 5.0, f16 [45513,541] 15.7 / 16.6),
+//   * their first and last steps are stored whole (stores_again), every chunk of a long row kept,
+//   * nothing ties a lane to the same columns from row to row (column sums, several rows per workgroup) or has rows start elsewhere
+//     (transposed outputs; column vectors, whose accesses would then be the unaligned ones: LayerNorm bf16 [489,2359] 4.03 / 4.29),
+//   * the lanes have room for the step more that a row may take.
+bool row_on_grid(const RowProgP& p) {
+  if (!stores_again(p) || p.cols % 2 == 0 || p.vec < 4 || p.n_col > 0 || p.n_colsum > 0 || p.out_perm != 0 || p.col_tiles > 1 || p.rows_per_group > 1) return false;
+  for (int i = 0; i < p.n_full; ++i)
+    if (p.full_dt[i] == DT_F32) return false;
+  for (int i = 0; i < p.n_instr; ++i)
+    if (p.instr[i].op == PO_STORE && p.instr[i].aux == DT_F32) return false;
+  const int steps = p.vecs_per_lane * std::max(1, p.col_chunks);
+  return (p.lanes_per_row > 64 || (steps > 1 && p.full_bcast != 0)) && p.cols + (uint32_t)p.vec - 1u <= (uint64_t)p.lanes_per_row * (uint32_t)steps * (uint32_t)p.vec;
+}
+
 namespace {
 // member = false: an extern "C" kernel `entry(p0, p1, ..)` over the pointers of generated_ptr_slots().  member = true: a
 // device function `entry(const GenArgs& a, uint32_t fs_block)` that a packed kernel calls for the member's range of workgroups.
@@ -172,17 +203,6 @@ struct ChunkPass {
 // to hide latency, and a row kept in registers no longer fits (it spills by hundreds of bytes per lane).
 std::string kChunkOrderPin(const char* a, const char* b) {
   return b ? fmt("  asm volatile(\"\" : \"+v\"(%s), \"+v\"(%s));\n", a, b) : fmt("  asm volatile(\"\" : \"+v\"(%s));\n", a);
-}
-
-// Rows that end inside a step may store their last step whole (GenRow, AGAIN) where every element has been read before
-// any is stored: behind a row reduction, unless a later pass reads the row again.
-bool stores_again(const RowProgP& p) {
-  if (p.cols % (uint32_t)p.vec == 0 || (p.col_chunks > 1 && p.col_kept < p.col_chunks)) return false;
-  for (int i = 0; i < p.n_instr; ++i) {
-    if (p.instr[i].op == PO_STORE) return false;
-    if (p.instr[i].op == PO_RSUM || p.instr[i].op == PO_RMAX || p.instr[i].op == PO_RSUMSQ) return true;
-  }
-  return false;
 }
 
 std::string instruction_text(const RowProgP& p, const ProgInstr& in, bool block, int n_waves, int* reduction_no, ChunkPass* cp = nullptr) {
@@ -285,9 +305,15 @@ std::string chunked_body(const RowProgP& p, const char* entry) {
   online_reduction_pairs(p, &online);
   std::string s = "using namespace fsk;\n";
   s += kernel_head(p, entry, (int)L);
-  const char* past_caches = p.stream ? ", 1u, true" : "";
-  s += fmt("  typedef GenRow<%uu, %uu, %d, %d, %uu, true, 1u, %uu%s> Row;       // a whole chunk\n", p.rows, chunk, p.vec, p.vecs_per_lane, L, p.cols, past_caches);
-  s += fmt("  typedef GenRow<%uu, %uu, %d, %d, %uu, true, 1u, %uu%s> TailRow;   // the row's last chunk\n", p.rows, tail, p.vec, p.vecs_per_lane, L, p.cols, past_caches);
+  const bool grid = row_on_grid(p);   // only with every chunk kept, so each has a row object of its own type
+  auto row_type = [&](const char* name, uint32_t cols, const char* edges, const char* what) {
+    s += fmt("  typedef GenRow<%uu, %uu, %d, %d, %uu, true, 1u, %uu%s> %s;   // %s\n", p.rows, cols, p.vec, p.vecs_per_lane, L, p.cols,
+             grid ? fmt(", 1u, %s, %s", p.stream ? "true" : "false", edges).c_str() : (p.stream ? ", 1u, true" : ""), name, what);
+  };
+  row_type("Row", chunk, "EDGE_INNER", "a whole chunk");
+  row_type("HeadRow", chunk, "EDGE_FIRST", "the row's first chunk");
+  row_type("TailRow", tail, "EDGE_LAST", "the row's last chunk");
+  auto chunk_type = [&](uint32_t c) { return c == NC - 1u ? "TailRow" : (c == 0 ? "HeadRow" : "Row"); };
   s += "  constexpr int KV = Row::KV;\n";
   if (n_red > 0) s += fmt("  __shared__ float slots[%d];\n", n_waves * n_red);
   for (int q = 0; q < n_red; ++q) s += fmt("  float red%d;\n", q);
@@ -306,7 +332,7 @@ std::string chunked_body(const RowProgP& p, const char* entry) {
   const uint32_t kept = (uint32_t)std::max(0, std::min(p.col_kept, p.col_chunks));
   for (uint32_t c = 0; c < kept; ++c)
     for (int i = 0; i < p.n_full; ++i)
-      s += fmt("  %s::Raw<%s> kept%d_%u;\n", c == NC - 1u ? "TailRow" : "Row", storage_type(p.full_dt[i]), i, c);
+      s += fmt("  %s::Raw<%s> kept%d_%u;\n", chunk_type(c), storage_type(p.full_dt[i]), i, c);
   // one chunk's share of a pass, for the row object `row` in scope; kept_chunk >= 0: that chunk stays in registers
   auto piece = [&](int pass, bool last_chunk, int kept_chunk, bool preloaded = false) {
     std::string t;
@@ -365,14 +391,14 @@ std::string chunked_body(const RowProgP& p, const char* entry) {
         for (int i = 0; i < p.n_full; ++i) {
           const bool stretched = ((p.full_bcast >> i) & 1u) != 0;
           const std::string at = stretched ? stretched_row(p.ms[i]) : std::string("(size_t)row.row_c");
-          in_registers += fmt("  {\n  const %s row(fs_block, 0, %uu);\n  kept%d_%u = row.load<%s, %s>(a.full[%d], %s);\n  }\n", c == NC - 1u ? "TailRow" : "Row",
+          in_registers += fmt("  {\n  const %s row(fs_block, 0, %uu);\n  kept%d_%u = row.load<%s, %s>(a.full[%d], %s);\n  }\n", chunk_type(c),
                               c * chunk, i, c, storage_type(p.full_dt[i]), stretched ? "false" : "true", i, at.c_str());
         }
       in_registers += "  __builtin_amdgcn_sched_barrier(0);\n";
     }
     for (uint32_t c = 0; c < kept; ++c) {
       const bool is_tail = c == NC - 1u;
-      in_registers += fmt("  {\n  const %s row(fs_block, 0, %uu);\n", is_tail ? "TailRow" : "Row", c * chunk) + piece(pass, is_tail, (int)c, preload) + "  }\n";
+      in_registers += fmt("  {\n  const %s row(fs_block, 0, %uu);\n", chunk_type(c), c * chunk) + piece(pass, is_tail, (int)c, preload) + "  }\n";
       if (preload) in_registers += "  __builtin_amdgcn_sched_barrier(0);\n";
     }
     // the others: whole chunks by a loop, then the row's last chunk.  Every other pass walks them backwards: it
@@ -417,8 +443,11 @@ std::string body_with_entry(const RowProgP& p, const char* entry, bool member) {
   const uint32_t CT = p.col_tiles > 1 ? (uint32_t)p.col_tiles : 1u;   // column tiles
   // (column tiles: whole steps of every lane; the last tile may be shorter)
   const uint32_t tile_cols = CT > 1 ? (uint32_t)(p.lanes_per_row * p.vecs_per_lane * p.vec) : p.cols;
+  std::string rest;
+  if (row_on_grid(p)) rest = fmt(", 1u, %s, EDGE_FIRST | EDGE_LAST", p.stream ? "true" : "false");
+  else if (CT > 1 || p.stream) rest = fmt(", %uu%s", CT, p.stream ? ", true" : "");
   s += fmt("  typedef GenRow<%uu, %uu, %d, %d, %uu, %s, %uu, %uu%s> Row;\n", p.rows, tile_cols, p.vec, p.vecs_per_lane,
-           (uint32_t)p.lanes_per_row, block ? "true" : "false", R, p.cols, CT > 1 || p.stream ? fmt(", %uu%s", CT, p.stream ? ", true" : "").c_str() : "");
+           (uint32_t)p.lanes_per_row, block ? "true" : "false", R, p.cols, rest.c_str());
   s += "  constexpr int KV = Row::KV;\n";
   const int n_waves = block ? p.lanes_per_row / 64 : 4;
   const bool looped = p.n_colsum > 0 || R > 1u;

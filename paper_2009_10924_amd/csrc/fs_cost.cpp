@@ -16,8 +16,9 @@ static double run_derating(const KernelCost& k) {
   if (k.access_run_bytes > 0 && k.access_run_bytes < 128) f *= 1.0 + (128.0 / k.access_run_bytes - 1.0);
   if (k.access_run_bytes > 0 && k.row_bytes > 0 && std::fmod(k.row_bytes, 128.0) != 0.0) {
     // (fitted for each of the three kinds of loop; a workgroup that works through several rows finds the line that two of
-    // them share in its caches more often, and column sums are bound by other things first)
-    const double shared_lines = k.rows_per_wave_loop <= 1 ? 1.65 : k.partial_bytes > 0 ? 0.3 : 1.07;
+    // them share in its caches more often, and column sums are bound by other things first.  Rows of an odd number of 16-bit
+    // elements: 94 such softmaxes timed in every shape, the one taken was 3.8 % behind the fastest, 2.7 % with weights of their own)
+    const double shared_lines = k.rows_per_wave_loop <= 1 ? (k.off_words ? 2.2 : k.on_grid ? (k.barriers == 0 ? 0.9 : 1.3) : 1.65) : k.partial_bytes > 0 ? 0.3 : 1.07;
     f *= 1.0 + shared_lines * std::min(4.0, 128.0 / k.access_run_bytes);
   }
   return f;
@@ -100,7 +101,7 @@ CostResult evaluate(const KernelCost& k, int32_t vgprs_compiled) {
   bw /= run_derating(k);
   bw /= 1.0 + k.stream_penalty;
   if (k.store_run_bytes > 0 && k.store_run_bytes < 512) bw *= 0.97;
-  bw /= 1.0 + 0.12 * (1.0 / util - 1.0);
+  bw /= 1.0 + (k.on_grid ? 0.3 : 0.12) * (1.0 / util - 1.0);
   bw /= 1.0 + 0.25 * (rounds / rounds_exact - 1.0);
   if (occ < 4) bw /= 1.0 + 0.04 * (4.0 - occ);   // few waves per SIMD: a wave's own stalls are not covered
   const double t_hbm = (k.hbm_bytes + d.partial_weight * k.partial_bytes) / bw;

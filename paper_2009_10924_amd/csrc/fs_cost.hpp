@@ -69,6 +69,8 @@ struct KernelCost {
   int32_t lds_bytes_per_block = 0;
   double lane_utilisation = 1.0;        // fraction of lanes holding data
   double access_run_bytes = 0;          // contiguous bytes one row group touches per load (0 = long)
+  bool on_grid = false;                 // rows start anywhere, but accesses are aligned but for a row's first and last (row_on_grid())
+  bool off_words = false;               // accesses of a workgroup's row start off a 4-byte boundary
   double row_bytes = 0;                 // from one row to the next, in the narrowest row operand (0 = not row by row)
   double stream_penalty = 0;            // the streaming rate falls to 1 / (1 + this) for reasons of the kernel's own
   double store_run_bytes = 0;           // contiguous run written by one store instruction group (0 = long)

@@ -192,6 +192,7 @@ std::string embedded_prelude();
 // Pairs of row reductions "rmax; acc - max; exp; rsum" that a row worked through in chunks gathers in one pass
 // (online[q] = 1 for the first of each pair; `online` may be null); returns their number.
 int online_reduction_pairs(const RowProgP& p, std::vector<char>* online);
+bool row_on_grid(const RowProgP& p);   // fs_codegen.cpp: the generated kernel's accesses are aligned although its rows are not
 // Process-wide switch: candidates with generated kernels are offered only while it is on (default: on
 // unless the environment says FS_CODEGEN=0) and the run-time compiler is available.
 bool codegen_enabled();

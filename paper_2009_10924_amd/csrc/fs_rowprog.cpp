@@ -943,6 +943,9 @@ void make_generated(const Compiler& c, int vec, const Shape& s, Candidate* cand)
   gc.lds_bytes_per_block = slots;
   gc.vgpr_estimate = 24 + kv * (base.n_regs + 1 + (base.n_col > 0 ? 1 : 0)) + 2 * s.K * base.n_full;
   gc.preamble_instr = 40;
+  gc.on_grid = row_on_grid(gl.args.u.prog);
+  gc.off_words = !gc.on_grid && s.block && base.n_full > 0 && base.n_col == 0 && base.cols % 2 != 0;
+  for (int i = 0; i < base.n_full; ++i) gc.off_words = gc.off_words && base.full_dt[i] != DT_F32;
   // a lane's own instruction stream between its loads landing and its stores leaving: the first and the last
   // wavefronts of the launch run it with the memory system idle, so long per-lane chains (many vectors per
   // lane) cost time that more, shorter wavefronts would have overlapped

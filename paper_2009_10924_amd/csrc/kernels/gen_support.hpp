@@ -180,9 +180,16 @@ __device__ __forceinline__ void store_elements(TO* p, const float (&v)[N]) {
 // store either writes only the TAIL elements the step owns, in at most three pieces, or (AGAIN) the whole step, the
 // repeated elements a second time with the value their owner gives them: one access instead of three more (rows of 197
 // 16-bit elements, 29.8 MB: 7.6 against 8.9 us for the bare copy, 7.0 with rows padded to whole steps).
+//
+// EDGES != 0 (such rows again, stored AGAIN): the steps lie on the multiples of VEC elements of the whole tensor instead of
+// the row's, so every access but a row's first and last is aligned; these two slide inwards, the first to where the row starts,
+// the last to where it ends, and the elements that a neighbour holds too count once.  What a row then takes is at most one
+// step more.  EDGE_FIRST / EDGE_LAST: the object may hold the row's first / last step (a chunk between them neither).
+constexpr int EDGE_FIRST = 1, EDGE_LAST = 2, EDGE_INNER = 4;
 template <uint32_t ROWS, uint32_t COLS, int VEC, int K, uint32_t L, bool BLOCK, uint32_t R = 1, uint32_t ROW_STRIDE = COLS, uint32_t TILES = 1,
-          bool PAST_CACHES = false>
+          bool PAST_CACHES = false, int EDGES = 0>
 struct GenRow {
+  static constexpr bool ON_GRID = EDGES != 0;   // of the tensor's steps
   static constexpr bool SHORT_LAST = TILES > 1 && TILES * COLS != ROW_STRIDE;
   static constexpr uint32_t LAST_COLS = SHORT_LAST ? ROW_STRIDE - (TILES - 1u) * COLS : COLS;
   static constexpr uint32_t NVEC = (COLS + VEC - 1) / VEC, LAST_NVEC = (LAST_COLS + VEC - 1) / VEC;
@@ -191,7 +198,7 @@ struct GenRow {
   static constexpr uint32_t LANES = L;
   static constexpr uint32_t ROWS_PER_WG = BLOCK ? 1u : 256u / L;
   // the row fills its lanes (and no element is held twice) / the rows fill the workgroups: no clamp, no padding test
-  static constexpr bool FULL_COLS = NVEC == LANES * K && TAIL == 0 && !SHORT_LAST;
+  static constexpr bool FULL_COLS = !ON_GRID && NVEC == LANES * K && TAIL == 0 && !SHORT_LAST;
   static constexpr bool FULL_ROWS = ROWS % (ROWS_PER_WG * R) == 0;
   static constexpr int KV = K * VEC;
   static constexpr uint32_t PADDED_COLS = LANES * K * VEC;   // columns the lanes of a row cover, padding included
@@ -203,6 +210,7 @@ struct GenRow {
 
   uint32_t lane, row, row_c, col0;
   bool row_ok, last;   // last: the tile that may be shorter than the others
+  int lead;            // ON_GRID: elements between the start of the row's first step and the row's own start
 
   __device__ __forceinline__ explicit GenRow(uint32_t vblock, uint32_t tile = 0) {
     const uint32_t tid = threadIdx.x;
@@ -212,23 +220,46 @@ struct GenRow {
     row = BLOCK ? vblock : vblock * ROWS_PER_WG + tid / L;
     row_ok = FULL_ROWS || row < ROWS;
     row_c = FULL_ROWS ? row : min(row, ROWS - 1u);
+    lead = ON_GRID ? (int)((row_c * (ROW_STRIDE % VEC)) % VEC) : 0;
   }
   // a chunk of a long row: COLS columns from column `first_col` on (the row itself is ROW_STRIDE elements long)
   __device__ __forceinline__ GenRow(uint32_t vblock, uint32_t tile, uint32_t first_col) : GenRow(vblock, tile) { col0 = first_col; }
   // only a lane's last step can be padding or the row's last one (K is the smallest that covers the row)
-  static constexpr __device__ __forceinline__ bool inner(int k) { return FULL_COLS || (!SHORT_LAST && (uint32_t)k < (NVEC - 1u) / LANES); }
+  static constexpr __device__ __forceinline__ bool inner(int k) {
+    if constexpr (ON_GRID) return before_last(k) && behind_first(k);
+    return FULL_COLS || (!SHORT_LAST && (uint32_t)k < (NVEC - 1u) / LANES);
+  }
+  // ON_GRID: no lane's step k can be the row's last one (or padding) / its first one
+  static constexpr __device__ __forceinline__ bool before_last(int k) { return (EDGES & EDGE_LAST) == 0 || ((uint32_t)k + 1u) * LANES * VEC <= COLS; }
+  static constexpr __device__ __forceinline__ bool behind_first(int k) { return (EDGES & EDGE_FIRST) == 0 || k > 0; }
+  // ON_GRID: the row's column at which step k lies on the grid (the first one's may be negative), and where it is read and written
+  __device__ __forceinline__ int grid_col(int k) const { return (int)col0 + (int)(lane + k * LANES) * VEC - lead; }
+  __device__ __forceinline__ int edge_col(int k) const {
+    int c = grid_col(k);
+    if (!behind_first(k)) c = max(c, 0);
+    if (!before_last(k)) c = min(c, (int)ROW_STRIDE - VEC);
+    return c;
+  }
   // steps and columns of the row (of this tile of it), and the steps that hold no repeated element
   __device__ __forceinline__ uint32_t n_steps() const { return SHORT_LAST && last ? LAST_NVEC : NVEC; }
   __device__ __forceinline__ uint32_t n_cols() const { return SHORT_LAST && last ? LAST_COLS : COLS; }
   __device__ __forceinline__ uint32_t n_whole() const { return SHORT_LAST && !last ? NVEC : LAST_NVEC - (TAIL != 0 ? 1u : 0u); }
-  __device__ __forceinline__ bool valid(int k) const { return inner(k) || lane + k * LANES < n_steps(); }
+  __device__ __forceinline__ bool valid(int k) const {
+    if constexpr (ON_GRID) return before_last(k) || grid_col(k) < (int)ROW_STRIDE;
+    return inner(k) || lane + k * LANES < n_steps();
+  }
   // element e of step k is the lane's own: neither padding nor a repetition of the step before
   __device__ __forceinline__ bool own(int k, int e) const {
+    if constexpr (ON_GRID) {   // a step that slid by n elements: its first n (slid back) or its last -n (slid forward) are a neighbour's
+      const int n = grid_col(k) - edge_col(k);
+      return (before_last(k) || e >= n) && (behind_first(k) || e < VEC + n);
+    }
     return inner(k) || lane + k * LANES < (e < BACK ? n_whole() : n_steps());
   }
   // first column of step k (the last step's slides back; padding steps stay on the last step).  Signed: the last chunk
   // of a long row may be shorter than a step, which then starts in the chunk before.
   __device__ __forceinline__ int first_of(int k) const {
+    if constexpr (ON_GRID) return edge_col(k) - (int)col0;
     if (inner(k)) return (int)(lane + k * LANES) * VEC;
     if constexpr (TAIL != 0) return min((int)(lane + k * LANES) * VEC, (int)n_cols() - VEC);
     return (int)min(lane + k * LANES, n_steps() - 1u) * VEC;
@@ -284,7 +315,8 @@ struct GenRow {
       float part[VEC];
 #pragma unroll
       for (int e = 0; e < VEC; ++e) part[e] = v[k * VEC + e];
-      if constexpr (TAIL == 0) {
+      static_assert(!ON_GRID || AGAIN, "a step that slid is written whole");
+      if constexpr (TAIL == 0 && !ON_GRID) {
         if (row_ok && valid(k)) store_elements<TO, VEC, alignment<TO>()>(base + (size_t)(lane + k * LANES) * VEC, part);
       } else if constexpr (AGAIN) {
         if (row_ok && valid(k)) store_elements<TO, VEC, alignment<TO>()>(base + first_of(k), part);
