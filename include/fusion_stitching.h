@@ -342,8 +342,9 @@ typedef struct fs_program_info {
   int32_t n_ops;          /* ops of the graph                                             */
   int32_t n_patterns;     /* fusion patterns of two or more ops in the chosen plan         */
   int32_t n_single_ops;   /* ops left in a kernel of their own                             */
-  int32_t n_steps;        /* fs_execute / packed launches issued per fs_program_execute    */
-  int32_t n_kernels;      /* kernel launches per fs_program_execute                        */
+  int32_t n_steps;        /* fs_execute / packed launches of the program's stages          */
+  int32_t n_kernels;      /* kernel launches of the program's stages; fs_program_execute   */
+                          /* takes fewer where it merges steps (see fs_program_describe)   */
   int32_t n_packs;        /* packed launches among the steps                               */
   int32_t beam_plans;     /* candidate plans the final choice was made among               */
   int32_t n_joint_folds;  /* column-sum folds moved behind the last step and issued as one launch (per 8): sums over
@@ -352,7 +353,7 @@ typedef struct fs_program_info {
   int64_t bytes_min;         /* graph inputs read once + graph outputs written once        */
   int64_t bytes_moved_model; /* bytes the plan's kernels move, tensors between patterns included */
   double f_total_us;         /* sum of the chosen patterns' delta-evaluator scores (Eq. 3), remote fusion included */
-  double predicted_us;       /* latency-evaluator estimate of one fs_program_execute        */
+  double predicted_us;       /* latency-evaluator estimate of the program's stages one after the other */
   double predicted_unfused_us; /* the same ops one kernel each, by the delta-evaluator's per-op term */
   int32_t n_stages;       /* 1 + the longest chain of external computations (fs_graph_external) between steps */
   int32_t reserved;
@@ -399,7 +400,9 @@ fs_status fs_program_pattern(const fs_program *p, int32_t index, int32_t *ops, i
  * scratch (`scratch ws+<offset> <bytes>`); then one line per packed launch (`pack <j>
  * launches=<n> members=<steps>`) and per joint fold launch (`joint_fold <j> folds=<n>
  * of_steps=<steps whose column sums it finishes>`, with `with_step=<i>` where the last step's
- * kernel runs them too: one launch for both, counted here and not at the step).  Errors: FS_ERR_INVALID_ARG.         */
+ * kernel runs them too: one launch for both, counted here and not at the step).  Where
+ * fs_program_execute merges steps that do not depend on each other, one line per launch of
+ * it follows (`merged <j> of <n> steps=<steps> folds_of=<steps>`).  Errors: FS_ERR_INVALID_ARG.         */
 int64_t fs_program_describe(const fs_program *p, char *text, size_t capacity);
 /* Enqueues the whole program on `hip_stream` and returns without waiting.  inputs /
  * outputs: DEVICE pointers in the graph's declaration order, 16-byte aligned.  `workspace`:

@@ -132,7 +132,8 @@ bool row_on_grid(const RowProgP& p) {
 
 namespace {
 // member = false: an extern "C" kernel `entry(p0, p1, ..)` over the pointers of generated_ptr_slots().  member = true: a
-// device function `entry(const GenArgs& a, uint32_t fs_block)` that a packed kernel calls for the member's range of workgroups.
+// device function `entry(const GenArgs& a, uint32_t fs_block, float* fs_lds)` that a kernel of several members calls for the member's
+// range of workgroups; fs_lds: what the kernel has set aside for its members' column sums (column_sum_lds_bytes()).
 std::string body_with_entry(const RowProgP& p, const char* entry, bool member = false);
 // `a.<field>[i]` of the pointer slot `slot` (kSlot*)
 std::string arg_field(int slot) {
@@ -434,7 +435,7 @@ std::string body_with_entry(const RowProgP& p, const char* entry, bool member) {
 
   std::string s;
   if (member) {
-    s += fmt("static __device__ __forceinline__ void %s(const GenArgs& a, const uint32_t fs_block) {\n", entry);
+    s += fmt("static __device__ __forceinline__ void %s(const GenArgs& a, const uint32_t fs_block, float* const fs_lds) {\n", entry);
   } else {
     s += "using namespace fsk;\n";
     s += kernel_head(p, entry, block ? p.lanes_per_row : 256);
@@ -502,13 +503,14 @@ std::string body_with_entry(const RowProgP& p, const char* entry, bool member) {
     // loads last and whose back edge comes from a round that issued its store last, the compiler has to wait for
     // everything, the store included, in every round.  With the first round peeled both ways into the loop look
     // alike and the wait leaves the stores in flight; the last round has no row to load ahead.
-    if (!block) s += fmt("  __shared__ __attribute__((aligned(16))) float colred[%d][4 * Row::PADDED_COLS];\n", p.n_colsum);
+    if (!block && member) s += "  float (*const colred)[4 * Row::PADDED_COLS] = reinterpret_cast<float (*)[4 * Row::PADDED_COLS]>(fs_lds);\n";
+    else if (!block) s += fmt("  __shared__ __attribute__((aligned(16))) float colred[%d][4 * Row::PADDED_COLS];\n", p.n_colsum);
     for (int i = 0; i < p.n_colsum; ++i)
       s += fmt("  float cs%d[KV];\n#pragma unroll\n  for (int j = 0; j < KV; ++j) cs%d[j] = 0.0f;\n", i, i);
     // neighbouring workgroups take neighbouring column tiles of the same rows
     const uint32_t rows_per_wg = (block ? 1u : 256u / (uint32_t)p.lanes_per_row) * R;
-    if (CT > 1) s += fmt("  const uint32_t tile = blockIdx.x %% %uu, row_wg = blockIdx.x / %uu;\n", CT, CT);
-    else s += "  const uint32_t tile = 0, row_wg = blockIdx.x;\n";
+    if (CT > 1) s += fmt("  const uint32_t tile = fs_block %% %uu, row_wg = fs_block / %uu;\n", CT, CT);
+    else s += "  const uint32_t tile = 0, row_wg = fs_block;\n";
     s += fmt("  constexpr uint32_t n_row_wgs = %uu;\n", (p.rows + rows_per_wg - 1u) / rows_per_wg);   // the grid's (a constant: nothing to fetch)
     s += "  Row nrow(row_wg, tile);\n";
     s += col_loads("nrow");
@@ -600,7 +602,7 @@ std::string generate_pack_kernel(const std::vector<RowProgP>& members, const std
   for (size_t m = 0; m < members.size(); ++m) {
     k += fmt("  if (b < %uu) {\n    GenArgs a{};\n", first + blocks[m]);
     for (int slot : (*ptr_slots)[m]) k += fmt("    %s = t.p[%zu];\n", arg_field(slot).c_str(), at++);
-    k += fmt("    fs_member_%zu(a, b - %uu);\n    return;\n  }\n", m, first);
+    k += fmt("    fs_member_%zu(a, b - %uu, nullptr);\n    return;\n  }\n", m, first);
     first += blocks[m];
   }
   k += "}\n";
@@ -611,33 +613,48 @@ std::string generate_pack_kernel(const std::vector<RowProgP>& members, const std
   return out;
 }
 
-// The kernel of `p` that also runs folds of column sums: workgroups [0, sum of blocks) take the folds one after the other, the
-// others the rows.  Everything about a fold but its three pointers is a constant.
-std::string generate_kernel_with_folds(const RowProgP& p, const std::vector<Launch>& folds, std::string* entry) {
-  std::string body = body_with_entry(p, "fs_rows", true);
-  const std::vector<int> slots = generated_ptr_slots(p);
-  std::string params, fields, jobs;
+int64_t column_sum_lds_bytes(const RowProgP& p) {
+  return p.lanes_per_row > 64 ? 0 : (int64_t)p.n_colsum * 4 * p.lanes_per_row * p.vecs_per_lane * p.vec * 4;
+}
+
+// One kernel over row programs and folds of column sums: workgroups [0, sum of the folds') take the folds one after the other, the
+// others the members in their order.  Everything but the pointers is a constant.  A workgroup is in one of them only, so all use
+// the same LDS (their sum would leave 3 workgroups per compute unit where the largest leaves 4: LayerNorm backward beside GELU).
+std::string generate_merged_kernel(const std::vector<RowProgP>& members, const std::vector<uint32_t>& blocks, const std::vector<Launch>& folds,
+                                   std::string* entry) {
+  std::string bodies, params, jobs;
   size_t n = 0;
-  for (size_t k = 0; k < slots.size(); ++k, ++n) {
-    params += fmt("%svoid* p%zu", n ? ", " : "", n);
-    fields += fmt("    %s = p%zu;\n", arg_field(slots[k]).c_str(), n);
-  }
+  int64_t lds = folds.empty() ? 16 : 4096;
+  for (const RowProgP& p : members) lds = std::max(lds, column_sum_lds_bytes(p));
   uint32_t first = 0;
+  for (const Launch& f : folds) first += f.shape.grid[0];
+  for (size_t m = 0; m < members.size(); ++m) {
+    const std::string name = fmt("fs_member_%zu", m);
+    bodies += body_with_entry(members[m], name.c_str(), true);
+    jobs += fmt("  if (b < %uu) {\n    GenArgs a{};\n", first + blocks[m]);
+    for (int slot : generated_ptr_slots(members[m])) {
+      params += fmt("%svoid* p%zu", n ? ", " : "", n);
+      jobs += fmt("    %s = p%zu;\n", arg_field(slot).c_str(), n++);
+    }
+    jobs += fmt("    %s(a, b - %uu, reinterpret_cast<float*>(sm));\n    return;\n  }\n", name.c_str(), first);
+    first += blocks[m];
+  }
+  std::string fold_jobs;
+  first = 0;
   for (const Launch& f : folds) {
     const GeluP& q = f.args.u.gelu;
     for (int i = 0; i < 3; ++i) params += fmt("%svoid* p%zu", n + i ? ", " : "", n + i);
-    jobs += fmt("  if (b < %uu) {\n    fold_tile<%s>(static_cast<const float*>(p%zu), static_cast<float*>(p%zu), static_cast<float*>(p%zu), %uu, %uu, %uu, %uu, "
-                "%uu, b - %uu, sm, %d);\n    return;\n  }\n",
-                first + f.shape.grid[0], q.fold_quads == 4 ? "4, 64" : "16, 16", n, n + 1, n + 2, q.n_row_tiles, q.fold_cols, q.cols, q.fold_split,
-                q.fold_out_cols, first, q.dt);
+    fold_jobs += fmt("  if (b < %uu) {\n    fold_tile<%s>(static_cast<const float*>(p%zu), static_cast<float*>(p%zu), static_cast<float*>(p%zu), %uu, %uu, %uu, %uu, "
+                     "%uu, b - %uu, sm, %d);\n    return;\n  }\n",
+                     first + f.shape.grid[0], q.fold_quads == 4 ? "4, 64" : "16, 16", n, n + 1, n + 2, q.n_row_tiles, q.fold_cols, q.cols, q.fold_split,
+                     q.fold_out_cols, first, q.dt);
     first += f.shape.grid[0];
     n += 3;
   }
   std::string k = fmt("extern \"C\" __global__ void __launch_bounds__(256) %s(%s) {\n", kEntryPlaceholder, params.c_str());
-  k += "  __shared__ f32x4 sm[256];\n  const uint32_t b = blockIdx.x;\n";
-  k += fmt("  if (b >= %uu) {\n    GenArgs a{};\n", first) + fields + fmt("    fs_rows(a, b - %uu);\n    return;\n  }\n", first) + jobs + "}\n";
-  const std::string text = "using namespace fsk;\n" + body + k;
-  *entry = fmt("fs_gen_folds_%08x", fnv1a(text));
+  k += fmt("  __shared__ f32x4 sm[%u];\n  const uint32_t b = blockIdx.x;\n", (unsigned)((lds + 15) / 16)) + fold_jobs + jobs + "}\n";
+  const std::string text = "using namespace fsk;\n" + bodies + k;
+  *entry = fmt("fs_gen_merged_%08x", fnv1a(text));
   std::string out = kEmbeddedFold + text;
   out.replace(out.find(kEntryPlaceholder), sizeof kEntryPlaceholder - 1, *entry);
   return out;

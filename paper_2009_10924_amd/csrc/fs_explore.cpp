@@ -845,13 +845,149 @@ void carry_folds(fs_program* prog) {
   }
   if (blocks >= (1ull << 31)) return;
   std::string entry, log;
-  const std::string source = embedded_prelude() + generate_kernel_with_folds(p, folds, &entry);
+  const std::string source = embedded_prelude() + generate_merged_kernel({p}, {own[0].shape.grid[0]}, folds, &entry);
   std::shared_ptr<GenKernel> kernel;
   if (gen_compile(source, entry.c_str(), &kernel, &log) != 0 || gen_resources(kernel.get()).scratch_bytes > 0 || gen_preload(kernel.get()) != 0) return;
   prog->carrier.step = last;
   prog->carrier.kernel = kernel;
   prog->carrier.shape = own[0].shape;
   prog->carrier.shape.grid[0] = (uint32_t)blocks;
+}
+
+// A step as a member of a merged kernel: its row program, the buffers of its pointers, its workgroups.
+struct Member {
+  RowProgP prog;
+  const BufRef* ptr = nullptr;
+  uint32_t blocks = 0;
+};
+
+// The kernel that the step runs by itself, or the form in which its pack runs it (the results are the same bit for bit); a lone
+// transpose, which moves bits, in its first form.
+bool member_of(const fs_program& prog, int step, Member* m) {
+  const fs_program::Step& s = prog.steps[step];
+  const Launch& own = s.plan->candidates[s.plan->chosen].launches[0];
+  auto generic = [&](const GenericForm& f) {
+    m->prog = s.plan->generic.in_form(f);
+    m->ptr = s.plan->generic.ptr;
+    m->blocks = f.blocks;
+    return true;
+  };
+  if (s.pack >= 0) {
+    const fs_program::Pack& pk = prog.packs[s.pack];
+    if (pk.pack->generated.size() != 1) return false;
+    const size_t at = std::find(pk.steps.begin(), pk.steps.end(), step) - pk.steps.begin();
+    return at < pk.pack->generated[0].forms.size() && generic(pk.pack->generated[0].forms[at]);
+  }
+  if (own.kernel == K_TRANSPOSE_ROWS && !s.plan->generic.forms.empty()) return generic(s.plan->generic.forms[0]);
+  if (own.kernel != K_ROW_GENERATED || own.shape.block[0] != 256 || own.args.u.prog.col_chunks > 1) return false;
+  m->prog = own.args.u.prog;
+  m->ptr = own.ptr;
+  m->blocks = own.shape.grid[0];
+  return true;
+}
+
+// The whole program in as few launches as its dependences allow: a step reads what others made one launch earlier or
+// before; folds of column sums run one launch after the step; steps with room to choose (and with nobody waiting for them) go
+// where the fewest bytes are, those without column sums also into the launch that finishes the last folds.  What the external
+// computations make is in place when the whole program is run, so they tie nothing together here (stage by stage, every step
+// keeps its launch).  What a launch that follows another one costs, 2.5 to 3.5 us, and what latency-bound steps (LayerNorm backward:
+// 256 workgroups, 2.5 times its bytes) leave of the memory's rate is what this saves.  Measured (us, step by step with the folds in
+// the last step's launch / merged), backward pass through a transformer block: 0.2 MB 19.4 / 12.2, 15 MB 25.6 / 20.1, 50 MB 28.0 / 21.9,
+// 201 MB 47.4 / 39.7, 319 MB 64.1 / 55.0, and eight more between them, 1.16 to 1.65 times: never slower, so the evaluator is not asked.
+// Only where every step is a generated kernel of 256 threads (or a transpose of rows) and no two tensors share a part of the workspace.
+void merge_steps(fs_program* prog) {
+  const int ns = (int)prog->steps.size();
+  if (!codegen_enabled() || ns < 2 || ns > 12) return;   // (twelve: what compiles in a few seconds)
+  std::vector<Member> members(ns);
+  typedef std::pair<int32_t, int64_t> Place;   // of a tensor between steps: an output of the graph or a part of the workspace
+  auto place = [](const BufRef& r) { return Place(r.kind, r.kind == BUF_OUTPUT ? r.slot : r.offset); };
+  std::map<Place, int> maker;
+  std::set<Place> by_fold;
+  std::map<int64_t, int64_t> scratch;   // the tensors in the workspace: where they begin and end
+  std::vector<std::vector<size_t>> folds(ns);
+  for (int s = 0; s < ns; ++s) {
+    if (!member_of(*prog, s, &members[s])) return;
+    const fs_program::Step& st = prog->steps[s];
+    for (size_t k = 0; k < st.out.size(); ++k) {
+      if (!maker.emplace(place(st.out[k]), s).second) return;
+      if (st.out[k].kind == BUF_WORKSPACE) scratch[st.out[k].offset] = st.out[k].offset + st.plan->output_bytes[k];
+    }
+    const std::vector<Launch>& launches = st.plan->candidates[st.plan->chosen].launches;
+    for (size_t l = 1; l < launches.size(); ++l) {
+      if (launches[l].kernel != K_COLFOLD) return;
+      folds[s].push_back(l);
+      for (int a = 1; a < 3; ++a)
+        if (launches[l].ptr[a].kind == BUF_OUTPUT) by_fold.insert(place(st.out[launches[l].ptr[a].slot]));
+    }
+  }
+  int64_t end = 0;
+  for (const auto& t : scratch) {   // memory that serves two tensors in turn ties their steps to their order
+    if (t.first < end) return;
+    end = t.second;
+  }
+  std::vector<int> at(ns, 0);              // a step's launch
+  std::vector<char> tied(ns, 0);           // it reads from another step, or another one from it
+  int last = 0;
+  for (int s = 0; s < ns; ++s) {
+    for (const BufRef& r : prog->steps[s].in) {
+      if (r.kind == BUF_INPUT) continue;
+      const auto made = maker.find(place(r));
+      if (made == maker.end() || made->second >= s || by_fold.count(place(r))) return;
+      at[s] = std::max(at[s], at[made->second] + 1);
+      tied[s] = tied[made->second] = 1;
+    }
+    last = std::max(last, at[s] + (folds[s].empty() ? 0 : 1));
+  }
+  const int n = last + 1;
+  if (n >= prog->info.n_kernels) return;
+  std::vector<int64_t> bytes(n, 0);
+  std::vector<int> free_steps;
+  for (int s = 0; s < ns; ++s) {
+    if (tied[s]) bytes[at[s]] += prog->steps[s].plan->bytes_min;
+    else free_steps.push_back(s);
+  }
+  std::stable_sort(free_steps.begin(), free_steps.end(), [&](int a, int b) { return prog->steps[a].plan->bytes_min > prog->steps[b].plan->bytes_min; });
+  for (int s : free_steps) {
+    for (int l = 0; l <= last - (folds[s].empty() ? 0 : 1); ++l)
+      if (bytes[l] < bytes[at[s]]) at[s] = l;
+    bytes[at[s]] += prog->steps[s].plan->bytes_min;
+  }
+  std::vector<fs_program::Merged> merged(n);
+  for (int l = 0; l < n; ++l) {
+    fs_program::Merged& m = merged[l];
+    std::vector<RowProgP> progs;
+    std::vector<uint32_t> blocks;
+    std::vector<Launch> fold_launches;
+    uint64_t total = 0;
+    // column sums first: their workgroups work the longest
+    for (int sums = 1; sums >= 0; --sums)
+      for (int s = 0; s < ns; ++s)
+        if (at[s] == l && (members[s].prog.n_colsum > 0) == (sums == 1)) m.steps.push_back(s);
+    for (int s : m.steps) {
+      progs.push_back(members[s].prog);
+      blocks.push_back(members[s].blocks);
+      total += members[s].blocks;
+      for (int slot : generated_ptr_slots(members[s].prog)) m.operands.push_back({s, members[s].ptr[slot]});
+    }
+    for (int s = 0; s < ns; ++s) {
+      if (at[s] != l - 1) continue;
+      for (size_t f : folds[s]) {
+        const Launch& launch = prog->steps[s].plan->candidates[prog->steps[s].plan->chosen].launches[f];
+        m.folds.push_back({s, f});
+        fold_launches.push_back(launch);
+        total += launch.shape.grid[0];
+        for (int a = 0; a < 3; ++a) m.operands.push_back({s, launch.ptr[a]});
+      }
+    }
+    if (total == 0 || total >= (1ull << 31) || m.operands.size() > kMergedMaxOperands) return;
+    std::string entry, log;
+    const std::string source = embedded_prelude() + generate_merged_kernel(progs, blocks, fold_launches, &entry);
+    if (gen_compile(source, entry.c_str(), &m.kernel, &log) != 0 || gen_resources(m.kernel.get()).scratch_bytes > 0 || gen_preload(m.kernel.get()) != 0) return;
+    m.shape = LaunchShape{};
+    m.shape.grid[0] = (uint32_t)total;
+    m.shape.block[0] = 256;
+  }
+  prog->merged = std::move(merged);
 }
 
 void fill_info(const Explorer& ex, fs_program* prog, int32_t beam_plans, double f_total_us, int64_t workspace_bytes) {
@@ -998,6 +1134,9 @@ fs_status fs_explore(const fs_graph* g, const fs_explore_opts* opts, fs_program*
   fill_info(ex, prog, (int32_t)plans.size(), built[best].f, workspace);
   prog->n_inputs = (int32_t)g->inputs.size();
   prog->n_outputs = (int32_t)g->outputs.size();
+  for (int t : g->inputs) prog->input_bytes.push_back(g->tensors[t].numel() * dtype_bytes(g->tensors[t].dtype));
+  for (int t : g->outputs) prog->output_bytes.push_back(g->tensors[t].numel() * dtype_bytes(g->tensors[t].store_as));
+  if (joint_folds && pack_tiny) merge_steps(prog);
   *out = prog;
   return FS_OK;
 } catch (...) {

@@ -157,6 +157,7 @@ struct fs_pack {
     std::shared_ptr<fs::GenKernel> kernel;
     uint32_t blocks = 0;
     std::vector<PtrRef> ptrs;
+    std::vector<fs::GenericForm> forms;   // the members', in their order
   };
   std::vector<GenLaunch> generated;    // non-empty: these run instead of `tables`
   fs_pack_info info{};
@@ -185,9 +186,12 @@ std::string generated_kernel_entry(const RowProgP& p);   // fs_gen_row_<hash of 
 // order of the kernel's pointer table; *entry: the kernel's name.
 std::string generate_pack_kernel(const std::vector<RowProgP>& members, const std::vector<uint32_t>& blocks,
                                  std::vector<std::vector<int>>* ptr_slots, std::string* entry);
-// Source (without the embedded device headers that every generated kernel has) of the kernel of `p` (256 threads, no column sums,
-// one row per lane group) that runs the K_COLFOLD launches `folds` as well; its parameters are p's pointers, then three per fold.
-std::string generate_kernel_with_folds(const RowProgP& p, const std::vector<Launch>& folds, std::string* entry);
+// Source (without the embedded device headers that every generated kernel has) of one kernel of 256 threads that runs the row
+// programs `members` (blocks[m] workgroups each) and the K_COLFOLD launches `folds`; its parameters are the members' pointers
+// (generated_ptr_slots()), then three per fold.
+std::string generate_merged_kernel(const std::vector<RowProgP>& members, const std::vector<uint32_t>& blocks, const std::vector<Launch>& folds,
+                                   std::string* entry);
+int64_t column_sum_lds_bytes(const RowProgP& p);   // LDS in which a workgroup folds its rows' column sums
 std::string embedded_prelude();
 // Pairs of row reductions "rmax; acc - max; exp; rsum" that a row worked through in chunks gathers in one pass
 // (online[q] = 1 for the first of each pair; `online` may be null); returns their number.

@@ -117,6 +117,8 @@ bool compile_packed(const fs_plan* const* plans, const std::vector<const Generic
   }
   *vgprs = res.vgprs;
   gl->blocks = (uint32_t)total;
+  gl->forms.clear();
+  for (const GenericForm* f : forms) gl->forms.push_back(*f);
   return true;
 }
 

@@ -84,6 +84,12 @@ int64_t fs_program_describe(const fs_program* p, char* text, size_t capacity) tr
     if (p->carrier.step >= 0) s += " with_step=" + std::to_string(p->carrier.step);   // one launch for both, counted here
     s += "\n";
   }
+  for (size_t j = 0; j < p->merged.size(); ++j) {
+    std::string steps, folds;
+    for (int m : p->merged[j].steps) steps += (steps.empty() ? "" : ",") + std::to_string(m);
+    for (const fs_program::JointFold& f : p->merged[j].folds) folds += (folds.empty() ? "" : ",") + std::to_string(f.step);
+    s += "merged " + std::to_string(j) + " of " + std::to_string(p->merged.size()) + " steps=" + steps + " folds_of=" + folds + "\n";
+  }
   const size_t need = s.size() + 1;
   if (capacity > 0) {
     const size_t n = std::min(capacity - 1, s.size());
@@ -96,6 +102,15 @@ int64_t fs_program_describe(const fs_program* p, char* text, size_t capacity) tr
 }
 
 }  // extern "C"
+
+// Whether an input shares memory with an output: the steps must then run in their order.
+static bool inputs_meet_outputs(const fs_program* p, const void* const* inputs, void* const* outputs) {
+  for (int i = 0; i < p->n_inputs; ++i)
+    for (int o = 0; o < p->n_outputs; ++o)
+      if ((uintptr_t)inputs[i] < (uintptr_t)outputs[o] + (uint64_t)p->output_bytes[o] && (uintptr_t)outputs[o] < (uintptr_t)inputs[i] + (uint64_t)p->input_bytes[i])
+        return true;
+  return false;
+}
 
 // The steps of stages first_stage..last_stage; the joint fold launches go with the program's last stage.
 static fs_status run_program(const fs_program* p, int32_t first_stage, int32_t last_stage, const void* const* inputs,
@@ -130,6 +145,16 @@ static fs_status run_program(const fs_program* p, int32_t first_stage, int32_t l
       default: return nullptr;
     }
   };
+  if (!p->merged.empty() && first_stage == 0 && last_stage == p->info.n_stages - 1 && !inputs_meet_outputs(p, inputs, outputs)) {
+    for (const fs_program::Merged& m : p->merged) {
+      void* ptrs[kMergedMaxOperands];
+      size_t n = 0;
+      for (const fs_program::Merged::Operand& o : m.operands) ptrs[n++] = operand(p->steps[o.step], o.ref);
+      const int err = gen_launch(m.kernel.get(), ptrs, sizeof(void*) * n, m.shape, hip_stream);
+      if (err != 0) return fail(FS_ERR_HIP, "fs_program_execute: launching merged steps failed: %s", hip_error_text(err));
+    }
+    return FS_OK;
+  }
   std::vector<char> pack_done(p->packs.size(), 0);
   std::vector<const void*> in;
   std::vector<void*> out;

@@ -13,6 +13,8 @@ void fs_pack_destroy(fs_pack* p);
 
 using namespace fs;
 
+constexpr size_t kMergedMaxOperands = 256;   // 2 KB of kernel arguments
+
 struct fs_program {
   struct Step {
     std::vector<int> ops;               // graph op indices
@@ -38,6 +40,18 @@ struct fs_program {
     std::shared_ptr<GenKernel> kernel;
     LaunchShape shape;
   } carrier;
+  // The whole program in fewer launches than step by step: each one kernel over steps (and folds of earlier ones' column sums)
+  // that do not depend on each other (see merge_steps).  Empty: none, the steps run one by one.
+  struct Merged {
+    std::vector<int> steps;
+    std::vector<JointFold> folds;
+    struct Operand { int step; BufRef ref; };   // of one of the step's launches
+    std::vector<Operand> operands;              // in the order of the kernel's parameters
+    std::shared_ptr<GenKernel> kernel;
+    LaunchShape shape;
+  };
+  std::vector<Merged> merged;
+  std::vector<int64_t> input_bytes, output_bytes;
   fs_program_info info{};
   int32_t n_inputs = 0, n_outputs = 0;
   ~fs_program() {

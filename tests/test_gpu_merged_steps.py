@@ -1,0 +1,73 @@
+"""A program run as a whole takes its independent steps, and the folds of column sums, in few launches; stage by stage every step
+has its own.  Both store the same bits, run after run on one workspace, also where an output shares memory with an input (which
+sends the whole run step by step)."""
+import numpy as np
+import pytest
+
+from paper_2009_10924_amd import binding as B
+from workloads import make_inputs, transformer_block_backward_graph
+
+pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not B.codegen_available(), reason="needs the run-time compiler")]
+
+
+def _runner(spec, graph):
+    import torch
+    inp = make_inputs(spec, seed=6)
+    stream = torch.cuda.current_stream().cuda_stream
+
+    def run(prog, staged, times=1, shared=()):
+        ins = [B.to_device(inp[t.name], t.dtype) for t in spec.inputs]
+        outs = B.alloc_outputs(spec)
+        for t in outs:
+            t.fill_(float("nan"))
+        for o, i in shared:
+            outs[o] = ins[i]
+        ws = prog.make_workspace()
+        ws.fill_(255)
+        a, b = [t.data_ptr() for t in ins], [t.data_ptr() for t in outs]
+        for _ in range(times):
+            if staged:
+                for k in range(prog.info["n_stages"]):
+                    prog.bind_stage(k, a, b, ws.data_ptr(), ws.numel(), stream)()
+            else:
+                prog.bind(a, b, ws.data_ptr(), ws.numel(), stream)()
+        torch.cuda.synchronize()
+        return [B.to_host(t, dt).view(np.uint8).copy() for (_, dt), t in zip(spec.outputs, outs)]
+    return run
+
+
+def _merged(prog):
+    return [l for l in prog.describe().splitlines() if l.startswith("merged ")]
+
+
+# one row per lane group and many, rows on workgroups, packed transposes, a batch of few rows, the benchmark's block
+@pytest.mark.parametrize("dims,dtype", [((2, 16, 4, 32, 128), "bf16"), ((6, 16, 4, 32, 512), "f16"), ((3, 34, 12, 64, 3072), "f16"), ((5, 67, 8, 64, 2048), "bf16"),
+                                        ((29, 88, 12, 32, 1536), "f16"), ((32, 128, 12, 64, 3072), "bf16")])
+def test_whole_run_equals_stage_by_stage(dims, dtype):
+    spec = transformer_block_backward_graph(*dims, dtype)
+    graph = B.Graph.from_spec(spec)
+    prog = B.Program(graph)
+    apart = B.Program(graph, no_joint_folds=True)
+    lines = _merged(prog)
+    assert len(lines) == 3 < prog.info["n_kernels"] and not _merged(apart), prog.describe()
+    run = _runner(spec, graph)
+    want = run(prog, True)
+    for got in (run(prog, False), run(prog, False, times=3), run(apart, False)):
+        for (name, _), a, b in zip(spec.outputs, got, want):
+            assert np.array_equal(a, b), name
+
+
+def test_an_output_that_shares_memory_with_an_input():
+    """The gradient of the scores over the gradient of the probabilities: every step still finds its inputs."""
+    spec = transformer_block_backward_graph(3, 24, 4, 32, 128, "bf16")
+    graph = B.Graph.from_spec(spec)
+    prog = B.Program(graph)
+    assert _merged(prog)
+    names = [t.name for t in spec.inputs]
+    shared = [(k, names.index("up_probs")) for k, (n, _) in enumerate(spec.outputs)
+              if any(o.out == n and o.opcode != "transpose" for o in spec.ops) and dict((t.name, tuple(t.dims)) for t in spec.inputs)["up_probs"]
+              == tuple(B.output_shapes(spec)[n])]
+    assert len(shared) == 1
+    run = _runner(spec, graph)
+    for (name, _), a, b in zip(spec.outputs, run(prog, False, shared=shared), run(prog, True, shared=shared)):
+        assert np.array_equal(a, b), name
