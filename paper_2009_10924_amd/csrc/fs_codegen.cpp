@@ -102,7 +102,7 @@ int online_reduction_pairs(const RowProgP& p, std::vector<char>* online) {
 // Rows that end inside a step may store their last step whole (GenRow, AGAIN) where every element has been read before
 // any is stored: behind a row reduction, unless a later pass reads the row again.
 static bool stores_again(const RowProgP& p) {
-  if (p.cols % (uint32_t)p.vec == 0 || (p.col_chunks > 1 && p.col_kept < p.col_chunks)) return false;
+  if (p.cols % (uint32_t)p.vec == 0 || (p.col_chunks > 1 && p.col_kept + p.col_lds < p.col_chunks)) return false;
   for (int i = 0; i < p.n_instr; ++i) {
     if (p.instr[i].op == PO_STORE) return false;
     if (p.instr[i].op == PO_RSUM || p.instr[i].op == PO_RMAX || p.instr[i].op == PO_RSUMSQ) return true;
@@ -334,11 +334,31 @@ std::string chunked_body(const RowProgP& p, const char* entry) {
   for (uint32_t c = 0; c < kept; ++c)
     for (int i = 0; i < p.n_full; ++i)
       s += fmt("  %s::Raw<%s> kept%d_%u;\n", chunk_type(c), storage_type(p.full_dt[i]), i, c);
-  // one chunk's share of a pass, for the row object `row` in scope; kept_chunk >= 0: that chunk stays in registers
+  // The next `in_lds` chunks stay in LDS instead: a lane keeps its own steps there and reads them back itself, so nothing waits for
+  // anybody.  What is left is read from memory again in every pass.
+  const uint32_t in_lds = (uint32_t)std::max(0, std::min(p.col_lds, p.col_chunks - (int)kept)), held = kept + in_lds;
+  for (int i = 0; i < p.n_full && in_lds > 0; ++i)
+    s += fmt("  __shared__ __attribute__((aligned(16))) Row::Step<%s> held%d[%u][%d][%u];\n", storage_type(p.full_dt[i]), i, in_lds, p.vecs_per_lane, L);
+  auto operand_at = [&](int i) {   // the row of operand i, and whether its loads are its last ones if its chunk is held
+    return std::pair<std::string, const char*>(((p.full_bcast >> i) & 1u) ? stretched_row(p.ms[i]) : std::string("(size_t)row.row_c"),
+                                               ((p.full_bcast >> i) & 1u) ? "false" : "true");
+  };
+  auto load_into = [&](const char* name, uint32_t c) {   // chunk c of every operand into <name><operand>_<c>
+    std::string t = fmt("  {\n  const %s row(fs_block, 0, %uu);\n", chunk_type(c), c * chunk);
+    for (int i = 0; i < p.n_full; ++i)
+      t += fmt("  %s%d_%u = row.load<%s, %s>(a.full[%d], %s);\n", name, i, c, storage_type(p.full_dt[i]), operand_at(i).second, i, operand_at(i).first.c_str());
+    return t + "  }\n";
+  };
+  // one chunk's share of a pass, for the row object `row` in scope; kept_chunk >= 0: that chunk is held
   auto piece = [&](int pass, bool last_chunk, int kept_chunk, bool preloaded = false) {
     std::string t;
     const bool last_pass = pass == n_red;
     for (int i = 0; i < p.n_full; ++i) {
+      if (kept_chunk >= (int)kept) {   // in LDS, from the first pass on
+        if (pass == 0) t += fmt("  const auto& raw_full%d = way%d_%d;\n  raw_full%d.park(held%d[%d]);\n", i, i, kept_chunk, i, i, kept_chunk - (int)kept);
+        else t += fmt("  %s::Raw<%s> raw_full%d;\n  raw_full%d.fetch(held%d[%d]);\n", chunk_type(kept_chunk), storage_type(p.full_dt[i]), i, i, i, kept_chunk - (int)kept);
+        continue;
+      }
       const bool stretched = ((p.full_bcast >> i) & 1u) != 0;
       const std::string at = stretched ? stretched_row(p.ms[i]) : std::string("(size_t)row.row_c");
       if (kept_chunk >= 0 && (pass > 0 || preloaded)) {
@@ -380,25 +400,26 @@ std::string chunked_body(const RowProgP& p, const char* entry) {
     s += "  {\n";
     if (fused) s += "  float m_run = -3.4028234664e38f, s_run = 0.0f;\n";
     else if (pass < n_red) s += fmt("  float part = %s;\n", is_max[pass] ? "-__builtin_huge_valf()" : "0.0f");
-    // the kept chunks, one block each
+    // the held chunks, one block each
     std::string in_registers;
     // A first pass that also exponentiates (a fused maximum + sum) has more live values per chunk than one that only
     // compares; left to itself the compiler interleaves the chunks' arithmetic and runs out of registers.  So the loads
     // of all kept chunks are issued first, and the chunks are then worked through one after the other, each behind a
     // scheduling barrier (a chunk's arithmetic starts when its own loads have landed).
     const bool preload = fused && pass == 0 && kept > 0;
+    // (chunks bound for LDS are loaded one ahead of the one that is worked on)
+    if (pass == 0)
+      for (uint32_t c = kept; c < held; ++c)
+        for (int i = 0; i < p.n_full; ++i) in_registers += fmt("  %s::Raw<%s> way%d_%u;\n", chunk_type(c), storage_type(p.full_dt[i]), i, c);
     if (preload) {
-      for (uint32_t c = 0; c < kept; ++c)
-        for (int i = 0; i < p.n_full; ++i) {
-          const bool stretched = ((p.full_bcast >> i) & 1u) != 0;
-          const std::string at = stretched ? stretched_row(p.ms[i]) : std::string("(size_t)row.row_c");
-          in_registers += fmt("  {\n  const %s row(fs_block, 0, %uu);\n  kept%d_%u = row.load<%s, %s>(a.full[%d], %s);\n  }\n", chunk_type(c),
-                              c * chunk, i, c, storage_type(p.full_dt[i]), stretched ? "false" : "true", i, at.c_str());
-        }
+      for (uint32_t c = 0; c < kept; ++c) in_registers += load_into("kept", c);
+      if (in_lds > 0) in_registers += load_into("way", kept);
       in_registers += "  __builtin_amdgcn_sched_barrier(0);\n";
     }
-    for (uint32_t c = 0; c < kept; ++c) {
+    for (uint32_t c = 0; c < held; ++c) {
       const bool is_tail = c == NC - 1u;
+      if (pass == 0 && c == kept && !preload) in_registers += load_into("way", c);
+      if (pass == 0 && c >= kept && c + 1u < held) in_registers += load_into("way", c + 1u);
       in_registers += fmt("  {\n  const %s row(fs_block, 0, %uu);\n", chunk_type(c), c * chunk) + piece(pass, is_tail, (int)c, preload) + "  }\n";
       if (preload) in_registers += "  __builtin_amdgcn_sched_barrier(0);\n";
     }
@@ -406,11 +427,11 @@ std::string chunked_body(const RowProgP& p, const char* entry) {
     // starts with the chunks the pass before read last, which the caches are likeliest to hold still
     const bool backwards = (walk & 1) != 0;
     std::string from_memory_whole, from_memory_last;
-    if (kept < NC - 1u)
+    if (held < NC - 1u)
       from_memory_whole = fmt("#pragma unroll 1\n  for (uint32_t chunk = %uu; chunk < %uu; ++chunk) {\n  const Row row(fs_block, 0, %s * %uu);\n",
-                              kept, NC - 1u, backwards ? fmt("(%uu - chunk)", NC - 2u + kept).c_str() : "chunk", chunk) +
+                              held, NC - 1u, backwards ? fmt("(%uu - chunk)", NC - 2u + held).c_str() : "chunk", chunk) +
                           piece(pass, false, -1) + "  }\n";
-    if (kept < NC) from_memory_last = fmt("  {\n  const TailRow row(fs_block, 0, %uu);\n", (NC - 1u) * chunk) + piece(pass, true, -1) + "  }\n";
+    if (held < NC) from_memory_last = fmt("  {\n  const TailRow row(fs_block, 0, %uu);\n", (NC - 1u) * chunk) + piece(pass, true, -1) + "  }\n";
     s += backwards ? from_memory_last + from_memory_whole + in_registers : in_registers + from_memory_whole + from_memory_last;
     if (fused) {
       // the lanes' maxima meet first; every lane then brings its sum to the row's maximum before the sums meet

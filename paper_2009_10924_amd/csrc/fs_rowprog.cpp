@@ -697,6 +697,7 @@ struct Compiler {
     p.col_tiles = 1;
     p.col_chunks = 1;
     p.col_kept = 0;
+    p.col_lds = 0;
     p.stream = streams_inputs(g) ? 1 : 0;
     if (n_colsum > 0) interpretable = false;
     return n_out + n_rout + n_colsum == (int)g.outputs.size();
@@ -716,6 +717,7 @@ struct Shape {
   uint32_t R = 1, CT = 1;
   uint32_t NC = 1;   // > 1: the row is worked through in NC chunks of L * K steps (rows beyond any workgroup's registers)
   uint32_t kept = 0; // of those, the first `kept` stay in registers in storage form after the first pass
+  uint32_t lds = 0;  // ... and the next `lds` in LDS
 };
 
 // Step widths to offer.  A pattern whose 16-bit vector inputs ask for 8 elements per step may also move float32
@@ -806,10 +808,23 @@ std::vector<Shape> enumerate_shapes(const Compiler& c, int vec, bool interpretab
         if (c.n_reductions == 0 || T == 256) continue;
         int regs_per_chunk = 0;   // registers a lane needs to keep one chunk of every row operand
         for (int i = 0; i < c.p.n_full; ++i) regs_per_chunk += (int)K * ((vec * dtype_bytes(c.p.full_dt[i]) + 3) / 4);
+        int lds_per_chunk = 0;    // bytes a lane keeps of one
+        for (int i = 0; i < c.p.n_full; ++i) lds_per_chunk += (int)K * vec * dtype_bytes(c.p.full_dt[i]);
         const int body = 24 + (int)K * vec * (c.p.n_regs + 1 + (c.p.n_col > 0 ? 1 : 0)) + 2 * (int)K * c.p.n_full;
         const int room = 512 / (int)(T / 256) - body - 8;
         if (regs_per_chunk == 0 || room < regs_per_chunk) continue;
         t.kept = std::min<uint32_t>(t.NC, (uint32_t)(room / regs_per_chunk));
+        // chunks that the registers have no room for may stay in LDS, as much of it as leaves the compute unit its 2048 / T
+        // workgroups' registers; where the compiled kernel would spill, the form with one chunk less in registers is the next.  (us, the rest read from memory in each pass / held in LDS: log-softmax f32
+        // [809,122867] 174.4 / 164.1, [30,131072] 16.2 / 14.4, bf16 [1500,128257], which then lies on the grid, 179.2 / 150.3; bf16
+        // [4096,128256], one chunk of eight, and f32 [1000,80000], one of ten, level)
+        const uint32_t room_lds = (uint32_t)((T == 1024 ? 156 : T == 512 ? 78 : 38) * 1024 / ((int)T * lds_per_chunk));
+        for (uint32_t less = 0; less < 2 && t.kept > less && t.kept < t.NC && room_lds > 0; ++less) {
+          Shape u = t;
+          u.kept = t.kept - less;
+          u.lds = std::min<uint32_t>(t.NC - u.kept, room_lds);
+          if (t.NC - u.kept - u.lds <= 64) shapes.push_back(u);
+        }
         if (t.NC - t.kept <= 64) shapes.push_back(t);   // the kept chunks are written out one by one: keep the source short
       }
   if (c.n_colsum == 0) {
@@ -858,6 +873,7 @@ void fill_launch(const fs_graph& g, const Compiler& c, int vec, const Shape& s, 
   q.col_tiles = (int32_t)s.CT;
   q.col_chunks = (int32_t)s.NC;
   q.col_kept = (int32_t)s.kept;
+  q.col_lds = (int32_t)s.lds;
   l->args.u.prog = q;
   auto in_ref = [&](int32_t t) {   // a transposed view binds the buffer of the input it views
     BufRef r;
@@ -970,20 +986,22 @@ void make_generated(const Compiler& c, int vec, const Shape& s, Candidate* cand)
   if (s.NC > 1) {
     // a pass over the row per reduction re-reads the operands (counted as device-memory traffic: the rows in flight
     // are larger than the caches in general) and repeats the arithmetic before its reduction
-    if (s.kept > 0)
-      snprintf(cand->info.kernel, sizeof cand->info.kernel, "row_generated<v%d,K%d,L%u,I%d,R%d,chunks%u,kept%u>", vec, s.K, s.L, base.n_instr,
-               base.n_regs, s.NC, s.kept);
-    else
-      snprintf(cand->info.kernel, sizeof cand->info.kernel, "row_generated<v%d,K%d,L%u,I%d,R%d,chunks%u>", vec, s.K, s.L, base.n_instr,
-               base.n_regs, s.NC);
+    const std::string held = (s.kept > 0 ? ",kept" + std::to_string(s.kept) : std::string()) + (s.lds > 0 ? ",lds" + std::to_string(s.lds) : std::string());
+    snprintf(cand->info.kernel, sizeof cand->info.kernel, "row_generated<v%d,K%d,L%u,I%d,R%d,chunks%u%s>", vec, s.K, s.L, base.n_instr, base.n_regs, s.NC,
+             held.c_str());
     double in_bytes = 0;
     int regs_per_chunk = 0;
     for (int i = 0; i < base.n_full; ++i) {
       if (!((base.full_bcast >> i) & 1u)) in_bytes += (double)dtype_bytes(base.full_dt[i]) * base.rows * base.cols;
       regs_per_chunk += s.K * ((vec * dtype_bytes(base.full_dt[i]) + 3) / 4);
     }
-    in_bytes *= 1.0 - (double)s.kept / s.NC;   // chunks kept in registers are not read again
-    gc.vgpr_estimate += regs_per_chunk * (int)s.kept;
+    in_bytes *= 1.0 - (double)(s.kept + s.lds) / s.NC;   // chunks held in registers or LDS are not read again
+    gc.vgpr_estimate += regs_per_chunk * (int)(s.kept + (s.lds > 0 ? 1 : 0));
+    int lane_bytes = 0;
+    for (int i = 0; i < base.n_full; ++i) lane_bytes += s.K * vec * dtype_bytes(base.full_dt[i]);
+    cand->info.lds_bytes += (int32_t)(s.lds * s.L) * lane_bytes;
+    gc.lds_bytes_per_block = cand->info.lds_bytes;
+    gc.lds_traffic_bytes = 2.0 * s.lds * s.L * lane_bytes * base.rows;
     // ... unless the rows the resident workgroups are working on fit the memory-side cache (with room for the
     // outputs passing through): wide workgroups keep fewer rows in flight
     const double wgs_per_cu = std::max(1.0, std::floor(2048.0 / s.L));

@@ -267,9 +267,19 @@ struct GenRow {
 
   // the lane's K steps of row `at_row` of a [.., COLS] tensor, in storage form; STREAM: read once, so the loads may
   // carry the streaming hint and then do not displace the operands that every row re-reads from cache
+  template <typename T> using Step = StepBits<VEC * (int)sizeof(T), alignment<T>()>;
   template <typename T>
   struct Raw {
-    StepBits<VEC * (int)sizeof(T), alignment<T>()> w[K];
+    Step<T> w[K];
+    // (a lane's own places in LDS: nobody else reads or writes them)
+    __device__ __forceinline__ void park(Step<T> (&lds)[K][L]) const {
+#pragma unroll
+      for (int k = 0; k < K; ++k) lds[k][threadIdx.x] = w[k];
+    }
+    __device__ __forceinline__ void fetch(const Step<T> (&lds)[K][L]) {
+#pragma unroll
+      for (int k = 0; k < K; ++k) w[k] = lds[k][threadIdx.x];
+    }
     __device__ __forceinline__ void forget_contents() {
 #pragma unroll
       for (int k = 0; k < K; ++k) fsk::forget_contents(w[k]);
@@ -280,7 +290,7 @@ struct GenRow {
     Raw<T> r;
     const T* base = static_cast<const T*>(p) + at_row * ROW_STRIDE + col0;
 #pragma unroll
-    for (int k = 0; k < K; ++k) r.w[k] = StepBits<VEC * (int)sizeof(T), alignment<T>()>::template load<STREAM && PAST_CACHES>(base + first_of(k));
+    for (int k = 0; k < K; ++k) r.w[k] = Step<T>::template load<STREAM && PAST_CACHES>(base + first_of(k));
     return r;
   }
 

@@ -270,6 +270,7 @@ struct RowProgP {
                                        // lanes_per_row * vecs_per_lane steps, once per row reduction and once more for the stores
   int32_t col_kept;                    // of those chunks, the first col_kept stay in registers in storage form after the first
                                        // pass (the later passes do not read them again)
+  int32_t col_lds;                     // ... and the next col_lds of them in LDS
   int32_t stream;                      // generated kernels: 1 = row inputs are read past the caches (see streams_inputs)
   ProgInstr instr[kProgMaxInstr];
 };

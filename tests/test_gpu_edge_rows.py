@@ -20,7 +20,7 @@ def _on_grid(spec, **opts):
 # every phase of a row against the grid (17 rows), one row, a last step of one element and of seven, rows that need the lane's last step
 SHAPES = [("scores", 17, 9), ("scores", 3, 15), ("scores", 17, 57), ("scores", 5, 119), ("scores", 17, 121), ("scores", 9, 249), ("scores", 1, 505),
           ("softmax", 17, 1025), ("softmax", 2, 2041), ("log_softmax", 17, 2049), ("log_softmax", 9, 8191), ("log_softmax", 1, 16385),
-          ("log_softmax", 9, 50257), ("log_softmax", 3, 65529)]
+          ("log_softmax", 9, 50257), ("log_softmax", 3, 65529), ("log_softmax", 3, 114681), ("log_softmax", 2, 131065)]
 
 
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
@@ -55,3 +55,27 @@ def test_in_place(rows, cols, dtype):
     plan.execute_ptrs([x.data_ptr()], [x.data_ptr()], 0, 0, torch.cuda.current_stream().cuda_stream)
     torch.cuda.synchronize()
     assert np.array_equal(B.to_host(x, dtype).view(np.uint8), raw[spec.outputs[0][0]].view(np.uint8))
+
+
+@pytest.mark.parametrize("kind,cols,dtype", [("softmax", 74000, "f32"), ("log_softmax", 106496, "f32"), ("log_softmax", 131072, "f32"), ("log_softmax", 90113, "f32"),
+                                             ("softmax", 114688 + 8, "bf16"), ("log_softmax", 128256, "f16")])
+def test_chunks_in_lds(kind, cols, dtype):
+    """Rows beyond a workgroup's registers whose next chunks wait in LDS, with chunks left for memory and without, and a row that ends
+    just behind one; three passes over a row and two."""
+    spec = (softmax_graph if kind == "softmax" else log_softmax_graph)(3, cols, dtype)
+    inp = make_inputs(spec, seed=cols)
+    ref = O.evaluate(spec, inp)
+    kernels = [c["kernel"] for c in B.Plan(B.Graph.from_spec(spec), "auto").candidates()]
+    assert any(",lds" in k for k in kernels), kernels
+    note(f"{spec.name}: worst {all_candidates(spec, inp, ref, floors_for(spec, inp, ref), repeat=2, unfused=False)}")
+
+
+def test_chunks_in_lds_of_several_operands():
+    """Two row operands, a column vector and a row statistic: RMS norm backward has column sums, so its forward with a residual."""
+    from workloads import add_bias_layernorm_graph
+    spec = add_bias_layernorm_graph(2, 70000, in_dtype="f32", out_dtype="bf16")
+    inp = make_inputs(spec, seed=1)
+    ref = O.evaluate(spec, inp)
+    kernels = [c["kernel"] for c in B.Plan(B.Graph.from_spec(spec), "auto").candidates()]
+    assert any(",lds" in k for k in kernels), kernels
+    note(f"{spec.name}: worst {all_candidates(spec, inp, ref, floors_for(spec, inp, ref), repeat=2, unfused=False)}")
