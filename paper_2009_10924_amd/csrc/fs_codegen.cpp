@@ -354,9 +354,16 @@ std::string chunked_body(const RowProgP& p, const char* entry) {
     std::string t;
     const bool last_pass = pass == n_red;
     for (int i = 0; i < p.n_full; ++i) {
-      if (kept_chunk >= (int)kept) {   // in LDS, from the first pass on
-        if (pass == 0) t += fmt("  const auto& raw_full%d = way%d_%d;\n  raw_full%d.park(held%d[%d]);\n", i, i, kept_chunk, i, i, kept_chunk - (int)kept);
-        else t += fmt("  %s::Raw<%s> raw_full%d;\n  raw_full%d.fetch(held%d[%d]);\n", chunk_type(kept_chunk), storage_type(p.full_dt[i]), i, i, i, kept_chunk - (int)kept);
+      if (kept_chunk >= (int)kept) {   // in LDS, from the first pass on (registers are told to forget as below)
+        const int at = kept_chunk - (int)kept;
+        if (pass > 0)
+          t += fmt("  %s::Raw<%s> raw_full%d;\n  raw_full%d.fetch(held%d[%d]);\n  raw_full%d.forget_contents();\n", chunk_type(kept_chunk),
+                   storage_type(p.full_dt[i]), i, i, i, at, i);
+        else if (preloaded)
+          t += fmt("  way%d_%d.forget_contents();\n  const auto& raw_full%d = way%d_%d;\n  raw_full%d.park(held%d[%d]);\n", i, kept_chunk, i, i, kept_chunk, i, i, at);
+        else
+          t += fmt("  const auto raw_full%d = row.load<%s, %s>(a.full[%d], %s);\n  raw_full%d.park(held%d[%d]);\n", i, storage_type(p.full_dt[i]),
+                   operand_at(i).second, i, operand_at(i).first.c_str(), i, i, at);
         continue;
       }
       const bool stretched = ((p.full_bcast >> i) & 1u) != 0;
@@ -401,27 +408,26 @@ std::string chunked_body(const RowProgP& p, const char* entry) {
     if (fused) s += "  float m_run = -3.4028234664e38f, s_run = 0.0f;\n";
     else if (pass < n_red) s += fmt("  float part = %s;\n", is_max[pass] ? "-__builtin_huge_valf()" : "0.0f");
     // the held chunks, one block each
-    std::string in_registers;
+    std::string on_chip;
     // A first pass that also exponentiates (a fused maximum + sum) has more live values per chunk than one that only
     // compares; left to itself the compiler interleaves the chunks' arithmetic and runs out of registers.  So the loads
     // of all kept chunks are issued first, and the chunks are then worked through one after the other, each behind a
     // scheduling barrier (a chunk's arithmetic starts when its own loads have landed).
     const bool preload = fused && pass == 0 && kept > 0;
     // (chunks bound for LDS are loaded one ahead of the one that is worked on)
-    if (pass == 0)
+    if (preload)
       for (uint32_t c = kept; c < held; ++c)
-        for (int i = 0; i < p.n_full; ++i) in_registers += fmt("  %s::Raw<%s> way%d_%u;\n", chunk_type(c), storage_type(p.full_dt[i]), i, c);
+        for (int i = 0; i < p.n_full; ++i) on_chip += fmt("  %s::Raw<%s> way%d_%u;\n", chunk_type(c), storage_type(p.full_dt[i]), i, c);
     if (preload) {
-      for (uint32_t c = 0; c < kept; ++c) in_registers += load_into("kept", c);
-      if (in_lds > 0) in_registers += load_into("way", kept);
-      in_registers += "  __builtin_amdgcn_sched_barrier(0);\n";
+      for (uint32_t c = 0; c < kept; ++c) on_chip += load_into("kept", c);
+      if (in_lds > 0) on_chip += load_into("way", kept);
+      on_chip += "  __builtin_amdgcn_sched_barrier(0);\n";
     }
     for (uint32_t c = 0; c < held; ++c) {
       const bool is_tail = c == NC - 1u;
-      if (pass == 0 && c == kept && !preload) in_registers += load_into("way", c);
-      if (pass == 0 && c >= kept && c + 1u < held) in_registers += load_into("way", c + 1u);
-      in_registers += fmt("  {\n  const %s row(fs_block, 0, %uu);\n", chunk_type(c), c * chunk) + piece(pass, is_tail, (int)c, preload) + "  }\n";
-      if (preload) in_registers += "  __builtin_amdgcn_sched_barrier(0);\n";
+      if (preload && c >= kept && c + 1u < held) on_chip += load_into("way", c + 1u);
+      on_chip += fmt("  {\n  const %s row(fs_block, 0, %uu);\n", chunk_type(c), c * chunk) + piece(pass, is_tail, (int)c, preload) + "  }\n";
+      if (preload) on_chip += "  __builtin_amdgcn_sched_barrier(0);\n";
     }
     // the others: whole chunks by a loop, then the row's last chunk.  Every other pass walks them backwards: it
     // starts with the chunks the pass before read last, which the caches are likeliest to hold still
@@ -432,7 +438,7 @@ std::string chunked_body(const RowProgP& p, const char* entry) {
                               held, NC - 1u, backwards ? fmt("(%uu - chunk)", NC - 2u + held).c_str() : "chunk", chunk) +
                           piece(pass, false, -1) + "  }\n";
     if (held < NC) from_memory_last = fmt("  {\n  const TailRow row(fs_block, 0, %uu);\n", (NC - 1u) * chunk) + piece(pass, true, -1) + "  }\n";
-    s += backwards ? from_memory_last + from_memory_whole + in_registers : in_registers + from_memory_whole + from_memory_last;
+    s += backwards ? from_memory_last + from_memory_whole + on_chip : on_chip + from_memory_whole + from_memory_last;
     if (fused) {
       // the lanes' maxima meet first; every lane then brings its sum to the row's maximum before the sums meet
       s += fmt("  red%d = Row::finish<OpMax>(m_run, slots + %d);\n", pass, n_waves * pass);

@@ -814,10 +814,11 @@ std::vector<Shape> enumerate_shapes(const Compiler& c, int vec, bool interpretab
         const int room = 512 / (int)(T / 256) - body - 8;
         if (regs_per_chunk == 0 || room < regs_per_chunk) continue;
         t.kept = std::min<uint32_t>(t.NC, (uint32_t)(room / regs_per_chunk));
-        // chunks that the registers have no room for may stay in LDS, as much of it as leaves the compute unit its 2048 / T
-        // workgroups' registers; where the compiled kernel would spill, the form with one chunk less in registers is the next.  (us, the rest read from memory in each pass / held in LDS: log-softmax f32
-        // [809,122867] 174.4 / 164.1, [30,131072] 16.2 / 14.4, bf16 [1500,128257], which then lies on the grid, 179.2 / 150.3; bf16
-        // [4096,128256], one chunk of eight, and f32 [1000,80000], one of ten, level)
+        // chunks that the registers have no room for may stay in LDS, as much of it as the registers leave workgroups on a
+        // compute unit to share; where the compiled kernel would spill, the form with one chunk less in registers is the next.
+        // (us, the rest read from memory in each pass / held in LDS: log-softmax f32 [809,122867] 174.4 / 164.1, [30,131072]
+        // 16.2 / 14.4, bf16 [1500,128257], which then lies on the grid, 179.2 / 150.3; bf16 [4096,128256], one chunk of eight, and
+        // f32 [1000,80000], one of ten, level)
         const uint32_t room_lds = (uint32_t)((T == 1024 ? 156 : T == 512 ? 78 : 38) * 1024 / ((int)T * lds_per_chunk));
         for (uint32_t less = 0; less < 2 && t.kept > less && t.kept < t.NC && room_lds > 0; ++less) {
           Shape u = t;
