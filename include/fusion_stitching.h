@@ -124,7 +124,7 @@ typedef struct fs_plan_opts {
  * kernel's own figures).                                                         */
 typedef struct fs_plan_info {
   int32_t scheme;            /* enum fs_scheme actually used                                   */
-  int32_t n_kernels;         /* launches per fs_execute                                        */
+  int32_t n_kernels;         /* launches per fs_execute (one where fs_plan_describe says at_once) */
   int32_t block[3];          /* workgroup shape of the dominant kernel                         */
   int32_t grid[3];           /* workgroups of the dominant kernel                              */
   int32_t lanes_per_row;
@@ -260,7 +260,8 @@ int64_t fs_plan_source(const fs_plan *p, char *text, size_t capacity);
  * fs_plan_info.workspace_bytes (may be null when that is 0); its contents on entry
  * do not matter (every kernel that reads it reads what an earlier kernel of the same
  * call wrote) and it is reusable afterwards.  Allocates nothing, never
- * synchronizes.  Two calls that share a workspace must be ordered on one stream.
+ * synchronizes.  A small pattern with column sums runs as one launch instead of two
+ * (`at_once` in fs_plan_describe) unless an output shares memory with an input or output.  Two calls that share a workspace must be ordered on one stream.
  * Errors: FS_ERR_INVALID_ARG, FS_ERR_WORKSPACE, FS_ERR_ALIGN, FS_ERR_HIP.         */
 fs_status fs_execute(const fs_plan *p, const void *const *inputs, void *const *outputs,
                      void *workspace, size_t workspace_bytes, void *hip_stream);

@@ -640,6 +640,90 @@ std::string generate_pack_kernel(const std::vector<RowProgP>& members, const std
   return out;
 }
 
+// Column sums formed by workgroups of their own: one takes `lanes` steps of columns and every row, so its sums are final and go
+// straight to the outputs (a.rout[first_out + i], dtype sum_dt[i]).  The row program runs once more for that, without its row reductions
+// (no sum depends on one, see sums_beside_rows()) and stores; what only those need is dead code to the device compiler.  Bound
+// by the latency of its loads: a thread issues those of all its rows at once.
+static std::string column_sum_member(const RowProgP& p, const char* entry, int lanes, int first_out, const int32_t* sum_dt) {
+  const uint32_t Q = (uint32_t)lanes, nvec = (p.cols + (uint32_t)p.vec - 1u) / (uint32_t)p.vec, CT = (nvec + Q - 1u) / Q, G = 256u / Q;
+  const uint32_t tile_cols = CT > 1 ? Q * (uint32_t)p.vec : p.cols, U = (p.rows + G - 1u) / G;   // U rows per thread
+  std::string s = fmt("static __device__ __forceinline__ void %s(const GenArgs& a, const uint32_t fs_block) {\n", entry);
+  s += fmt("  typedef GenRow<%uu, %uu, %d, 1, %uu, false, %uu, %uu, %uu> Row;\n", p.rows, tile_cols, p.vec, Q, U, p.cols, CT);
+  s += "  constexpr int KV = Row::KV;\n";
+  s += fmt("  __shared__ __attribute__((aligned(16))) float colred[%d][4 * Row::PADDED_COLS];\n", p.n_colsum);
+  for (int i = 0; i < p.n_colsum; ++i) s += fmt("  float cs%d[KV];\n#pragma unroll\n  for (int j = 0; j < KV; ++j) cs%d[j] = 0.0f;\n", i, i);
+  s += "  const Row first(0u, fs_block);\n";
+  for (int i = 0; i < p.n_col; ++i)
+    s += fmt("  float c%d[KV];\n  first.unpack_to<%s>(first.load<%s, false>(a.col[%d], 0), c%d);\n", i, storage_type(p.col_dt[i]), storage_type(p.col_dt[i]), i, i);
+  for (uint32_t u = 0; u < U; ++u) {
+    const std::string pre = fmt("u%u_", u), rv = pre + "row";
+    s += fmt("  const Row %s(%uu, fs_block);\n", rv.c_str(), u);
+    if ((p.full_bcast | p.rscal_bcast) != 0)
+      s += fmt("  const uint32_t %sq1 = %s.row_c / %uu, %slead2 = %s.row_c - %sq1 * %uu, %slead0 = %sq1 / %uu, %slead1 = %sq1 - %slead0 * %uu;\n", pre.c_str(),
+               rv.c_str(), p.od[2].d, pre.c_str(), rv.c_str(), pre.c_str(), p.od[2].d, pre.c_str(), pre.c_str(), p.od[1].d, pre.c_str(), pre.c_str(), pre.c_str(),
+               p.od[1].d);
+    for (int i = 0; i < p.n_full; ++i)
+      s += fmt("  const auto %sfull%d = %s.load<%s, false>(a.full[%d], %s);\n", pre.c_str(), i, rv.c_str(), storage_type(p.full_dt[i]), i,
+               ((p.full_bcast >> i) & 1u) ? stretched_row(p.ms[i], pre.c_str()).c_str() : fmt("(size_t)%s.row_c", rv.c_str()).c_str());
+    for (int i = 0; i < p.n_rscal; ++i)
+      s += fmt("  const float %srscal%d = load1(static_cast<const %s*>(a.rscal[%d]) + %s);\n", pre.c_str(), i, storage_type(p.rscal_dt[i]), i,
+               ((p.rscal_bcast >> i) & 1u) ? stretched_row(p.rms[i], pre.c_str()).c_str() : fmt("(size_t)%s.row_c", rv.c_str()).c_str());
+  }
+  for (uint32_t u = 0; u < U; ++u) {
+    s += fmt("  {\n  const Row& row = u%u_row;\n  float acc[KV], sacc = 0.0f;\n#pragma unroll\n  for (int j = 0; j < KV; ++j) acc[j] = 0.0f;\n", u);
+    for (int r = 0; r < p.n_regs; ++r) s += fmt("  float r%d[KV];\n", r);
+    for (int r = 0; r < p.n_sregs; ++r) s += fmt("  float s%d = 0.0f;\n", r);
+    for (int i = 0; i < p.n_full; ++i) {
+      const bool parked = p.full_reg[i] != 255, to_acc = p.acc_input == i;
+      const std::string reg = parked ? fmt("r%d", p.full_reg[i]) : std::string("acc");
+      if (parked || to_acc) s += fmt("  row.unpack_to<%s>(u%u_full%d, %s);\n", storage_type(p.full_dt[i]), u, i, reg.c_str());
+      if (parked && to_acc) s += fmt("#pragma unroll\n  for (int j = 0; j < KV; ++j) acc[j] = %s[j];\n", reg.c_str());
+    }
+    for (int i = 0; i < p.n_rscal; ++i) s += fmt("  s%d = u%u_rscal%d;\n", p.rscal_sreg[i], u, i);
+    int reduction_no = 0;
+    for (int i = 0; i < p.n_instr; ++i) {
+      const ProgInstr& in = p.instr[i];
+      if (in.op == PO_STORE || in.op == PO_STORE_SCAL) continue;
+      if (in.op == PO_RSUM || in.op == PO_RMAX || in.op == PO_RSUMSQ) {
+        s += "  sacc = 0.0f;\n";
+        if (in.flags & PF_KEEP) s += fmt("  s%d = sacc;\n", in.dst);
+        continue;
+      }
+      s += instruction_text(p, in, false, 4, &reduction_no);
+    }
+    s += "  }\n";
+  }
+  for (int i = 0; i < p.n_colsum; ++i) s += fmt("  first.colsum_park(cs%d, colred[%d]);\n", i, i);
+  s += "  __syncthreads();\n";
+  for (int i = 0; i < p.n_colsum; ++i)
+    s += fmt("  first.colsum_finish<%s>(colred[%d], a.rout[%d]);\n", storage_type(sum_dt[i]), i, first_out + i);
+  return s + "}\n";
+}
+
+std::string generate_sums_beside_rows(const SumsBesideRows& k, std::string* entry) {
+  std::string params, fields;
+  for (size_t n = 0; n < k.slots.size(); ++n) {
+    params += fmt("%svoid* p%zu", n ? ", " : "", n);
+    fields += fmt("  %s = p%zu;\n", arg_field(k.slots[n]).c_str(), n);
+  }
+  std::string text = "using namespace fsk;\n" + column_sum_member(k.prog, "fs_sums", k.sum_lanes, k.first_sum_out, k.sum_dt);
+  if (k.row_blocks > 0) {
+    RowProgP rows = k.prog;   // without its column sums
+    rows.n_colsum = 0;
+    rows.n_instr = 0;
+    for (int i = 0; i < k.prog.n_instr; ++i)
+      if (k.prog.instr[i].op != PO_COLSUM) rows.instr[rows.n_instr++] = k.prog.instr[i];
+    text += body_with_entry(rows, "fs_rows", true);
+  }
+  text += fmt("extern \"C\" __global__ void __launch_bounds__(256) %s(%s) {\n  GenArgs a{};\n", kEntryPlaceholder, params.c_str()) + fields;
+  text += k.row_blocks > 0 ? fmt("  if (blockIdx.x < %uu) fs_sums(a, blockIdx.x);\n  else fs_rows(a, blockIdx.x - %uu, nullptr);\n}\n", k.sum_blocks, k.sum_blocks)
+                           : std::string("  fs_sums(a, blockIdx.x);\n}\n");
+  *entry = fmt("fs_gen_sums_%08x", fnv1a(text));
+  std::string out = embedded_prelude() + text;
+  out.replace(out.find(kEntryPlaceholder), sizeof kEntryPlaceholder - 1, *entry);
+  return out;
+}
+
 int64_t column_sum_lds_bytes(const RowProgP& p) {
   return p.lanes_per_row > 64 ? 0 : (int64_t)p.n_colsum * 4 * p.lanes_per_row * p.vecs_per_lane * p.vec * 4;
 }

@@ -132,6 +132,21 @@ struct GenericProgram {
 };
 }  // namespace fs
 
+namespace fs {
+// One launch for a pattern with column sums that no row reduction feeds: some workgroups form the sums, each of its columns over all
+// rows, the others run the rows.  The inputs are read twice, so no output may share memory with one.
+struct SumsBesideRows {
+  RowProgP prog;                        // in the shape that the rows take
+  uint32_t row_blocks = 0, sum_blocks = 0;
+  int32_t sum_lanes = 0;                // steps of columns that a workgroup sums
+  int32_t first_sum_out = 0;            // the sums are the per-row outputs (kSlotRout) from here on
+  int32_t sum_dt[kProgMaxColSums] = {};
+  std::vector<int> slots;               // pointer slots in the order of the kernel's parameters
+  BufRef ptr[kMaxPtrs];
+  std::shared_ptr<GenKernel> kernel;    // null: the plan has no such form
+};
+}  // namespace fs
+
 struct fs_plan {
   fs::GenericProgram generic;
   std::vector<fs::Candidate> candidates;
@@ -139,6 +154,7 @@ struct fs_plan {
   int32_t n_inputs = 0, n_outputs = 0;
   std::vector<int64_t> input_bytes, output_bytes;
   fs::PackForm pack;
+  fs::SumsBesideRows at_once;   // what fs_execute runs instead of the chosen candidate where it may
   int64_t bytes_min = 0;
   fs_plan_opts opts = {-1, 0, 0, 0};   // what the caller asked for (a re-choice after a failed compile honours it)
 };
@@ -174,6 +190,8 @@ std::string build_stitched(const fs_graph& g, std::vector<Candidate>* out, PackF
 // Candidates that run `g` as an interpreted row program (fs_rowprog.cpp); false if `g` is not a
 // pattern of element-wise ops and last-axis reductions over one row space.
 bool build_row_program(const fs_graph& g, std::vector<Candidate>* out);
+// The graph's column sums and rows as one launch, where that is the faster form (fs_rowprog.cpp); false: it is not, or has none.
+bool sums_beside_rows(const fs_graph& g, SumsBesideRows* out);
 // Generated row kernels (fs_codegen.cpp): HIP source of the kernel specialised to the program `p` and its
 // launch shape; the body alone (without the embedded device headers) for listings.
 std::string generate_row_kernel(const RowProgP& p);
@@ -191,6 +209,7 @@ std::string generate_pack_kernel(const std::vector<RowProgP>& members, const std
 // (generated_ptr_slots()), then three per fold.
 std::string generate_merged_kernel(const std::vector<RowProgP>& members, const std::vector<uint32_t>& blocks, const std::vector<Launch>& folds,
                                    std::string* entry);
+std::string generate_sums_beside_rows(const SumsBesideRows& k, std::string* entry);   // a whole source
 int64_t column_sum_lds_bytes(const RowProgP& p);   // LDS in which a workgroup folds its rows' column sums
 std::string embedded_prelude();
 // Pairs of row reductions "rmax; acc - max; exp; rsum" that a row worked through in chunks gathers in one pass
@@ -204,9 +223,12 @@ bool codegen_enabled();
 // the chosen candidate's kernel; if that fails, or the kernel spills registers, it moves the choice to the
 // next best candidate (unless the caller fixed the candidate, then it fails).
 fs_status create_plan(const fs_graph* g, int32_t scheme, const fs_plan_opts* opts, bool complete, fs_plan** out);
-// The first `n_launches` launches of the plan's chosen candidate (arguments already validated by the caller).
+// The first `n_launches` launches of the plan's chosen candidate, all of them as one launch where the plan has that form and may take
+// it (arguments already validated by the caller).
 fs_status run_launches(const fs_plan* p, const void* const* inputs, void* const* outputs, void* workspace, void* hip_stream,
                        size_t n_launches);
+// Whether an output shares memory with an input or with another output.
+bool outputs_share_memory(const std::vector<int64_t>& input_bytes, const std::vector<int64_t>& output_bytes, const void* const* inputs, void* const* outputs);
 // The checks every execute entry point makes on its pointer arrays (null, alignment); `who` names the caller in the message.
 fs_status check_execute_args(const fs_plan* p, const void* const* inputs, void* const* outputs, const char* who);
 // How many kernel launches that makes (folds of column partial sums that follow each other go out as one).

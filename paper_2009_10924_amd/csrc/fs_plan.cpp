@@ -195,10 +195,38 @@ size_t fs::launches_issued(const fs_plan* p, size_t n_launches) {
   return issued;
 }
 
+bool fs::outputs_share_memory(const std::vector<int64_t>& input_bytes, const std::vector<int64_t>& output_bytes, const void* const* inputs, void* const* outputs) {
+  auto meet = [&](size_t o, const void* other, int64_t bytes) {
+    return (uintptr_t)other < (uintptr_t)outputs[o] + (uint64_t)output_bytes[o] && (uintptr_t)outputs[o] < (uintptr_t)other + (uint64_t)bytes;
+  };
+  for (size_t o = 0; o < output_bytes.size(); ++o) {
+    for (size_t i = 0; i < input_bytes.size(); ++i)
+      if (meet(o, inputs[i], input_bytes[i])) return true;
+    for (size_t q = 0; q < o; ++q)
+      if (meet(o, outputs[q], output_bytes[q])) return true;
+  }
+  return false;
+}
+
 fs_status fs::run_launches(const fs_plan* p, const void* const* inputs, void* const* outputs, void* workspace, void* hip_stream,
                        size_t n_launches) {
   const Candidate& c = p->candidates[p->chosen];
   const size_t end = std::min(n_launches, c.launches.size());
+  const SumsBesideRows& once = p->at_once;
+  // (not loaded here: loading is nothing for a call under capture, which the two launches of a fixed family can be)
+  if (once.kernel && end == c.launches.size() && gen_loaded(once.kernel.get()) && !outputs_share_memory(p->input_bytes, p->output_bytes, inputs, outputs)) {
+    void* ptrs[kGenArgPtrs];
+    size_t n = 0;
+    for (int slot : once.slots) {
+      const BufRef& r = once.ptr[slot];
+      ptrs[n++] = r.kind == BUF_INPUT ? const_cast<void*>(inputs[r.slot]) : outputs[r.slot];
+    }
+    LaunchShape shape;
+    shape.grid[0] = once.sum_blocks + once.row_blocks;
+    shape.block[0] = 256;
+    const int err = gen_launch(once.kernel.get(), ptrs, sizeof(void*) * n, shape, hip_stream);
+    return err == 0 ? FS_OK : fail(FS_ERR_HIP, "fs_execute: launching rows and column sums failed: %s", hip_error_text(err));
+  }
   auto address = [&](const BufRef& r) -> void* {
     switch (r.kind) {
       case BUF_INPUT: return const_cast<void*>(inputs[r.slot]);
@@ -253,6 +281,21 @@ fs_status fs::run_launches(const fs_plan* p, const void* const* inputs, void* co
     if (err != 0) return fail(FS_ERR_HIP, "fs_execute: launching %s failed: %s", kernel_name(l.kernel), hip_error_text(err));
   }
   return FS_OK;
+}
+
+// A plan that was left to choose and has a fold of column sums to launch: the form without one, if it has it.
+static void add_at_once(const fs_graph& g, fs_plan* p) {
+  const fs_plan_opts& o = p->opts;
+  const std::vector<Launch>& launches = p->candidates[p->chosen].launches;
+  if (!codegen_enabled() || o.candidate >= 0 || o.block_threads > 0 || o.lanes_per_row > 0 || o.vecs_per_lane > 0 || launches.size() < 2 ||
+      launches.back().kernel != K_COLFOLD)
+    return;
+  SumsBesideRows k;
+  std::string entry, log;
+  if (!sums_beside_rows(g, &k) || gen_compile(generate_sums_beside_rows(k, &entry), entry.c_str(), &k.kernel, &log) != 0 ||
+      gen_resources(k.kernel.get()).scratch_bytes > 0 || gen_preload(k.kernel.get()) != 0)
+    return;
+  p->at_once = k;
 }
 
 fs_status fs::check_execute_args(const fs_plan* p, const void* const* inputs, void* const* outputs, const char* who) {
@@ -360,6 +403,7 @@ fs_status fs::create_plan(const fs_graph* g, int32_t scheme, const fs_plan_opts*
       }
       return s;
     }
+    if (scheme == FS_SCHEME_AUTO) add_at_once(*g, p);
   }
   *out = p;
   return FS_OK;
@@ -489,6 +533,8 @@ int64_t fs_plan_describe(const fs_plan* p, char* text, size_t capacity) try {
       s += line;
     }
   }
+  if (p->at_once.kernel)   // what fs_execute runs instead of the launches above, unless an output shares memory with an input or output
+    s += "at_once sum_workgroups=" + std::to_string(p->at_once.sum_blocks) + " row_workgroups=" + std::to_string(p->at_once.row_blocks) + "\n";
   if (capacity > 0) {
     const size_t n = std::min(capacity - 1, s.size());
     memcpy(text, s.data(), n);

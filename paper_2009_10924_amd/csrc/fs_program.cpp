@@ -103,20 +103,6 @@ int64_t fs_program_describe(const fs_program* p, char* text, size_t capacity) tr
 
 }  // extern "C"
 
-// Whether an output shares memory with an input or with another output: the steps must then run in their order.
-static bool outputs_share_memory(const fs_program* p, const void* const* inputs, void* const* outputs) {
-  auto meet = [&](int o, const void* other, int64_t bytes) {
-    return (uintptr_t)other < (uintptr_t)outputs[o] + (uint64_t)p->output_bytes[o] && (uintptr_t)outputs[o] < (uintptr_t)other + (uint64_t)bytes;
-  };
-  for (int o = 0; o < p->n_outputs; ++o) {
-    for (int i = 0; i < p->n_inputs; ++i)
-      if (meet(o, inputs[i], p->input_bytes[i])) return true;
-    for (int q = 0; q < o; ++q)
-      if (meet(o, outputs[q], p->output_bytes[q])) return true;
-  }
-  return false;
-}
-
 // The steps of stages first_stage..last_stage; the joint fold launches go with the program's last stage.
 static fs_status run_program(const fs_program* p, int32_t first_stage, int32_t last_stage, const void* const* inputs,
                              void* const* outputs, void* workspace, size_t workspace_bytes, void* hip_stream) {
@@ -150,7 +136,9 @@ static fs_status run_program(const fs_program* p, int32_t first_stage, int32_t l
       default: return nullptr;
     }
   };
-  if (!p->merged.empty() && first_stage == 0 && last_stage == p->info.n_stages - 1 && !outputs_share_memory(p, inputs, outputs)) {
+  // (steps that share memory must run in their order)
+  if (!p->merged.empty() && first_stage == 0 && last_stage == p->info.n_stages - 1 &&
+      !outputs_share_memory(p->input_bytes, p->output_bytes, inputs, outputs)) {
     for (const fs_program::Merged& m : p->merged) {
       void* ptrs[kMergedMaxOperands];
       size_t n = 0;

@@ -1130,4 +1130,67 @@ bool build_row_program(const fs_graph& g, std::vector<Candidate>* out) {
   return !out->empty();
 }
 
+// No column sum depends on a row reduction.
+static bool sums_need_no_reduction(const RowProgP& p) {
+  bool acc = false, sacc = false, reg[256] = {}, sreg[256] = {};   // holds something that a row reduction went into
+  for (int i = 0; i < p.n_instr; ++i) {
+    const ProgInstr& in = p.instr[i];
+    if (in.op == PO_STORE || in.op == PO_STORE_SCAL) continue;
+    if (in.op == PO_COLSUM) {
+      if (acc) return false;
+      continue;
+    }
+    const bool reduces = in.op == PO_RSUM || in.op == PO_RMAX || in.op == PO_RSUMSQ, scalar = reduces || (in.flags & PF_SCALAR) != 0;
+    bool& to = scalar ? sacc : acc;
+    const bool b = in.b_kind == PK_REG ? reg[in.b] : in.b_kind == PK_SCAL ? sreg[in.b] : in.b_kind == PK_SACC ? sacc : in.b_kind == PK_ACC ? acc : false;
+    to = reduces || b || (to && in.op != PO_LOAD);
+    if (in.flags & PF_KEEP) (scalar ? sreg : reg)[in.dst] = to;
+  }
+  return true;
+}
+
+// What a fold launch costs, 2.5 to 3 us on top of a call that takes 3.3, is saved where the sums are formed by workgroups that read the
+// inputs again.  One takes as many steps of columns as leave 48 such workgroups, at most 8; the line lies where its threads still take all
+// their rows in one batch of loads and the rows that these workgroups visit, rows x workgroups, stay at most 24576: past either
+// the second reading costs what the launch does.  Measured (us, two launches / one; bias + GELU backward, LayerNorm backward, RMS norm
+// backward): bf16 [64,768] 6.2 / 3.3, 5.7 / 3.2, 6.1 / 3.7; [512,768] 6.3 / 3.6, 5.9 / 3.1, 6.5 / 3.8; [1024,768], beyond it, 6.2 / 7.0, 6.2 / 6.4,
+// 6.1 / 5.6; [256,3072] 6.1 / 4.2, 6.8 / 3.9, 6.1 / 3.6; [512,3072], beyond it, 6.3 / 7.6, 8.1 / 5.5, 7.0 / 4.7; f32 [512,768] 6.6 / 3.7, 6.3 / 4.4,
+// 6.3 / 3.8; [256,3072] 6.1 / 3.7, 7.0 / 4.0, 6.1 / 3.7.  The arithmetic is done twice as well: patterns of more than these three have are
+// left out.
+bool sums_beside_rows(const fs_graph& g, SumsBesideRows* out) {
+  Compiler c(g);
+  if (g.cut_out || !c.run() || c.n_colsum == 0 || c.n_rout + c.n_colsum > kProgMaxOperands || !sums_need_no_reduction(c.p)) return false;
+  if (c.p.stream || c.p.n_full > 3 || c.n_colsum > 2 || c.vec_instr > 20 || c.trans > 4) return false;
+  const int vec = c.p.vec;
+  const uint32_t nvec = (c.p.cols + (uint32_t)vec - 1u) / (uint32_t)vec;
+  uint32_t lanes = 8;
+  while (lanes > 2 && nvec < lanes * 48u) lanes /= 2;
+  const uint32_t sum_blocks = (nvec + lanes - 1u) / lanes;
+  if (nvec > 256u * 8u || (uint64_t)c.p.rows * lanes > 8u * 256u || (uint64_t)c.p.rows * sum_blocks > 24576u) return false;
+  out->sum_lanes = (int32_t)lanes;
+  out->sum_blocks = sum_blocks;
+  Shape s{1, 1, false, true};   // the rows': as few steps per lane as 256 threads allow
+  while (s.L < 64 && s.L < nvec) s.L <<= 1;
+  s.block = nvec > 128;
+  if (s.block) s.L = 256;
+  s.K = (int)((nvec + s.L - 1) / s.L);
+  Launch l;
+  fill_launch(g, c, vec, s, 0, &l);
+  out->prog = l.args.u.prog;
+  out->row_blocks = c.n_out + c.n_rout > 0 ? l.shape.grid[0] : 0;
+  out->first_sum_out = c.n_rout;
+  for (int k = 0; k < kMaxPtrs; ++k) out->ptr[k] = l.ptr[k];
+  RowProgP rows = out->prog;
+  rows.n_colsum = 0;
+  out->slots = generated_ptr_slots(rows);
+  for (int i = 0; i < c.n_colsum; ++i) {
+    const int slot = kSlotRout + c.n_rout + i;
+    out->sum_dt[i] = c.colsum_dt[i];
+    out->ptr[slot].kind = BUF_OUTPUT;
+    out->ptr[slot].slot = c.colsum_slot[i];
+    out->slots.push_back(slot);
+  }
+  return true;
+}
+
 }  // namespace fs

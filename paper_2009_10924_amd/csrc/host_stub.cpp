@@ -188,6 +188,7 @@ int gen_compile(const std::string& src, const char* entry, std::shared_ptr<GenKe
 }
 GenResources gen_resources(const GenKernel*) { return GenResources(); }
 int gen_preload(GenKernel*) { return 0; }
+bool gen_loaded(const GenKernel*) { return true; }
 int gen_launch(GenKernel* k, const void* args, size_t args_bytes, const LaunchShape& shape, void*) {
   if (!k || !args || args_bytes == 0 || args_bytes % sizeof(void*) != 0 || check_shape(shape)) return 1;
   ++g_launches;

@@ -285,6 +285,11 @@ int gen_preload(GenKernel* k) {
   return function_here(k, &f);
 }
 
+bool gen_loaded(const GenKernel* k) {
+  int dev = 0;
+  return hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < kMaxDevices && k->fn[dev].load(std::memory_order_acquire) != nullptr;
+}
+
 int gen_launch(GenKernel* k, const void* args, size_t args_bytes, const LaunchShape& s, void* stream) {
   hipFunction_t f = nullptr;
   const int e = function_here(k, &f);

@@ -441,6 +441,15 @@ struct GenRow {
       }
     }
   }
+  // The same where the workgroup has seen all rows: its sums are final, in their own dtype.
+  template <typename TO>
+  __device__ __forceinline__ void colsum_finish(const float* lds, void* out) const {
+    static_assert(!BLOCK, "");
+    for (uint32_t c = threadIdx.x; c < n_cols(); c += 256u) {
+      const uint32_t at = c < n_whole() * VEC ? c : c + BACK;
+      store1(static_cast<TO*>(out) + col0 + c, ((lds[at] + lds[PADDED_COLS + at]) + lds[2u * PADDED_COLS + at]) + lds[3u * PADDED_COLS + at]);
+    }
+  }
   __device__ __forceinline__ void colsum_flush(const float (&sum)[KV], const float* lds, float* dst) const {
     if constexpr (BLOCK) {
       // a workgroup per row: every lane owns its columns alone, the sums over the workgroup's rows are complete
