@@ -143,7 +143,7 @@ struct SumsBesideRows {
   int32_t sum_dt[kProgMaxColSums] = {};
   std::vector<int> slots;               // pointer slots in the order of the kernel's parameters
   BufRef ptr[kMaxPtrs];
-  std::shared_ptr<GenKernel> kernel;    // null: the plan has no such form
+  std::shared_ptr<GenKernel> kernel;
 };
 }  // namespace fs
 
@@ -154,7 +154,7 @@ struct fs_plan {
   int32_t n_inputs = 0, n_outputs = 0;
   std::vector<int64_t> input_bytes, output_bytes;
   fs::PackForm pack;
-  fs::SumsBesideRows at_once;   // what fs_execute runs instead of the chosen candidate where it may
+  std::unique_ptr<fs::SumsBesideRows> at_once;   // what fs_execute runs instead of the chosen candidate where it may; null: nothing
   int64_t bytes_min = 0;
   fs_plan_opts opts = {-1, 0, 0, 0};   // what the caller asked for (a re-choice after a failed compile honours it)
 };

@@ -208,25 +208,28 @@ bool fs::outputs_share_memory(const std::vector<int64_t>& input_bytes, const std
   return false;
 }
 
+static fs_status run_at_once(const SumsBesideRows& once, const void* const* inputs, void* const* outputs, void* hip_stream) {
+  void* ptrs[kGenArgPtrs];
+  size_t n = 0;
+  for (int slot : once.slots) {
+    const BufRef& r = once.ptr[slot];
+    ptrs[n++] = r.kind == BUF_INPUT ? const_cast<void*>(inputs[r.slot]) : outputs[r.slot];
+  }
+  LaunchShape shape;
+  shape.grid[0] = once.sum_blocks + once.row_blocks;
+  shape.block[0] = 256;
+  const int err = gen_launch(once.kernel.get(), ptrs, sizeof(void*) * n, shape, hip_stream);
+  return err == 0 ? FS_OK : fail(FS_ERR_HIP, "fs_execute: launching rows and column sums failed: %s", hip_error_text(err));
+}
+
 fs_status fs::run_launches(const fs_plan* p, const void* const* inputs, void* const* outputs, void* workspace, void* hip_stream,
                        size_t n_launches) {
   const Candidate& c = p->candidates[p->chosen];
   const size_t end = std::min(n_launches, c.launches.size());
-  const SumsBesideRows& once = p->at_once;
   // (not loaded here: loading is nothing for a call under capture, which the two launches of a fixed family can be)
-  if (once.kernel && end == c.launches.size() && gen_loaded(once.kernel.get()) && !outputs_share_memory(p->input_bytes, p->output_bytes, inputs, outputs)) {
-    void* ptrs[kGenArgPtrs];
-    size_t n = 0;
-    for (int slot : once.slots) {
-      const BufRef& r = once.ptr[slot];
-      ptrs[n++] = r.kind == BUF_INPUT ? const_cast<void*>(inputs[r.slot]) : outputs[r.slot];
-    }
-    LaunchShape shape;
-    shape.grid[0] = once.sum_blocks + once.row_blocks;
-    shape.block[0] = 256;
-    const int err = gen_launch(once.kernel.get(), ptrs, sizeof(void*) * n, shape, hip_stream);
-    return err == 0 ? FS_OK : fail(FS_ERR_HIP, "fs_execute: launching rows and column sums failed: %s", hip_error_text(err));
-  }
+  if (p->at_once && end == c.launches.size() && gen_loaded(p->at_once->kernel.get()) &&
+      !outputs_share_memory(p->input_bytes, p->output_bytes, inputs, outputs))
+    return run_at_once(*p->at_once, inputs, outputs, hip_stream);
   auto address = [&](const BufRef& r) -> void* {
     switch (r.kind) {
       case BUF_INPUT: return const_cast<void*>(inputs[r.slot]);
@@ -295,7 +298,7 @@ static void add_at_once(const fs_graph& g, fs_plan* p) {
   if (!sums_beside_rows(g, &k) || gen_compile(generate_sums_beside_rows(k, &entry), entry.c_str(), &k.kernel, &log) != 0 ||
       gen_resources(k.kernel.get()).scratch_bytes > 0 || gen_preload(k.kernel.get()) != 0)
     return;
-  p->at_once = k;
+  p->at_once = std::make_unique<SumsBesideRows>(k);
 }
 
 fs_status fs::check_execute_args(const fs_plan* p, const void* const* inputs, void* const* outputs, const char* who) {
@@ -533,8 +536,8 @@ int64_t fs_plan_describe(const fs_plan* p, char* text, size_t capacity) try {
       s += line;
     }
   }
-  if (p->at_once.kernel)   // what fs_execute runs instead of the launches above, unless an output shares memory with an input or output
-    s += "at_once sum_workgroups=" + std::to_string(p->at_once.sum_blocks) + " row_workgroups=" + std::to_string(p->at_once.row_blocks) + "\n";
+  if (p->at_once)   // what fs_execute runs instead of the launches above, unless an output shares memory with an input or output
+    s += "at_once sum_workgroups=" + std::to_string(p->at_once->sum_blocks) + " row_workgroups=" + std::to_string(p->at_once->row_blocks) + "\n";
   if (capacity > 0) {
     const size_t n = std::min(capacity - 1, s.size());
     memcpy(text, s.data(), n);
