@@ -817,8 +817,8 @@ std::vector<Shape> enumerate_shapes(const Compiler& c, int vec, bool interpretab
         // chunks that the registers have no room for may stay in LDS, as much of it as the registers leave workgroups on a
         // compute unit to share; where the compiled kernel would spill, the form with one chunk less in registers is the next.
         // (us, the rest read from memory in each pass / held in LDS: log-softmax f32 [809,122867] 174.4 / 164.1, [30,131072]
-        // 16.2 / 14.4, bf16 [1500,128257], which then lies on the grid, 179.2 / 150.3; bf16 [4096,128256], one chunk of eight, and
-        // f32 [1000,80000], one of ten, level)
+        // 16.2 / 14.4, bf16 [1500,128257], which then lies on the grid, 179.2 / 150.3.  A single chunk beyond the registers gains for
+        // that only: bf16 [4096,128256], one of eight, 358.0 / 359.7, f32 [1000,80000], one of ten, level; see make_generated())
         const uint32_t room_lds = (uint32_t)((T == 1024 ? 156 : T == 512 ? 78 : 38) * 1024 / ((int)T * lds_per_chunk));
         for (uint32_t less = 0; less < 2 && t.kept > less && t.kept < t.NC && room_lds > 0; ++less) {
           Shape u = t;
@@ -996,7 +996,9 @@ void make_generated(const Compiler& c, int vec, const Shape& s, Candidate* cand)
       if (!((base.full_bcast >> i) & 1u)) in_bytes += (double)dtype_bytes(base.full_dt[i]) * base.rows * base.cols;
       regs_per_chunk += s.K * ((vec * dtype_bytes(base.full_dt[i]) + 3) / 4);
     }
-    in_bytes *= 1.0 - (double)(s.kept + s.lds) / s.NC;   // chunks held in registers or LDS are not read again
+    // chunks held in registers or LDS are not read again; a single one in LDS costs what it saves unless its row is on the grid by it
+    const uint32_t held_chunks = s.lds == 1 && !gc.on_grid ? s.kept : s.kept + s.lds;
+    in_bytes *= 1.0 - (double)held_chunks / s.NC;
     gc.vgpr_estimate += regs_per_chunk * (int)(s.kept + (s.lds > 0 ? 1 : 0));
     int lane_bytes = 0;
     for (int i = 0; i < base.n_full; ++i) lane_bytes += s.K * vec * dtype_bytes(base.full_dt[i]);
