@@ -211,7 +211,9 @@ fs_status fs_plan_candidate(const fs_plan *p, int32_t index, fs_plan_info *out);
  * sums over all rows adds `colsums <n> partials <buffer> rows_per_group <r> col_tiles <t>`
  * (and `launch colfold` entries after it, one per fold; folds that follow each other
  * are issued as ONE kernel launch, which `launches=` counts); a row worked through in pieces adds
- * `chunks <n> of <w> columns[, the first <k> kept in registers]`.
+ * `chunks <n> of <w> columns[, the first <k> kept in registers]`.  The last line of a plan whose
+ * fs_execute runs one launch instead of those listed names that one: `at_once sum_workgroups=<n>
+ * row_workgroups=<n> entry=<name> block=256 vgprs=<n> lds=<bytes>`.
  * Errors: FS_ERR_INVALID_ARG.                                                          */
 int64_t fs_plan_describe(const fs_plan *p, char *text, size_t capacity);
 
@@ -244,8 +246,9 @@ int64_t fs_plan_describe(const fs_plan *p, char *text, size_t capacity);
 int32_t fs_codegen_enable(int32_t on);
 /* 1 if the run-time compiler could be loaded in this process, else 0.                 */
 int32_t fs_codegen_available(void);
-/* Writes the HIP source of the plan's generated kernel(s) (the kernel function only, not
- * the fixed device headers it is compiled with) into `text` (HOST buffer of `capacity`
+/* Writes the HIP source of the plan's generated kernel(s), the one-launch form of a small
+ * pattern with column sums among them (the kernel functions only, not the fixed device
+ * headers they are compiled with), into `text` (HOST buffer of `capacity`
  * bytes, NUL-terminated, truncated if too small) and returns the size needed including
  * the NUL (1 for a plan without a generated kernel), or a negative error.
  * Errors: FS_ERR_INVALID_ARG.                                                          */
@@ -403,7 +406,8 @@ fs_status fs_program_pattern(const fs_program *p, int32_t index, int32_t *ops, i
  * of_steps=<steps whose column sums it finishes>`, with `with_step=<i>` where the last step's
  * kernel runs them too: one launch for both, counted here and not at the step).  Where
  * fs_program_execute merges steps that do not depend on each other, one line per launch of
- * it follows (`merged <j> of <n> steps=<steps> folds_of=<steps>`).  Errors: FS_ERR_INVALID_ARG.         */
+ * it follows (`merged <j> of <n> steps=<steps> folds_of=<steps> entry=<name> workgroups=<n>
+ * vgprs=<n> lds=<bytes>`).  Errors: FS_ERR_INVALID_ARG.                                     */
 int64_t fs_program_describe(const fs_program *p, char *text, size_t capacity);
 /* Enqueues the whole program on `hip_stream` and returns without waiting.  inputs /
  * outputs: DEVICE pointers in the graph's declaration order, 16-byte aligned.  `workspace`:

@@ -719,9 +719,8 @@ std::string generate_sums_beside_rows(const SumsBesideRows& k, std::string* entr
   text += k.row_blocks > 0 ? fmt("  if (blockIdx.x < %uu) fs_sums(a, blockIdx.x);\n  else fs_rows(a, blockIdx.x - %uu, nullptr);\n}\n", k.sum_blocks, k.sum_blocks)
                            : std::string("  fs_sums(a, blockIdx.x);\n}\n");
   *entry = fmt("fs_gen_sums_%08x", fnv1a(text));
-  std::string out = embedded_prelude() + text;
-  out.replace(out.find(kEntryPlaceholder), sizeof kEntryPlaceholder - 1, *entry);
-  return out;
+  text.replace(text.find(kEntryPlaceholder), sizeof kEntryPlaceholder - 1, *entry);
+  return text;
 }
 
 int64_t column_sum_lds_bytes(const RowProgP& p) {

@@ -980,9 +980,9 @@ void merge_steps(fs_program* prog) {
       }
     }
     if (total == 0 || total >= (1ull << 31) || m.operands.size() > kMergedMaxOperands) return;
-    std::string entry, log;
-    const std::string source = embedded_prelude() + generate_merged_kernel(progs, blocks, fold_launches, &entry);
-    if (gen_compile(source, entry.c_str(), &m.kernel, &log) != 0 || gen_resources(m.kernel.get()).scratch_bytes > 0 || gen_preload(m.kernel.get()) != 0) return;
+    std::string log;
+    const std::string source = embedded_prelude() + generate_merged_kernel(progs, blocks, fold_launches, &m.entry);
+    if (gen_compile(source, m.entry.c_str(), &m.kernel, &log) != 0 || gen_resources(m.kernel.get()).scratch_bytes > 0 || gen_preload(m.kernel.get()) != 0) return;
     m.shape = LaunchShape{};
     m.shape.grid[0] = (uint32_t)total;
     m.shape.block[0] = 256;

@@ -143,6 +143,7 @@ struct SumsBesideRows {
   int32_t sum_dt[kProgMaxColSums] = {};
   std::vector<int> slots;               // pointer slots in the order of the kernel's parameters
   BufRef ptr[kMaxPtrs];
+  std::string text, entry;              // the kernel's source (without the embedded device headers) and name
   std::shared_ptr<GenKernel> kernel;
 };
 }  // namespace fs
@@ -209,7 +210,7 @@ std::string generate_pack_kernel(const std::vector<RowProgP>& members, const std
 // (generated_ptr_slots()), then three per fold.
 std::string generate_merged_kernel(const std::vector<RowProgP>& members, const std::vector<uint32_t>& blocks, const std::vector<Launch>& folds,
                                    std::string* entry);
-std::string generate_sums_beside_rows(const SumsBesideRows& k, std::string* entry);   // a whole source
+std::string generate_sums_beside_rows(const SumsBesideRows& k, std::string* entry);   // likewise without the headers
 int64_t column_sum_lds_bytes(const RowProgP& p);   // LDS in which a workgroup folds its rows' column sums
 std::string embedded_prelude();
 // Pairs of row reductions "rmax; acc - max; exp; rsum" that a row worked through in chunks gathers in one pass

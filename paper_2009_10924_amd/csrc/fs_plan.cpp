@@ -294,9 +294,11 @@ static void add_at_once(const fs_graph& g, fs_plan* p) {
       launches.back().kernel != K_COLFOLD)
     return;
   SumsBesideRows k;
-  std::string entry, log;
-  if (!sums_beside_rows(g, &k) || gen_compile(generate_sums_beside_rows(k, &entry), entry.c_str(), &k.kernel, &log) != 0 ||
-      gen_resources(k.kernel.get()).scratch_bytes > 0 || gen_preload(k.kernel.get()) != 0)
+  std::string log;
+  if (!sums_beside_rows(g, &k)) return;
+  k.text = generate_sums_beside_rows(k, &k.entry);
+  if (gen_compile(embedded_prelude() + k.text, k.entry.c_str(), &k.kernel, &log) != 0 || gen_resources(k.kernel.get()).scratch_bytes > 0 ||
+      gen_preload(k.kernel.get()) != 0)
     return;
   p->at_once = std::make_unique<SumsBesideRows>(k);
 }
@@ -536,8 +538,11 @@ int64_t fs_plan_describe(const fs_plan* p, char* text, size_t capacity) try {
       s += line;
     }
   }
-  if (p->at_once)   // what fs_execute runs instead of the launches above, unless an output shares memory with an input or output
-    s += "at_once sum_workgroups=" + std::to_string(p->at_once->sum_blocks) + " row_workgroups=" + std::to_string(p->at_once->row_blocks) + "\n";
+  if (p->at_once) {   // what fs_execute runs instead of the launches above, unless an output shares memory with an input or output
+    const GenResources res = gen_resources(p->at_once->kernel.get());
+    s += "at_once sum_workgroups=" + std::to_string(p->at_once->sum_blocks) + " row_workgroups=" + std::to_string(p->at_once->row_blocks) +
+         " entry=" + p->at_once->entry + " block=256 vgprs=" + std::to_string(res.vgprs) + " lds=" + std::to_string(res.static_lds) + "\n";
+  }
   if (capacity > 0) {
     const size_t n = std::min(capacity - 1, s.size());
     memcpy(text, s.data(), n);
@@ -554,6 +559,7 @@ int64_t fs_plan_source(const fs_plan* p, char* text, size_t capacity) try {
   std::string s;
   for (const Launch& l : p->candidates[p->chosen].launches)
     if (l.kernel == K_ROW_GENERATED) s += generate_row_kernel_body(l.args.u.prog);
+  if (p->at_once) s += p->at_once->text;
   if (capacity > 0) {
     const size_t n = std::min(capacity - 1, s.size());
     memcpy(text, s.data(), n);

@@ -88,7 +88,10 @@ int64_t fs_program_describe(const fs_program* p, char* text, size_t capacity) tr
     std::string steps, folds;
     for (int m : p->merged[j].steps) steps += (steps.empty() ? "" : ",") + std::to_string(m);
     for (const fs_program::JointFold& f : p->merged[j].folds) folds += (folds.empty() ? "" : ",") + std::to_string(f.step);
-    s += "merged " + std::to_string(j) + " of " + std::to_string(p->merged.size()) + " steps=" + steps + " folds_of=" + folds + "\n";
+    s += "merged " + std::to_string(j) + " of " + std::to_string(p->merged.size()) + " steps=" + steps + " folds_of=" + folds;
+    const GenResources res = gen_resources(p->merged[j].kernel.get());
+    s += " entry=" + p->merged[j].entry + " workgroups=" + std::to_string(p->merged[j].shape.grid[0]) + " vgprs=" + std::to_string(res.vgprs) +
+         " lds=" + std::to_string(res.static_lds) + "\n";
   }
   const size_t need = s.size() + 1;
   if (capacity > 0) {

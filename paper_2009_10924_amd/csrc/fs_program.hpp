@@ -47,6 +47,7 @@ struct fs_program {
     std::vector<JointFold> folds;
     struct Operand { int step; BufRef ref; };   // of one of the step's launches
     std::vector<Operand> operands;              // in the order of the kernel's parameters
+    std::string entry;                          // the kernel's name
     std::shared_ptr<GenKernel> kernel;
     LaunchShape shape;
   };
