@@ -20,6 +20,7 @@
 // placed by lifetime; fold launches of column sums that nothing reads move behind the last step
 // and run as one.
 #include <algorithm>
+#include <cmath>
 #include <cstring>
 #include <map>
 #include <set>
@@ -854,24 +855,36 @@ void carry_folds(fs_program* prog) {
   prog->carrier.shape.grid[0] = (uint32_t)blocks;
 }
 
-// A step as a member of a merged kernel: its row program, the buffers of its pointers, its workgroups.
+// A step as a member of a merged kernel: its row program, the buffers of its pointers, its workgroups; what the evaluator knows of it.
 struct Member {
   RowProgP prog;
   const BufRef* ptr = nullptr;
   uint32_t blocks = 0;
+  const KernelCost* cost = nullptr;
+  int32_t vgprs = 0;
+  double seconds = 0;        // by itself, without a fold launch
+  bool loops = false;        // its workgroups work through many rows: column sums, or rows one after the other
+  bool reduces = false;      // ... with a row reduction in every round
 };
 
 // The kernel that the step runs by itself, or the form in which its pack runs it (the results are the same bit for bit); a lone
 // transpose, which moves bits, in its first form.
 bool member_of(const fs_program& prog, int step, Member* m) {
   const fs_program::Step& s = prog.steps[step];
-  const Launch& own = s.plan->candidates[s.plan->chosen].launches[0];
-  auto generic = [&](const GenericForm& f) {
-    m->prog = s.plan->generic.in_form(f);
-    m->ptr = s.plan->generic.ptr;
-    m->blocks = f.blocks;
+  const Candidate& chosen = s.plan->candidates[s.plan->chosen];
+  const Launch& own = chosen.launches[0];
+  auto fill = [&](const RowProgP& p, const BufRef* ptr, uint32_t blocks, const KernelCost& cost, int32_t vgprs) {
+    m->prog = p;
+    m->ptr = ptr;
+    m->blocks = blocks;
+    m->cost = &cost;
+    m->vgprs = vgprs;
+    m->seconds = evaluate(cost, vgprs).seconds - (p.n_colsum > 0 ? device().fold_s : 0.0);
+    m->loops = p.n_colsum > 0 || p.rows_per_group > 1;
+    for (int i = 0; i < p.n_instr; ++i) m->reduces = m->reduces || p.instr[i].op == PO_RSUM || p.instr[i].op == PO_RMAX || p.instr[i].op == PO_RSUMSQ;
     return true;
   };
+  auto generic = [&](const GenericForm& f) { return fill(s.plan->generic.in_form(f), s.plan->generic.ptr, f.blocks, f.cost, f.cost.vgpr_estimate); };
   if (s.pack >= 0) {
     const fs_program::Pack& pk = prog.packs[s.pack];
     if (pk.pack->generated.size() != 1) return false;
@@ -880,10 +893,55 @@ bool member_of(const fs_program& prog, int step, Member* m) {
   }
   if (own.kernel == K_TRANSPOSE_ROWS && !s.plan->generic.forms.empty()) return generic(s.plan->generic.forms[0]);
   if (own.kernel != K_ROW_GENERATED || own.shape.block[0] != 256 || own.args.u.prog.col_chunks > 1) return false;
-  m->prog = own.args.u.prog;
-  m->ptr = own.ptr;
-  m->blocks = own.shape.grid[0];
-  return true;
+  return fill(own.args.u.prog, own.ptr, own.shape.grid[0], chosen.cost, own.gen ? gen_resources(own.gen.get()).vgprs : 0);
+}
+
+// Workgroups of one launch of these steps that a compute unit holds: all have the registers of the hungriest and the LDS of the largest.
+double groups_per_cu(const std::vector<Member>& members, const std::vector<int>& steps) {
+  KernelCost launch;   // of 256 threads
+  int32_t vgprs = 0;
+  launch.waves = launch.elems = 1e9;
+  launch.lds_bytes_per_block = 4096;
+  for (int s : steps) {
+    launch.lds_bytes_per_block = std::max(launch.lds_bytes_per_block, (int32_t)column_sum_lds_bytes(members[s].prog));
+    vgprs = std::max(vgprs, members[s].vgprs > 0 ? members[s].vgprs : members[s].cost->vgpr_estimate);
+  }
+  return evaluate(launch, vgprs).waves_per_simd;   // (four wavefronts on four SIMDs)
+}
+
+// What being in one launch costs its members.  Few of its workgroups may fit a compute unit (groups_per_cu), so
+//   * members that stream (no loop over rows) may be left with fewer bytes in flight than it takes, 40 KB a compute unit: `lean`
+//     lists them, longest first, if the looping members, whose workgroups wait for latencies, are not at work for as long as
+//     they stream.  Measured (us, apart / in one launch with / in a later one): LayerNorm backward [512,768] and RMS norm backward
+//     beside a gate of 201 MB, 32 bytes a lane on 3 workgroups 39.3 / 41.5 / 36.9; of 805 MB 141.1 / 153.2 / 137.4; a gate of 403 MB beside
+//     both of [16384,768] 94.1 / 100.5 / 92.9.  On 64 bytes a lane (49 KB) it pays: 104.0 / 97.8;
+//   * looping members with row reductions whose workgroups are not all resident leave a part of the chip idle in the last round
+//     (`ragged`, seconds; the evaluator's weight).  LayerNorm and RMS norm backward, 768 workgroups where 512 fit, apart / in one
+//     launch: 177 MB 38.6 / 38.2, 302 MB 72.2 / 73.3 (with a gate), 453 MB 89.3 / 94.2.
+void cost_of_sharing(const std::vector<Member>& members, const std::vector<int>& steps, std::vector<int>* lean, double* ragged) {
+  const DeviceModel& d = device();
+  const double per_cu = groups_per_cu(members, steps);
+  const double Bps = d.hbm_peak_Bps * d.stream_fraction;
+  double looping_s = 0, streaming_s = 0, rounds = 0, bytes = 0;
+  lean->clear();
+  for (int s : steps) {
+    const Member& m = members[s];
+    if (m.loops) {
+      looping_s += m.seconds;
+      if (m.reduces) {
+        rounds += m.blocks / (d.n_cu * per_cu);
+        bytes += m.cost->hbm_bytes;
+      }
+      continue;
+    }
+    if (per_cu < evaluate(*m.cost, m.vgprs).waves_per_simd && per_cu * 256.0 * m.cost->bytes_in_flight_per_lane < 40960.0) {
+      lean->push_back(s);
+      streaming_s += m.cost->hbm_bytes / Bps;
+    }
+  }
+  std::stable_sort(lean->begin(), lean->end(), [&](int a, int b) { return members[a].cost->hbm_bytes > members[b].cost->hbm_bytes; });
+  if (looping_s == 0 || streaming_s <= looping_s) lean->clear();
+  *ragged = rounds > 1.0 ? bytes / Bps * 0.25 * (std::ceil(rounds - 1e-9) / rounds - 1.0) : 0.0;
 }
 
 // The whole program in as few launches as its dependences allow: a step reads what others made one launch earlier or
@@ -891,9 +949,11 @@ bool member_of(const fs_program& prog, int step, Member* m) {
 // where the fewest bytes are, those without column sums also into the launch that finishes the last folds.  What the external
 // computations make is in place when the whole program is run, so they tie nothing together here (stage by stage, every step
 // keeps its launch).  What a launch that follows another one costs, 2.5 to 3.5 us, and what latency-bound steps (LayerNorm backward:
-// 256 workgroups, 2.5 times its bytes) leave of the memory's rate is what this saves.  Measured (us, step by step with the folds in
-// the last step's launch / merged), backward pass through a transformer block: 0.2 MB 19.4 / 12.2, 15 MB 25.6 / 20.1, 50 MB 28.0 / 21.9,
-// 201 MB 47.4 / 39.7, 319 MB 64.1 / 55.0, and eight more between them, 1.16 to 1.65 times: never slower, so the evaluator is not asked.
+// 256 workgroups, 2.5 times its bytes) leave of the memory's rate is what this saves; where sharing a launch costs more than that
+// (cost_of_sharing), the step goes to another one or the program stays step by step.  Measured (us, step by step with the folds in
+// the last step's launch / merged), the kernels of a backward pass through a transformer block with its matrix products' results in
+// place: 0.2 MB 19.4 / 12.2, 15 MB 25.6 / 20.1, 50 MB 28.0 / 21.9, 201 MB 47.4 / 39.7, 319 MB 64.1 / 55.0;
+// 44 programs of one to three patterns with column sums beside gates, normalisations and transposes, 10 MB to 1.4 GB: 1.09 times, the worst level.
 // Only where every step is a generated kernel of 256 threads (or a transpose of rows) and no two tensors share a part of the workspace.
 void merge_steps(fs_program* prog) {
   const int ns = (int)prog->steps.size();
@@ -952,6 +1012,27 @@ void merge_steps(fs_program* prog) {
       if (bytes[l] < bytes[at[s]]) at[s] = l;
     bytes[at[s]] += prog->steps[s].plan->bytes_min;
   }
+  std::vector<char> loops_in(n, 0);
+  for (int s = 0; s < ns; ++s) loops_in[at[s]] |= members[s].loops;
+  for (int l = 0; l < n; ++l)
+    for (;;) {
+      std::vector<int> here, lean;
+      double ragged = 0;
+      for (int s = 0; s < ns; ++s)
+        if (at[s] == l) here.push_back(s);
+      if (here.size() < 2) break;
+      cost_of_sharing(members, here, &lean, &ragged);
+      if (ragged > (double)(here.size() - 1) * device().launch_s) return;
+      if (lean.empty()) break;
+      const auto movable = std::find_if(lean.begin(), lean.end(), [&](int s) { return !tied[s]; });   // (no folds: it does not loop)
+      int to = -1;
+      for (int k = 0; k < n; ++k)
+        if (!loops_in[k] && (to < 0 || bytes[k] < bytes[to])) to = k;
+      if (movable == lean.end() || to < 0) return;
+      bytes[l] -= prog->steps[*movable].plan->bytes_min;
+      bytes[to] += prog->steps[*movable].plan->bytes_min;
+      at[*movable] = to;
+    }
   std::vector<fs_program::Merged> merged(n);
   for (int l = 0; l < n; ++l) {
     fs_program::Merged& m = merged[l];
@@ -959,10 +1040,26 @@ void merge_steps(fs_program* prog) {
     std::vector<uint32_t> blocks;
     std::vector<Launch> fold_launches;
     uint64_t total = 0;
-    // column sums first: their workgroups work the longest
+    // column sums first: their workgroups work the longest.  Where they are not all resident, one moves before others whose workgroups
+    // have less than half its own's bytes (GELU backward [4096,3072] and LayerNorm backward [32768,768], in that order 50.2 us, in
+    // the other 42.4, apart 44.7; where they are closer neither order is always the better: 19 and 76 MB 40.2 / 42.3, 38 and 151 MB
+    // 37.0 / 36.1)
+    double looping = 0;
+    for (int s = 0; s < ns; ++s)
+      if (at[s] == l) {
+        m.steps.push_back(s);
+        if (members[s].loops) looping += members[s].blocks;
+      }
+    const bool in_rounds = looping > device().n_cu * groups_per_cu(members, m.steps);
+    m.steps.clear();
+    auto per_group = [&](int s) { return members[s].cost->hbm_bytes / members[s].blocks; };
     for (int sums = 1; sums >= 0; --sums)
-      for (int s = 0; s < ns; ++s)
-        if (at[s] == l && (members[s].prog.n_colsum > 0) == (sums == 1)) m.steps.push_back(s);
+      for (int s = 0; s < ns; ++s) {
+        if (at[s] != l || (members[s].prog.n_colsum > 0) != (sums == 1)) continue;
+        size_t to = m.steps.size();
+        while (sums == 1 && in_rounds && to > 0 && per_group(s) > 2.0 * per_group(m.steps[to - 1])) --to;
+        m.steps.insert(m.steps.begin() + to, s);
+      }
     for (int s : m.steps) {
       progs.push_back(members[s].prog);
       blocks.push_back(members[s].blocks);

@@ -102,6 +102,18 @@ def reference_given_stored(spec, inputs, raw):
     return O.evaluate(spec, inputs, stored={n: O.to_f64(raw[n], dts[n]) for n in names}) if names else O.evaluate(spec, inputs)
 
 
+def side_by_side(members):
+    """One graph that holds the graphs `members` with no edge between them."""
+    from workloads.graphs import GraphSpec, OpSpec, TensorSpec
+    inputs, ops, outputs = [], [], []
+    for k, m in enumerate(members):
+        ren = lambda n, k=k: f"s{k}_{n}"  # noqa: E731
+        inputs += [TensorSpec(ren(t.name), t.dtype, t.dims) for t in m.inputs]
+        ops += [OpSpec(ren(o.out), o.opcode, tuple(ren(i) for i in o.inputs), dict(o.attr)) for o in m.ops]
+        outputs += [(ren(n), dt) for n, dt in m.outputs]
+    return GraphSpec(name="pattern_side_by_side", inputs=inputs, ops=ops, outputs=outputs)
+
+
 def note(msg: str) -> None:
     print(msg, flush=True)
     sys.stdout.flush()

@@ -5,7 +5,10 @@ import numpy as np
 import pytest
 
 from paper_2009_10924_amd import binding as B
-from workloads import make_inputs, transformer_block_backward_graph
+from workloads import (gelu_backward_graph, layernorm_backward_bias_graph, make_inputs, rmsnorm_backward_graph, silu_gate_graph,
+                       transformer_block_backward_graph)
+
+from .gpu_util import side_by_side
 
 pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not B.codegen_available(), reason="needs the run-time compiler")]
 
@@ -86,3 +89,20 @@ def test_outputs_that_share_memory():
         shared = [(same[a], ~same[b])]
         for (name, _), x, y in zip(spec.outputs, run(prog, False, shared=shared), run(prog, True, shared=shared)):
             assert np.array_equal(x, y), (name, shared)
+
+
+# a gate beside the sums, one moved behind them, the longer workgroups first, and three programs of one launch for all sums
+@pytest.mark.parametrize("members", [lambda: [layernorm_backward_bias_graph(33, 768, "bf16"), rmsnorm_backward_graph(70, 1536, "bf16"), silu_gate_graph(100, 2048, "bf16")],
+                                     lambda: [layernorm_backward_bias_graph(64, 768, "f16"), rmsnorm_backward_graph(64, 1536, "f16"), silu_gate_graph(16384, 2048, "bf16")],
+                                     lambda: [gelu_backward_graph(1024, 3072), layernorm_backward_bias_graph(8192, 768, "bf16")],
+                                     lambda: [layernorm_backward_bias_graph(129, 768, "f32"), layernorm_backward_bias_graph(65, 512, "f32")]])
+def test_independent_patterns_equal_launches_of_their_own(members):
+    spec = side_by_side(members())
+    graph = B.Graph.from_spec(spec)
+    prog = B.Program(graph)
+    assert len(_merged(prog)) == 2
+    run = _runner(spec, graph)
+    want = run(B.Program(graph, no_joint_folds=True), False)
+    for got in (run(prog, False), run(prog, False, times=3)):
+        for (name, _), a, b in zip(spec.outputs, got, want):
+            assert np.array_equal(a, b), name

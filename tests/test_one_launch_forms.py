@@ -5,7 +5,10 @@ import re
 import pytest
 
 from paper_2009_10924_amd import binding as B
-from workloads import (bias_gelu_dbias_graph, layernorm_backward_graph, rmsnorm_backward_graph, rmsnorm_graph, transformer_block_backward_graph)
+from workloads import (bias_gelu_dbias_graph, gelu_backward_graph, layernorm_backward_bias_graph, layernorm_backward_graph,
+                       rmsnorm_backward_graph, rmsnorm_graph, silu_gate_graph, transformer_block_backward_graph)
+
+from .gpu_util import side_by_side
 
 pytestmark = pytest.mark.skipif(not B.codegen_available(), reason="the HIP run-time compiler is not installed here")
 
@@ -32,3 +35,25 @@ def test_merged_launches_name_their_kernels():
     prog = B.Program(B.Graph.from_spec(transformer_block_backward_graph(2, 16, 4, 32, 128, "bf16")))
     lines = [l for l in prog.describe().splitlines() if l.startswith("merged ")]
     assert lines and all(re.search(r" entry=fs_gen_merged_[0-9a-f]{8} workgroups=[1-9]\d* vgprs=\d+ lds=\d+$", l) for l in lines), lines
+
+
+def _steps_of_launches(members):
+    """(launches of the program's stages, the steps of each merged launch)"""
+    prog = B.Program(B.Graph.from_spec(side_by_side(members)))
+    merged = [re.search(r" steps=([\d,]*) ", l)[1] for l in prog.describe().splitlines() if l.startswith("merged ")]
+    return prog.info["n_kernels"], merged
+
+
+def test_steps_that_would_cost_a_launch_more_than_it_saves_stay_out_of_it():
+    """A step that streams 32 bytes a lane goes to a launch without looping workgroups unless they are at work as long; on 64 bytes it
+    stays.  Where the longest workgroups are not all resident they come first; where those with row reductions need a second
+    round, nothing is merged."""
+    norms = [layernorm_backward_bias_graph(512, 768, "bf16"), rmsnorm_backward_graph(512, 1536, "bf16")]
+    assert _steps_of_launches(norms + [silu_gate_graph(16384, 2048, "bf16")]) == (3, ["0,1", "2"])
+    assert _steps_of_launches(norms + [silu_gate_graph(1024, 2048, "bf16")]) == (3, ["0,1,2", ""])
+    wide = [layernorm_backward_bias_graph(2048, 1024, "bf16")] * 2
+    assert _steps_of_launches(wide + [silu_gate_graph(2048, 4096, "bf16")]) == (3, ["0,1,2", ""])
+    assert _steps_of_launches([gelu_backward_graph(1024, 3072), layernorm_backward_bias_graph(8192, 768, "bf16")]) == (3, ["1,0", ""])
+    assert _steps_of_launches([gelu_backward_graph(8192, 3072), layernorm_backward_bias_graph(8192, 768, "bf16")]) == (3, ["0,1", ""])
+    assert _steps_of_launches([layernorm_backward_bias_graph(32768, 768, "bf16"), rmsnorm_backward_graph(32768, 1536, "bf16"),
+                               silu_gate_graph(4096, 2048, "bf16")]) == (3, [])
