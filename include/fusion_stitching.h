@@ -246,12 +246,12 @@ int64_t fs_plan_describe(const fs_plan *p, char *text, size_t capacity);
 int32_t fs_codegen_enable(int32_t on);
 /* 1 if the run-time compiler could be loaded in this process, else 0.                 */
 int32_t fs_codegen_available(void);
-/* Writes the HIP source of the plan's generated kernel(s), the one-launch form of a small
- * pattern with column sums among them (the kernel functions only, not the fixed device
- * headers they are compiled with), into `text` (HOST buffer of `capacity`
- * bytes, NUL-terminated, truncated if too small) and returns the size needed including
- * the NUL (1 for a plan without a generated kernel), or a negative error.
- * Errors: FS_ERR_INVALID_ARG.                                                          */
+/* Writes the HIP source of the generated kernel(s) of the plan's listed launches, or, where
+ * those are all compiled in, of the one launch that runs instead (`at_once` in
+ * fs_plan_describe), into `text` (the kernel functions only, not the fixed device headers
+ * they are compiled with; HOST buffer of `capacity` bytes, NUL-terminated, truncated if too
+ * small) and returns the size needed including the NUL (1 for a plan without a generated
+ * kernel), or a negative error.  Errors: FS_ERR_INVALID_ARG.                            */
 int64_t fs_plan_source(const fs_plan *p, char *text, size_t capacity);
 
 /* ---- execution (the run-time hot path) --------------------------------------- */

@@ -559,7 +559,7 @@ int64_t fs_plan_source(const fs_plan* p, char* text, size_t capacity) try {
   std::string s;
   for (const Launch& l : p->candidates[p->chosen].launches)
     if (l.kernel == K_ROW_GENERATED) s += generate_row_kernel_body(l.args.u.prog);
-  if (p->at_once) s += p->at_once->text;
+  if (s.empty() && p->at_once) s = p->at_once->text;
   if (capacity > 0) {
     const size_t n = std::min(capacity - 1, s.size());
     memcpy(text, s.data(), n);
