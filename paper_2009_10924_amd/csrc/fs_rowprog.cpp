@@ -718,6 +718,7 @@ struct Shape {
   uint32_t NC = 1;   // > 1: the row is worked through in NC chunks of L * K steps (rows beyond any workgroup's registers)
   uint32_t kept = 0; // of those, the first `kept` stay in registers in storage form after the first pass
   uint32_t lds = 0;  // ... and the next `lds` in LDS
+  uint32_t most = 0; // (lds > 0) what the registers alone hold, of NC
 };
 
 // Step widths to offer.  A pattern whose 16-bit vector inputs ask for 8 elements per step may also move float32
@@ -817,12 +818,12 @@ std::vector<Shape> enumerate_shapes(const Compiler& c, int vec, bool interpretab
         // chunks that the registers have no room for may stay in LDS, as much of it as the registers leave workgroups on a
         // compute unit to share; where the compiled kernel would spill, the form with one chunk less in registers is the next.
         // (us, the rest read from memory in each pass / held in LDS: log-softmax f32 [809,122867] 174.4 / 164.1, [30,131072]
-        // 16.2 / 14.4, bf16 [1500,128257], which then lies on the grid, 179.2 / 150.3.  A single chunk beyond the registers gains for
-        // that only: bf16 [4096,128256], one of eight, 358.0 / 359.7, f32 [1000,80000], one of ten, level; see make_generated())
-        const uint32_t room_lds = (uint32_t)((T == 1024 ? 156 : T == 512 ? 78 : 38) * 1024 / ((int)T * lds_per_chunk));
+        // 16.2 / 14.4, bf16 [1500,128257], which then lies on the grid, 179.2 / 150.3; where it does not pay, see make_generated())
+        const uint32_t room_lds = (uint32_t)((T == 1024 ? 156 : 78) * 1024 / ((int)T * lds_per_chunk));
         for (uint32_t less = 0; less < 2 && t.kept > less && t.kept < t.NC && room_lds > 0; ++less) {
           Shape u = t;
           u.kept = t.kept - less;
+          u.most = t.kept;
           u.lds = std::min<uint32_t>(t.NC - u.kept, room_lds);
           if (t.NC - u.kept - u.lds <= 64) shapes.push_back(u);
         }
@@ -996,12 +997,26 @@ void make_generated(const Compiler& c, int vec, const Shape& s, Candidate* cand)
       if (!((base.full_bcast >> i) & 1u)) in_bytes += (double)dtype_bytes(base.full_dt[i]) * base.rows * base.cols;
       regs_per_chunk += s.K * ((vec * dtype_bytes(base.full_dt[i]) + 3) / 4);
     }
-    // chunks held in registers or LDS are not read again; a single one in LDS costs what it saves unless its row is on the grid by it
-    const uint32_t held_chunks = s.lds == 1 && !gc.on_grid ? s.kept : s.kept + s.lds;
-    in_bytes *= 1.0 - (double)held_chunks / s.NC;
-    gc.vgpr_estimate += regs_per_chunk * (int)(s.kept + (s.lds > 0 ? 1 : 0));
     int lane_bytes = 0;
     for (int i = 0; i < base.n_full; ++i) lane_bytes += s.K * vec * dtype_bytes(base.full_dt[i]);
+    // Chunks held in registers or LDS are not read again.  Past the first rows of all compute units those in LDS count as what
+    // the registers alone would hold where
+    //   * these leave a compute unit 160 KB or less to read again, which its cache then mostly holds: rows of 500 and 1500 times
+    //     98304 float32, us in registers / with two or three chunks of 32 KB in LDS, softmax 65.7 / 69.3, 201 / 213, RMS norm 67.6 / 75.7,
+    //     215 / 220; of 131072, six and seven chunks beyond the registers, four of them in LDS, softmax 352 / 336, RMS norm 306 / 290;
+    //   * LDS holds no less than the registers: softmax backward bf16 [500,98304], 1024 lanes with two chunks in each 51.7, 512 lanes
+    //     with ten in registers 46.9 (by the bytes read again the first would be 8 % ahead).  Not so where column vectors take
+    //     the registers (LayerNorm bf16 [500,70000], one chunk in registers and two in LDS 46.8, without LDS 52.5, f16 [832,61340] 82.2 / 92.3);
+    // unless the row is on the grid by it.  Over 517 rows of 33000 to 131072 elements (softmax, log-softmax, softmax backward, RMS
+    // norm, LayerNorm; 50 to 1500 rows) the choice is 1.043 times as fast as without LDS, 17 of them slower by 1.5 to 5 % (52 by up
+    // to 11 % when all counted as held but a single one).
+    const uint32_t groups_per_cu = std::max(1u, 1024u / s.L);
+    const bool cached = (double)(s.NC - s.most) * lane_bytes * s.L * groups_per_cu <= 160.0 * 1024;
+    const bool more_in_lds = s.kept <= s.lds;
+    const bool as_registers = s.lds > 0 && !gc.on_grid && base.rows > 1.3 * d.n_cu && (more_in_lds ? base.n_col == 0 : cached);
+    const uint32_t held_chunks = as_registers ? s.most : s.kept + s.lds;
+    in_bytes *= 1.0 - (double)held_chunks / s.NC;
+    gc.vgpr_estimate += regs_per_chunk * (int)(s.kept + (s.lds > 0 ? 1 : 0));
     cand->info.lds_bytes += (int32_t)(s.lds * s.L) * lane_bytes;
     gc.lds_bytes_per_block = cand->info.lds_bytes;
     gc.lds_traffic_bytes = 2.0 * s.lds * s.L * lane_bytes * base.rows;
