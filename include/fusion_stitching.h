@@ -211,9 +211,9 @@ fs_status fs_plan_candidate(const fs_plan *p, int32_t index, fs_plan_info *out);
  * sums over all rows adds `colsums <n> partials <buffer> rows_per_group <r> col_tiles <t>`
  * (and `launch colfold` entries after it, one per fold; folds that follow each other
  * are issued as ONE kernel launch, which `launches=` counts); a row worked through in pieces adds
- * `chunks <n> of <w> columns[, the first <k> kept in registers]`.  The last line of a plan whose
- * fs_execute runs one launch instead of those listed names that one: `at_once sum_workgroups=<n>
- * row_workgroups=<n> entry=<name> block=256 vgprs=<n> lds=<bytes>`.
+ * `chunks <n> of <w> columns[, the first <k> kept in registers[ and LDS (<r> + <l>)]]`.  The last
+ * line of a plan whose fs_execute runs one launch instead of those listed names that one:
+ * `at_once sum_workgroups=<n> row_workgroups=<n> entry=<name> block=256 vgprs=<n> lds=<bytes>`.
  * Errors: FS_ERR_INVALID_ARG.                                                          */
 int64_t fs_plan_describe(const fs_plan *p, char *text, size_t capacity);
 
@@ -227,8 +227,8 @@ int64_t fs_plan_describe(const fs_plan *p, char *text, size_t capacity);
  * are shared between plans with identical source and stay loaded until the process ends.
  * Generated kernels only: row lengths that are no multiple of 4 elements; rows of more than
  * 2048 128-bit vectors (workgroups of 512 / 1024 threads; beyond 8192 vectors the row is
- * worked through in chunks, one pass per row reduction, the chunks kept in registers where
- * they fit); sums over all rows of a pattern (reduce_sum along axis 0 of a rank-2 value, or
+ * worked through in chunks, one pass per row reduction, the chunks kept in registers, and
+ * further ones in LDS, where they fit and that pays); sums over all rows of a pattern (reduce_sum along axis 0 of a rank-2 value, or
  * a chain of reduce_sums along each leading axis in turn; a graph output nothing else
  * reads, float32 or rounded once to a 16-bit dtype; the plan then has a workspace and a
  * second launch that folds the partial sums); more than 4 full-shaped inputs.

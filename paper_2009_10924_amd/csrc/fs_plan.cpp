@@ -527,7 +527,7 @@ int64_t fs_plan_describe(const fs_plan* p, char* text, size_t capacity) try {
     if (q.col_chunks > 1)   // the row in pieces of lanes * vecs steps, a pass per row reduction and one for the stores
       s += "  chunks " + std::to_string(q.col_chunks) + " of " + std::to_string(q.lanes_per_row * q.vecs_per_lane * q.vec) + " columns" +
            (q.col_kept > 0 ? ", the first " + std::to_string(q.col_kept + q.col_lds) + " kept in registers" : std::string()) +
-           (q.col_lds > 0 ? " (the last " + std::to_string(q.col_lds) + " of them in LDS)" : std::string()) + "\n";
+           (q.col_lds > 0 ? " and LDS (" + std::to_string(q.col_kept) + " + " + std::to_string(q.col_lds) + ")" : std::string()) + "\n";
     static const char* op_names[] = {"add", "sub", "rsub", "mul", "div", "rdiv", "max", "square", "exp", "rsqrt", "tanh", "gelu",
                                      "gelu_grad", "log", "sigmoid", "relu", "abs", "sqrt", "cvt", "load", "rsum", "rmax", "rsumsq", "store", "store_scal", "colsum"};
     static const char* kind_names[] = {"acc", "sacc", "reg", "scal", "imm", "col"};
