@@ -115,7 +115,12 @@ static bool stores_again(const RowProgP& p) {
 //     boundary (us, every step unaligned / on the grid: log-softmax bf16 [2048,50257] 89.0 / 76.5, [809,9269] 6.86 / 5.69, f16
 //     [34,88897] 12.4 / 9.4; float32 and even lengths gain nothing),
 //   * a workgroup works on a row, or a wavefront's lanes on several steps of rows with a stretched operand beside them (attention
-//     rows f16 [7,8,587,587] 14.0 / 12.3; softmax without a mask on a wavefront bf16 [30000,210] 4.98 / 5.0, f16 [45513,541] 15.7 / 16.6),
+//     rows f16 [7,8,587,587] 14.0 / 12.3, 68 shapes of 27 such sizes 1.03 times) and at most one exponential or the like per element:
+//     the steps that may slide take more instructions, which shows where arithmetic is half of the time (the same rows with a tanh
+//     soft-cap before the exponential, f16 [2,12,587,587] 8.6 / 9.0 and 10.0 / 11.0, 66 shapes 0.96 times).  Without a stretched operand it is level
+//     on lane groups (126 shapes of softmaxes 1.01, f16 [175182,137] 17.6 / 17.2 to [60913,197] 9.5 / 9.8; log-softmax and softmax
+//     backward 1.00), and so it is with one step per lane, where the fastest shapes lose (attention rows f16 [25,12,197,197] on 32 lanes
+//     9.9 / 10.4, [34,12,171,171] 10.3 / 10.9, softmax f16 [180451,133] 20.0 / 21.7),
 //   * their first and last steps are stored whole (stores_again), every chunk of a long row kept,
 //   * nothing ties a lane to the same columns from row to row (column sums, several rows per workgroup) or has rows start elsewhere
 //     (transposed outputs; column vectors, whose accesses would then be the unaligned ones: LayerNorm bf16 [489,2359] 4.03 / 4.29),
@@ -126,8 +131,13 @@ bool row_on_grid(const RowProgP& p) {
     if (p.full_dt[i] == DT_F32) return false;
   for (int i = 0; i < p.n_instr; ++i)
     if (p.instr[i].op == PO_STORE && p.instr[i].aux == DT_F32) return false;
+  int heavy = 0;
+  for (int i = 0; i < p.n_instr; ++i) {
+    const int32_t op = p.instr[i].op;
+    heavy += !(p.instr[i].flags & PF_SCALAR) && (op == PO_EXP || op == PO_LOG || op == PO_TANH || op == PO_SIGMOID || op == PO_GELU || op == PO_GELU_GRAD);
+  }
   const int steps = p.vecs_per_lane * std::max(1, p.col_chunks);
-  return (p.lanes_per_row > 64 || (steps > 1 && p.full_bcast != 0)) && p.cols + (uint32_t)p.vec - 1u <= (uint64_t)p.lanes_per_row * (uint32_t)steps * (uint32_t)p.vec;
+  return (p.lanes_per_row > 64 || (steps > 1 && p.full_bcast != 0 && heavy <= 1)) && p.cols + (uint32_t)p.vec - 1u <= (uint64_t)p.lanes_per_row * (uint32_t)steps * (uint32_t)p.vec;
 }
 
 namespace {
