@@ -264,7 +264,10 @@ int64_t fs_plan_source(const fs_plan *p, char *text, size_t capacity);
  * do not matter (every kernel that reads it reads what an earlier kernel of the same
  * call wrote) and it is reusable afterwards.  Allocates nothing, never
  * synchronizes.  A small pattern with column sums runs as one launch instead of two
- * (`at_once` in fs_plan_describe) unless an output shares memory with an input or output.  Two calls that share a workspace must be ordered on one stream.
+ * (`at_once` in fs_plan_describe) unless an output shares memory with an input or another
+ * output, or the call is captured before its kernel is loaded on the current device (plan
+ * creation loads it on the device that is current then, a call outside capture on any
+ * other).  Two calls that share a workspace must be ordered on one stream.
  * Errors: FS_ERR_INVALID_ARG, FS_ERR_WORKSPACE, FS_ERR_ALIGN, FS_ERR_HIP.         */
 fs_status fs_execute(const fs_plan *p, const void *const *inputs, void *const *outputs,
                      void *workspace, size_t workspace_bytes, void *hip_stream);

@@ -226,9 +226,9 @@ fs_status fs::run_launches(const fs_plan* p, const void* const* inputs, void* co
                        size_t n_launches) {
   const Candidate& c = p->candidates[p->chosen];
   const size_t end = std::min(n_launches, c.launches.size());
-  // (not loaded here: loading is nothing for a call under capture, which the two launches of a fixed family can be)
-  if (p->at_once && end == c.launches.size() && gen_loaded(p->at_once->kernel.get()) &&
-      !outputs_share_memory(p->input_bytes, p->output_bytes, inputs, outputs))
+  // (a call under capture cannot load the kernel; the two launches of a compiled-in family need nothing loaded)
+  if (p->at_once && end == c.launches.size() && !outputs_share_memory(p->input_bytes, p->output_bytes, inputs, outputs) &&
+      gen_ready(p->at_once->kernel.get(), hip_stream))
     return run_at_once(*p->at_once, inputs, outputs, hip_stream);
   auto address = [&](const BufRef& r) -> void* {
     switch (r.kind) {

@@ -175,7 +175,13 @@ const char* hip_error_text(int) { return "launch refused by the host stub"; }
 
 // "compilation" of generated kernels: succeeds when FS_STUB_COMPILE_OK is set (the source is kept, so that identical
 // sources share a kernel as in the product), otherwise fails like a missing run-time compiler would
-struct GenKernel { std::string source; };
+struct GenKernel {
+  std::string source;
+  bool loaded = false;
+};
+namespace {
+bool g_device = true, g_capturing = false;   // what fs_stub_state() says of the machine
+}
 bool gen_available() { return true; }
 int gen_compile(const std::string& src, const char* entry, std::shared_ptr<GenKernel>* out, std::string* log) {
   if (getenv("FS_STUB_COMPILE_OK") && entry && src.find(entry) != std::string::npos) {
@@ -187,10 +193,18 @@ int gen_compile(const std::string& src, const char* entry, std::shared_ptr<GenKe
   return 1;
 }
 GenResources gen_resources(const GenKernel*) { return GenResources(); }
-int gen_preload(GenKernel*) { return 0; }
-bool gen_loaded(const GenKernel*) { return true; }
+int gen_preload(GenKernel* k) {
+  k->loaded = k->loaded || g_device;
+  return 0;
+}
+bool gen_ready(GenKernel* k, void*) {
+  k->loaded = k->loaded || (g_device && !g_capturing);
+  return k->loaded;
+}
 int gen_launch(GenKernel* k, const void* args, size_t args_bytes, const LaunchShape& shape, void*) {
   if (!k || !args || args_bytes == 0 || args_bytes % sizeof(void*) != 0 || check_shape(shape)) return 1;
+  if (!k->loaded && (g_capturing || !g_device)) return 1;   // nothing can be loaded now
+  k->loaded = true;
   ++g_launches;
   return 0;
 }
@@ -212,4 +226,5 @@ extern "C" fs_status fs_stream_probe(void*, const void*, size_t, size_t, int32_t
   return fs::fail(FS_ERR_HIP, "fs_stream_probe: not part of the host stub");
 }
 extern "C" long fs_stub_launch_count(void) { return fs::g_launches; }
+extern "C" void fs_stub_state(int device, int capturing) { fs::g_device = device != 0, fs::g_capturing = capturing != 0; }
 extern "C" int fs_stub_check_argument_words(void) { return fs::check_words(); }

@@ -285,9 +285,15 @@ int gen_preload(GenKernel* k) {
   return function_here(k, &f);
 }
 
-bool gen_loaded(const GenKernel* k) {
+bool gen_ready(GenKernel* k, void* stream) {
   int dev = 0;
-  return hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < kMaxDevices && k->fn[dev].load(std::memory_order_acquire) != nullptr;
+  if (hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < kMaxDevices && k->fn[dev].load(std::memory_order_acquire) != nullptr) return true;
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusActive;
+  hipFunction_t f;
+  if (hipStreamIsCapturing(static_cast<hipStream_t>(stream), &capture) == hipSuccess && capture == hipStreamCaptureStatusNone && function_here(k, &f) == 0)
+    return true;
+  (void)hipGetLastError();   // (the caller has another way)
+  return false;
 }
 
 int gen_launch(GenKernel* k, const void* args, size_t args_bytes, const LaunchShape& s, void* stream) {

@@ -347,7 +347,8 @@ int gen_compile(const std::string& source, const char* entry, std::shared_ptr<Ge
 GenResources gen_resources(const GenKernel* k);
 // Loads the kernel's module on the current device if there is one (otherwise the first launch does).
 int gen_preload(GenKernel* k);
-bool gen_loaded(const GenKernel* k);   // on the current device
+// Whether a launch on `stream` finds the module loaded on the current device; loads it unless the stream is being captured.
+bool gen_ready(GenKernel* k, void* stream);
 // Launches with `args` (args_bytes of by-value kernel arguments).  Returns hipError_t as int.
 int gen_launch(GenKernel* k, const void* args, size_t args_bytes, const LaunchShape& shape, void* stream);
 

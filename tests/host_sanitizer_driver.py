@@ -11,9 +11,9 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 sys.path.insert(0, ROOT)
 
 from paper_2009_10924_amd import binding as B                                            # noqa: E402
-from workloads import (EXPLORE_CONFIGS, FULL_CONFIGS, GENERIC_CONFIGS, NEXT_CONFIGS, PACK_CONFIGS, gelu_backward_graph,  # noqa: E402
-                       independent_tiny_patterns_graph, layernorm_backward_bias_graph, random_multi_pattern, random_row_pattern,
-                       transpose_graph)
+from workloads import (EXPLORE_CONFIGS, FULL_CONFIGS, GENERIC_CONFIGS, NEXT_CONFIGS, PACK_CONFIGS, bias_gelu_dbias_graph,  # noqa: E402
+                       gelu_backward_graph, independent_tiny_patterns_graph, layernorm_backward_bias_graph, layernorm_backward_graph,
+                       random_multi_pattern, random_row_pattern, transpose_graph)
 
 
 def fake(n, base):
@@ -43,6 +43,38 @@ def run_program(spec, **opts):
     return prog
 
 
+def launches_of(lib, call):
+    before = lib.fs_stub_launch_count()
+    call()
+    return lib.fs_stub_launch_count() - before
+
+
+def one_launch_forms(lib):
+    """A small pattern with column sums runs as one launch wherever its kernel can be loaded, also if the plan was made without a device;
+    under capture before that, and where an output shares memory with anything, as two."""
+    for spec in (layernorm_backward_graph(64, 768, "bf16"), bias_gelu_dbias_graph(64, 768, "bf16")):
+        n_in, n_out = len(spec.inputs), len(spec.outputs)
+        ins = fake(n_in, 0x100000)
+        outs = [0x40000000 + 0x100000 * i for i in range(n_out)]
+        lib.fs_stub_state(0, 0)
+        plan = B.Plan(B.Graph.from_spec(spec), "auto")
+        ws = plan.info["workspace_bytes"]
+        assert "at_once " in plan.describe()
+        run = lambda i=ins, o=outs: launches_of(lib, lambda: plan.execute_ptrs(i, o, 0x70000000, ws, 0))  # noqa: E731
+        lib.fs_stub_state(1, 1)
+        assert run() == 2                      # captured before anything could load the kernel
+        lib.fs_stub_state(1, 0)
+        assert run() == 1 and launches_of(lib, lambda: plan.execute_static_ptrs(ins, outs, 0)) == 1
+        lib.fs_stub_state(1, 1)
+        assert run() == 1                      # loaded by now
+        lib.fs_stub_state(1, 0)
+        size = 64 * 768 * 2
+        big = [k for k, t in enumerate(spec.inputs) if tuple(t.dims) == (64, 768)][0]
+        for at, launches in ((0, 2), (16, 2), (size - 16, 2), (size, 1), (16 - size, 2), (-size, 1)):
+            assert run(o=[ins[big] + at] + outs[1:]) == launches, at   # over an input, into it from either side, beside it
+        assert run(o=[outs[0], outs[0] + size - 16] + outs[2:]) == 2 and run(o=[outs[0], outs[0] + size] + outs[2:]) == 1
+
+
 def main():
     lib = B.load()
     lib.fs_stub_launch_count.restype = ctypes.c_long
@@ -51,6 +83,7 @@ def main():
     for compile_ok in ("", "1"):
         if compile_ok:
             os.environ["FS_STUB_COMPILE_OK"] = "1"      # generated kernels "compile": the generator's whole path runs
+            one_launch_forms(lib)
         for name, make in list(FULL_CONFIGS.items()) + list(NEXT_CONFIGS.items()) + list(GENERIC_CONFIGS.items()):
             spec = make()
             plan = run_plan(spec)
