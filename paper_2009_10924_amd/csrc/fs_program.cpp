@@ -139,9 +139,10 @@ static fs_status run_program(const fs_program* p, int32_t first_stage, int32_t l
       default: return nullptr;
     }
   };
-  // (steps that share memory must run in their order)
+  // (steps that share memory must run in their order; a call under capture cannot load the kernels, which lone transposes do not need)
   if (!p->merged.empty() && first_stage == 0 && last_stage == p->info.n_stages - 1 &&
-      !outputs_share_memory(p->input_bytes, p->output_bytes, inputs, outputs)) {
+      !outputs_share_memory(p->input_bytes, p->output_bytes, inputs, outputs) &&
+      std::all_of(p->merged.begin(), p->merged.end(), [&](const fs_program::Merged& m) { return gen_ready(m.kernel.get(), hip_stream); })) {
     for (const fs_program::Merged& m : p->merged) {
       void* ptrs[kMergedMaxOperands];
       size_t n = 0;

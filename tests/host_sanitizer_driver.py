@@ -14,6 +14,7 @@ from paper_2009_10924_amd import binding as B                                   
 from workloads import (EXPLORE_CONFIGS, FULL_CONFIGS, GENERIC_CONFIGS, NEXT_CONFIGS, PACK_CONFIGS, bias_gelu_dbias_graph,  # noqa: E402
                        gelu_backward_graph, independent_tiny_patterns_graph, layernorm_backward_bias_graph, layernorm_backward_graph,
                        random_multi_pattern, random_row_pattern, transpose_graph)
+from tests.gpu_util import side_by_side                                                  # noqa: E402
 
 
 def fake(n, base):
@@ -75,6 +76,25 @@ def one_launch_forms(lib):
         assert run(o=[outs[0], outs[0] + size - 16] + outs[2:]) == 2 and run(o=[outs[0], outs[0] + size] + outs[2:]) == 1
 
 
+def merged_launches(lib):
+    """Two lone transposes run as one launch wherever its kernel can be loaded; captured before that, in the two kernels that are compiled
+    in.  A result that lies in another's buffer, or over an input, sends the run step by step."""
+    spec = side_by_side([transpose_graph((64, 128, 12, 64), (0, 2, 1, 3), "bf16"), transpose_graph((64, 256, 12, 64), (0, 2, 1, 3), "f32")])
+    lib.fs_stub_state(0, 0)
+    prog = B.Program(B.Graph.from_spec(spec))
+    assert "merged 0 of 1 steps=0,1 " in prog.describe() and prog.info["n_kernels"] == 2
+    ins, outs = [0x10000000, 0x20000000], [0x40000000, 0x50000000]
+    run = lambda o=outs: launches_of(lib, prog.bind(ins, o, 0x70000000, prog.info["workspace_bytes"], 0))  # noqa: E731
+    lib.fs_stub_state(1, 1)
+    assert run() == 2
+    lib.fs_stub_state(1, 0)
+    assert run() == 1
+    lib.fs_stub_state(1, 1)
+    assert run() == 1
+    lib.fs_stub_state(1, 0)
+    assert run([ins[1], outs[1]]) == 2 and run([outs[0], outs[0] + 64]) == 2
+
+
 def main():
     lib = B.load()
     lib.fs_stub_launch_count.restype = ctypes.c_long
@@ -84,6 +104,7 @@ def main():
         if compile_ok:
             os.environ["FS_STUB_COMPILE_OK"] = "1"      # generated kernels "compile": the generator's whole path runs
             one_launch_forms(lib)
+            merged_launches(lib)
         for name, make in list(FULL_CONFIGS.items()) + list(NEXT_CONFIGS.items()) + list(GENERIC_CONFIGS.items()):
             spec = make()
             plan = run_plan(spec)
