@@ -781,6 +781,13 @@ std::string generate_merged_kernel(const std::vector<RowProgP>& members, const s
 }
 
 std::string embedded_prelude() { return std::string(kEmbeddedDeviceUtils) + kEmbeddedGenSupport; }
+GenSource gen_source(const std::string& text, const std::string& entry) {
+  GenSource s;
+  s.text = text;
+  s.entry = entry;
+  s.headers = text.find("using namespace fsk;\n", embedded_prelude().size());   // (every kernel's own text begins so)
+  return s;
+}
 
 std::string generate_row_kernel(const RowProgP& p) {
   std::string s;

@@ -1034,6 +1034,7 @@ void merge_steps(fs_program* prog) {
       at[*movable] = to;
     }
   std::vector<fs_program::Merged> merged(n);
+  std::vector<GenSource> sources;
   for (int l = 0; l < n; ++l) {
     fs_program::Merged& m = merged[l];
     std::vector<RowProgP> progs;
@@ -1077,12 +1078,17 @@ void merge_steps(fs_program* prog) {
       }
     }
     if (total == 0 || total >= (1ull << 31) || m.operands.size() > kMergedMaxOperands) return;
-    std::string log;
     const std::string source = embedded_prelude() + generate_merged_kernel(progs, blocks, fold_launches, &m.entry);
-    if (gen_compile(source, m.entry.c_str(), &m.kernel, &log) != 0 || gen_resources(m.kernel.get()).scratch_bytes > 0 || gen_preload(m.kernel.get()) != 0) return;
+    sources.push_back(gen_source(source, m.entry));
     m.shape = LaunchShape{};
     m.shape.grid[0] = (uint32_t)total;
     m.shape.block[0] = 256;
+  }
+  gen_compile_together(sources);
+  for (int l = 0; l < n; ++l) {
+    fs_program::Merged& m = merged[l];
+    std::string log;
+    if (gen_compile(sources[l].text, m.entry.c_str(), &m.kernel, &log) != 0 || gen_resources(m.kernel.get()).scratch_bytes > 0 || gen_preload(m.kernel.get()) != 0) return;
   }
   prog->merged = std::move(merged);
 }
@@ -1192,6 +1198,9 @@ fs_status fs_explore(const fs_graph* g, const fs_explore_opts* opts, fs_program*
     if ((int)k != best) built[k].destroy();
   if (best < 0) return fail(first_error != FS_OK ? first_error : FS_ERR_UNSUPPORTED_PATTERN, "fs_explore: %s", first_text.c_str());
 
+  std::vector<GenSource> sources;
+  for (const fs_program::Step& s : built[best].steps) compiled_ahead(*s.plan, &sources);
+  gen_compile_together(sources);
   for (fs_program::Step& s : built[best].steps) {
     fs_status st = complete_plan(s.plan);
     if (st == FS_ERR_UNSUPPORTED_PATTERN) {

@@ -213,6 +213,7 @@ std::string generate_merged_kernel(const std::vector<RowProgP>& members, const s
 std::string generate_sums_beside_rows(const SumsBesideRows& k, std::string* entry);   // likewise without the headers
 int64_t column_sum_lds_bytes(const RowProgP& p);   // LDS in which a workgroup folds its rows' column sums
 std::string embedded_prelude();
+GenSource gen_source(const std::string& text, const std::string& entry);   // of a generated kernel's whole text
 // Pairs of row reductions "rmax; acc - max; exp; rsum" that a row worked through in chunks gathers in one pass
 // (online[q] = 1 for the first of each pair; `online` may be null); returns their number.
 int online_reduction_pairs(const RowProgP& p, std::vector<char>* online);
@@ -222,7 +223,9 @@ bool row_on_grid(const RowProgP& p);   // fs_codegen.cpp: the generated kernel's
 bool codegen_enabled();
 // fs_plan_create without the last step: generated kernels are not compiled yet.  complete_plan() compiles
 // the chosen candidate's kernel; if that fails, or the kernel spills registers, it moves the choice to the
-// next best candidate (unless the caller fixed the candidate, then it fails).
+// next best candidate (unless the caller fixed the candidate, then it fails).  compiled_ahead() appends the
+// kernels that it will compile first, for gen_compile_together().
+void compiled_ahead(const fs_plan& p, std::vector<GenSource>* out);
 fs_status create_plan(const fs_graph* g, int32_t scheme, const fs_plan_opts* opts, bool complete, fs_plan** out);
 // The first `n_launches` launches of the plan's chosen candidate, all of them as one launch where the plan has that form and may take
 // it (arguments already validated by the caller).

@@ -143,6 +143,11 @@ static void fill_generic_forms(const fs_graph& g, fs_plan* p) {
     }
 }
 
+void compiled_ahead(const fs_plan& p, std::vector<GenSource>* out) {
+  for (const Launch& l : p.candidates[p.chosen].launches)
+    if (l.kernel == K_ROW_GENERATED && !l.gen) out->push_back(gen_source(generate_row_kernel(l.args.u.prog), generated_kernel_entry(l.args.u.prog)));
+}
+
 fs_status complete_plan(fs_plan* p) {
   const fs_plan_opts& o = p->opts;
   for (;;) {
@@ -286,21 +291,20 @@ fs_status fs::run_launches(const fs_plan* p, const void* const* inputs, void* co
   return FS_OK;
 }
 
-// A plan that was left to choose and has a fold of column sums to launch: the form without one, if it has it.
-static void add_at_once(const fs_graph& g, fs_plan* p) {
-  const fs_plan_opts& o = p->opts;
-  const std::vector<Launch>& launches = p->candidates[p->chosen].launches;
-  if (!codegen_enabled() || o.candidate >= 0 || o.block_threads > 0 || o.lanes_per_row > 0 || o.vecs_per_lane > 0 || launches.size() < 2 ||
-      launches.back().kernel != K_COLFOLD)
-    return;
-  SumsBesideRows k;
+// A plan that was left to choose and has a fold of column sums to launch may have a form without one.
+static bool folds_by_choice(const fs_plan& p) {
+  const fs_plan_opts& o = p.opts;
+  const std::vector<Launch>& launches = p.candidates[p.chosen].launches;
+  return codegen_enabled() && o.candidate < 0 && o.block_threads <= 0 && o.lanes_per_row <= 0 && o.vecs_per_lane <= 0 && launches.size() >= 2 &&
+         launches.back().kernel == K_COLFOLD;
+}
+
+static void add_at_once(fs_plan* p, SumsBesideRows* k) {
   std::string log;
-  if (!sums_beside_rows(g, &k)) return;
-  k.text = generate_sums_beside_rows(k, &k.entry);
-  if (gen_compile(embedded_prelude() + k.text, k.entry.c_str(), &k.kernel, &log) != 0 || gen_resources(k.kernel.get()).scratch_bytes > 0 ||
-      gen_preload(k.kernel.get()) != 0)
+  if (!folds_by_choice(*p) || gen_compile(embedded_prelude() + k->text, k->entry.c_str(), &k->kernel, &log) != 0 ||
+      gen_resources(k->kernel.get()).scratch_bytes > 0 || gen_preload(k->kernel.get()) != 0)
     return;
-  p->at_once = std::make_unique<SumsBesideRows>(k);
+  p->at_once = std::make_unique<SumsBesideRows>(*k);
 }
 
 fs_status fs::check_execute_args(const fs_plan* p, const void* const* inputs, void* const* outputs, const char* who) {
@@ -396,6 +400,14 @@ fs_status fs::create_plan(const fs_graph* g, int32_t scheme, const fs_plan_opts*
   for (int t : g->outputs) p->output_bytes.push_back(g->tensors[t].numel() * dtype_bytes(g->tensors[t].store_as));
   if (scheme != FS_SCHEME_UNFUSED && codegen_enabled()) fill_generic_forms(*g, p);
   if (complete) {
+    SumsBesideRows once;
+    const bool may_run_at_once = scheme == FS_SCHEME_AUTO && folds_by_choice(*p) && sums_beside_rows(*g, &once);
+    if (may_run_at_once) {   // its kernel and the plan's own in one run of the compiler
+      once.text = generate_sums_beside_rows(once, &once.entry);
+      std::vector<GenSource> sources = {gen_source(embedded_prelude() + once.text, once.entry)};
+      compiled_ahead(*p, &sources);
+      gen_compile_together(sources);
+    }
     const fs_status s = complete_plan(p);
     if (s != FS_OK) {
       delete p;
@@ -408,7 +420,7 @@ fs_status fs::create_plan(const fs_graph* g, int32_t scheme, const fs_plan_opts*
       }
       return s;
     }
-    if (scheme == FS_SCHEME_AUTO) add_at_once(*g, p);
+    if (may_run_at_once) add_at_once(p, &once);
   }
   *out = p;
   return FS_OK;

@@ -192,6 +192,7 @@ int gen_compile(const std::string& src, const char* entry, std::shared_ptr<GenKe
   if (log) *log = "host stub: no compiler (" + std::to_string(src.size()) + " bytes of source)";
   return 1;
 }
+void gen_compile_together(const std::vector<GenSource>&) {}
 GenResources gen_resources(const GenKernel*) { return GenResources(); }
 int gen_preload(GenKernel* k) {
   k->loaded = k->loaded || g_device;

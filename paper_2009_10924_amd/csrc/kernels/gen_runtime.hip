@@ -8,6 +8,7 @@
 #include <hip/hip_runtime.h>
 #include <hip/hiprtc.h>
 
+#include <algorithm>
 #include <atomic>
 #include <cstdio>
 #include <cstdlib>
@@ -61,20 +62,36 @@ const Rtc& rtc() {
   return r;
 }
 
-// Value of an unsigned integer entry `key` of the kernel's metadata note (MessagePack, as the
-// AMDGPU code-object format defines it): the key's bytes are searched for and the integer that
-// follows is decoded.  -1 if absent.
-int64_t metadata_uint(const std::string& code, const char* key) {
+// Whether `code` holds the MessagePack string `text` at `at` (fixstr 0xa0|len or str8 0xd9 len in front of it).
+bool is_string_at(const std::string& code, size_t at, const std::string& text) {
+  if (at == 0 || at > code.size() || code.compare(at, text.size(), text) != 0) return false;
+  const unsigned char before = (unsigned char)code[at - 1];
+  return (text.size() < 32 && before == (0xa0u | text.size())) || (at >= 2 && (unsigned char)code[at - 2] == 0xd9 && before == text.size());
+}
+
+// Which of the code object's kernels `entry` is, in the order of its metadata note; -1 if none.
+int kernel_index(const std::string& code, const std::string& entry) {
+  const std::string key = ".symbol", symbol = entry + ".kd";
+  int index = 0;
+  for (size_t at = code.find(key); at != std::string::npos; at = code.find(key, at + key.size())) {
+    if (!is_string_at(code, at, key)) continue;
+    const size_t value = at + key.size() + (symbol.size() < 32 ? 1 : 2);
+    if (is_string_at(code, value, symbol)) return index;
+    ++index;
+  }
+  return -1;
+}
+
+// Value of an unsigned integer entry `key` of the metadata note (MessagePack, as the AMDGPU code-object format
+// defines it; every kernel has each key once) for the kernel of that index: the key's bytes are searched for and the
+// integer that follows is decoded.  -1 if absent.
+int64_t metadata_uint(const std::string& code, const char* key, int index) {
   const size_t klen = strlen(key);
   size_t at = 0;
   while ((at = code.find(key, at)) != std::string::npos) {
     const size_t v = at + klen;
     if (at == 0 || v >= code.size()) return -1;
-    // the key must be a MessagePack string of exactly this length (fixstr 0xa0|len or str8 0xd9 len)
-    const unsigned char before = (unsigned char)code[at - 1];
-    const bool fixstr = klen < 32 && before == (0xa0u | klen);
-    const bool str8 = at >= 2 && (unsigned char)code[at - 2] == 0xd9 && before == klen;
-    if (fixstr || str8) {
+    if (is_string_at(code, at, key) && index-- == 0) {
       const unsigned char t = (unsigned char)code[v];
       auto be = [&](int n) -> int64_t {
         if (v + 1 + n > code.size()) return -1;
@@ -144,9 +161,15 @@ void cache_write(const std::string& source, const std::string& code) {
 
 }  // namespace
 
+// A code object and, per device, its module; kernels compiled in one run share it.
+struct GenCode {
+  std::string bytes;
+  hipModule_t module[kMaxDevices] = {};   // (under big_lock())
+};
+
 struct GenKernel {
   std::string entry;
-  std::string code;                      // the code object
+  std::shared_ptr<GenCode> code;
   int32_t vgprs = 0, static_lds = 0, scratch_bytes = 0, spilled_vgprs = 0;
   std::atomic<hipFunction_t> fn[kMaxDevices];
   GenKernel() {
@@ -172,9 +195,12 @@ int function_here(GenKernel* k, hipFunction_t* out) {
     std::lock_guard<std::mutex> guard(big_lock());
     f = k->fn[dev].load(std::memory_order_acquire);
     if (!f) {
-      hipModule_t mod = nullptr;
-      e = hipModuleLoadData(&mod, k->code.data());
-      if (e != hipSuccess) return (int)e;
+      hipModule_t& mod = k->code->module[dev];
+      if (!mod) e = hipModuleLoadData(&mod, k->code->bytes.data());
+      if (e != hipSuccess) {
+        mod = nullptr;
+        return (int)e;
+      }
       e = hipModuleGetFunction(&f, mod, k->entry.c_str());
       if (e != hipSuccess) return (int)e;
       k->fn[dev].store(f, std::memory_order_release);
@@ -184,50 +210,35 @@ int function_here(GenKernel* k, hipFunction_t* out) {
   return 0;
 }
 
-}  // namespace
+// The kernel `entry` of `code`, kept under its source; null: the code holds no such kernel.  (Under big_lock().)
+std::shared_ptr<GenKernel> keep(const std::string& source, const std::string& entry, const std::shared_ptr<GenCode>& code) {
+  const int index = kernel_index(code->bytes, entry);
+  if (index < 0) return nullptr;
+  auto figure = [&](const char* key) { return (int32_t)std::max<int64_t>(0, metadata_uint(code->bytes, key, index)); };
+  auto k = std::make_shared<GenKernel>();
+  k->entry = entry;
+  k->code = code;
+  k->vgprs = figure(".vgpr_count");
+  k->static_lds = figure(".group_segment_fixed_size");
+  k->scratch_bytes = figure(".private_segment_fixed_size");
+  k->spilled_vgprs = figure(".vgpr_spill_count");
+  cache()[source] = k;
+  return k;
+}
 
-bool gen_available() { return rtc().ok; }
+std::shared_ptr<GenKernel> keep_from_disk(const std::string& source, const std::string& entry) {
+  auto code = std::make_shared<GenCode>();
+  return cache_read(source, &code->bytes) ? keep(source, entry, code) : nullptr;
+}
 
-int gen_compile(const std::string& source, const char* entry, std::shared_ptr<GenKernel>* out, std::string* log) {
+// One run of the compiler.  Null: it failed, and *log says why.
+std::shared_ptr<GenCode> compile_text(const std::string& source, std::string* log) {
   const Rtc& r = rtc();
-  if (!r.ok) {
-    if (log) *log = "the HIP run-time compiler (libhiprtc) could not be loaded";
-    return (int)hipErrorNotSupported;
-  }
-  if (const char* inject = getenv("FS_CODEGEN_INJECT_FAILURE"); inject && inject[0] == '1') {
-    // for tests of the fall-back paths: behave as if the compiler had rejected the source
-    if (log) *log = "compilation failure injected by FS_CODEGEN_INJECT_FAILURE";
-    return (int)hipErrorUnknown;
-  }
-  std::lock_guard<std::mutex> guard(big_lock());
-  auto it = cache().find(source);
-  if (it != cache().end()) {
-    *out = it->second;
-    return 0;
-  }
-  auto finish = [&](const std::shared_ptr<GenKernel>& k) {
-    const int64_t vg = metadata_uint(k->code, ".vgpr_count"), lds = metadata_uint(k->code, ".group_segment_fixed_size"),
-                  scratch = metadata_uint(k->code, ".private_segment_fixed_size"), spill = metadata_uint(k->code, ".vgpr_spill_count");
-    k->vgprs = vg > 0 ? (int32_t)vg : 0;
-    k->static_lds = lds > 0 ? (int32_t)lds : 0;
-    k->scratch_bytes = scratch > 0 ? (int32_t)scratch : 0;
-    k->spilled_vgprs = spill > 0 ? (int32_t)spill : 0;
-    cache()[source] = k;
-    *out = k;
-  };
-  {
-    auto k = std::make_shared<GenKernel>();
-    k->entry = entry;
-    if (cache_read(source, &k->code)) {
-      finish(k);
-      return 0;
-    }
-  }
   hiprtcProgram prog = nullptr;
   hiprtcResult rc = r.create(&prog, source.c_str(), "fs_generated.hip", 0, nullptr, nullptr);
   if (rc != HIPRTC_SUCCESS) {
     if (log) *log = r.error_string(rc);
-    return (int)hipErrorUnknown;
+    return nullptr;
   }
   // same code generation settings as the library's own kernels; packed-fp32 VALU ops stay off, leading kernel arguments are
   // preloaded into scalar registers
@@ -243,25 +254,79 @@ int gen_compile(const std::string& source, const char* entry, std::shared_ptr<Ge
     }
     if (rc != HIPRTC_SUCCESS && log->empty()) *log = r.error_string(rc);
   }
-  if (rc != HIPRTC_SUCCESS) {
-    r.destroy(&prog);
-    return (int)hipErrorUnknown;
-  }
-  auto k = std::make_shared<GenKernel>();
-  k->entry = entry;
-  size_t n = 0;
-  rc = r.code_size(prog, &n);
+  auto code = std::make_shared<GenCode>();
   if (rc == HIPRTC_SUCCESS) {
-    k->code.assign(n, '\0');
-    rc = r.code(prog, &k->code[0]);
+    size_t n = 0;
+    rc = r.code_size(prog, &n);
+    if (rc == HIPRTC_SUCCESS) {
+      code->bytes.assign(n, '\0');
+      rc = r.code(prog, &code->bytes[0]);
+    }
+    if (log && (rc != HIPRTC_SUCCESS || n == 0)) *log = "the run-time compiler returned no code object";
   }
   r.destroy(&prog);
-  if (rc != HIPRTC_SUCCESS || k->code.empty()) {
-    if (log) *log = "the run-time compiler returned no code object";
+  return rc == HIPRTC_SUCCESS && !code->bytes.empty() ? code : nullptr;
+}
+
+// (for tests of the fall-back paths: behave as if the compiler had rejected the source)
+bool failure_injected() {
+  const char* inject = getenv("FS_CODEGEN_INJECT_FAILURE");
+  return inject && inject[0] == '1';
+}
+
+}  // namespace
+
+bool gen_available() { return rtc().ok; }
+
+void gen_compile_together(const std::vector<GenSource>& sources) {
+  if (!rtc().ok || failure_injected()) return;
+  std::lock_guard<std::mutex> guard(big_lock());
+  std::vector<const GenSource*> fresh;
+  const GenSource* widest = nullptr;   // whose headers are all that the others have, and perhaps more
+  for (const GenSource& s : sources) {
+    bool known = cache().count(s.text) != 0 || keep_from_disk(s.text, s.entry) != nullptr;
+    for (const GenSource* f : fresh) known = known || f->text == s.text;
+    if (known) continue;
+    fresh.push_back(&s);
+    if (!widest || s.headers > widest->headers) widest = &s;
+  }
+  if (fresh.size() < 2) return;
+  std::string text = widest->text.substr(0, widest->headers);
+  for (size_t i = 0; i < fresh.size(); ++i) {
+    if (text.compare(0, fresh[i]->headers, fresh[i]->text, 0, fresh[i]->headers) != 0) return;
+    text += "namespace fs_source_" + std::to_string(i) + " {\n" + fresh[i]->text.substr(fresh[i]->headers) + "}\n";
+  }
+  const std::shared_ptr<GenCode> code = compile_text(text, nullptr);
+  if (!code) return;
+  for (const GenSource* s : fresh)
+    if (keep(s->text, s->entry, code)) cache_write(s->text, code->bytes);
+}
+
+int gen_compile(const std::string& source, const char* entry, std::shared_ptr<GenKernel>* out, std::string* log) {
+  if (!rtc().ok) {
+    if (log) *log = "the HIP run-time compiler (libhiprtc) could not be loaded";
+    return (int)hipErrorNotSupported;
+  }
+  if (failure_injected()) {
+    if (log) *log = "compilation failure injected by FS_CODEGEN_INJECT_FAILURE";
     return (int)hipErrorUnknown;
   }
-  cache_write(source, k->code);
-  finish(k);
+  std::lock_guard<std::mutex> guard(big_lock());
+  auto it = cache().find(source);
+  if (it != cache().end()) {
+    *out = it->second;
+    return 0;
+  }
+  *out = keep_from_disk(source, entry);
+  if (*out) return 0;
+  const std::shared_ptr<GenCode> code = compile_text(source, log);
+  if (!code) return (int)hipErrorUnknown;
+  *out = keep(source, entry, code);
+  if (!*out) {
+    if (log) *log = "the run-time compiler returned no kernel of that name";
+    return (int)hipErrorUnknown;
+  }
+  cache_write(source, code->bytes);
   return 0;
 }
 
@@ -271,7 +336,7 @@ GenResources gen_resources(const GenKernel* k) {
   r.static_lds = k->static_lds;
   r.scratch_bytes = k->scratch_bytes;
   r.spilled_vgprs = k->spilled_vgprs;
-  r.code_bytes = (int64_t)k->code.size();
+  r.code_bytes = (int64_t)k->code->bytes.size();
   return r;
 }
 

@@ -5,6 +5,7 @@
 #include <cstdint>
 #include <memory>
 #include <string>
+#include <vector>
 
 namespace fs {
 
@@ -344,6 +345,14 @@ bool gen_available();
 // Compiles `source` (HIP, one extern "C" kernel `entry`) for gfx950; needs no GPU.  Identical sources share one
 // compiled kernel for the life of the process.  Returns 0 or a hipError_t; *log receives the compiler's messages.
 int gen_compile(const std::string& source, const char* entry, std::shared_ptr<GenKernel>* out, std::string* log);
+struct GenSource {
+  std::string text, entry;
+  size_t headers = 0;   // of the text: the fixed device headers in front of the kernel
+};
+// Compiles those of `sources` that are new in one run of the compiler, for gen_compile() to find: most of a run is the compiler's start
+// (s on the host: an empty source 0.3, one row kernel 0.3 to 0.6, the nine of a transformer block's backward pass 3.8 one by one and
+// 1.6 at once).  Where it fails, gen_compile() compiles them one by one.
+void gen_compile_together(const std::vector<GenSource>& sources);
 GenResources gen_resources(const GenKernel* k);
 // Loads the kernel's module on the current device if there is one (otherwise the first launch does).
 int gen_preload(GenKernel* k);
