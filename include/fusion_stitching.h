@@ -228,17 +228,23 @@ int64_t fs_plan_describe(const fs_plan *p, char *text, size_t capacity);
  * Generated kernels only: row lengths that are no multiple of 4 elements; rows of more than
  * 2048 128-bit vectors (workgroups of 512 / 1024 threads; beyond 8192 vectors the row is
  * worked through in chunks, one pass per row reduction, the chunks kept in registers, and
- * further ones in LDS, where they fit and that pays); sums over all rows of a pattern (reduce_sum along axis 0 of a rank-2 value, or
- * a chain of reduce_sums along each leading axis in turn; a graph output nothing else
- * reads, float32 or rounded once to a 16-bit dtype; the plan then has a workspace and a
- * second launch that folds the partial sums); more than 4 full-shaped inputs.
+ * further ones in LDS, where they fit and that pays); sums over all rows of a pattern
+ * (reduce_sum along axis 0 of a rank-2 value, or a chain of reduce_sums along each leading
+ * axis in turn; a graph output nothing else reads, float32 or rounded once to a 16-bit
+ * dtype; the plan then has a workspace and a second launch that folds the partial sums);
+ * more than 4 full-shaped inputs.
  * Compilation needs no GPU; the module is loaded on the device that is current at plan
  * creation (or, without one, by the first fs_execute: do that one outside stream capture).
  * If the compiler is not available, compilation fails or the kernel would spill registers,
  * the choice falls back to the next best candidate (for FS_SCHEME_AUTO in the end to the
  * per-op plan).  Environment: FS_CODEGEN=0 switches generated kernels off by default;
  * FS_CODEGEN_CACHE_DIR=<existing directory> keeps compiled code objects there between
- * processes (files fs_gfx950_<hash>.co, verified against the full source when read).    */
+ * processes (files fs_gfx950_<hash>.co, verified against the full source when read).
+ * A run of the compiler takes 0.3 to 0.5 s; a plan or program whose sources are new to the
+ * process needs one or two, a plan of compiled-in kernels none (under a millisecond).  Small
+ * column sums are the exception: the one launch of `at_once` (see fs_execute) is a generated
+ * kernel also where the launches that it replaces are compiled in.  A caller that makes many
+ * short-lived plans creates them with fs_codegen_enable(0), or names a cache directory.   */
 
 /* Process-wide switch for offering generated kernels (default 1; the environment variable
  * FS_CODEGEN=0 sets the default to 0).  Affects plans, scores and programs created
@@ -267,7 +273,11 @@ int64_t fs_plan_source(const fs_plan *p, char *text, size_t capacity);
  * (`at_once` in fs_plan_describe) unless an output shares memory with an input or another
  * output, or the call is captured before its kernel is loaded on the current device (plan
  * creation loads it on the device that is current then, a call outside capture on any
- * other).  Two calls that share a workspace must be ordered on one stream.
+ * other).  The same call gives the same bits every time.  The one launch and the two add up
+ * in different orders, so their last bits may differ; and where rows of an odd number of
+ * 16-bit elements lie on the tensor's 16-byte grid, which lane adds which elements depends
+ * on the row's index, so that equal rows of a tensor may round differently.
+ * Two calls that share a workspace must be ordered on one stream.
  * Errors: FS_ERR_INVALID_ARG, FS_ERR_WORKSPACE, FS_ERR_ALIGN, FS_ERR_HIP.         */
 fs_status fs_execute(const fs_plan *p, const void *const *inputs, void *const *outputs,
                      void *workspace, size_t workspace_bytes, void *hip_stream);
@@ -426,10 +436,12 @@ fs_status fs_program_execute(const fs_program *p, const void *const *inputs, voi
  * A program whose graph declares external computations (fs_graph_external) is run stage by
  * stage: after stage k the caller runs, on the same stream, the external computations whose
  * operands are complete (every graph output that feeds one is written by the end of the
- * stage that makes it) and whose results stage k+1 reads.  fs_program_execute issues all
- * stages back to back (for timing the program's own kernels with the external results
- * already in place).  Column sums that nothing reads, external computations included, may
- * only be complete after the LAST stage (their joint fold launch runs there).
+ * stage that makes it) and whose results stage k+1 reads.  fs_program_execute runs the
+ * whole program at once, for timing its own kernels: every external result has to be in
+ * place before the call, and steps of different stages may run side by side (`merged` in
+ * fs_program_describe), which stage by stage they never do.  Column sums that nothing reads,
+ * external computations included, may only be complete after the LAST stage (their joint
+ * fold launch runs there).
  * Errors: as fs_program_execute.                                                           */
 fs_status fs_program_execute_stage(const fs_program *p, int32_t stage, const void *const *inputs, void *const *outputs,
                                    void *workspace, size_t workspace_bytes, void *hip_stream);
