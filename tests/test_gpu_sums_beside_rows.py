@@ -80,3 +80,35 @@ def test_where_it_is_not_offered():
     g.output(g.op("reduce_sum", [y], axis=0), "f32")
     g.finalize()
     assert "at_once" not in B.Plan(g, "auto").describe()
+
+
+@pytest.mark.gpu
+def test_under_capture_on_another_stream_and_without_a_workspace():
+    """Replayed from a captured graph, on a stream of its own beside the default one's work, and through fs_execute_static: the same bits."""
+    import torch
+    from .test_gpu_graph_capture import _capture_and_replay
+    for kind in sorted(GRAPHS):
+        spec = GRAPHS[kind](200, 768, "bf16")
+        assert _at_once(spec)
+        plan = B.Plan(B.Graph.from_spec(spec), "auto")
+        inp = make_inputs(spec, seed=3)
+        ins = [B.to_device(inp[t.name], t.dtype) for t in spec.inputs]
+        outs, again = B.alloc_outputs(spec), B.alloc_outputs(spec)
+        ws = plan.make_workspace()
+        i, o, a = ([t.data_ptr() for t in ts] for ts in (ins, outs, again))
+
+        def call(stream):
+            plan.execute_ptrs(i, o, ws.data_ptr(), ws.numel(), stream)
+        _capture_and_replay(call, outs, lambda k: ins[0].mul_(1.0))
+        call(torch.cuda.current_stream().cuda_stream)
+        side = torch.cuda.Stream()
+        for run in (lambda: plan.execute_ptrs(i, a, ws.data_ptr(), ws.numel(), side.cuda_stream), lambda: plan.execute_static_ptrs(i, a, side.cuda_stream)):
+            for t in again:
+                t.fill_(float("nan"))
+            torch.cuda.synchronize()
+            run()
+            ins[0].mul_(1.0)   # (the default stream's own)
+            side.synchronize()
+            torch.cuda.synchronize()
+            for x, y in zip(again, outs):
+                assert torch.equal(x.view(torch.uint8), y.view(torch.uint8)), kind
