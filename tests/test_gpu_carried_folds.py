@@ -1,5 +1,6 @@
 """The joint folds of a program that ride in its last step's launch: the sums are those of folds in launches of their own, bit
-for bit, run as a whole, stage by stage, and several times over on one workspace."""
+for bit, stage by stage and several times over on one workspace; run as a whole, such a program takes merged launches, which store
+the same bits too."""
 import numpy as np
 import pytest
 

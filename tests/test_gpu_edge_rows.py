@@ -71,7 +71,7 @@ def test_chunks_in_lds(kind, cols, dtype):
 
 
 def test_chunks_in_lds_of_several_operands():
-    """Two row operands, a column vector and a row statistic: RMS norm backward has column sums, so its forward with a residual."""
+    """Two row operands and column vectors: the sum of input and residual, plus a bias, normalised."""
     from workloads import add_bias_layernorm_graph
     spec = add_bias_layernorm_graph(2, 70000, in_dtype="f32", out_dtype="bf16")
     inp = make_inputs(spec, seed=1)
