@@ -374,7 +374,7 @@ def measure_program(name, steps, warmup):
     t_unf = timed(ucalls, max(5, steps // 8))
     steps_info = prog.patterns()
     return {"workload": spec.name, "ops": info["n_ops"], "patterns": info["n_patterns"], "single_ops": info["n_single_ops"],
-            "launches": info["n_kernels"], "packs": info["n_packs"], "stages": info["n_stages"], "joint_folds": info["n_joint_folds"],
+            "launches": prog.describe().count("\nmerged ") or info["n_kernels"], "packs": info["n_packs"], "stages": info["n_stages"], "joint_folds": info["n_joint_folds"],
             "workspace_bytes": info["workspace_bytes"],
             "bytes_min": info["bytes_min"], "us": t_prog, "GBps": info["bytes_min"] / t_prog / 1e3,
             "frac_of_peak": info["bytes_min"] / t_prog / 1e3 / HBM_PEAK_GBPS,
